@@ -88,7 +88,8 @@ kf_status check_cfg(const kf_score_cfg* cfg) {
 //                         survivor index list U*cap int32
 //                select : survivor index list U*cap int32
 //                prefill: row normalisers U*G*n_pad floats, then row keys U*G*n_pad uint32, then
-//                         (G > 1) per-query-head column sums U*G*n_pad floats
+//                         (G > 1 or parts > 1) column sums U*G*parts*n_pad floats, then (parts > 1) the
+//                         rows' partial statistics U*G*parts*n_pad float2
 //              (G = query heads per cached head)
 struct WsLayout {
     size_t region, fused_idx, wide, total;  // wide: boundary entries of the two-launch ordered eviction
@@ -106,7 +107,13 @@ size_t decode_region(int64_t U, const kf_cache* c) {
            align_up((size_t)U * G * c->cap * sizeof(float), 256) + align_up((size_t)U * sizeof(int32_t), 256);
 }
 
-WsLayout ws_layout(const kf_cache* c, int32_t n_max) {
+size_t prefill_region(int64_t UQ, size_t n_pad, int32_t G, int32_t parts) {
+    const size_t row = align_up((size_t)UQ * n_pad * sizeof(float), 256);
+    return 2 * row + ((G > 1 || parts > 1) ? (size_t)parts * row : 0) + (parts > 1 ? (size_t)parts * 2 * row : 0);
+}
+
+// parts: of prompt scoring's tile walks (1: whole, what a prompt of n_max rows needs at least)
+WsLayout ws_layout(const kf_cache* c, int32_t n_max, int32_t parts = 1) {
     const int64_t U = (int64_t)c->L * c->B * c->H;
     WsLayout w;
     w.region = 256;
@@ -117,7 +124,7 @@ WsLayout ws_layout(const kf_cache* c, int32_t n_max) {
     if (n_max > 0) {
         const size_t n_pad = align_up((size_t)n_max, kf::kPrefillRowPad);
         const int32_t G = group_of(c);
-        const size_t pre = (G > 1 ? 3 : 2) * align_up((size_t)U * G * n_pad * sizeof(float), 256);
+        const size_t pre = prefill_region(U * G, n_pad, G, parts);
         if (pre > x) x = pre;
     }
     w.wide = w.region + x;
@@ -190,7 +197,18 @@ size_t kf_workspace_bytes(const kf_cache* c, int32_t n_max) {
     if (!c || c->L < 1 || c->B < 1 || c->H < 1 || c->cap < 1 || !supported(c->dtype, c->d)) return 0;
     if (!group_supported(c->q_per_kv)) return 0;
     if (n_max < 0) n_max = 0;
-    return ws_layout(c, n_max).total;
+    size_t total = ws_layout(c, n_max).total;
+    // a shorter prompt may be scored in parts and then need more: the most that any length up to n_max takes
+    const int64_t UQ = (int64_t)c->L * c->B * c->H * group_of(c);
+    for (int64_t n = kf::kPrefillRowPad; UQ * n < kf::kPrefillPartsRowLimit; n += kf::kPrefillRowPad) {
+        const int32_t len = n < n_max ? (int32_t)n : n_max;
+        if (len > 0) {
+            const size_t t = ws_layout(c, len, kf::plan_prefill(UQ, len).parts).total;
+            if (t > total) total = t;
+        }
+        if (n >= n_max) break;
+    }
+    return total;
 }
 
 kf_status kf_decode_launch_shape(const kf_cache* c, int32_t m_hint, int32_t* splits, int32_t* chunk) {
@@ -217,12 +235,17 @@ kf_status kf_prefill_score(const kf_cache* c, const void* Q, int32_t n, const kf
     if (!Q) return fail(KF_EINVAL, "Q is NULL");
     if ((uintptr_t)Q & 15) return fail(KF_EINVAL, "Q must be 16-byte aligned");
     if (n < 1 || n > c->cap) return fail(KF_EINVAL, "prompt length %d outside [1, cap=%d]", n, c->cap);
-    const WsLayout w = ws_layout(c, n);
+    const int32_t G = group_of(c);
+    const int64_t U = (int64_t)c->L * c->B * c->H * G;  // query units
+    kf::PrefillParts parts = kf::plan_prefill(U, n);
+    WsLayout w = ws_layout(c, n, parts.parts);
+    if (parts.parts > 1 && workspace_bytes < w.total) {  // no room for the parts' records: whole walks
+        parts = kf::kPrefillWhole;
+        w = ws_layout(c, n);
+    }
     st = check_ws(workspace, workspace_bytes, w.total);
     if (st != KF_OK) return st;
 
-    const int32_t G = group_of(c);
-    const int64_t U = (int64_t)c->L * c->B * c->H * G;  // query units
     if ((U + 7) / 8 * 8 * ((n + 127) / 128) > kMaxGrid)  // one workgroup per 128 prompt rows of a unit
         return fail(KF_EUNSUPPORTED, "%lld query units of %d prompt rows exceed the largest launch", (long long)U, n);
     const size_t n_pad = align_up((size_t)n, kf::kPrefillRowPad);
@@ -238,7 +261,11 @@ kf_status kf_prefill_score(const kf_cache* c, const void* Q, int32_t n, const kf
     a.ws_err = (int32_t*)workspace + KF_WS_ERROR_WORD;
     a.ws_c = (float*)((char*)workspace + w.region);
     a.ws_r = (uint32_t*)((char*)workspace + w.region + align_up((size_t)U * n_pad * sizeof(float), 256));
-    a.ws_f = (float*)((char*)workspace + w.region + 2 * align_up((size_t)U * n_pad * sizeof(float), 256));
+    const size_t row = align_up((size_t)U * n_pad * sizeof(float), 256);
+    a.ws_f = (float*)((char*)workspace + w.region + 2 * row);
+    a.ws_part = (float2*)((char*)workspace + w.region + (2 + (size_t)parts.parts) * row);
+    a.parts = parts.parts;
+    a.part_tiles = parts.tiles;
     a.G = G;
     a.B = c->B;
     a.H = c->H * G;

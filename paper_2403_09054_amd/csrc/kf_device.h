@@ -111,14 +111,17 @@ __host__ __device__ __forceinline__ uint64_t mix64(uint64_t z) {
     return z;
 }
 
-__host__ __device__ __forceinline__ uint32_t mix32(uint32_t x) {
-    x ^= x >> 16;
+// The first step of mix32 is linear over xor: fold16(a ^ b) == fold16(a) ^ fold16(b).  A loop that combines a
+// row key with many key positions therefore folds the two sides once, outside, and starts at mix32_folded.
+__host__ __device__ __forceinline__ uint32_t fold16(uint32_t x) { return x ^ (x >> 16); }
+__host__ __device__ __forceinline__ uint32_t mix32_folded(uint32_t x) {
     x *= 0x6A09E667u;
     x ^= x >> 15;
     x *= 0xBB67AE85u;
     x ^= x >> 16;
     return x;
 }
+__host__ __device__ __forceinline__ uint32_t mix32(uint32_t x) { return mix32_folded(fold16(x)); }
 
 constexpr uint32_t kQposMul = 0x9E3779B9u;
 constexpr uint32_t kKposMul = 0x243F6A89u;

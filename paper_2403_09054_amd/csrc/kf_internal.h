@@ -167,13 +167,25 @@ struct PrefillArgs {
     int32_t* ws_err;       // device error counter
     float* ws_c;        // [U][n_pad] per-row log2 normaliser            (U = L*B*H query units)
     uint32_t* ws_r;     // [U][n_pad] per-row noise key
-    float* ws_f;        // [U][n_pad] per-query-head column sums (G > 1 only)
+    float* ws_f;        // [U][parts][n_pad] column sums per query head and part (G > 1 or parts > 1 only)
+    float2* ws_part;    // [U][parts][n_pad] reference exponent and sum of a row's parts (parts > 1 only)
     int32_t B, H, cap, layer0, n, n_pad;  // H counts QUERY heads; the caches hold H/G heads
     int32_t G;          // query heads per cached head
+    int32_t parts;      // workgroups that share the tile walk of a 128-row block, at most ...
+    int32_t part_tiles; // ... and the tiles each of them walks
     int32_t noise;
     float inv_tau;
     float scale;
 };
+// Parts of the blocks' tile walks for U query units of up to n rows.
+constexpr int32_t kPrefillMaxPartTiles = 64;
+constexpr int32_t kPrefillMaxParts = 32;  // bounds the scratch: 12 bytes per row and part
+constexpr int64_t kPrefillPartsRowLimit = 2 * 1024 * 128;  // U * n from which no prompt is cut
+struct PrefillParts {
+    int32_t parts, tiles;
+};
+constexpr PrefillParts kPrefillWhole{1, 1 << 26};
+PrefillParts plan_prefill(int64_t U, int32_t n);
 hipError_t launch_prefill(const PrefillArgs& a, int64_t U, int32_t d, int32_t dtype, hipStream_t stream);
 
 constexpr int32_t kPrefillRowPad = 128;  // n is padded to this for the row-statistics arrays

@@ -16,8 +16,12 @@
 //           key and sees 16 of the tile's 32 queries: z_ij = 2^(y2_ij - c_i) is
 //           added into the lane's column sum.
 // Per logit the work is one 32-bit hash, two logarithms and one exponential;
-// that, not the MFMA rate, bounds the kernel, so the per-logit instruction count
-// is what is trimmed.  With the Gumbel adjustment (the method; the other
+// that, not the MFMA rate, bounds the kernel (vector pipe 97 % busy, 1.9 T logit
+// evaluations per second and pass at d = 128, 32768 rows), so the per-logit
+// instruction count is what is trimmed: 16.7 a pass (20.5 and 17.6 before the
+// hash's first step left the loop, the masking compares moved into the edge
+// tiles' branch and the accumulators into ordinary registers: 32 heads x 32768
+// rows 20.3 -> 18.4 ms, 256 x 4096 with position bias 3.13 -> 2.81 ms).  With the Gumbel adjustment (the method; the other
 // adjustments keep the plain form): pass 1 sums every term against a reference
 // exponent instead of searching each tile's maximum first -- the reference
 // starts at the row's own diagonal term (so the sum cannot vanish), follows the
@@ -35,6 +39,11 @@ typedef float f32x16 __attribute__((ext_vector_type(16)));
 
 constexpr int kPrefillThreads = 256;  // 4 waves, 32 queries (pass 1) or keys (pass 2) each
 constexpr int kTile = 32;
+// Waves per SIMD to compile for: four, three where a lane's own row takes 64 registers.  (With two or more the
+// compiler keeps the MFMA accumulators in ordinary registers; allowed more than 256 registers per lane it puts
+// them into accumulation registers and copies every one of a tile's 16 logits back with an instruction of its own.)
+template <typename T, int D>
+constexpr int kPrefillMinWaves = D * sizeof(T) >= 512 ? 3 : 4;
 
 // One "group" = the 16 bytes a lane loads from a row: it feeds one bf16 MFMA
 // (K = 16: 8 elements from each half of the wave) or four fp32 MFMAs (K = 2).
@@ -67,15 +76,39 @@ struct Mma<float> {
     }
 };
 
-// Workgroup -> (unit, block of 128 rows).  Consecutive workgroup ids are dealt
+// Workgroup -> (unit, block of 128 rows, part of the block's tile walk).  Consecutive workgroup ids are dealt
 // round-robin to the chip's 8 XCDs, each with an L2 of its own; the blocks of
 // one unit re-read the same K / Q rows, so all blocks of a unit are given ids
 // that are equal modulo 8 and therefore share one L2.
 constexpr int kXcds = 8;
-__device__ __forceinline__ void unit_and_block(int nblk, int64_t& u, int& blk) {
+__device__ __forceinline__ void unit_and_block(int nblk, int parts, int64_t& u, int& blk, int& part) {
     const unsigned xcd = blockIdx.x % kXcds, local = blockIdx.x / kXcds;
-    u = (int64_t)(local / nblk) * kXcds + xcd;
-    blk = (int)(local % nblk);
+    u = (int64_t)(local / (nblk * parts)) * kXcds + xcd;
+    const int in_unit = (int)(local % (nblk * parts));
+    blk = in_unit / parts;
+    part = in_unit % parts;
+}
+
+// M + log2(S).  The hardware logarithm's error grows with its result and leans to one side: of a sum of 2^8 it
+// left every row's normaliser low and with it every score high by 4e-7.  So the sum's exponent is taken off
+// first (exact) and only its mantissa goes through the logarithm.
+__device__ __forceinline__ float log2_of_sum(float M, float S) {
+    const uint32_t b = __float_as_uint(S), ex = b >> 23;
+    if (ex == 0u || ex >= 255u) return M + hw_log2(S);  // zero, denormal, infinite, NaN, negative
+    return (M + (float)((int)ex - 127)) + hw_log2(__uint_as_float((b & 0x7FFFFFu) | 0x3F800000u));
+}
+
+// Log2 of a row's normaliser from the partial sums its parts left: sum over p of S_p * 2^(M_p).
+__device__ __forceinline__ float merged_normaliser(const float2* rec, size_t stride, int parts) {
+    float M = -INFINITY, S = 0.0f;
+    for (int p = 0; p < parts; ++p) {
+        const float2 r = rec[p * stride];
+        if (!(r.y > 0.0f) && r.y == r.y) continue;  // nothing in this part (a NaN sum is carried on)
+        const float Mn = fmaxf(M, r.x);
+        S = (M > -INFINITY ? S * hw_exp2(M - Mn) : 0.0f) + r.y * hw_exp2(r.x - Mn);
+        M = Mn;
+    }
+    return log2_of_sum(M, S);
 }
 
 // Row of the 32x32 accumulator tile that register r of this lane holds
@@ -93,8 +126,8 @@ struct LogitParams {
     float c1;       // log2(e) / tau
     int noise;
 };
-__device__ __forceinline__ float logit2_gumbel(const LogitParams& lp, float acc, float dist, uint32_t hash_in) {
-    const float l2t = hw_log2(neg_log2_uniform(mix32(hash_in)));
+__device__ __forceinline__ float logit2_gumbel(const LogitParams& lp, float acc, float dist, uint32_t folded) {
+    const float l2t = hw_log2(neg_log2_uniform(mix32_folded(folded)));
     return fmaf(acc, lp.sc1, fmaf(dist, -lp.slope1, fmaf(l2t, -lp.inv_tau, lp.gz)));
 }
 __device__ __forceinline__ float logit2_other(const LogitParams& lp, float acc, float dist, uint32_t rkey,
@@ -122,79 +155,126 @@ struct TileStage {
     static constexpr int kBufBytes = kTile * kPitch;
     static_assert(kPieces % kPrefillThreads == 0, "a tile is a whole number of pieces per thread");
 
-    // rows [row0, row0+32) of `rows` (clamped to n-1) -> registers
-    static __device__ __forceinline__ void fetch(const T* rows, int row0, int n, uint4 (&reg)[NP]) {
+    // A thread's pieces of a tile on their way from memory to LDS (vector values, passed by value: an array of
+    // uint4 handed around by reference ended up in scratch memory, each tile's loads waited for at once).
+    struct Regs {
+        u32x4_t r[NP];
+    };
+    // rows [row0, row0+32) of `rows` -> registers; rows from n on repeat row n-1.  A whole tile (workgroup-uniform)
+    // is addressed by a scalar base and an offset that a thread keeps for all tiles, without vector arithmetic.
+    static __device__ __forceinline__ Regs fetch(const T* rows, int row0, int n) {
+        const char* base = (const char*)rows + (size_t)row0 * kRowBytes;
+        Regs reg;
+        if (row0 + kTile <= n) {
+#pragma unroll
+            for (int i = 0; i < NP; ++i) reg.r[i] = *(const u32x4_t*)(base + (threadIdx.x + i * kPrefillThreads) * 16u);
+        } else {
+            const uint32_t last = (uint32_t)(n - 1 - row0);
+#pragma unroll
+            for (int i = 0; i < NP; ++i) {
+                const uint32_t p = threadIdx.x + i * kPrefillThreads;
+                reg.r[i] = *(const u32x4_t*)(base + (min(p / PPR, last) * kRowBytes + (p % PPR) * 16u));
+            }
+        }
+        return reg;
+    }
+    static __device__ __forceinline__ void park(char* buf, const Regs reg) {
 #pragma unroll
         for (int i = 0; i < NP; ++i) {
             const int p = threadIdx.x + i * kPrefillThreads;
-            const int r = min(row0 + p / PPR, n - 1);
-            reg[i] = *(const uint4*)((const char*)rows + (size_t)r * kRowBytes + (p % PPR) * 16);
+            *(u32x4_t*)(buf + (p / PPR) * kPitch + (p % PPR) * 16) = reg.r[i];
         }
     }
-    static __device__ __forceinline__ void park(char* buf, const uint4 (&reg)[NP]) {
+    // The 32x32 products of the parked tile (A operand) with the lane's own row `own` (B operand).  The LDS reads
+    // go out in batches ahead of their MFMAs: left to itself the compiler reads, waits and multiplies one 16-byte
+    // piece at a time, D/16 LDS round trips per tile that only other waves can cover.
+    static constexpr int kGroups = D / (2 * ElemTraits<T>::kPerVec);
+    static constexpr int kBatch = kGroups < 8 ? kGroups : 8;
+    static __device__ __forceinline__ f32x16 products(const char* buf, int n0, int half, const uint4 (&own)[kGroups]) {
+        const char* p = buf + n0 * kPitch + half * 16;
+        f32x16 acc;
 #pragma unroll
-        for (int i = 0; i < NP; ++i) {
-            const int p = threadIdx.x + i * kPrefillThreads;
-            *(uint4*)(buf + (p / PPR) * kPitch + (p % PPR) * 16) = reg[i];
+        for (int r = 0; r < 16; ++r) acc[r] = 0.0f;
+#pragma unroll
+        for (int g0 = 0; g0 < kGroups; g0 += kBatch) {
+            uint4 a[kBatch];
+#pragma unroll
+            for (int g = 0; g < kBatch; ++g) a[g] = *(const uint4*)(p + (g0 + g) * 32);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int g = 0; g < kBatch; ++g) acc = Mma<T>::group(a[g], own[g0 + g], acc);
         }
-    }
-    // the 16 bytes lane (row n0, half) feeds MFMA group g
-    static __device__ __forceinline__ uint4 operand(const char* buf, int n0, int half, int g) {
-        return *(const uint4*)(buf + n0 * kPitch + (2 * g + half) * 16);
+        return acc;
     }
 };
 
 // ------------------------------------------------------------------ pass 1
-// <q, k> over the elements of the 16-byte pieces a and b
+// <q, k> over the elements of the 16-byte pieces x and y
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
 template <typename T>
-__device__ __forceinline__ float dot_piece(const uint4& x, const uint4& y) {
-    constexpr int EPV = ElemTraits<T>::kPerVec;
-    float xf[EPV], yf[EPV];
-    unpack16<T>(x, xf);
-    unpack16<T>(y, yf);
-    float d = 0.0f;
+__device__ __forceinline__ float dot_piece(const uint4& x, const uint4& y, float d) {
+    const uint32_t xs[4] = {x.x, x.y, x.z, x.w}, ys[4] = {y.x, y.y, y.z, y.w};
 #pragma unroll
-    for (int e = 0; e < EPV; ++e) d = fmaf(xf[e], yf[e], d);
+    for (int e = 0; e < 4; ++e) {
+        if constexpr (sizeof(T) == 4)
+            d = fmaf(__uint_as_float(xs[e]), __uint_as_float(ys[e]), d);
+        else if constexpr (__is_same(T, bf16_t))
+            d = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, xs[e]), __builtin_bit_cast(bf16x2, ys[e]), d, false);
+        else
+            d = __builtin_amdgcn_fdot2(__builtin_bit_cast(f16x2, xs[e]), __builtin_bit_cast(f16x2, ys[e]), d, false);
+    }
     return d;
 }
 
 // Sum over this lane's 16 logits of a tile of 2^(y2 - reference), Gumbel adjustment; `base` is the
-// adjustment's constant part less the reference (and the position bias of the lane's first key).  MASK: keep only the keys up to `room` places behind the
-// lane's first one (the tile crosses the diagonal).
+// adjustment's constant part less the reference (and the position bias of the lane's first key), rfold the
+// folded row key, kfold the folded key positions of the tile (this lane's: words 8*q4 + 4*half + e).  MASK:
+// keep only the keys up to `room` places behind the lane's first one (the tile crosses the diagonal).
 template <bool BIAS, bool MASK>
-__device__ __forceinline__ float tile_sum(const LogitParams& lp, const f32x16& acc, float base, uint32_t rkey,
-                                          uint32_t kmul, int room) {
+__device__ __forceinline__ float tile_sum(const LogitParams& lp, const f32x16& acc, float base, uint32_t rfold,
+                                          const uint32_t* kfold, int half, int room) {
     float ssum = 0.0f;
 #pragma unroll
-    for (int r = 0; r < 16; ++r) {
-        const int ro = (r >> 2) * 8 + (r & 3);
-        const float l2t = hw_log2(neg_log2_uniform(mix32(rkey ^ (kmul + (uint32_t)ro * kKposMul))));
-        // position bias -slope*(dist0 - ro): its dist0 part rides in `base`, the ro part is a literal multiple
-        const float t = fmaf(l2t, -lp.inv_tau, BIAS ? fmaf(lp.slope1, (float)ro, base) : base);
-        const float e = hw_exp2(fmaf(acc[r], lp.sc1, t));
-        ssum += (!MASK || ro <= room) ? e : 0.0f;
+    for (int q4 = 0; q4 < 4; ++q4) {
+        const uint4 k4 = *(const uint4*)&kfold[q4 * 8 + half * 4];
+        const uint32_t ks[4] = {k4.x, k4.y, k4.z, k4.w};
+#pragma unroll
+        for (int e4 = 0; e4 < 4; ++e4) {
+            const int ro = q4 * 8 + e4;
+            const float l2t = hw_log2(neg_log2_uniform(mix32_folded(rfold ^ ks[e4])));
+            // position bias -slope*(dist0 - ro): its dist0 part rides in `base`, the ro part is a literal multiple
+            const float t = fmaf(l2t, -lp.inv_tau, BIAS ? fmaf(lp.slope1, (float)ro, base) : base);
+            const float e = hw_exp2(fmaf(acc[q4 * 4 + e4], lp.sc1, t));
+            ssum += (!MASK || ro <= room) ? e : 0.0f;
+        }
     }
     return ssum;
 }
 
 // GUMBEL: the method's adjustment, trimmed form; otherwise any adjustment, plain form.  BIAS: slopes given.
 template <typename T, int D, bool GUMBEL, bool BIAS>
-__global__ void __launch_bounds__(kPrefillThreads) prefill_rowstats_kernel(const PrefillArgs a, int nblk, int64_t units) {
+__global__ void __launch_bounds__(kPrefillThreads, (kPrefillMinWaves<T, D>)) prefill_rowstats_kernel(const PrefillArgs a, int nblk, int64_t units) {
     constexpr int EPV = ElemTraits<T>::kPerVec;
     constexpr int NG = D / (2 * EPV);
     using Stage = TileStage<T, D>;
     __shared__ __attribute__((aligned(16))) char kbuf[2][Stage::kBufBytes];
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    __shared__ __attribute__((aligned(16))) uint32_t kfold[2][kTile];  // folded positions of the tile's keys
+    const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int n0 = lane & 31, half = lane >> 5;
     int64_t u;
-    int blk;
-    unit_and_block(nblk, u, blk);
+    int blk, part;
+    unit_and_block(nblk, a.parts, u, blk, part);
     if (u >= units) return;  // workgroup-uniform
     const int rb = nblk - 1 - blk;  // longest rows first
     const int h = (int)(u % a.H), b = (int)((u / a.H) % a.B), l = a.layer0 + (int)(u / ((int64_t)a.H * a.B));
     const int n = a.seq_n ? a.seq_n[b] : a.n;  // this sequence's prompt length; rows n..a.n-1 are padding
     // workgroup-uniform exits: a length out of range (the second pass reports it), a block inside the padding
     if (n < 1 || n > a.n || rb * (4 * kTile) >= n) return;
+    // this workgroup's tiles [jt_first, jt_last] of the block's walk
+    const int jt_first = part * a.part_tiles;
+    const int jt_last = min(min(rb * (4 * kTile) + 4 * kTile - 1, n - 1) / kTile, jt_first + a.part_tiles - 1);
+    if (jt_first > jt_last) return;  // workgroup-uniform: the block has fewer parts
     const int i0 = rb * (4 * kTile) + wv * kTile;
     const bool active = i0 < n;  // wave-uniform; inactive waves still fetch tiles and meet the barriers
     const int i = i0 + n0;
@@ -216,9 +296,12 @@ __global__ void __launch_bounds__(kPrefillThreads) prefill_rowstats_kernel(const
     lp.inv_tau = a.inv_tau;
     lp.gz = -kLog2Ln2 * a.inv_tau;
     lp.noise = a.noise;
-    // key position of accumulator register r is jb + half*4 + (r>>2)*8 + (r&3); its hash input
-    // is rkey ^ (k_pos * kKposMul): the lane part of the product is formed once
-    const uint32_t kmul_lane = (uint32_t)(half * 4) * kKposMul;
+    // a logit's hash input is rkey ^ (k_pos * kKposMul); both sides enter the loop folded (mix32's first step),
+    // the keys' side as a table that travels with the tile
+    const uint32_t rfold = fold16(rkey);
+    auto park_keys = [&](int buf, int jt) {
+        if (threadIdx.x < kTile) kfold[buf][threadIdx.x] = fold16((uint32_t)(jt * kTile + threadIdx.x) * kKposMul);
+    };
 
     float M = -INFINITY, Ssum = 0.0f;
     if constexpr (GUMBEL) {
@@ -228,38 +311,42 @@ __global__ void __launch_bounds__(kPrefillThreads) prefill_rowstats_kernel(const
         const T* krow = Ku + (size_t)min(i, n - 1) * D + half * EPV;
         float dot = 0.0f;
 #pragma unroll
-        for (int g = 0; g < NG; ++g) dot += dot_piece<T>(bq[g], *(const uint4*)(krow + g * 2 * EPV));
+        for (int g = 0; g < NG; ++g) dot = dot_piece<T>(bq[g], *(const uint4*)(krow + g * 2 * EPV), dot);
         dot += __shfl_xor(dot, 32, kWave);
-        M = logit2_gumbel(lp, dot, 0.0f, rkey ^ ((uint32_t)i * kKposMul));
+        M = logit2_gumbel(lp, dot, 0.0f, rfold ^ fold16((uint32_t)i * kKposMul));
     }
-    const int jt_end = min(i0 + kTile - 1, n - 1) / kTile;                      // this wave's last key tile
-    const int jt_last = min(rb * (4 * kTile) + 4 * kTile - 1, n - 1) / kTile;   // the workgroup's
-    uint4 stage[Stage::NP];
-    Stage::fetch(Ku, 0, n, stage);
+    const int jt_end = min(i0 + kTile - 1, n - 1) / kTile;  // this wave's last key tile
+    typename Stage::Regs stage = Stage::fetch(Ku, jt_first * kTile, n);
     Stage::park(kbuf[0], stage);
+    if constexpr (GUMBEL) park_keys(0, jt_first);
     __syncthreads();
-    for (int jt = 0; jt <= jt_last; ++jt) {
-        // the next tile (the last one again at the end: rows stay in range), in flight during this tile's work
-        Stage::fetch(Ku, min(jt + 1, jt_last) * kTile, n, stage);
+    for (int jt = jt_first; jt <= jt_last; ++jt) {
+        const int cur = (jt - jt_first) & 1;
+        // the next tile (the last one again at the end: rows stay in range), in flight during this tile's work;
+        // asking two tiles ahead measured the same
+        stage = Stage::fetch(Ku, min(jt + 1, jt_last) * kTile, n);
         if (active && jt <= jt_end) {
-            const char* kb = kbuf[jt & 1];
-            f32x16 acc;
-#pragma unroll
-            for (int r = 0; r < 16; ++r) acc[r] = 0.0f;
-#pragma unroll
-            for (int g = 0; g < NG; ++g) acc = Mma<T>::group(Stage::operand(kb, n0, half, g), bq[g], acc);
+            const char* kb = kbuf[cur];
+            const f32x16 acc = Stage::products(kb, n0, half, bq);
             const int jb = jt * kTile;
             const int jl = jb + half * 4;                       // first key of this lane in the tile
-            const uint32_t kmul = (uint32_t)jb * kKposMul + kmul_lane;
             const float dist0 = (float)(i - jl);
             if constexpr (GUMBEL) {
                 // every term against the reference as it stands, (gz - M) folded into the chain: no search for the
                 // tile's maximum, no subtraction per logit.  A later, larger logit just gives a term above one.
-                const bool diag = jb + kTile - 1 > i0;  // the tile crosses the diagonal for some lane: causal mask
+                // Only the wave's last tile crosses the diagonal.  Its masking compares are kept inside their branch
+                // (the empty asm makes them depend on it): hoisted, they cost every tile an instruction per logit.
+                const bool diag = jt == jt_end;
                 for (int attempt = 0;; ++attempt) {
                     const float base = BIAS ? fmaf(dist0, -lp.slope1, lp.gz - M) : lp.gz - M;
-                    const float ssum = diag ? tile_sum<BIAS, true>(lp, acc, base, rkey, kmul, i - jl)
-                                            : tile_sum<BIAS, false>(lp, acc, base, rkey, kmul, 0);
+                    float ssum;
+                    if (diag) {
+                        int room = i - jl;
+                        asm volatile("" : "+v"(room));
+                        ssum = tile_sum<BIAS, true>(lp, acc, base, rfold, kfold[cur], half, room);
+                    } else {
+                        ssum = tile_sum<BIAS, false>(lp, acc, base, rfold, kfold[cur], half, 0);
+                    }
                     const float Snew = Ssum + ssum;
                     // a sum beyond fp32 in some lane (a logit 2^120 above its row's reference): that lane raises its
                     // reference and the wave sums the tile again (the other lanes arrive at the same sums as
@@ -308,7 +395,10 @@ __global__ void __launch_bounds__(kPrefillThreads) prefill_rowstats_kernel(const
             }
             }
         }
-        if (jt < jt_last) Stage::park(kbuf[(jt + 1) & 1], stage);
+        if (jt < jt_last) {
+            Stage::park(kbuf[cur ^ 1], stage);
+            if constexpr (GUMBEL) park_keys(cur ^ 1, jt + 1);
+        }
         __syncthreads();
     }
     if (!active) return;
@@ -317,38 +407,84 @@ __global__ void __launch_bounds__(kPrefillThreads) prefill_rowstats_kernel(const
     const float Mt = fmaxf(M, M2);
     const float St = (M > -INFINITY ? Ssum * hw_exp2(M - Mt) : 0.0f) + (M2 > -INFINITY ? S2 * hw_exp2(M2 - Mt) : 0.0f);
     if (half == 0 && i < n) {
+        if (a.parts > 1) {  // the second pass puts the parts together
+            a.ws_part[((size_t)u * a.parts + part) * a.n_pad + i] = make_float2(Mt, St);
+            if (part == 0) a.ws_r[(size_t)u * a.n_pad + i] = GUMBEL ? rfold : rkey;
+            return;
+        }
         // log2 of the row's normaliser; the trimmed second pass wants it subtracted from the adjustment's
         // constant part, so that is what is left for it
-        const float c = Mt + hw_log2(St);
+        const float c = log2_of_sum(Mt, St);
         a.ws_c[(size_t)u * a.n_pad + i] = GUMBEL ? lp.gz - c : c;
-        a.ws_r[(size_t)u * a.n_pad + i] = rkey;
+        a.ws_r[(size_t)u * a.n_pad + i] = GUMBEL ? rfold : rkey;
     }
 }
 
 // ------------------------------------------------------------------ pass 2
-template <typename T, int D, bool GUMBEL, bool BIAS>
-__global__ void __launch_bounds__(kPrefillThreads) prefill_colsum_kernel(const PrefillArgs a, int nblk, int64_t units) {
+// Sum of this lane's 16 terms of a tile, a part of its key's column sum.  cs, rs: the tile's row statistics and row noise
+// keys (folded with the Gumbel adjustment); i_first: the lane's first query row.  MASK: the tile crosses the
+// diagonal or the end of the prompt.
+template <bool GUMBEL, bool BIAS, bool MASK>
+__device__ __forceinline__ float column_sum(const LogitParams& lp, const f32x16& acc, const float* cs, const uint32_t* rs,
+                                            int i_first, int half, int j, uint32_t kfold, int n) {
+    float sum = 0.0f;  // of the tile: a long prompt's column takes n/2 terms, added one by one they would lose 1e-5
+#pragma unroll
+    for (int q4 = 0; q4 < 4; ++q4) {  // 4 consecutive query rows each
+        const float4 c4 = *(const float4*)&cs[q4 * 8 + half * 4];
+        const uint4 r4 = *(const uint4*)&rs[q4 * 8 + half * 4];
+        const float cv[4] = {c4.x, c4.y, c4.z, c4.w};
+        const uint32_t rv[4] = {r4.x, r4.y, r4.z, r4.w};
+        const float dist0 = (float)(i_first + q4 * 8 - j);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const float x = acc[q4 * 4 + e];
+            float z;
+            if constexpr (GUMBEL) {
+                // cv holds (adjustment's constant part - row normaliser): z = 2^(x2 - log2(t)/tau + cv)
+                const float l2t = hw_log2(neg_log2_uniform(mix32_folded(rv[e] ^ kfold)));
+                float t = fmaf(l2t, -lp.inv_tau, cv[e]);
+                if (BIAS) t = fmaf(dist0 + (float)e, -lp.slope1, t);
+                z = hw_exp2(fmaf(x, lp.sc1, t));
+            } else {
+                z = hw_exp2(logit2_other(lp, x, dist0 + (float)e, rv[e], (uint32_t)j) - cv[e]);
+            }
+            const int i = i_first + q4 * 8 + e;
+            sum += (!MASK || (i >= j && i < n)) ? z : 0.0f;
+        }
+    }
+    return sum;
+}
+
+// PARTS: the query tiles of a column block are cut into parts, one workgroup each.
+template <typename T, int D, bool GUMBEL, bool BIAS, bool PARTS>
+__global__ void __launch_bounds__(kPrefillThreads, (kPrefillMinWaves<T, D>)) prefill_colsum_kernel(const PrefillArgs a, int nblk, int64_t units) {
     constexpr int EPV = ElemTraits<T>::kPerVec;
     constexpr int NG = D / (2 * EPV);
     using Stage = TileStage<T, D>;
     __shared__ __attribute__((aligned(16))) char qbuf[2][Stage::kBufBytes];
     __shared__ __attribute__((aligned(16))) float cbuf[2][kTile];     // the tile's row normalisers ...
     __shared__ __attribute__((aligned(16))) uint32_t rbuf[2][kTile];  // ... and row noise keys
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    __shared__ __attribute__((aligned(16))) float call[PARTS ? kPrefillMaxPartTiles * kTile : 4];     // all tiles'
+    __shared__ __attribute__((aligned(16))) uint32_t rall[PARTS ? kPrefillMaxPartTiles * kTile : 4];  // (PARTS)
+    const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int n0 = lane & 31, half = lane >> 5;
     int64_t u;
-    int cb;  // longest columns (lowest keys) first
-    unit_and_block(nblk, u, cb);
+    int cb, part;  // longest columns (lowest keys) first
+    unit_and_block(nblk, PARTS ? a.parts : 1, u, cb, part);
     if (u >= units) return;  // workgroup-uniform
     const int h = (int)(u % a.H), b = (int)((u / a.H) % a.B);
     const int n = a.seq_n ? a.seq_n[b] : a.n;  // this sequence's prompt length; rows n..a.n-1 are padding
     const bool first_of_group = (u % a.G) == 0;
     if (n < 1 || n > a.n) {  // workgroup-uniform: the unit is skipped and counted
-        if (cb == 0 && threadIdx.x == 0 && first_of_group) atomicAdd(a.ws_err, 1);
+        if (cb == 0 && part == 0 && threadIdx.x == 0 && first_of_group) atomicAdd(a.ws_err, 1);
         return;
     }
     if (cb == 0 && threadIdx.x == 0 && first_of_group) a.len[u / a.G] = n;
     if (cb * (4 * kTile) >= n) return;  // workgroup-uniform: the block lies in the padding
+    // this workgroup's query tiles it_end, it_end-1, .. it_first
+    const int it_end = (n - 1) / kTile - (PARTS ? part * a.part_tiles : 0);
+    const int it_first = PARTS ? max(cb * 4, it_end - a.part_tiles + 1) : cb * 4;
+    if (it_end < it_first) return;  // workgroup-uniform: the block has fewer parts
     const int j0 = cb * (4 * kTile) + wv * kTile;
     const bool active = j0 < n;  // wave-uniform; inactive waves still fetch tiles and meet the barriers
     const int j = j0 + n0;
@@ -368,92 +504,74 @@ __global__ void __launch_bounds__(kPrefillThreads) prefill_colsum_kernel(const P
     lp.inv_tau = a.inv_tau;
     lp.gz = -kLog2Ln2 * a.inv_tau;
     lp.noise = a.noise;
-    const uint32_t kmul = (uint32_t)j * kKposMul;  // this lane's key in every hash
+    const uint32_t kfold = fold16((uint32_t)j * kKposMul);  // this lane's key in every hash (row keys come folded)
     const float* wc = a.ws_c + (size_t)u * a.n_pad;
     const uint32_t* wr = a.ws_r + (size_t)u * a.n_pad;
 
     float colsum = 0.0f;
     const int it_begin = j0 / kTile;                    // this wave's first query tile (the diagonal one)
-    const int it_first = cb * 4, it_end = (n - 1) / kTile;  // the workgroup's range of query tiles
     // a tile's 32 row statistics ride with the tile: one wave fetches them (n_pad covers whole tiles)
-    uint4 stage[Stage::NP];
-    float c_st = 0.0f;
-    uint32_t r_st = 0u;
-    auto fetch_stats = [&](int it) {
-        if (threadIdx.x < kTile) {
-            c_st = wc[it * kTile + threadIdx.x];
-            r_st = wr[it * kTile + threadIdx.x];
-        }
+    struct Staged {
+        typename Stage::Regs rows;
+        float c;
+        uint32_t r;
     };
-    auto park_stats = [&](int buf) {
-        if (threadIdx.x < kTile) {
-            cbuf[buf][threadIdx.x] = c_st;
-            rbuf[buf][threadIdx.x] = r_st;
+    if constexpr (PARTS) {
+        // row statistics of all this workgroup's tiles, put together from pass 1's parts
+        const int row0 = it_first * kTile, rows = (it_end - it_first + 1) * kTile;
+        for (int r = threadIdx.x; r < rows; r += kPrefillThreads) {
+            const int i = row0 + r;  // rows from n on: left over, masked below
+            const float c = merged_normaliser(a.ws_part + (size_t)u * a.parts * a.n_pad + i, a.n_pad,
+                                              i < n ? (i / kTile) / a.part_tiles + 1 : 0);
+            call[r] = GUMBEL ? lp.gz - c : c;
+            rall[r] = i < n ? wr[i] : 0u;
+        }
+    }
+    auto fetch = [&](int it) {
+        Staged s;
+        s.rows = Stage::fetch(Qu, it * kTile, n);
+        s.c = 0.0f;
+        s.r = 0u;
+        if (!PARTS && threadIdx.x < kTile) {
+            s.c = wc[it * kTile + threadIdx.x];
+            s.r = wr[it * kTile + threadIdx.x];
+        }
+        return s;
+    };
+    auto park = [&](int buf, const Staged& s) {
+        Stage::park(qbuf[buf], s.rows);
+        if (!PARTS && threadIdx.x < kTile) {
+            cbuf[buf][threadIdx.x] = s.c;
+            rbuf[buf][threadIdx.x] = s.r;
         }
     };
     // The query tiles are walked from the LAST one down: every column block of a unit then starts at the same
     // tile and the blocks, which run at the same time on one XCD, ask its L2 for the same rows at about the
     // same time (walking up, each block starts at its own diagonal and the L2 sees 16 unrelated streams:
     // 2.7 GB instead of 1.0 GB fetched on the GPT-J-shaped workload).
-    Stage::fetch(Qu, it_end * kTile, n, stage);
-    fetch_stats(it_end);
-    Stage::park(qbuf[0], stage);
-    park_stats(0);
+    Staged stage = fetch(it_end);
+    park(0, stage);
     __syncthreads();
     for (int it = it_end; it >= it_first; --it) {
         const int cur = (it_end - it) & 1;
         // the next tile (the first one again at the end: rows stay in range), in flight during this tile's work
-        Stage::fetch(Qu, max(it - 1, it_first) * kTile, n, stage);
-        fetch_stats(max(it - 1, it_first));
+        stage = fetch(max(it - 1, it_first));
         if (active && it >= it_begin) {
             const char* qb = qbuf[cur];
-            f32x16 acc;
-#pragma unroll
-            for (int r = 0; r < 16; ++r) acc[r] = 0.0f;
-#pragma unroll
-            for (int g = 0; g < NG; ++g) acc = Mma<T>::group(Stage::operand(qb, n0, half, g), bk[g], acc);
+            const f32x16 acc = Stage::products(qb, n0, half, bk);
             const int ib = it * kTile;
+            const float* cs = PARTS ? call + (it - it_first) * kTile : cbuf[cur];
+            const uint32_t* rs = PARTS ? rall + (it - it_first) * kTile : rbuf[cur];
             const bool edge = (ib < j0 + kTile) || (ib + kTile > n);  // crosses the diagonal or the end of the prompt
-            float z[16];
-#pragma unroll
-            for (int q4 = 0; q4 < 4; ++q4) {
-                const int ir = ib + q4 * 8 + half * 4;  // 4 consecutive query rows
-                const float4 c4 = *(const float4*)&cbuf[cur][q4 * 8 + half * 4];
-                const uint4 r4 = *(const uint4*)&rbuf[cur][q4 * 8 + half * 4];
-                const float cs[4] = {c4.x, c4.y, c4.z, c4.w};
-                const uint32_t rs[4] = {r4.x, r4.y, r4.z, r4.w};
-                const float dist0 = (float)(ir - j);
-                if constexpr (GUMBEL) {
-                    // cs holds (adjustment's constant part - row normaliser): z = 2^(x2 - log2(t)/tau + cs)
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        const float l2t = hw_log2(neg_log2_uniform(mix32(rs[e] ^ kmul)));
-                        float t = fmaf(l2t, -lp.inv_tau, cs[e]);
-                        if (BIAS) t = fmaf(dist0 + (float)e, -lp.slope1, t);
-                        z[q4 * 4 + e] = hw_exp2(fmaf(acc[q4 * 4 + e], lp.sc1, t));
-                    }
-                } else {
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        const float y = logit2_other(lp, acc[q4 * 4 + e], dist0 + (float)e, rs[e], (uint32_t)j);
-                        z[q4 * 4 + e] = hw_exp2(y - cs[e]);
-                    }
-                }
-            }
             if (edge) {
-#pragma unroll
-                for (int r = 0; r < 16; ++r) {
-                    const int i = ib + (r >> 2) * 8 + half * 4 + (r & 3);
-                    z[r] = (i >= j && i < n) ? z[r] : 0.0f;
-                }
+                int first = ib + half * 4;  // (the empty asm keeps the masking compares inside this branch, as in pass 1)
+                asm volatile("" : "+v"(first));
+                colsum += column_sum<GUMBEL, BIAS, true>(lp, acc, cs, rs, first, half, j, kfold, n);
+            } else {
+                colsum += column_sum<GUMBEL, BIAS, false>(lp, acc, cs, rs, ib + half * 4, half, j, kfold, n);
             }
-#pragma unroll
-            for (int r = 0; r < 16; ++r) colsum += z[r];
         }
-        if (it > it_first) {
-            Stage::park(qbuf[cur ^ 1], stage);
-            park_stats(cur ^ 1);
-        }
+        if (it > it_first) park(cur ^ 1, stage);
         __syncthreads();
     }
     if (!active) return;
@@ -461,14 +579,16 @@ __global__ void __launch_bounds__(kPrefillThreads) prefill_colsum_kernel(const P
     if (half == 0 && j < n) {
         // one query head per cached head: the column sum is the score; else the heads' sums are
         // added up by the launch that follows
-        if (a.G == 1) a.score[(size_t)u * a.cap + j] = colsum;
+        if (PARTS) a.ws_f[((size_t)u * a.parts + part) * a.n_pad + j] = colsum;
+        else if (a.G == 1) a.score[(size_t)u * a.cap + j] = colsum;
         else a.ws_f[(size_t)u * a.n_pad + j] = colsum;
-        if (first_of_group) a.pos[(size_t)(u / a.G) * a.cap + j] = j;
+        if (first_of_group && part == 0) a.pos[(size_t)(u / a.G) * a.cap + j] = j;
     }
 }
 
-// Grouped-query attention: the score of a cached head is the sum of its query heads' column sums
-// (added in head order, so the result does not depend on scheduling).
+// Grouped-query attention: the score of a cached head is the sum of its query heads' column sums; a column
+// block walked in parts: the sum of its parts' (added in head order, then part order, so the result does not
+// depend on scheduling).
 __global__ void __launch_bounds__(256) prefill_group_sum_kernel(const PrefillArgs a, int64_t kv_units) {
     const int64_t u = blockIdx.x;
     const int j = blockIdx.y * 256 + threadIdx.x;
@@ -476,31 +596,59 @@ __global__ void __launch_bounds__(256) prefill_group_sum_kernel(const PrefillArg
     const int hkv = a.H / a.G, b = (int)((u / hkv) % a.B);
     const int n = a.seq_n ? a.seq_n[b] : a.n;
     if (n > a.n || j >= n) return;
+    // parts of this column's block: its query tiles run from the prompt's last one down to the block's first
+    const int tiles = (n - 1) / kTile + 1 - j / (4 * kTile) * 4;
+    const int parts = a.parts > 1 ? (tiles + a.part_tiles - 1) / a.part_tiles : 1;
     float s = 0.0f;
-    for (int g = 0; g < a.G; ++g) s += a.ws_f[((size_t)u * a.G + g) * a.n_pad + j];
+    for (int g = 0; g < a.G; ++g)
+#pragma unroll 4
+        for (int p = 0; p < parts; ++p) s += a.ws_f[(((size_t)u * a.G + g) * a.parts + p) * a.n_pad + j];
     a.score[(size_t)u * a.cap + j] = s;
+}
+
+// How the tile walks of a launch's 128-row blocks are cut.  A block's walk is serial, up to n/32 tiles, and the
+// blocks of a unit are of all lengths: with few units the launch lasts as long as the longest block while most of
+// the chip has run out of work (16 heads x 2048 tokens: 136 blocks' worth of work in 256 workgroups, 88 us a pass
+// for 10 us of arithmetic).  Below kPrefillPartsRowLimit rows in all the walks are cut
+// into parts of equal length, one workgroup each, so that about kPrefillPartsWanted workgroups have work: 16 heads x
+// 2048 rows x 256 168 -> 98 us (both passes), 16 x 4096 x 128 397 -> 228, 64 x 2048 x 256 359 -> 273; wanting 768 to
+// 3072 workgroups measured within 20 %, fewer or more slower.  Above the limit the longest walk is a small share of
+// the launch and the parts' records would only cost.
+constexpr int64_t kPrefillPartsWanted = 1536;
+constexpr int64_t kPrefillMinPartTiles = 4;
+PrefillParts plan_prefill(int64_t U, int32_t n) {
+    const int64_t nblk = (n + 4 * kTile - 1) / (4 * kTile);
+    if (U * 4 * kTile * nblk >= kPrefillPartsRowLimit) return kPrefillWhole;
+    const int64_t steps = U * nblk * (nblk + 1) / 2 * 4;  // tiles walked by all blocks
+    int64_t tiles = (steps + kPrefillPartsWanted - 1) / kPrefillPartsWanted;
+    if (tiles < kPrefillMinPartTiles) tiles = kPrefillMinPartTiles;
+    if (tiles > kPrefillMaxPartTiles) tiles = kPrefillMaxPartTiles;
+    const int64_t parts = (nblk * 4 + tiles - 1) / tiles;
+    if (parts <= 1 || parts > kPrefillMaxParts) return kPrefillWhole;
+    return {(int32_t)parts, (int32_t)tiles};
+}
+
+template <typename T, int D, bool GUMBEL, bool BIAS>
+static hipError_t launch_passes(const PrefillArgs& a, int64_t U, hipStream_t st) {
+    const int nblk = (a.n + 4 * kTile - 1) / (4 * kTile);
+    const int64_t groups = (U + kXcds - 1) / kXcds;  // units are dealt to XCDs in groups of 8
+    const dim3 grid((unsigned)(groups * kXcds * nblk * a.parts)), block(kPrefillThreads);
+    hipLaunchKernelGGL((prefill_rowstats_kernel<T, D, GUMBEL, BIAS>), grid, block, 0, st, a, nblk, U);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    if (a.parts > 1) hipLaunchKernelGGL((prefill_colsum_kernel<T, D, GUMBEL, BIAS, true>), grid, block, 0, st, a, nblk, U);
+    else hipLaunchKernelGGL((prefill_colsum_kernel<T, D, GUMBEL, BIAS, false>), grid, block, 0, st, a, nblk, U);
+    return hipGetLastError();
 }
 
 template <typename T, int D>
 static hipError_t launch_prefill_t(const PrefillArgs& a, int64_t U, hipStream_t st) {
-    const int nblk = (a.n + 4 * kTile - 1) / (4 * kTile);
-    const int64_t groups = (U + kXcds - 1) / kXcds;  // units are dealt to XCDs in groups of 8
-    const dim3 grid((unsigned)(groups * kXcds * nblk)), block(kPrefillThreads);
     // four builds of each pass: the Gumbel adjustment in the trimmed form or any adjustment in the plain form,
     // with or without the position-bias term
     const bool gum = a.noise == kNoiseGumbel, bias = a.slopes != nullptr;
-    if (gum && bias) hipLaunchKernelGGL((prefill_rowstats_kernel<T, D, true, true>), grid, block, 0, st, a, nblk, U);
-    else if (gum) hipLaunchKernelGGL((prefill_rowstats_kernel<T, D, true, false>), grid, block, 0, st, a, nblk, U);
-    else if (bias) hipLaunchKernelGGL((prefill_rowstats_kernel<T, D, false, true>), grid, block, 0, st, a, nblk, U);
-    else hipLaunchKernelGGL((prefill_rowstats_kernel<T, D, false, false>), grid, block, 0, st, a, nblk, U);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    if (gum && bias) hipLaunchKernelGGL((prefill_colsum_kernel<T, D, true, true>), grid, block, 0, st, a, nblk, U);
-    else if (gum) hipLaunchKernelGGL((prefill_colsum_kernel<T, D, true, false>), grid, block, 0, st, a, nblk, U);
-    else if (bias) hipLaunchKernelGGL((prefill_colsum_kernel<T, D, false, true>), grid, block, 0, st, a, nblk, U);
-    else hipLaunchKernelGGL((prefill_colsum_kernel<T, D, false, false>), grid, block, 0, st, a, nblk, U);
-    e = hipGetLastError();
-    if (e != hipSuccess || a.G == 1) return e;
+    hipError_t e = gum ? (bias ? launch_passes<T, D, true, true>(a, U, st) : launch_passes<T, D, true, false>(a, U, st))
+                       : (bias ? launch_passes<T, D, false, true>(a, U, st) : launch_passes<T, D, false, false>(a, U, st));
+    if (e != hipSuccess || (a.G == 1 && a.parts == 1)) return e;
     hipLaunchKernelGGL(prefill_group_sum_kernel, dim3((unsigned)(U / a.G), (unsigned)((a.n + 255) / 256)), dim3(256), 0,
                        st, a, U / a.G);
     return hipGetLastError();

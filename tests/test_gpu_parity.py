@@ -1261,6 +1261,47 @@ def test_grouped_query_prefill_matches_oracle(dtype, d, G, n):
     assert_close_score(host(gc.score), oc.score, oc.len, "grouped prefill score", rtol=SCORE_RTOL_PREFILL)
 
 
+@pytest.mark.parametrize("dtype,d,G,n,noise,biased", [
+    (ko.BF16, 128, 1, 129, ko.NOISE_GUMBEL, False), (ko.BF16, 128, 2, 257, ko.NOISE_GUMBEL, True),
+    (ko.F16, 256, 1, 513, ko.NOISE_GUMBEL, True), (ko.F32, 64, 1, 640, ko.NOISE_GAUSSIAN, False),
+    (ko.BF16, 64, 4, 1000, ko.NOISE_NONE, True), (ko.F32, 128, 1, 384, ko.NOISE_GUMBEL, False)])
+def test_prefill_in_parts_and_whole_match_oracle(dtype, d, G, n, noise, biased):
+    """Few units: the blocks' tile walks are cut into parts, whose records take workspace.  A workspace without
+    room for them is served by whole walks; both against the oracle, at lengths next to the blocks' edges and with
+    sequences of different lengths."""
+    rng = np.random.default_rng(9300 + d + n)
+    L, B, H = 1, 3, 2
+    n_seq = np.array([n, max(1, n - 128), n // 2 + 1], np.int32)
+    oc = random_cache(rng, L, B, H, d, n + 3, dtype, 0)
+    Q = rnd(rng, (L, B, H * G, n, d), dtype)
+    seeds = np.array([5, 6, 7], np.uint64)
+    slopes = (0.5 ** np.arange(1, H * G + 1)).astype(np.float32) if biased else None
+    scale = float(1.0 / np.sqrt(np.float32(d)))
+    gc = upload(oc, G)
+    dQ, dseeds, dslopes, dn = dev(Q), dev(seeds), dev(slopes) if biased else None, dev(n_seq)
+    oc.prefill_score(Q, n, 1.0, scale, noise, seeds, slopes, q_per_kv=G, n_seq=n_seq)
+    ws = kf.new_workspace(gc, n)
+
+    def run(nbytes):
+        gc.score.fill_(-1.0)
+        kf.kf_prefill_score(gc, dQ, n, 1.0, scale, noise, dseeds, dslopes, ws[:nbytes], seq_n=dn)
+        torch.cuda.synchronize()
+        np.testing.assert_array_equal(host(gc.len), oc.len)
+        assert_close_score(host(gc.score), oc.score, oc.len, "prefill score, %d bytes" % nbytes, rtol=SCORE_RTOL_PREFILL)
+
+    run(ws.numel())
+    lo, hi = 0, ws.numel()  # the smallest workspace that is accepted
+    while hi - lo > 256:
+        mid = (lo + hi) // 512 * 256
+        try:
+            kf.kf_prefill_score(gc, dQ, n, 1.0, scale, noise, dseeds, dslopes, ws[:mid], seq_n=dn)
+            hi = mid
+        except kf.KeyformerError:
+            lo = mid
+    assert hi < ws.numel()
+    run(hi)
+
+
 @pytest.mark.parametrize("G,shared,layout", [(4, False, kf.LAYOUT_ORDERED), (2, True, kf.LAYOUT_ORDERED),
                                             (8, False, kf.LAYOUT_SLOT)])
 def test_grouped_query_lockstep(G, shared, layout):

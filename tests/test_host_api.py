@@ -200,6 +200,14 @@ def test_unknown_score_mode_is_rejected():
            None, 0x5000, WS, 0, score_mode=2)
 
 
+def test_workspace_for_long_prompts_suffices_for_shorter_ones():
+    # a short prompt of few units is scored in parts and takes more per row than a long one
+    for L, B, H, g in ((1, 1, 16, 1), (1, 1, 1, 1), (2, 4, 8, 4), (28, 1, 16, 1)):
+        c = fake_cache(L=L, B=B, H=H, cap=40000, q_per_kv=g)
+        sizes = [kf.kf_workspace_bytes(c, n) for n in (0, 1, 127, 128, 129, 1000, 1024, 2048, 4000, 9000, 16384, 33000, 40000)]
+        assert all(a <= b for a, b in zip(sizes, sizes[1:])), (L, B, H, g, sizes)
+
+
 def test_query_group_validation_and_sizes():
     for g in (3, 5, 16):
         expect(binding.KF_EUNSUPPORTED, kf.kf_select_evict, fake_cache(q_per_kv=g), 8, 2, None, WS, 0)
