@@ -37,6 +37,12 @@ constexpr int64_t kMaxGrid = 0x7fffffff;  // workgroups of a one-dimensional lau
 constexpr int64_t kTailMergeMaxTokens = 4096;
 constexpr int64_t kWideMaxUnits = 256;
 constexpr int32_t kPreselMinTokens = 4096;
+// A step of at most this many units is bound by the chain of memory round trips through its launches, not by bytes:
+// its splits are short, ask for everything at once, and (ordered layout) one launch merges, selects and moves the
+// rows instead of two.  28 layers of 16 heads, d = 256, k = 1024, a call each: 646 -> 466 us per token (slot layout
+// 499 -> 447); 32 heads x 1024 x 128 24 -> 19 us, 64 x 2048 x 128 32.4 -> 28.3, 128 x 2048 x 128 48.5 -> 47.4 us;
+// with 256 units the repeated merging costs what the saved launch gains.
+constexpr int64_t kFewMaxUnits = 128;
 
 bool supported(int32_t dtype, int32_t d) {
     if (dtype == KF_BF16 || dtype == KF_F16) return d == 64 || d == 128 || d == 256;
@@ -93,6 +99,8 @@ kf_status check_cfg(const kf_score_cfg* cfg) {
 //              (G = query heads per cached head)
 struct WsLayout {
     size_t region, fused_idx, wide, total;  // wide: boundary entries of the two-launch ordered eviction
+    size_t few_bytes;                       // behind total: records and old scores of a step of few units; a
+                                            // workspace without them is served by the other launches
     int32_t nb;                             // boundary slots per unit
 };
 
@@ -105,6 +113,11 @@ size_t decode_region(int64_t U, const kf_cache* c) {
     const kf::DecodePlan p = kf::plan_decode(U, c->cap, c->d, c->dtype, G);
     return align_up((size_t)U * p.S * G * (c->d + 4) * sizeof(float), 256) +
            align_up((size_t)U * G * c->cap * sizeof(float), 256) + align_up((size_t)U * sizeof(int32_t), 256);
+}
+
+// Split records of a step of few units.
+size_t few_records(int64_t U, const kf_cache* c) {
+    return wide_part((size_t)U * kf::few_max_splits(U) * group_of(c) * (c->d + 4) * sizeof(float));
 }
 
 size_t prefill_region(int64_t UQ, size_t n_pad, int32_t G, int32_t parts) {
@@ -133,7 +146,19 @@ WsLayout ws_layout(const kf_cache* c, int32_t n_max, int32_t parts = 1) {
     w.total = w.wide + wide_part((size_t)U * 4) + wide_part((size_t)U * w.nb * 2 * row_bytes) +
               2 * wide_part((size_t)U * w.nb * 4) + wide_part((size_t)U * kf::kPreselMaxSlices * 8) +
               wide_part((size_t)U * kf::kPreselMaxSlices * 4);
+    w.few_bytes = 0;
+    if (U <= kFewMaxUnits && c->cap < kPreselMinTokens)
+        w.few_bytes = few_records(U, c) + wide_part((size_t)U * c->cap * 4);
     return w;
+}
+
+// Whether a decode step of up to m tokens takes the form for few units, and the splits it then has.
+bool few_plan(const kf_cache* c, const WsLayout& w, size_t workspace_bytes, int32_t m, kf::DecodePlan* plan) {
+    if (w.few_bytes == 0 || workspace_bytes - w.few_bytes < w.total || workspace_bytes < w.few_bytes) return false;
+    const kf::DecodePlan p = kf::plan_decode_few((int64_t)c->L * c->B * c->H, m, c->d, c->dtype, group_of(c));
+    if (p.S < 2 || p.chunk > kf::kFewMaxChunk) return false;
+    *plan = p;
+    return true;
 }
 
 // Whether the two-launch ordered eviction is the faster one for U units of budget k.
@@ -197,14 +222,15 @@ size_t kf_workspace_bytes(const kf_cache* c, int32_t n_max) {
     if (!c || c->L < 1 || c->B < 1 || c->H < 1 || c->cap < 1 || !supported(c->dtype, c->d)) return 0;
     if (!group_supported(c->q_per_kv)) return 0;
     if (n_max < 0) n_max = 0;
-    size_t total = ws_layout(c, n_max).total;
+    const WsLayout w0 = ws_layout(c, n_max);
+    size_t total = w0.total + w0.few_bytes;
     // a shorter prompt may be scored in parts and then need more: the most that any length up to n_max takes
     const int64_t UQ = (int64_t)c->L * c->B * c->H * group_of(c);
     for (int64_t n = kf::kPrefillRowPad; UQ * n < kf::kPrefillPartsRowLimit; n += kf::kPrefillRowPad) {
         const int32_t len = n < n_max ? (int32_t)n : n_max;
         if (len > 0) {
-            const size_t t = ws_layout(c, len, kf::plan_prefill(UQ, len).parts).total;
-            if (t > total) total = t;
+            const WsLayout w = ws_layout(c, len, kf::plan_prefill(UQ, len).parts);
+            if (w.total > total) total = w.total;
         }
         if (n >= n_max) break;
     }
@@ -219,8 +245,10 @@ kf_status kf_decode_launch_shape(const kf_cache* c, int32_t m_hint, int32_t* spl
     if (m_hint < 0 || m_hint > c->cap) return fail(KF_EINVAL, "m_hint %d outside [0, cap=%d]", m_hint, c->cap);
     if (!group_supported(c->q_per_kv))
         return fail(KF_EUNSUPPORTED, "%d query heads per cached head is not built", c->q_per_kv);
-    const kf::DecodePlan p =
-        kf::plan_decode((int64_t)c->L * c->B * c->H, m_hint ? m_hint : c->cap, c->d, c->dtype, group_of(c));
+    const int32_t m = m_hint ? m_hint : c->cap;
+    kf::DecodePlan p;
+    if (!few_plan(c, ws_layout(c, 0), SIZE_MAX, m, &p))
+        p = kf::plan_decode((int64_t)c->L * c->B * c->H, m, c->d, c->dtype, group_of(c));
     *splits = p.S;
     *chunk = p.chunk;
     return KF_OK;
@@ -314,10 +342,12 @@ static kf_status prepare_decode(kf_cache* c, const void* q, const void* k_new, c
 
     const int64_t U = (int64_t)c->L * c->B * c->H;
     const int32_t G = group_of(c);
-    const kf::DecodePlan p = kf::plan_decode(U, m_hint, c->d, c->dtype, G);
+    kf::DecodePlan p;
+    a->few = few_plan(c, w, workspace_bytes, m_hint, &p) ? 1 : 0;
+    if (!a->few) p = kf::plan_decode(U, m_hint, c->d, c->dtype, G);
     // the partial-record region is sized for the plan at m = cap, the largest
     const kf::DecodePlan pmax = kf::plan_decode(U, c->cap, c->d, c->dtype, G);
-    if (p.S > pmax.S) return fail(KF_EWORKSPACE, "internal: split count %d exceeds the sized %d", p.S, pmax.S);
+    if (!a->few && p.S > pmax.S) return fail(KF_EWORKSPACE, "internal: split count %d exceeds the sized %d", p.S, pmax.S);
     if (U * p.S > kMaxGrid)
         return fail(KF_EUNSUPPORTED, "%lld units in %d splits each exceed the largest launch", (long long)U, p.S);
     a->K = c->K;
@@ -332,7 +362,7 @@ static kf_status prepare_decode(kf_cache* c, const void* q, const void* k_new, c
     a->seeds = cfg->seeds;
     a->slopes = cfg->alibi_slopes;
     a->ws_err = (int32_t*)workspace + KF_WS_ERROR_WORD;
-    a->ws_part = (float*)((char*)workspace + w.region);
+    a->ws_part = (float*)((char*)workspace + (a->few ? w.total : w.region));
     a->ws_e =
         (float*)((char*)workspace + w.region + align_up((size_t)U * pmax.S * G * (c->d + 4) * sizeof(float), 256));
     a->ws_m = (int32_t*)((char*)a->ws_e + align_up((size_t)U * G * c->cap * sizeof(float), 256));
@@ -366,6 +396,10 @@ static kf_status prepare_decode(kf_cache* c, const void* q, const void* k_new, c
     a->dtau = 0.0f;
     a->inv_tau = 1.0f / cfg->tau;
     a->scale = cfg->scale;
+    a->few_rows = a->few_nb = 0;
+    a->few_f = nullptr;
+    a->few_brow = nullptr;
+    a->few_bpos = nullptr;
     *plan = p;
     return KF_OK;
 }
@@ -586,6 +620,16 @@ static kf_status fused_step(kf_cache* c, const void* q, const void* k_new, const
         e = kf::launch_decode(da, U, c->d, c->dtype, p.lds_bytes, (hipStream_t)stream);
         if (e == hipSuccess) e = share_after_decode(c, da, (hipStream_t)stream);
         if (e == hipSuccess) e = kf::launch_select(sa, U, (hipStream_t)stream);
+    } else if (da.few && layout == KF_LAYOUT_ORDERED) {
+        // few units: two launches, each a single round of workgroups that ask for all they need at once
+        da.few_rows = sa.chunk_rows;
+        da.few_nb = sa.nb;
+        da.few_f = (float*)((char*)da.ws_part + few_records(U, c));
+        da.few_brow = sa.ws_brow;
+        da.few_bpos = sa.ws_bpos;
+        sa.wide = 0;  // of the units that take the general way
+        e = kf::launch_decode_split(da, U, c->d, c->dtype, p.lds_bytes, (hipStream_t)stream);
+        if (e == hipSuccess) e = kf::launch_step_finish(da, sa, U, c->d, (hipStream_t)stream);
     } else if (da.S > 1 && (int64_t)da.S * da.chunk <= kTailMergeMaxTokens && !sa.presel) {
         // few units in splits: the merge rides in the selection launch, whatever the number of query heads
         if (layout == KF_LAYOUT_SLOT || sa.wide) {

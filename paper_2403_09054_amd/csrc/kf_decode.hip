@@ -117,21 +117,6 @@ __device__ __forceinline__ void halve(const float (&in)[N], float (&out)[N / 2],
     }
 }
 
-// Wave-wide max / sum: the data-parallel moves fold a 16-lane row, two exchanges through the LDS crossbar
-// (lane ^ 16, lane ^ 32) fold the four rows.  Every lane ends up with the result.
-__device__ __forceinline__ float wave_max_fast(float v) {
-    v = fmaxf(v, dpp_move<0xB1>(v));
-    v = fmaxf(v, dpp_move<0x4E>(v));
-    v = fmaxf(v, dpp_move<0x141>(v));
-    v = fmaxf(v, dpp_move<0x140>(v));
-    v = fmaxf(v, __builtin_bit_cast(float, __builtin_amdgcn_ds_swizzle(__builtin_bit_cast(int, v), 0x401F)));
-    return fmaxf(v, __shfl_xor(v, 32, kWave));
-}
-__device__ __forceinline__ float wave_sum_fast(float v) {
-    v = group_sum<32>(v);
-    return v + __shfl_xor(v, 32, kWave);
-}
-
 typedef _Float16 f16x2_t __attribute__((ext_vector_type(2)));
 template <>
 struct QueryPiece<f16_t> {
@@ -155,7 +140,7 @@ __device__ __forceinline__ void block_sum_n(float (&v)[N], float* red) {
     constexpr int NW = NT / 64;
     constexpr bool kTwoLevel = N * NW > 32;
 #pragma unroll
-    for (int i = 0; i < N; ++i) v[i] = kTwoLevel ? wave_sum_fast(v[i]) : wave_sum(v[i]);
+    for (int i = 0; i < N; ++i) v[i] = wave_sum(v[i]);
     __syncthreads();
     if ((threadIdx.x & 63) == 0) {
 #pragma unroll
@@ -255,10 +240,21 @@ __device__ __forceinline__ float joined_weight(uint32_t w) {
     return __uint_as_float(w & 0xFFFF0000u) + __uint_as_float(w << 16);
 }
 
+// First chunk-boundary slot of a split that starts at row jf (slot 0 is no boundary).
+__device__ __forceinline__ int few_boundary(const DecodeArgs& a, int jf) {
+    return max(1, (jf + a.few_rows - 1) / a.few_rows) * a.few_rows;
+}
+
 // One workgroup streams the cache rows [j0, j1) of one cached head ("unit") once
 // and serves the G query heads that read it (G = 1: ordinary multi-head
 // attention; G > 1: grouped-query attention, query head hq = h*G + g).
-template <typename T, int D, int NT, int G>
+//
+// FEW: the form for splits of a small launch (a few units: one sequence, one layer).  Such a launch is a single
+// wave of workgroups whose time is the chain of memory round trips in it, so everything a workgroup may need is
+// asked for at once, before the unit's length is known: its first K and V tiles, the old scores of its tokens and
+// the rows at the chunk boundaries of the eviction that follows (see step_finish_kernel).  Rows past the unit's
+// length are read (they lie in the unit's own cache) and dropped.
+template <typename T, int D, int NT, int G, bool FEW>
 __device__ __forceinline__ void decode_block(const DecodeArgs& a) {
     constexpr int EPV = ElemTraits<T>::kPerVec;  // elements per 16-byte vector
     constexpr int LPR = D / EPV;                 // lanes that share one row
@@ -289,9 +285,66 @@ __device__ __forceinline__ void decode_block(const DecodeArgs& a) {
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     const int sub = lane / LPR, cl = lane % LPR;
     const int S = a.S;
-    const int64_t u = blockIdx.x / S;
-    const int s = blockIdx.x % S;
-    const int h = (int)(u % a.H), b = (int)((u / a.H) % a.B), l = a.layer0 + (int)(u / ((int64_t)a.H * a.B));
+    // (the grid is below 2^31 workgroups: 32-bit divisions)
+    const uint32_t ui = blockIdx.x / (uint32_t)S, lb = ui / (uint32_t)a.H;
+    const int64_t u = ui;
+    const int s = (int)(blockIdx.x - ui * (uint32_t)S);
+    const int h = (int)(ui - lb * (uint32_t)a.H), b = (int)(lb % (uint32_t)a.B), l = a.layer0 + (int)(lb / (uint32_t)a.B);
+    const bool rnd_l = (a.noise == kNoiseGumbel || a.noise == kNoiseGaussian);
+    const uint64_t seed_b = rnd_l ? a.seeds[b] : 0;
+
+    const char* Ku = (const char*)a.K + (size_t)u * a.cap * ROWB;
+    const char* Vu = (const char*)a.V + (size_t)u * a.cap * ROWB;
+    const T* qu = (const T*)a.q + (size_t)u * G * D;
+    const char* knew = (const char*)a.k_new + (size_t)u * ROWB;
+    const char* vnew = (const char*)a.v_new + (size_t)u * ROWB;
+    float* fu = a.score + (size_t)u * a.cap;
+    int32_t* pu = a.pos + (size_t)u * a.cap;
+
+    if constexpr (FEW)  // all arguments at once: fetched where they are first used, each line is a wait of its own
+        asm volatile("" ::"s"(a.K), "s"(a.q), "s"(a.len), "s"(a.seeds), "s"(a.slopes), "s"(a.step), "s"(a.ws_part),
+                     "s"(a.q_pos), "s"(a.fuse_k), "s"(a.seq_q_pos), "s"(a.seq_tau), "s"(a.inv_tau), "s"(a.few_f));
+    uint4 cur[UNR], nxt[UNR];
+    uint4 vfirst[FEW ? UNR : 1];
+    float f_old[FEW ? kFewTokens : 1];
+    uint4 brow[FEW ? kFewPieces : 1];
+    int32_t bpos = 0;
+    constexpr int NV = G * UNR, VPL = (NV + LPR - 1) / LPR;  // logits a lane adjusts per tile, see phase 1
+    uint4 qraw[FEW ? G : 1];
+    int pfirst[FEW ? VPL : 1];
+    const int jf = s * a.chunk;  // first row of the split
+    if constexpr (FEW) {
+        auto load_first = [&](const char* rows, uint4(&raw)[UNR]) {
+#pragma unroll
+            for (int i = 0; i < UNR; ++i) {
+                const int j = min(jf + wv * RPW + i * RPB + sub, a.cap - 1);
+                raw[i] = stream_load((const uint4*)(rows + (size_t)j * ROWB + (size_t)cl * 16));
+            }
+        };
+        if constexpr (!MfmaLogits<T, G>::value) load_first(Ku, cur);
+        load_first(Vu, vfirst);
+        if constexpr (!MfmaLogits<T, G>::value) {
+#pragma unroll
+            for (int g = 0; g < G; ++g) qraw[g] = ((const uint4*)(qu + (size_t)g * D))[cl];
+#pragma unroll
+            for (int r = 0; r < VPL; ++r)
+                pfirst[r] = pu[min(jf + wv * RPW + min(cl / G + r * (LPR / G), UNR - 1) * RPB + sub, a.cap - 1)];
+        }
+        if (a.few_f) {
+#pragma unroll
+            for (int i = 0; i < kFewTokens; ++i) f_old[i] = fu[min(jf + tid + i * NT, a.cap - 1)];
+            // boundary rows R, 2R, ... of this split: piece p is 16 bytes of K (first half of the pieces) or V
+#pragma unroll
+            for (int i = 0; i < kFewPieces; ++i) {
+                const int p = tid + i * NT, row = few_boundary(a, jf) + p / (2 * LPR) * a.few_rows;
+                brow[i] = make_uint4(0u, 0u, 0u, 0u);
+                if (row < min(jf + a.chunk, a.cap))
+                    brow[i] = *(const uint4*)((p % (2 * LPR) < LPR ? Ku : Vu) + (size_t)row * ROWB + (size_t)(p % LPR) * 16);
+            }
+            const int row = few_boundary(a, jf) + tid * a.few_rows;
+            if (row < min(jf + a.chunk, a.cap)) bpos = pu[row];
+        }
+    }
 
     // query position and temperature of this step: from the host, or from the device step counter
     // (same fp32 operations, in the same order, as the host's schedule function)
@@ -330,14 +383,6 @@ __device__ __forceinline__ void decode_block(const DecodeArgs& a) {
     const bool owner = (s == S - 1);
     const int cnt = cnt_c + (owner ? 1 : 0);
 
-    const char* Ku = (const char*)a.K + (size_t)u * a.cap * ROWB;
-    const char* Vu = (const char*)a.V + (size_t)u * a.cap * ROWB;
-    const T* qu = (const T*)a.q + (size_t)u * G * D;
-    const char* knew = (const char*)a.k_new + (size_t)u * ROWB;
-    const char* vnew = (const char*)a.v_new + (size_t)u * ROWB;
-    float* fu = a.score + (size_t)u * a.cap;
-    int32_t* pu = a.pos + (size_t)u * a.cap;
-
     // Whole-step launch (S == 1): a unit exactly one token over its budget evicts in this launch, and the
     // new token then goes straight into the freed slot instead of being appended first.
     const bool over = a.fuse_k > 0 && m > a.fuse_k;
@@ -374,8 +419,6 @@ __device__ __forceinline__ void decode_block(const DecodeArgs& a) {
     };
 
     // ---- phase 1: stream K (next tile in flight while this one is reduced), logits into LDS
-    uint4 cur[UNR], nxt[UNR];
-    const bool rnd_l = (a.noise == kNoiseGumbel || a.noise == kNoiseGaussian);
     if constexpr (MfmaLogits<T, G>::value) {
         if constexpr (D >= 128) {
             // Rows of 256 bytes and more.  An MFMA row slot holds a QUARTER of a cache row: slot i = 4*r + s
@@ -410,7 +453,7 @@ __device__ __forceinline__ void decode_block(const DecodeArgs& a) {
             for (int hh = 0; hh < 2; ++hh) {
                 const int hq = h * G + hh * 4 + r4;
                 slope_l[hh] = a.slopes ? a.slopes[hq] : 0.0f;
-                rkey_l[hh] = rnd_l ? row_key(unit_key(a.seeds[b], (uint32_t)l, (uint32_t)hq), (uint32_t)q_pos) : 0u;
+                rkey_l[hh] = rnd_l ? row_key(unit_key(seed_b, (uint32_t)l, (uint32_t)hq), (uint32_t)q_pos) : 0u;
             }
             float mx_l[2] = {-INFINITY, -INFINITY}, my_l[2] = {-INFINITY, -INFINITY};
             // rows past the split re-read its last row (the address stays inside the cache); their logits are dropped
@@ -510,7 +553,7 @@ __device__ __forceinline__ void decode_block(const DecodeArgs& a) {
             const int g_l = mrow & (G - 1), r_l = (mrow >= G) ? 2 : 0;
             const int hq_l = h * G + g_l;
             const float slope_l = a.slopes ? a.slopes[hq_l] : 0.0f;
-            const uint32_t rkey_l = rnd_l ? row_key(unit_key(a.seeds[b], (uint32_t)l, (uint32_t)hq_l), (uint32_t)q_pos) : 0u;
+            const uint32_t rkey_l = rnd_l ? row_key(unit_key(seed_b, (uint32_t)l, (uint32_t)hq_l), (uint32_t)q_pos) : 0u;
             float mx_l = -INFINITY, my_l = -INFINITY;
             // rows past the split re-read its last row (the address stays inside the cache); their logits are dropped
             auto load_rows = [&](int base, uint4(&raw)[KK], int(&pos2)[2]) {
@@ -575,7 +618,7 @@ __device__ __forceinline__ void decode_block(const DecodeArgs& a) {
     } else {
         QueryPiece<T> qp[G];
 #pragma unroll
-        for (int g = 0; g < G; ++g) qp[g].load(((const uint4*)(qu + (size_t)g * D))[cl]);
+        for (int g = 0; g < G; ++g) qp[g].load(FEW ? qraw[FEW ? g : 0] : ((const uint4*)(qu + (size_t)g * D))[cl]);
 
         // After the lane-group sums every lane of a row holds all G x UNR logits of its row group.  Lane cl
         // keeps those numbered cl, cl + LPR, ...: number v is head v % G (always cl % G: one head per lane) of
@@ -583,12 +626,11 @@ __device__ __forceinline__ void decode_block(const DecodeArgs& a) {
         // next tile is in flight -- the vector units have time to spare during the K stream, and the statistics
         // pass after it (one more sweep over all logits with the memory pipeline empty, all workgroups of a
         // small launch at the same time) shrinks to the two running maxima kept per lane.
-        constexpr int NV = G * UNR, VPL = (NV + LPR - 1) / LPR;
         static_assert(LPR % G == 0, "a lane's logits belong to one head");
         const int g_l = cl % G, i_l = cl / G;
         const int hq_l = h * G + g_l;
         const float slope_l = a.slopes ? a.slopes[hq_l] : 0.0f;
-        const uint32_t rkey_l = rnd_l ? row_key(unit_key(a.seeds[b], (uint32_t)l, (uint32_t)hq_l), (uint32_t)q_pos) : 0u;
+        const uint32_t rkey_l = rnd_l ? row_key(unit_key(seed_b, (uint32_t)l, (uint32_t)hq_l), (uint32_t)q_pos) : 0u;
         float mx_l = -INFINITY, my_l = -INFINITY;
         int pcur[VPL], pnxt[VPL];
         // positions of this lane's rows of the tile at `base` (rows past the split: its last row, dropped later)
@@ -636,8 +678,13 @@ __device__ __forceinline__ void decode_block(const DecodeArgs& a) {
         {
             int base = base0;
             if (base < j1) {
-                load_tile(Ku, base, cur);
-                load_pos(base, pcur);
+                if constexpr (FEW) {
+#pragma unroll
+                    for (int r = 0; r < VPL; ++r) pcur[r] = pfirst[r];
+                } else {
+                    load_tile(Ku, base, cur);
+                    load_pos(base, pcur);
+                }
             }
             // steady state: the next tile needs no bounds checks, so the loop body is
             // branch-free and only the older tile's loads are waited for
@@ -667,8 +714,8 @@ __device__ __forceinline__ void decode_block(const DecodeArgs& a) {
         // per head, the wave's maxima; row NW of the table takes the new token's own logits, or nothing
 #pragma unroll
         for (int g = 0; g < G; ++g) {
-            const float mx = wave_max_fast(g == g_l ? mx_l : -INFINITY);
-            const float my = wave_max_fast(g == g_l ? my_l : -INFINITY);
+            const float mx = wave_max(g == g_l ? mx_l : -INFINITY);
+            const float my = wave_max(g == g_l ? my_l : -INFINITY);
             if (lane == 0) {
                 red_s[2 * G * wv + 2 * g] = mx;
                 red_s[2 * G * wv + 2 * g + 1] = my;
@@ -687,7 +734,7 @@ __device__ __forceinline__ void decode_block(const DecodeArgs& a) {
                 float x = -INFINITY, y = -INFINITY;
                 if (owner) {
                     const int hq = h * G + g;
-                    const uint32_t rk = rnd_l ? row_key(unit_key(a.seeds[b], (uint32_t)l, (uint32_t)hq), (uint32_t)q_pos) : 0u;
+                    const uint32_t rk = rnd_l ? row_key(unit_key(seed_b, (uint32_t)l, (uint32_t)hq), (uint32_t)q_pos) : 0u;
                     x = (p * a.scale) * kLog2e;
                     y = (x + zeta_log2e(a.noise, rk, (uint32_t)q_pos)) * inv_tau;
                     xs[g * CS + cnt_c] = x;
@@ -699,7 +746,15 @@ __device__ __forceinline__ void decode_block(const DecodeArgs& a) {
         }
     }
     // first V tile: in flight while the softmax statistics are formed
-    if (base0 < j1) load_tile(Vu, base0, cur);
+    if constexpr (FEW) {
+#pragma unroll
+        for (int i = 0; i < UNR; ++i) {
+            const bool in = base0 + i * RPB + sub < j1;  // rows past the split weigh nothing, whatever they hold
+            cur[i] = in ? vfirst[i] : make_uint4(0u, 0u, 0u, 0u);
+        }
+    } else if (base0 < j1) {
+        load_tile(Vu, base0, cur);
+    }
     __syncthreads();
 
     // ---- phase 1.5: position bias, logit adjustment, the two softmaxes' statistics
@@ -994,11 +1049,7 @@ __device__ __forceinline__ void decode_block(const DecodeArgs& a) {
         }
         // ---- eviction by this workgroup (slot layout): the candidate with the smallest score leaves
         const unsigned long long mine = best;
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1) {
-            const unsigned long long t2 = __shfl_xor(best, o, kWave);
-            best = t2 < best ? t2 : best;
-        }
+        best = wave_min(best);
         if (lane == 0) evict_min[wv] = best;
         if (tid == 0) evict_slot = -1;
         __syncthreads();  // also orders the score stores above before the one into the freed slot
@@ -1047,6 +1098,21 @@ __device__ __forceinline__ void decode_block(const DecodeArgs& a) {
             for (int g = 0; g < G; ++g) we[(size_t)g * a.cap + slot] = ys[g * CS + t];
         }
     }
+    if constexpr (FEW) {
+        if (a.few_f) {
+#pragma unroll
+            for (int i = 0; i < kFewTokens; ++i)
+                if (tid + i * NT < cnt_c) a.few_f[(size_t)u * a.cap + j0 + tid + i * NT] = f_old[i];
+#pragma unroll
+            for (int i = 0; i < kFewPieces; ++i) {
+                const int p = tid + i * NT, row = few_boundary(a, jf) + p / (2 * LPR) * a.few_rows;
+                if (row < j1)
+                    ((uint4*)a.few_brow)[((size_t)u * a.few_nb + row / a.few_rows - 1) * 2 * LPR + p % (2 * LPR)] = brow[i];
+            }
+            const int row = few_boundary(a, jf) + tid * a.few_rows;
+            if (row < j1) a.few_bpos[(size_t)u * a.few_nb + row / a.few_rows - 1] = bpos;
+        }
+    }
     if (owner && tid == 0) a.ws_m[u] = m;  // tokens scored in this unit: the merge reads the length from here
     const float* orows = red_o;
     if constexpr (BIG) {  // as above: the waves' partial outputs take the place of the logits
@@ -1067,9 +1133,9 @@ __device__ __forceinline__ void decode_block(const DecodeArgs& a) {
 
 // (The 8-wave workgroup is compiled for four waves per SIMD, i.e. two per CU -- at most 128 registers per lane: with a few more its
 // medium-length units lose the second workgroup that overlaps their statistics and folds, 67 -> 48 % of peak.)
-template <typename T, int D, int NT, int G>
+template <typename T, int D, int NT, int G, bool FEW>
 __global__ void __launch_bounds__(NT, NT >= 512 ? 4 : 1) decode_kernel(const DecodeArgs a) {
-    decode_block<T, D, NT, G>(a);
+    decode_block<T, D, NT, G, FEW>(a);
     // Whole-step launch with the step number in device memory: every workgroup read the number when it
     // started, so the one that finishes last may move it on (and clears the ticket counter for the next launch).
     if (a.step_inc && threadIdx.x == 0) {
@@ -1271,6 +1337,29 @@ DecodePlan plan_decode(int64_t U, int32_t m, int32_t d, int32_t dtype, int32_t G
     return p;
 }
 
+int32_t few_max_splits(int64_t U) {
+    const int64_t S = kFewWorkgroups / U;
+    return (int32_t)(S < 1 ? 1 : S > kFewMaxSplits ? kFewMaxSplits : S);
+}
+// Splits of a small launch (FEW form of the decode kernel): as short as one round of loads per wave, about two
+// workgroups per CU (16 heads x 1024 x 256, ordered / slot step of 28 layers: 256 splits in all 470 / 423 us,
+// 512 466 / 447, 1024 the same; 64 heads x 2048 x 128: 256 31.0 / 23.5 us, 512 28.3 / 20.8).
+DecodePlan plan_decode_few(int64_t U, int32_t m, int32_t d, int32_t dtype, int32_t G) {
+    const int rpb = rows_per_block(d, dtype);
+    const int64_t rows = m > 1 ? m - 1 : 1;
+    const int tile = rpb * kDecodeUnroll;
+    int64_t S = (rows + tile - 1) / tile;
+    if (S > few_max_splits(U)) S = few_max_splits(U);
+    int64_t chunk = (rows + S - 1) / S;
+    chunk = (chunk + rpb - 1) / rpb * rpb;
+    S = (rows + chunk - 1) / chunk;
+    DecodePlan p;
+    p.S = (int32_t)S;
+    p.chunk = (int32_t)chunk;
+    p.lds_bytes = decode_lds_bytes(G, chunk, d);
+    return p;
+}
+
 template <typename T, int D, int G>
 static hipError_t launch_decode_g(const DecodeArgs& a, int64_t U, size_t lds, hipStream_t st, bool merge) {
     const dim3 grid((unsigned)(U * a.S)), block(kDecodeThreads);
@@ -1282,11 +1371,11 @@ static hipError_t launch_decode_g(const DecodeArgs& a, int64_t U, size_t lds, hi
         // 1024 tokens 71 / 74.5 %; 2048 tokens 73-78 / 80 %.  Splits (few units) take the 8 waves from 16 KB
         // of logits on: 64 units x 4 splits of 512 rows, 8 heads 61 -> 52 us, 4 heads 43 -> 39 us.
         const size_t logits = (size_t)2 * G * (a.chunk + 1) * sizeof(float);
-        const size_t big_from = a.S > 1 ? kDecodeBigMinLogitsSplit : (G == 8 ? kDecodeBigMinLogits8 : kDecodeBigMinLogits4);
+        const size_t big_from = a.few ? (size_t)-1 : a.S > 1 ? kDecodeBigMinLogitsSplit : (G == 8 ? kDecodeBigMinLogits8 : kDecodeBigMinLogits4);
         if (logits > big_from) {
             const size_t lds_big = decode_lds_bytes_big(G, a.chunk, D);
             if (lds_big > kDecodeLdsWhole) return hipErrorInvalidValue;
-            hipLaunchKernelGGL((decode_kernel<T, D, kDecodeThreadsBig, G>), grid, dim3(kDecodeThreadsBig), lds_big, st, a);
+            hipLaunchKernelGGL((decode_kernel<T, D, kDecodeThreadsBig, G, false>), grid, dim3(kDecodeThreadsBig), lds_big, st, a);
             hipError_t e2 = hipGetLastError();
             if (e2 == hipSuccess && a.S > 1 && merge) {
                 const int32_t slices = decode_merge_slices(a.S, a.chunk);
@@ -1301,12 +1390,13 @@ static hipError_t launch_decode_g(const DecodeArgs& a, int64_t U, size_t lds, hi
         if (a.S == 1 && lds > kDecodeLdsPair) {  // a unit too long for two workgroups per CU: one of 8 waves
             const size_t lds_big = decode_lds_bytes_big(G, a.chunk, D);
             if (lds_big > kDecodeLdsWhole) return hipErrorInvalidValue;
-            hipLaunchKernelGGL((decode_kernel<T, D, kDecodeThreadsBig, G>), grid, dim3(kDecodeThreadsBig), lds_big, st, a);
+            hipLaunchKernelGGL((decode_kernel<T, D, kDecodeThreadsBig, G, false>), grid, dim3(kDecodeThreadsBig), lds_big, st, a);
             return hipGetLastError();
         }
     }
     if (lds > kDecodeLdsPair) return hipErrorInvalidValue;
-    hipLaunchKernelGGL((decode_kernel<T, D, kDecodeThreads, G>), grid, block, lds, st, a);
+    if (a.few) hipLaunchKernelGGL((decode_kernel<T, D, kDecodeThreads, G, true>), grid, block, lds, st, a);
+    else hipLaunchKernelGGL((decode_kernel<T, D, kDecodeThreads, G, false>), grid, block, lds, st, a);
     hipError_t e = hipGetLastError();
     if (e == hipSuccess && a.S > 1 && merge) {
         const int32_t slices = decode_merge_slices(a.S, a.chunk);

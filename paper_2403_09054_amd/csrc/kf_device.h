@@ -196,15 +196,45 @@ __device__ __forceinline__ float zeta_log2e(int noise, uint32_t rkey, uint32_t k
 }
 
 // ---------------------------------------------------------------- reductions
+// Wave-wide, without the LDS crossbar: data-parallel moves fold the rows of 16 lanes, two row broadcasts carry the
+// rows' results on to lane 63, which is read back as a scalar.  (Six exchanges through the crossbar cost a trip of
+// about 50 ns each, in series.)  Lanes that a move has no source for keep `idle`.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ uint32_t dpp_or(uint32_t idle, uint32_t v) {
+    return (uint32_t)__builtin_amdgcn_update_dpp((int)idle, (int)v, CTRL, ROWS, 0xF, false);
+}
+template <typename OP>
+__device__ __forceinline__ float wave_fold(float v, float idle, OP op) {
+    const uint32_t id = __float_as_uint(idle);
+    v = op(v, __uint_as_float(dpp_or<0x111, 0xF>(id, __float_as_uint(v))));  // row_shr:1
+    v = op(v, __uint_as_float(dpp_or<0x112, 0xF>(id, __float_as_uint(v))));  // row_shr:2
+    v = op(v, __uint_as_float(dpp_or<0x114, 0xF>(id, __float_as_uint(v))));  // row_shr:4
+    v = op(v, __uint_as_float(dpp_or<0x118, 0xF>(id, __float_as_uint(v))));  // row_shr:8
+    v = op(v, __uint_as_float(dpp_or<0x142, 0xA>(id, __float_as_uint(v))));  // row_bcast:15 into rows 1 and 3
+    v = op(v, __uint_as_float(dpp_or<0x143, 0xC>(id, __float_as_uint(v))));  // row_bcast:31 into rows 2 and 3
+    return __uint_as_float((uint32_t)__builtin_amdgcn_readlane((int)__float_as_uint(v), 63));
+}
 __device__ __forceinline__ float wave_max(float v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, kWave));
-    return v;
+    return wave_fold(v, -INFINITY, [](float a, float b) { return fmaxf(a, b); });
 }
 __device__ __forceinline__ float wave_sum(float v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, kWave);
-    return v;
+    return wave_fold(v, 0.0f, [](float a, float b) { return a + b; });
+}
+template <int CTRL, int ROWS>
+__device__ __forceinline__ unsigned long long min_step(unsigned long long v) {
+    const unsigned long long t = ((unsigned long long)dpp_or<CTRL, ROWS>(~0u, (uint32_t)(v >> 32)) << 32) |
+                                 dpp_or<CTRL, ROWS>(~0u, (uint32_t)v);
+    return t < v ? t : v;
+}
+__device__ __forceinline__ unsigned long long wave_min(unsigned long long v) {
+    v = min_step<0x111, 0xF>(v);
+    v = min_step<0x112, 0xF>(v);
+    v = min_step<0x114, 0xF>(v);
+    v = min_step<0x118, 0xF>(v);
+    v = min_step<0x142, 0xA>(v);
+    v = min_step<0x143, 0xC>(v);
+    return ((unsigned long long)(uint32_t)__builtin_amdgcn_readlane((int)(v >> 32), 63) << 32) |
+           (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)v, 63);
 }
 
 // Block-wide reductions through a small LDS array (>= NT/64 floats).  Every

@@ -55,7 +55,21 @@ struct DecodeArgs {
     int32_t* pre_slot;            // [U][pre_slices] its slot
     float inv_tau;
     float scale;
+    // Small launch (FEW form of the decode kernel).  With few_f the splits also leave copies of what the
+    // eviction launch overwrites while its other workgroups still read it.
+    int32_t few;
+    int32_t few_rows;   // R: slots per workgroup of the eviction launch
+    int32_t few_nb;     // boundary slots kept per unit
+    float* few_f;       // NULL, or [U][cap]: the scores before this step
+    void* few_brow;     // [U][few_nb][2][row_bytes] K and V rows at slots R, 2R, ...
+    int32_t* few_bpos;  // [U][few_nb] their positions
 };
+// Limits of the FEW form: tokens per split (old scores and boundary rows are held in registers) and splits.
+constexpr int32_t kFewTokens = 2;    // per thread of 256
+constexpr int32_t kFewPieces = 2;    // 16-byte pieces of boundary rows per thread
+constexpr int32_t kFewMaxChunk = 512;
+constexpr int32_t kFewWorkgroups = 512;  // splits of all units together
+constexpr int32_t kFewMaxSplits = 64;
 
 // Launch shape of the decode kernel for U units of up to m tokens.
 struct DecodePlan {
@@ -63,6 +77,8 @@ struct DecodePlan {
     size_t lds_bytes;
 };
 DecodePlan plan_decode(int64_t U, int32_t m, int32_t d, int32_t dtype, int32_t G);
+DecodePlan plan_decode_few(int64_t U, int32_t m, int32_t d, int32_t dtype, int32_t G);
+int32_t few_max_splits(int64_t U);  // of any m
 hipError_t launch_decode(const DecodeArgs& a, int64_t U, int32_t d, int32_t dtype, size_t lds_bytes,
                          hipStream_t stream);
 // Workgroups per unit of the merge launch that follows a split decode launch.
@@ -148,6 +164,9 @@ struct ForkArgs {
 hipError_t launch_fork(const ForkArgs& f, hipStream_t stream);
 // decode merge + select + compact of every unit in one launch (after the split kernel of a fused step)
 hipError_t launch_step_tail(const DecodeArgs& d, const SelectArgs& a, int64_t U, int32_t hd, hipStream_t stream);
+// merge + selection + compaction of a small launch, several workgroups per unit (after a FEW split launch with few_f)
+constexpr int32_t kFinishMaxTokens = 4096;
+hipError_t launch_step_finish(const DecodeArgs& d, const SelectArgs& a, int64_t U, int32_t hd, hipStream_t stream);
 // the row-shifting launch of the two-launch eviction (after a selection launch that ran with a.wide set)
 hipError_t launch_shift(const SelectArgs& a, int64_t U, hipStream_t stream);
 // the split kernel alone (no merge launch): first half of a fused step

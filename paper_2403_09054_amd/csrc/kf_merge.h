@@ -37,11 +37,7 @@ __device__ __forceinline__ void publish_slice_min(const DecodeArgs& a, int64_t u
     __shared__ int wslot_s[NT / kWave];
     const int tid = threadIdx.x, lane = tid % kWave, wv = tid / kWave;
     unsigned long long best = mine.best;
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-        const unsigned long long t = __shfl_xor(best, o, kWave);
-        best = t < best ? t : best;
-    }
+    best = wave_min(best);
     // slots and positions are unique: one lane of the wave owns the wave's minimum
     const unsigned long long owner = __ballot(mine.best == best && best != ~0ull);
     const int wslot = __shfl(mine.slot, owner ? __ffsll((long long)owner) - 1 : 0, kWave);

@@ -144,11 +144,7 @@ __device__ __forceinline__ void evict_one(const SelectArgs& a, int64_t u, int n,
         preload_range<G>(L, wr0, wr1, wNI, wfirst, whas_last, wlast_i, wlast);
     }
 
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-        const unsigned long long t = __shfl_xor(best, o, kWave);
-        best = t < best ? t : best;
-    }
+    best = wave_min(best);
     if (lane == 0) wmin[wv] = best;
     __syncthreads();
     best = wmin[0];
@@ -249,11 +245,7 @@ __global__ void __launch_bounds__(kPreselThreads) presel_kernel(const SelectArgs
         }
     }
     const unsigned long long mine = best;
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-        const unsigned long long t = __shfl_xor(best, o, kWave);
-        best = t < best ? t : best;
-    }
+    best = wave_min(best);
     // slots and positions are unique: one lane of the wave owns the wave's minimum
     const unsigned long long owner = __ballot(mine == best && best != ~0ull);
     const int wslot = __shfl(best_slot, owner ? __ffsll((long long)owner) - 1 : 0, kWave);
@@ -317,11 +309,7 @@ __device__ __forceinline__ void evict_one_slot(const SelectArgs& a, int64_t u, i
             best = pack < best ? pack : best;
             if (c < 2) mine[c] = pack;
         }
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1) {
-            const unsigned long long t = __shfl_xor(best, o, kWave);
-            best = t < best ? t : best;
-        }
+        best = wave_min(best);
         if (lane == 0) wmin_s[wv] = best;
         if (tid == 0) s_slot = -1;
         __syncthreads();
@@ -392,11 +380,7 @@ __device__ __forceinline__ void evict_find(const SelectArgs& a, int64_t u, int n
             const unsigned long long pack = ((unsigned long long)float_key(fu[j]) << 32) | (uint32_t)(~(uint32_t)j);
             best = pack < best ? pack : best;
         }
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1) {
-            const unsigned long long t = __shfl_xor(best, o, kWave);
-            best = t < best ? t : best;
-        }
+        best = wave_min(best);
         if (lane == 0) wmin_f[wv] = best;
         __syncthreads();
         best = wmin_f[0];
@@ -700,6 +684,196 @@ __global__ void __launch_bounds__(NT) step_tail_kernel(const DecodeArgs d, const
     }
     select_unit<NT>(a, u);
     advance_step(a);
+}
+
+// Second and last launch of a generation step of few units in the ordered layout: merge of the split records,
+// selection and compaction, several workgroups per unit.  Such a launch is bound by its chain of memory round trips,
+// not by bytes, so one launch whose workgroups repeat each other's small work replaces two (merge + selection, then
+// the row shift): workgroup (unit, chunk) merges the statistics and forms ALL the unit's new scores in LDS, finds the
+// evicted slot by itself and moves the R entries of its own chunk.  The split launch left copies of what one
+// workgroup overwrites while another still reads it: the old scores, and the rows and positions at slots R, 2R, ...
+// (a chunk's last source is the next chunk's first destination).  Rows that move whatever slot leaves are loaded
+// before it is known.  One more workgroup per unit writes the attention outputs (and does what the others leave).
+constexpr int kFinishThreads = 256;
+template <int D, int G>
+__global__ void __launch_bounds__(kFinishThreads) step_finish_kernel(const DecodeArgs d, const SelectArgs a, int64_t units) {
+    constexpr int NT = kFinishThreads, NW = NT / kWave, PW = D + 4, TOK = 4;
+    __shared__ float w_p[G * kFewMaxSplits], w_e[G * kFewMaxSplits], inv_p[G];
+    __shared__ float f_new[kFinishMaxTokens + 1];
+    __shared__ unsigned long long wmin_f[NW];
+    const uint32_t ci = blockIdx.x / (uint32_t)units, ui = blockIdx.x - ci * (uint32_t)units;
+    const int64_t u = ui;  // chunk-major: every XCD gets chunks of every kind
+    const int c = (int)ci - 1;  // -1: the attention outputs
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    const int k = a.k, w = a.w, S = d.S;
+    const int m = d.ws_m[u];  // tokens the splits scored; 0: they skipped the unit
+    if (m != k + 1) {         // within budget, or far over it: one workgroup does the unit the general way
+        if (c < 0) {
+            if (m > 0) merge_unit<D, NT, G>(d, u, m - 1, w_p, w_e, 0, m, true);
+            __syncthreads();
+            select_unit<NT>(a, u);
+        }
+        advance_step(a);  // (the first workgroup of the launch is one of these)
+        return;
+    }
+    const int R = a.chunk_rows, PPR = a.row_bytes >> 4;
+    const int lo = c * R, hi = min(k, lo + R), rows = hi - lo;  // destinations [lo, hi), sources lo+1 .. hi
+    const int saved = lo + R < k ? lo + R : -1;                 // this source comes from the copy
+    uint4* Kr = (uint4*)((char*)a.K + (size_t)u * a.cap * a.row_bytes);
+    uint4* Vr = (uint4*)((char*)a.V + (size_t)u * a.cap * a.row_bytes);
+    const uint4* brow = (const uint4*)((const char*)a.ws_brow + ((size_t)u * a.nb + c) * 2 * a.row_bytes);
+    float* fu = a.score + (size_t)u * a.cap;
+    int32_t* pu = a.pos + (size_t)u * a.cap;
+
+    // ---- everything that can be asked for now: split statistics, increments, old scores, positions, certain rows
+    constexpr int HPW = (G + NW - 1) / NW;  // heads per wave: one wave merges a head's statistics, a lane a split
+    const float* parts = d.ws_part + (size_t)u * S * G * PW;
+    float4 rec[HPW];
+#pragma unroll
+    for (int i = 0; i < HPW; ++i) {
+        const int g = wv + i * NW;
+        rec[i] = make_float4(-INFINITY, 0.0f, -INFINITY, 0.0f);
+        if (g < G && lane < S) rec[i] = *reinterpret_cast<const float4*>(parts + ((size_t)lane * G + g) * PW + D);
+    }
+    const float* we = d.ws_e + (size_t)u * G * a.cap;
+    const float* f_old = d.few_f + (size_t)u * a.cap;
+    float te[TOK][G], tf[TOK];
+    auto load_tokens = [&](int j0) {
+#pragma unroll
+        for (int i = 0; i < TOK; ++i) {
+            const int j = j0 + i * NT;
+#pragma unroll
+            for (int g = 0; g < G; ++g) te[i][g] = j <= k ? we[(size_t)g * a.cap + j] : 0.0f;
+            tf[i] = j < k ? f_old[j] : 0.0f;  // the new token (slot k) starts from zero
+        }
+    };
+    // the outputs' first split records, or what the scores and the move need
+    constexpr int OREC = 16, OPT = (G * D + NT - 1) / NT;  // records in flight, outputs per thread
+    float orec[OREC];
+    auto load_records = [&](int o, int s0) {
+        const int idx = tid + o * NT;
+        const float* pr = parts + (size_t)(idx / D) * PW + idx % D;
+#pragma unroll
+        for (int i = 0; i < OREC; ++i) orec[i] = (idx < G * D && s0 + i < S) ? pr[(size_t)(s0 + i) * G * PW] : 0.0f;
+    };
+    if (c < 0) load_records(0, 0);
+    else load_tokens(tid);
+    int32_t p_next = 0;
+    if (c >= 0 && tid < rows) p_next = (lo + tid + 1 == saved) ? a.ws_bpos[(size_t)u * a.nb + c] : pu[lo + tid + 1];
+    uint4 kreg[kWidePieces], vreg[kWidePieces];
+    auto load_rows = [&]() {  // branch-free: a lane past the chunk's end re-reads the last source
+#pragma unroll
+        for (int i = 0; i < kWidePieces; ++i) {
+            const int p = tid + i * NT, q = p % PPR;
+            const int src = lo + min(p / PPR, rows - 1) + 1;
+            kreg[i] = stream_load(src == saved ? brow + q : Kr + (size_t)src * PPR + q);
+            vreg[i] = stream_load(src == saved ? brow + PPR + q : Vr + (size_t)src * PPR + q);
+        }
+    };
+    const bool sure = c >= 0 && hi > k - w;  // the chunk reaches into the part behind the candidates, which moves in any case
+    if (sure) load_rows();
+
+    // ---- statistics of the splits -> weights
+#pragma unroll
+    for (int i = 0; i < HPW; ++i) {
+        const int g = wv + i * NW;
+        const float Mx = wave_max(rec[i].x), My = wave_max(rec[i].z);
+        const float wp = rec[i].y > 0.0f ? hw_exp2(rec[i].x - Mx) : 0.0f;  // empty splits weigh nothing
+        const float we_ = rec[i].w > 0.0f ? hw_exp2(rec[i].z - My) : 0.0f;
+        const float sumP = wave_sum(fmaf(wp, rec[i].y, 0.0f)), invE = 1.0f / wave_sum(fmaf(we_, rec[i].w, 0.0f));  // as merge_unit, to the bit
+        if (g < G && lane < S) {
+            w_p[g * S + lane] = wp;
+            w_e[g * S + lane] = we_ * invE;
+        }
+        if (g < G && lane == 0) inv_p[g] = 1.0f / sumP;
+    }
+    __syncthreads();
+    if (c < 0) {
+        for (int o = 0; o < OPT; ++o) {
+            const int idx = tid + o * NT, g = idx / D;
+            float sum = 0.0f;
+            for (int s0 = 0; s0 < S; s0 += OREC) {  // summed in split order
+                if (o > 0 || s0 > 0) load_records(o, s0);
+#pragma unroll
+                for (int i = 0; i < OREC; ++i)
+                    if (s0 + i < S && idx < G * D) sum = fmaf(w_p[g * S + s0 + i], orec[i], sum);
+            }
+            if (idx < G * D) d.out[u * G * D + idx] = sum * inv_p[g];
+        }
+        if (tid == 0) a.len[u] = k;
+        advance_step(a);
+        return;
+    }
+
+    // ---- new scores of the whole unit, smallest candidate (the highest slot among equals)
+    unsigned long long best = ~0ull;
+    for (int j0 = tid; j0 <= k; j0 += TOK * NT) {
+        if (j0 != tid) load_tokens(j0);
+#pragma unroll
+        for (int i = 0; i < TOK; ++i) {
+            const int j = j0 + i * NT;
+            if (j > k) break;
+            const int split = j == k ? S - 1 : j / d.chunk;  // the new token belongs to the last split
+            float df = 0.0f;
+#pragma unroll
+            for (int g = 0; g < G; ++g) df = fmaf(te[i][g], w_e[g * S + split], df);
+            const float f = j == k ? df : tf[i] + df;
+            f_new[j] = f;
+            if (j < k + 1 - w) {
+                const unsigned long long pack = ((unsigned long long)float_key(f) << 32) | (uint32_t)(~(uint32_t)j);
+                best = pack < best ? pack : best;
+            }
+        }
+    }
+    best = wave_min(best);
+    if (lane == 0) wmin_f[wv] = best;
+    __syncthreads();
+    best = wmin_f[0];
+#pragma unroll
+    for (int i = 1; i < NW; ++i) best = wmin_f[i] < best ? wmin_f[i] : best;
+    const int e = (int)(~(uint32_t)(best & 0xFFFFFFFFull));  // evicted slot, in [0, k+1-w)
+
+    // ---- move the chunk
+    if (!sure && hi > e) load_rows();
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // every source of this chunk is in registers ...
+    __syncthreads();                                  // ... of every wave, before any of them is overwritten
+    if (hi > e) {
+#pragma unroll
+        for (int i = 0; i < kWidePieces; ++i) {
+            const int p = tid + i * NT, r = p / PPR, q = p % PPR;
+            if (r < rows && lo + r >= e) {
+                stream_store(Kr + (size_t)(lo + r) * PPR + q, kreg[i]);
+                stream_store(Vr + (size_t)(lo + r) * PPR + q, vreg[i]);
+            }
+        }
+    }
+    if (tid < rows) {
+        const int i = lo + tid;
+        fu[i] = f_new[i + (i >= e ? 1 : 0)];
+        if (i >= e) pu[i] = p_next;
+        if (a.idx_is_output) a.idx[(size_t)u * k + i] = i + (i >= e ? 1 : 0);
+    }
+}
+
+template <int D>
+static hipError_t launch_step_finish_d(const DecodeArgs& d, const SelectArgs& a, int64_t U, hipStream_t st) {
+    const int nchunks = (a.k + a.chunk_rows - 1) / a.chunk_rows;
+    const dim3 grid((unsigned)(U * (nchunks + 1))), block(kFinishThreads);
+    switch (d.G) {
+        case 1: hipLaunchKernelGGL((step_finish_kernel<D, 1>), grid, block, 0, st, d, a, U); break;
+        case 2: hipLaunchKernelGGL((step_finish_kernel<D, 2>), grid, block, 0, st, d, a, U); break;
+        case 4: hipLaunchKernelGGL((step_finish_kernel<D, 4>), grid, block, 0, st, d, a, U); break;
+        case 8: hipLaunchKernelGGL((step_finish_kernel<D, 8>), grid, block, 0, st, d, a, U); break;
+        default: return hipErrorInvalidValue;
+    }
+    return hipGetLastError();
+}
+
+hipError_t launch_step_finish(const DecodeArgs& d, const SelectArgs& a, int64_t U, int32_t hd, hipStream_t stream) {
+    if (hd == 64) return launch_step_finish_d<64>(d, a, U, stream);
+    if (hd == 128) return launch_step_finish_d<128>(d, a, U, stream);
+    if (hd == 256) return launch_step_finish_d<256>(d, a, U, stream);
+    return hipErrorInvalidValue;
 }
 
 template <int NT, int G>

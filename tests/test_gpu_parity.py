@@ -876,6 +876,69 @@ def test_fused_step_equals_the_two_calls(dtype, d, cap, layout):
     assert_close_out(results[0][0], out_ref)
 
 
+@pytest.mark.parametrize("dtype,d,k,w,G,layout", [
+    (ko.BF16, 256, 64, 12, 1, 0), (ko.BF16, 256, 65, 0, 1, 0), (ko.BF16, 256, 128, 128, 2, 0), (ko.F16, 128, 129, 30, 1, 0),
+    (ko.BF16, 128, 1501, 300, 4, 0), (ko.F32, 64, 513, 100, 8, 0), (ko.BF16, 64, 4090, 800, 1, 0), (ko.BF16, 128, 384, 77, 8, 0),
+    (ko.F32, 128, 200, 40, 1, 1), (ko.BF16, 256, 1024, 205, 1, 1)])
+def test_step_of_few_units_at_the_edges_of_its_chunks(dtype, d, k, w, G, layout):
+    """The form for few units (short splits; merge, selection and row shift in one launch): budgets next to the
+    chunks of rows that its workgroups move, units at, under and far over the budget and a full one.  Bit for bit
+    what the two calls leave, and what the larger launches leave on a workspace without room for this form's
+    records, up to the order of its sums."""
+    rng = np.random.default_rng(k + d + G)
+    L, B, H = 1, 2, 3
+    cap = k + 4
+    lens = np.full((L, B, H), k, np.int32)
+    if layout == 0:
+        lens[0, 0, 1] = k // 2
+        lens[0, 1, 0] = k + 2      # two tokens too many after the step: the general selection
+        lens[0, 1, 1] = cap        # full: the step is refused, the selection still evicts
+    oc = random_cache(rng, L, B, H, d, cap, dtype, lens)
+    oc.pos[...] = np.arange(cap)
+    oc.score[0, 0, 0, k // 3:k // 3 + 2] = 0.0   # small scores, likely the evicted one
+    q, kn, vn = rnd(rng, (L, B, H * G, d), dtype), rnd(rng, (L, B, H, d), dtype), rnd(rng, (L, B, H, d), dtype)
+    seeds = np.array([5, 6], np.uint64)
+    probe = upload(oc, G)
+    full = kf.kf_workspace_bytes(probe)
+    assert kf.kf_decode_launch_shape(probe, cap)[0] > 1
+    lo, hi = 0, full  # the smallest workspace that a selection accepts: none of the form's records
+    while hi - lo > 256:
+        mid = (lo + hi) // 512 * 256
+        try:
+            kf.kf_select_evict(upload(oc, G), k, w, None, torch.zeros(mid, dtype=torch.uint8, device="cuda"), layout=layout)
+            hi = mid
+        except kf.KeyformerError:
+            lo = mid
+    assert hi < full
+    results = []
+    for fused, nbytes in ((False, full), (True, full), (True, hi)):
+        gc = upload(oc, G)
+        ws = torch.zeros(nbytes, dtype=torch.uint8, device="cuda")
+        out = torch.zeros((L, B, H * G, d), dtype=torch.float32, device="cuda")
+        kept = torch.full((L, B, H, k), -7, dtype=torch.int32, device="cuda")
+        args = (dev(q), dev(kn), dev(vn), cap + 3, 0, 1.6, 0.11, kf.NOISE_GUMBEL, dev(seeds), None, out)
+        if fused:
+            kf.kf_decode_select_step(gc, *args, k=k, w=w, layout=layout, kept_idx=kept, workspace=ws)
+        else:
+            kf.kf_decode_step(gc, *args, ws)
+            kf.kf_select_evict(gc, k, w, kept, ws, layout=layout)
+        torch.cuda.synchronize()
+        assert error_word(ws) == (1 if layout == 0 else 0)
+        lens_now = host(gc.len)
+        live = [host(t).copy() for t in (gc.K, gc.V, gc.pos, gc.score)]
+        for l, b, h in np.ndindex(L, B, H):
+            for t in live:
+                t[l, b, h, int(lens_now[l, b, h]):] = 0
+        results.append([lens_now.copy(), host(kept).copy()] + live + [host(out).copy()])
+    for a, b in zip(results[0], results[1]):
+        np.testing.assert_array_equal(a, b)
+    for a, b in zip(results[1][:5], results[2][:5]):
+        np.testing.assert_array_equal(a, b)
+    # sums of at most k terms of either sign in another order: a few units in the last place of the largest
+    for a, b in zip(results[1][5:], results[2][5:]):
+        np.testing.assert_allclose(a, b, rtol=2e-5, atol=2e-5 * float(np.abs(b).max()) * 0.05)
+
+
 @pytest.mark.parametrize("sweep_seed", SWEEP_SEEDS)
 def test_fused_step_on_random_shapes_equals_the_two_calls(sweep_seed):
     """Seeded sweep: kf_decode_select_step against kf_decode_step + kf_select_evict, bit for bit, over element
