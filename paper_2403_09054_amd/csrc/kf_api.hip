@@ -552,7 +552,7 @@ kf_status kf_select_evict_into(const kf_cache* src, kf_cache* dst, int32_t dst_l
     a.presel = 0;
     a.presel_done = 0;
     const int64_t U = (int64_t)src->L * src->B * src->H;
-    hipError_t e = kf::launch_select(a, U, (hipStream_t)stream);
+    hipError_t e = kf::launch_select_list(a, U, (hipStream_t)stream);
     if (e != hipSuccess) return fail(KF_EDEVICE, "select launch: %s", hipGetErrorString(e));
     kf::GatherArgs g;
     g.src_K = src->K;

@@ -220,6 +220,16 @@ __device__ __forceinline__ float wave_max(float v) {
 __device__ __forceinline__ float wave_sum(float v) {
     return wave_fold(v, 0.0f, [](float a, float b) { return a + b; });
 }
+// Sum over the lanes up to and including this one.
+__device__ __forceinline__ uint32_t wave_scan(uint32_t v) {
+    v += dpp_or<0x111, 0xF>(0u, v);
+    v += dpp_or<0x112, 0xF>(0u, v);
+    v += dpp_or<0x114, 0xF>(0u, v);
+    v += dpp_or<0x118, 0xF>(0u, v);
+    v += dpp_or<0x142, 0xA>(0u, v);
+    v += dpp_or<0x143, 0xC>(0u, v);
+    return v;
+}
 template <int CTRL, int ROWS>
 __device__ __forceinline__ unsigned long long min_step(unsigned long long v) {
     const unsigned long long t = ((unsigned long long)dpp_or<CTRL, ROWS>(~0u, (uint32_t)(v >> 32)) << 32) |

@@ -132,6 +132,8 @@ constexpr int32_t kPreselMaxSlices = 16;
 // rows per workgroup of the wide shift: 2048 16-byte pieces per tensor, i.e. 32 KB of K and 32 KB of V
 inline int32_t wide_chunk_rows(int32_t row_bytes) { return 2048 / (row_bytes >> 4); }
 hipError_t launch_select(const SelectArgs& a, int64_t U, hipStream_t stream);
+// the survivor lists alone (a.move == 0)
+hipError_t launch_select_list(const SelectArgs& a, int64_t U, hipStream_t stream);
 struct GatherArgs {
     const void* src_K;
     const void* src_V;

@@ -904,6 +904,111 @@ hipError_t launch_step_tail(const DecodeArgs& d, const SelectArgs& a, int64_t U,
     return launch_step_tail_nt<kSelectThreads>(d, a, U, hd, stream);
 }
 
+// Survivor lists alone, for the eviction into another cache: the selection of select_unit with the unit's keys held
+// in registers.  A thread owns KPT neighbouring slots, so the stable ranks take one wave scan and one exchange
+// between the waves instead of a sweep with two barriers per NT slots, and the radix passes read no memory.  Each
+// pass has a histogram of its own and every wave finds the digit by itself: one barrier a pass.  select_kernel spent
+// 96 us on 2048 units of 2048 tokens (sixteen waves a unit, two units a CU at a time, five reads of the scores, some
+// thirty barriers each); this takes 24, next to a row copy of 374 (one unit-layer of 32 heads x 32768 tokens: the call
+// 211 -> 113 us).
+template <int NT, int KPT>
+__global__ void __launch_bounds__(NT) select_list_kernel(const SelectArgs a) {
+    constexpr int NW = NT / kWave;
+    __shared__ __attribute__((aligned(16))) uint32_t hist[4][256];
+    __shared__ uint32_t wtot[NW];
+    const int64_t u = (int64_t)blockIdx.x;
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    const int n = a.len[u];
+    const int k = a.k, w = a.w;
+    int32_t* idx = a.idx + (size_t)u * k;
+    if (n <= k) {  // under budget: nothing leaves
+        for (int i = tid; i < k; i += NT) idx[i] = (i < n) ? i : -1;
+        return;
+    }
+    const int ncand = n - w, nkey = k - w;
+    const float* fu = a.score + (size_t)u * a.cap;
+    const int j0 = tid * KPT;
+    uint32_t key[KPT];
+#pragma unroll
+    for (int i = 0; i < KPT; ++i) key[i] = (j0 + i < ncand) ? float_key(fu[j0 + i]) : 0u;
+    for (int i = tid; i < 4 * 256; i += NT) (&hist[0][0])[i] = 0u;
+    __syncthreads();
+
+    // ---- threshold T = the nkey-th largest key, need = how many candidates equal to it survive
+    uint32_t T = 0xFFFFFFFFu, need = 0;
+    if (nkey > 0) {
+        uint32_t prefix = 0, mask = 0, remaining = (uint32_t)nkey;
+#pragma unroll
+        for (int pass = 0; pass < 4; ++pass) {
+            const int shift = 24 - 8 * pass;
+#pragma unroll
+            for (int i = 0; i < KPT; ++i)
+                if (j0 + i < ncand && (key[i] & mask) == prefix) atomicAdd(&hist[pass][(key[i] >> shift) & 255u], 1u);
+            __syncthreads();
+            // lane owns bins 255-4*lane .. 252-4*lane: highest digits first
+            const uint4 h = *(const uint4*)&hist[pass][252 - 4 * lane];
+            const uint32_t c[4] = {h.w, h.z, h.y, h.x};
+            const uint32_t tot = c[0] + c[1] + c[2] + c[3];
+            uint32_t above = wave_scan(tot) - tot;
+            uint32_t digit = 0, rem = 0;
+            bool mine = false;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                if (above < remaining && remaining <= above + c[i]) {
+                    digit = (uint32_t)(255 - 4 * lane - i);
+                    rem = remaining - above;
+                    mine = true;
+                }
+                above += c[i];
+            }
+            const unsigned long long owner = __ballot(mine);  // exactly one lane
+            const int src = owner ? __ffsll((long long)owner) - 1 : 0;
+            prefix |= (uint32_t)__builtin_amdgcn_readlane((int)digit, src) << shift;
+            remaining = (uint32_t)__builtin_amdgcn_readlane((int)rem, src);
+            mask |= 0xFFu << shift;
+        }
+        T = prefix;
+        need = remaining;
+    }
+
+    // ---- stable ranks: survivors above T and candidates equal to it before this thread's slots (16 bits each)
+    uint32_t mine = 0;
+#pragma unroll
+    for (int i = 0; i < KPT; ++i)
+        if (j0 + i < ncand && nkey > 0) mine += (key[i] > T ? 1u : 0u) + (key[i] == T ? 0x10000u : 0u);
+    const uint32_t upto = wave_scan(mine);
+    if (lane == 63) wtot[wv] = upto;
+    __syncthreads();
+    uint32_t before = upto - mine;
+#pragma unroll
+    for (int i = 0; i < NW; ++i) before += i < wv ? wtot[i] : 0u;
+    uint32_t gt = before & 0xFFFFu, eq = before >> 16;
+#pragma unroll
+    for (int i = 0; i < KPT; ++i) {
+        if (j0 + i < ncand && nkey > 0) {
+            const bool above = key[i] > T, same = key[i] == T;
+            if (above || (same && eq < need)) {
+                const uint32_t dst = gt + min(eq, need);
+                if (dst < (uint32_t)nkey) idx[dst] = j0 + i;  // always true; keeps a logic error in bounds
+            }
+            gt += above ? 1u : 0u;
+            eq += same ? 1u : 0u;
+        }
+    }
+    for (int i = tid; i < w; i += NT) idx[nkey + i] = ncand + i;  // the recent window
+}
+
+// Units of up to `cap` tokens: two waves' worth of latency per unit matters as little as their number is large, so
+// short units take four waves (eight of them fit a CU), longer ones sixteen; beyond 32768 tokens select_kernel.
+hipError_t launch_select_list(const SelectArgs& a, int64_t U, hipStream_t stream) {
+    const dim3 grid((unsigned)U);
+    if (a.cap <= 256 * 8) hipLaunchKernelGGL((select_list_kernel<256, 8>), grid, dim3(256), 0, stream, a);
+    else if (a.cap <= 1024 * 8) hipLaunchKernelGGL((select_list_kernel<1024, 8>), grid, dim3(1024), 0, stream, a);
+    else if (a.cap <= 1024 * 32) hipLaunchKernelGGL((select_list_kernel<1024, 32>), grid, dim3(1024), 0, stream, a);
+    else return launch_select(a, U, stream);
+    return hipGetLastError();
+}
+
 // Out-of-place compaction: survivor i of unit u (slot idx[u][i] of the source
 // cache) goes to slot i of the destination cache.  Source and destination do
 // not overlap, so any number of workgroups can share a unit: a workgroup copies

@@ -1365,6 +1365,39 @@ def test_prefill_in_parts_and_whole_match_oracle(dtype, d, G, n, noise, biased):
     run(hi)
 
 
+@pytest.mark.parametrize("cap,k,w", [(2047, 1000, 200), (2048, 2047, 2047), (2049, 1, 0), (8192, 3000, 0), (8193, 4000, 4000),
+                                     (32768, 9830, 1966), (32769, 20000, 100), (64, 10, 9)])
+def test_survivor_lists_at_the_edges_of_their_register_forms(cap, k, w):
+    """kf_select_evict_into's lists against a stable sort: lengths next to each form's largest, many ties, signed
+    zeros, infinities; units at, under and over the budget."""
+    rng = np.random.default_rng(cap + k)
+    L, B, H, d = 1, 2, 3, 64
+    oc = random_cache(rng, L, B, H, d, cap, ko.BF16, cap)
+    oc.score[0, 0, 1] = rng.integers(0, 5, cap)                               # few distinct scores
+    oc.score[0, 0, 2] = np.where(rng.random(cap) < 0.5, -0.0, 0.0)
+    oc.score[0, 1, 0, ::7] = np.inf
+    oc.score[0, 1, 1] = -oc.score[0, 1, 1]
+    oc.len[0, 1, 2] = k
+    oc.len[0, 1, 1] = min(cap, k + 1)
+    gc, dst = upload(oc), kf.Cache.allocate(L, B, H, d, k, ko.BF16)
+    kept = torch.full((L, B, H, k), -7, dtype=torch.int32, device="cuda")
+    kf.kf_select_evict_into(gc, dst, 0, k, w, kept, kf.new_workspace(gc))
+    torch.cuda.synchronize()
+    for u in np.ndindex(L, B, H):
+        n = int(oc.len[u])
+        if n <= k:
+            want = np.where(np.arange(k) < n, np.arange(k), -1)
+        else:
+            bits = oc.score[u][:n - w].view(np.uint32)                        # the order of the bit patterns: -0.0 below 0.0
+            key = np.where(bits >> 31, ~bits, bits | 0x80000000).astype(np.int64)
+            top = np.sort(np.argsort(-key, kind="stable")[:k - w])
+            want = np.concatenate([top, np.arange(n - w, n)])
+        np.testing.assert_array_equal(host(kept)[u], want)
+        m = min(n, k)
+        np.testing.assert_array_equal(host(dst.K)[u][:m], oc.K[u][want[:m]])
+        np.testing.assert_array_equal(host(dst.score)[u][:m], oc.score[u][want[:m]])
+
+
 @pytest.mark.parametrize("G,shared,layout", [(4, False, kf.LAYOUT_ORDERED), (2, True, kf.LAYOUT_ORDERED),
                                             (8, False, kf.LAYOUT_SLOT)])
 def test_grouped_query_lockstep(G, shared, layout):
