@@ -37,11 +37,17 @@ constexpr int64_t kMaxGrid = 0x7fffffff;  // workgroups of a one-dimensional lau
 constexpr int64_t kTailMergeMaxTokens = 4096;
 constexpr int64_t kWideMaxUnits = 256;
 constexpr int32_t kPreselMinTokens = 4096;
+// Bytes of window rows up to which the decode launch of an ordered step leaves them in the caches for the row shift
+// (the chip's memory-side cache holds 256 MB).  Caches of several layers in turn: 2048 heads x 1024 x 128 (215 MB)
+// 276 -> 267 us a step, 1024 x 2048 x 128 (215 MB) 278 -> 264, 448 x 1024 x 256 (94 MB) 140 -> 133, 256 x 2048 x 128
+// 80 -> 76; 8192 x 2048 x 128 (1.7 GB), where they are gone again, 2038 -> 2099.
+constexpr int64_t kKeepMaxBytes = 256ll << 20;
 // A step of at most this many units is bound by the chain of memory round trips through its launches, not by bytes:
 // its splits are short, ask for everything at once, and (ordered layout) one launch merges, selects and moves the
 // rows instead of two.  28 layers of 16 heads, d = 256, k = 1024, a call each: 646 -> 466 us per token (slot layout
-// 499 -> 447); 32 heads x 1024 x 128 24 -> 19 us, 64 x 2048 x 128 32.4 -> 28.3, 128 x 2048 x 128 48.5 -> 47.4 us;
-// with 256 units the repeated merging costs what the saved launch gains.
+// 499 -> 447); 32 heads x 1024 x 128 24 -> 19 us, 64 x 2048 x 128 32.4 -> 28.3;
+// 128 x 2048 x 128, bound by its bytes, 48.5 -> 47.4 and with more units the repeated merging costs what the saved
+// launch gains.
 constexpr int64_t kFewMaxUnits = 128;
 
 bool supported(int32_t dtype, int32_t d) {
@@ -117,7 +123,7 @@ size_t decode_region(int64_t U, const kf_cache* c) {
 
 // Split records of a step of few units.
 size_t few_records(int64_t U, const kf_cache* c) {
-    return wide_part((size_t)U * kf::few_max_splits(U) * group_of(c) * (c->d + 4) * sizeof(float));
+    return wide_part((size_t)U * kf::few_max_splits(U, group_of(c)) * group_of(c) * (c->d + 4) * sizeof(float));
 }
 
 size_t prefill_region(int64_t UQ, size_t n_pad, int32_t G, int32_t parts) {
@@ -155,10 +161,7 @@ WsLayout ws_layout(const kf_cache* c, int32_t n_max, int32_t parts = 1) {
 // Whether a decode step of up to m tokens takes the form for few units, and the splits it then has.
 bool few_plan(const kf_cache* c, const WsLayout& w, size_t workspace_bytes, int32_t m, kf::DecodePlan* plan) {
     if (w.few_bytes == 0 || workspace_bytes - w.few_bytes < w.total || workspace_bytes < w.few_bytes) return false;
-    const kf::DecodePlan p = kf::plan_decode_few((int64_t)c->L * c->B * c->H, m, c->d, c->dtype, group_of(c));
-    if (p.S < 2 || p.chunk > kf::kFewMaxChunk) return false;
-    *plan = p;
-    return true;
+    return kf::plan_decode_few((int64_t)c->L * c->B * c->H, m, c->d, c->dtype, group_of(c), plan);
 }
 
 // Whether the two-launch ordered eviction is the faster one for U units of budget k.
@@ -397,6 +400,7 @@ static kf_status prepare_decode(kf_cache* c, const void* q, const void* k_new, c
     a->inv_tau = 1.0f / cfg->tau;
     a->scale = cfg->scale;
     a->few_rows = a->few_nb = 0;
+    a->keep_w = 0;
     a->few_f = nullptr;
     a->few_brow = nullptr;
     a->few_bpos = nullptr;
@@ -608,6 +612,8 @@ static kf_status fused_step(kf_cache* c, const void* q, const void* k_new, const
         sa.step_inc = step;
     }
     const int64_t U = (int64_t)c->L * c->B * c->H;
+    // the rows that the eviction is going to move, if the memory-side cache can hold them until then
+    if (layout == KF_LAYOUT_ORDERED && U * w * 2 * sa.row_bytes <= kKeepMaxBytes) da.keep_w = w;
     hipError_t e;
     if (da.S == 1 && layout == KF_LAYOUT_SLOT && !da.shared) {
         // one workgroup owns each unit and nothing orders the slots: the whole step is one launch

@@ -240,6 +240,11 @@ __device__ __forceinline__ float joined_weight(uint32_t w) {
     return __uint_as_float(w & 0xFFFF0000u) + __uint_as_float(w << 16);
 }
 
+template <bool V>
+struct Flag {
+    static constexpr bool value = V;
+};
+
 // First chunk-boundary slot of a split that starts at row jf (slot 0 is no boundary).
 __device__ __forceinline__ int few_boundary(const DecodeArgs& a, int jf) {
     return max(1, (jf + a.few_rows - 1) / a.few_rows) * a.few_rows;
@@ -400,10 +405,18 @@ __device__ __forceinline__ void decode_block(const DecodeArgs& a) {
     const int base0 = j0 + wv * RPW;
     // a tile starting at `base` is "plain" (no bounds checks) if all its rows are below j1
     auto plain = [&](int base) { return base + (UNR - 1) * RPB + RPW <= j1; };
-    auto load_plain = [&](const char* rows, int base, uint4(&raw)[UNR]) {
+    // Rows from jkeep on are loaded the ordinary way, into the caches: the eviction that follows in the same step
+    // moves them and finds them in the memory-side cache.  The others stream past the caches.  (A loop for each kind:
+    // with a choice per tile the compiler merges both kinds of load into ordinary ones, or waits for each tile.)
+    const int jkeep = FEW ? 0 : a.keep_w > 0 ? m - a.keep_w : 0x7FFFFFFF;
+    auto load_plain = [&](auto keep, const char* rows, int base, uint4(&raw)[UNR]) {
         const char* p = rows + (size_t)base * ROWB + lane_off;
 #pragma unroll
-        for (int i = 0; i < UNR; ++i) raw[i] = stream_load((const uint4*)(p + (size_t)i * RPB * ROWB));
+        for (int i = 0; i < UNR; ++i) {
+            const uint4* q = (const uint4*)(p + (size_t)i * RPB * ROWB);
+            if constexpr (decltype(keep)::value) raw[i] = *q;
+            else raw[i] = stream_load(q);
+        }
     };
     auto load_edge = [&](const char* rows, int base, uint4(&raw)[UNR]) {
 #pragma unroll
@@ -414,7 +427,7 @@ __device__ __forceinline__ void decode_block(const DecodeArgs& a) {
         }
     };
     auto load_tile = [&](const char* rows, int base, uint4(&raw)[UNR]) {
-        if (plain(base)) load_plain(rows, base, raw);
+        if (plain(base)) load_plain(Flag<FEW>(), rows, base, raw);
         else load_edge(rows, base, raw);
     };
 
@@ -688,16 +701,20 @@ __device__ __forceinline__ void decode_block(const DecodeArgs& a) {
             }
             // steady state: the next tile needs no bounds checks, so the loop body is
             // branch-free and only the older tile's loads are waited for
-            while (plain(base + TILE)) {
-                load_plain(Ku, base + TILE, nxt);
-                load_pos(base + TILE, pnxt);
-                logits_of(base, pcur);
+            auto steady = [&](auto keep, int limit) {
+                while (plain(base + TILE) && base + TILE < limit) {
+                    load_plain(keep, Ku, base + TILE, nxt);
+                    load_pos(base + TILE, pnxt);
+                    logits_of(base, pcur);
 #pragma unroll
-                for (int i = 0; i < UNR; ++i) cur[i] = nxt[i];
+                    for (int i = 0; i < UNR; ++i) cur[i] = nxt[i];
 #pragma unroll
-                for (int r = 0; r < VPL; ++r) pcur[r] = pnxt[r];
-                base += TILE;
-            }
+                    for (int r = 0; r < VPL; ++r) pcur[r] = pnxt[r];
+                    base += TILE;
+                }
+            };
+            if constexpr (!FEW) steady(Flag<false>(), jkeep);
+            steady(Flag<true>(), 0x7FFFFFFF);
             while (base < j1) {  // the last one or two tiles of the split
                 if (base + TILE < j1) {
                     load_edge(Ku, base + TILE, nxt);
@@ -865,13 +882,17 @@ __device__ __forceinline__ void decode_block(const DecodeArgs& a) {
     };
     {
         int base = base0;
-        while (plain(base + TILE)) {
-            load_plain(Vu, base + TILE, nxt);
-            weigh(base);
+        auto steady = [&](auto keep, int limit) {
+            while (plain(base + TILE) && base + TILE < limit) {
+                load_plain(keep, Vu, base + TILE, nxt);
+                weigh(base);
 #pragma unroll
-            for (int i = 0; i < UNR; ++i) cur[i] = nxt[i];
-            base += TILE;
-        }
+                for (int i = 0; i < UNR; ++i) cur[i] = nxt[i];
+                base += TILE;
+            }
+        };
+        if constexpr (!FEW) steady(Flag<false>(), jkeep);
+        steady(Flag<true>(), 0x7FFFFFFF);
         while (base < j1) {
             if (base + TILE < j1) load_edge(Vu, base + TILE, nxt);
             weigh(base);
@@ -1337,27 +1358,29 @@ DecodePlan plan_decode(int64_t U, int32_t m, int32_t d, int32_t dtype, int32_t G
     return p;
 }
 
-int32_t few_max_splits(int64_t U) {
-    const int64_t S = kFewWorkgroups / U;
-    return (int32_t)(S < 1 ? 1 : S > kFewMaxSplits ? kFewMaxSplits : S);
+// Not for splits that are long all the same (the launch is then bound by bytes and wants its workgroups spread evenly),
+// nor for many query heads with more than a few splits of them (a record and a pass over them per head and split).
+int32_t few_max_splits(int64_t U, int32_t G) {
+    int64_t S = kFewWorkgroups / U;
+    if (S > kFewMaxSplits / G) S = kFewMaxSplits / G;
+    return (int32_t)(S < 1 ? 1 : S);
 }
-// Splits of a small launch (FEW form of the decode kernel): as short as one round of loads per wave, about two
-// workgroups per CU (16 heads x 1024 x 256, ordered / slot step of 28 layers: 256 splits in all 470 / 423 us,
-// 512 466 / 447, 1024 the same; 64 heads x 2048 x 128: 256 31.0 / 23.5 us, 512 28.3 / 20.8).
-DecodePlan plan_decode_few(int64_t U, int32_t m, int32_t d, int32_t dtype, int32_t G) {
+bool plan_decode_few(int64_t U, int32_t m, int32_t d, int32_t dtype, int32_t G, DecodePlan* plan) {
     const int rpb = rows_per_block(d, dtype);
     const int64_t rows = m > 1 ? m - 1 : 1;
     const int tile = rpb * kDecodeUnroll;
     int64_t S = (rows + tile - 1) / tile;
-    if (S > few_max_splits(U)) S = few_max_splits(U);
+    if (S > few_max_splits(U, G)) S = few_max_splits(U, G);
     int64_t chunk = (rows + S - 1) / S;
     chunk = (chunk + rpb - 1) / rpb * rpb;
     S = (rows + chunk - 1) / chunk;
-    DecodePlan p;
-    p.S = (int32_t)S;
-    p.chunk = (int32_t)chunk;
-    p.lds_bytes = decode_lds_bytes(G, chunk, d);
-    return p;
+    if (S < 2 || chunk > kFewMaxChunk || chunk * d * (dtype == KF_F32 ? 4 : 2) > kFewChunkBytes) return false;
+    if (G >= 4 && chunk > kFewMaxChunkGrouped) return false;
+    if (plan_decode(U, m, d, dtype, G).S < 2) return false;  // one workgroup finishes the unit: nothing to merge
+    plan->S = (int32_t)S;
+    plan->chunk = (int32_t)chunk;
+    plan->lds_bytes = decode_lds_bytes(G, chunk, d);
+    return true;
 }
 
 template <typename T, int D, int G>

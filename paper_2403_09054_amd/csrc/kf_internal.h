@@ -53,6 +53,7 @@ struct DecodeArgs {
     int32_t pre_slices, pre_k, pre_w, pre_layout;
     unsigned long long* pre_min;  // [U][pre_slices] (score key, tie-break) pack, ~0 if the slice has no candidate
     int32_t* pre_slot;            // [U][pre_slices] its slot
+    int32_t keep_w;  // the last keep_w rows of a unit are loaded into the caches: the step's eviction moves them; 0: none
     float inv_tau;
     float scale;
     // Small launch (FEW form of the decode kernel).  With few_f the splits also leave copies of what the
@@ -68,7 +69,9 @@ struct DecodeArgs {
 constexpr int32_t kFewTokens = 2;    // per thread of 256
 constexpr int32_t kFewPieces = 2;    // 16-byte pieces of boundary rows per thread
 constexpr int32_t kFewMaxChunk = 512;
-constexpr int32_t kFewWorkgroups = 512;  // splits of all units together
+constexpr int32_t kFewMaxChunkGrouped = 128;     // with 4 or 8 query heads
+constexpr int32_t kFewChunkBytes = 64 * 1024;    // of K, and as much of V
+constexpr int32_t kFewWorkgroups = 512;          // splits of all units together
 constexpr int32_t kFewMaxSplits = 64;
 
 // Launch shape of the decode kernel for U units of up to m tokens.
@@ -77,8 +80,8 @@ struct DecodePlan {
     size_t lds_bytes;
 };
 DecodePlan plan_decode(int64_t U, int32_t m, int32_t d, int32_t dtype, int32_t G);
-DecodePlan plan_decode_few(int64_t U, int32_t m, int32_t d, int32_t dtype, int32_t G);
-int32_t few_max_splits(int64_t U);  // of any m
+bool plan_decode_few(int64_t U, int32_t m, int32_t d, int32_t dtype, int32_t G, DecodePlan* plan);
+int32_t few_max_splits(int64_t U, int32_t G);  // of any m
 hipError_t launch_decode(const DecodeArgs& a, int64_t U, int32_t d, int32_t dtype, size_t lds_bytes,
                          hipStream_t stream);
 // Workgroups per unit of the merge launch that follows a split decode launch.

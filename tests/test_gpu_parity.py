@@ -877,7 +877,7 @@ def test_fused_step_equals_the_two_calls(dtype, d, cap, layout):
 
 
 @pytest.mark.parametrize("dtype,d,k,w,G,layout", [
-    (ko.BF16, 256, 64, 12, 1, 0), (ko.BF16, 256, 65, 0, 1, 0), (ko.BF16, 256, 128, 128, 2, 0), (ko.F16, 128, 129, 30, 1, 0),
+    (ko.BF16, 256, 192, 30, 1, 0), (ko.BF16, 256, 193, 0, 1, 0), (ko.BF16, 256, 128, 128, 2, 0), (ko.F16, 128, 129, 30, 1, 0),
     (ko.BF16, 128, 1501, 300, 4, 0), (ko.F32, 64, 513, 100, 8, 0), (ko.BF16, 64, 4090, 800, 1, 0), (ko.BF16, 128, 384, 77, 8, 0),
     (ko.F32, 128, 200, 40, 1, 1), (ko.BF16, 256, 1024, 205, 1, 1)])
 def test_step_of_few_units_at_the_edges_of_its_chunks(dtype, d, k, w, G, layout):
