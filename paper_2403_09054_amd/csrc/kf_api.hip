@@ -389,6 +389,7 @@ static kf_status prepare_decode(kf_cache* c, const void* q, const void* k_new, c
     a->pre_min = nullptr;
     a->pre_slot = nullptr;
     a->fuse_w = 0;
+    a->fuse_ordered = 0;
     a->fuse_idx = nullptr;
     a->step_inc = nullptr;
     a->ws_ticket = (int32_t*)workspace + KF_WS_TICKET_WORD;
@@ -615,8 +616,15 @@ static kf_status fused_step(kf_cache* c, const void* q, const void* k_new, const
     // the rows that the eviction is going to move, if the memory-side cache can hold them until then
     if (layout == KF_LAYOUT_ORDERED && U * w * 2 * sa.row_bytes <= kKeepMaxBytes) da.keep_w = w;
     hipError_t e;
-    if (da.S == 1 && layout == KF_LAYOUT_SLOT && !da.shared) {
-        // one workgroup owns each unit and nothing orders the slots: the whole step is one launch
+    // a few small units: the workgroup that scored one also moves its rows (2 heads x 64 x 64 in fp32, whose two
+    // launches were all host and launch time, 17.9 -> 15.7 us a step); cap: no unit is further over its budget
+    const bool small_ordered = layout == KF_LAYOUT_ORDERED && U <= kWideMaxUnits && c->cap == k + 1 && da.chunk >= k &&
+                               (int64_t)k * sa.row_bytes <= kf::kFuseOrderedBytes &&
+                               2 * da.G * (int64_t)(da.chunk + 1) * 4 <= 24 * 1024;  // a 4-wave workgroup: see launch_decode_g
+    if (da.S == 1 && !da.shared && (layout == KF_LAYOUT_SLOT || small_ordered)) {
+        // one workgroup owns each unit and nothing orders the slots, or it orders them: the whole step is one launch
+        da.fuse_ordered = layout == KF_LAYOUT_ORDERED;
+        if (da.fuse_ordered) da.keep_w = 0;
         da.fuse_k = k;
         da.fuse_w = w;
         da.fuse_idx = kept_idx;

@@ -250,6 +250,38 @@ __device__ __forceinline__ int few_boundary(const DecodeArgs& a, int jf) {
     return max(1, (jf + a.few_rows - 1) / a.few_rows) * a.few_rows;
 }
 
+// Ordered eviction of a small unit by one workgroup: K, V and pos entries (e, k] move down by one slot; the entry that
+// becomes slot k-1 comes from klast / vlast / plast.  Front to back in tiles held in registers; a tile's last source is
+// read before the next tile overwrites it.  Called by the whole workgroup.
+template <int NT>
+__device__ __forceinline__ void close_gap(u32x4_t* Ku, u32x4_t* Vu, const u32x4_t* klast, const u32x4_t* vlast, int32_t* pu, int32_t plast,
+                                          int PPR, int e, int k) {
+    constexpr int DEPTH = 4;
+    const int tid = threadIdx.x, rpt = DEPTH * NT / PPR;  // rows per tile
+    for (int b = e; b < k; b += rpt) {
+        u32x4_t kr[DEPTH], vr[DEPTH];
+#pragma unroll
+        for (int i = 0; i < DEPTH; ++i) {
+            const int p = tid + i * NT, q = p % PPR, src = min(b + p / PPR, k - 1) + 1;
+            kr[i] = *(src == k ? klast + q : (const u32x4_t*)Ku + (size_t)src * PPR + q);
+            vr[i] = *(src == k ? vlast + q : (const u32x4_t*)Vu + (size_t)src * PPR + q);
+        }
+        int32_t ps = 0;  // (a tile has at most DEPTH * NT / 8 rows)
+        if (tid < rpt && b + tid < k) ps = b + tid + 1 == k ? plast : pu[b + tid + 1];
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        __syncthreads();  // every source of the tile is in registers
+#pragma unroll
+        for (int i = 0; i < DEPTH; ++i) {
+            const int p = tid + i * NT, q = p % PPR, dst = b + p / PPR;
+            if (dst < k) {
+                Ku[(size_t)dst * PPR + q] = kr[i];
+                Vu[(size_t)dst * PPR + q] = vr[i];
+            }
+        }
+        if (tid < rpt && b + tid < k) pu[b + tid] = ps;
+    }
+}
+
 // One workgroup streams the cache rows [j0, j1) of one cached head ("unit") once
 // and serves the G query heads that read it (G = 1: ordinary multi-head
 // attention; G > 1: grouped-query attention, query head hq = h*G + g).
@@ -375,6 +407,35 @@ __device__ __forceinline__ void decode_block(const DecodeArgs& a) {
                 // whole-step launch: the selection would have refused this unit as well (slot layout,
                 // more than one token over budget) and reported it on its own
                 if (a.fuse_k > 0 && len0 > a.fuse_k + 1) atomicAdd(a.ws_err, 1);
+            }
+        }
+        if constexpr (!FEW && !BIG) {
+            // ordered whole-step launch: the selection evicts from a full unit all the same, by the scores it has
+            // (the launch is only made when a unit cannot hold more than one token over its budget)
+            if (a.fuse_ordered && len0 < 0 && a.fuse_idx)
+                for (int i = tid; i < a.fuse_k; i += NT) a.fuse_idx[(size_t)u * a.fuse_k + i] = -1;
+            if (a.fuse_ordered && len0 == a.fuse_k + 1) {
+                const int k = a.fuse_k;
+                unsigned long long best = ~0ull;
+                for (int j = tid; j < len0; j += NT) {
+                    const float f = fu[j];
+                    smem[j] = f;
+                    const unsigned long long pack = ((unsigned long long)float_key(f) << 32) | (uint32_t)(~(uint32_t)j);
+                    if (j < len0 - a.fuse_w) best = pack < best ? pack : best;
+                }
+                best = wave_min(best);
+                if (lane == 0) evict_min[wv] = best;
+                __syncthreads();
+#pragma unroll
+                for (int i = 0; i < NW; ++i) best = evict_min[i] < best ? evict_min[i] : best;
+                const int e = (int)(~(uint32_t)(best & 0xFFFFFFFFull));
+                for (int i = tid; i < k; i += NT) {
+                    fu[i] = smem[i + (i >= e ? 1 : 0)];
+                    if (a.fuse_idx) a.fuse_idx[(size_t)u * k + i] = i + (i >= e ? 1 : 0);
+                }
+                close_gap<NT>((u32x4_t*)Ku, (u32x4_t*)Vu, (const u32x4_t*)Ku + (size_t)k * LPR, (const u32x4_t*)Vu + (size_t)k * LPR, pu,
+                              pu[k], LPR, e, k);
+                if (tid == 0) a.len[u] = k;
             }
         }
         return;
@@ -1015,6 +1076,18 @@ __device__ __forceinline__ void decode_block(const DecodeArgs& a) {
             float df = 0.0f;
 #pragma unroll
             for (int g = 0; g < G; ++g) df = fmaf(ys[g * CS + t], inv[g], df);
+            if (!BIG && !FEW && evict_here && a.fuse_ordered) {  // the new scores wait in LDS for their slots
+                const float f_new = t == cnt_c ? df : fu[slot] + df;
+                ys[t] = f_new;
+                if (slot < m - a.fuse_w) {
+                    const unsigned long long pack = ((unsigned long long)float_key(f_new) << 32) | (uint32_t)(~(uint32_t)slot);
+                    if (pack < best) {
+                        best = pack;
+                        best_slot = slot;
+                    }
+                }
+                continue;
+            }
             if (evict_here) {
                 // the scores are needed at once: read, add, keep the sum for the selection
                 float f_new = df;
@@ -1093,6 +1166,15 @@ __device__ __forceinline__ void decode_block(const DecodeArgs& a) {
                 a.len[u] = m;
                 atomicAdd(a.ws_err, 1);
             }
+            return;
+        }
+        if (!BIG && !FEW && a.fuse_ordered) {
+            for (int i = tid; i < k; i += NT) {
+                fu[i] = ys[i + (i >= e ? 1 : 0)];
+                if (a.fuse_idx) a.fuse_idx[(size_t)u * k + i] = i + (i >= e ? 1 : 0);
+            }
+            close_gap<NT>((u32x4_t*)Ku, (u32x4_t*)Vu, (const u32x4_t*)knew, (const u32x4_t*)vnew, pu, q_pos, LPR, e, k);
+            if (tid == 0) a.len[u] = k;
             return;
         }
         if (e != len0) {  // e == len0: the new token itself leaves (only without a recent window)

@@ -44,6 +44,7 @@ struct DecodeArgs {
     // Whole step in this launch (single split, slot layout): after the scores are updated the workgroup
     // evicts for its unit and stores the new token straight into the freed slot.  fuse_k = 0: off.
     int32_t fuse_k, fuse_w;
+    int32_t fuse_ordered;  // ... or, ordered layout, a small unit: moves the rows behind the evicted slot down itself
     int32_t* fuse_idx;  // NULL, or [U][k] survivor list as the selection kernel writes it
     int32_t* step_inc;   // NULL, or the device step counter the launch's last workgroup advances (whole-step launch)
     int32_t* ws_ticket;  // [1] workgroups of this launch that are done (zero between launches)
@@ -65,6 +66,8 @@ struct DecodeArgs {
     void* few_brow;     // [U][few_nb][2][row_bytes] K and V rows at slots R, 2R, ...
     int32_t* few_bpos;  // [U][few_nb] their positions
 };
+constexpr int32_t kFuseOrderedBytes = 64 * 1024;  // of K, and as much of V, that the workgroup of a unit moves itself
+
 // Limits of the FEW form: tokens per split (old scores and boundary rows are held in registers) and splits.
 constexpr int32_t kFewTokens = 2;    // per thread of 256
 constexpr int32_t kFewPieces = 2;    // 16-byte pieces of boundary rows per thread

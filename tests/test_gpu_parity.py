@@ -939,6 +939,46 @@ def test_step_of_few_units_at_the_edges_of_its_chunks(dtype, d, k, w, G, layout)
         np.testing.assert_allclose(a, b, rtol=2e-5, atol=2e-5 * float(np.abs(b).max()) * 0.05)
 
 
+@pytest.mark.parametrize("dtype,d,k,w,G", [(ko.F32, 64, 64, 16, 1), (ko.BF16, 128, 127, 127, 2), (ko.BF16, 64, 120, 0, 1),
+                                           (ko.F16, 256, 33, 5, 4), (ko.BF16, 256, 1, 0, 1), (ko.F32, 128, 100, 1, 8)])
+def test_small_ordered_step_in_one_launch_equals_the_two_calls(dtype, d, k, w, G):
+    """A few small units: the workgroup that scores a unit also moves its rows.  Units at, under and above the budget
+    (a full one is refused and still loses a token), eviction of the first, an inner and the newest candidate."""
+    rng = np.random.default_rng(4400 + k + d)
+    L, B, H, cap = 1, 2, 4, k + 1
+    lens = np.full((L, B, H), k, np.int32)
+    lens[0, 0, 1] = k // 2
+    lens[0, 1, 0] = cap
+    oc = random_cache(rng, L, B, H, d, cap, dtype, lens)
+    oc.score[0, 0, 2, 0] = -1.0                                  # the first candidate leaves
+    oc.score[0, 0, 3, max(0, k - w - 1):k - w + 1] = -2.0         # tied: the later of the two (if it is a candidate)
+    q, kn, vn = rnd(rng, (L, B, H * G, d), dtype), rnd(rng, (L, B, H, d), dtype), rnd(rng, (L, B, H, d), dtype)
+    seeds = np.array([5, 6], np.uint64)
+    results = []
+    for fused in (False, True):
+        gc = upload(oc, G)
+        assert kf.kf_decode_launch_shape(gc, cap)[0] == 1
+        ws = kf.new_workspace(gc)
+        out = torch.zeros((L, B, H * G, d), dtype=torch.float32, device="cuda")
+        kept = torch.full((L, B, H, k), -7, dtype=torch.int32, device="cuda")
+        args = (dev(q), dev(kn), dev(vn), 5 * cap, 0, 1.6, 0.11, kf.NOISE_GUMBEL, dev(seeds), None, out)
+        if fused:
+            kf.kf_decode_select_step(gc, *args, k=k, w=w, kept_idx=kept, workspace=ws)
+        else:
+            kf.kf_decode_step(gc, *args, ws)
+            kf.kf_select_evict(gc, k, w, kept, ws)
+        torch.cuda.synchronize()
+        assert error_word(ws) == 1
+        lens_now = host(gc.len)
+        live = [host(t).copy() for t in (gc.K, gc.V, gc.score, gc.pos)]
+        for l, b, h in np.ndindex(L, B, H):
+            for t in live:
+                t[l, b, h, int(lens_now[l, b, h]):] = 0
+        results.append([host(out).copy(), host(kept).copy(), lens_now.copy()] + live)
+    for a, b in zip(*results):
+        np.testing.assert_array_equal(a, b)
+
+
 @pytest.mark.parametrize("sweep_seed", SWEEP_SEEDS)
 def test_fused_step_on_random_shapes_equals_the_two_calls(sweep_seed):
     """Seeded sweep: kf_decode_select_step against kf_decode_step + kf_select_evict, bit for bit, over element
