@@ -21,7 +21,8 @@
 // instruction count is what is trimmed: 16.7 a pass (20.5 and 17.6 before the
 // hash's first step left the loop, the masking compares moved into the edge
 // tiles' branch and the accumulators into ordinary registers: 32 heads x 32768
-// rows 20.3 -> 18.4 ms, 256 x 4096 with position bias 3.13 -> 2.81 ms).  With the Gumbel adjustment (the method; the other
+// rows 20.3 -> 18.4 ms, 256 x 4096 with position bias 3.13 -> 2.81 ms), and at
+// temperature 1, where the adjustment is a quotient, 16 (17.5 and 2.59 ms).  With the Gumbel adjustment (the method; the other
 // adjustments keep the plain form): pass 1 sums every term against a reference
 // exponent instead of searching each tile's maximum first -- the reference
 // starts at the row's own diagonal term (so the sum cannot vanish), follows the
@@ -227,11 +228,22 @@ __device__ __forceinline__ float dot_piece(const uint4& x, const uint4& y, float
     return d;
 }
 
+// s + sum of e[i]/t[i], t = -l2u: the Gumbel factor (-ln u)^(-1/tau) at temperature 1 (its ln 2 rides in the
+// exponents).  Two quotients share a reciprocal, e0/t0 + e1/t1 = (e0*t1 + e1*t0) / (t0*t1); t lies in [8e-8, 24].
+__device__ __forceinline__ float add_over_t(const float (&e)[4], const float (&l2u)[4], float s) {
+#pragma unroll
+    for (int i = 0; i < 4; i += 2) {
+        const float num = fmaf(e[i], l2u[i + 1], e[i + 1] * l2u[i]);
+        s = fmaf(-num, __builtin_amdgcn_rcpf(l2u[i] * l2u[i + 1]), s);
+    }
+    return s;
+}
+
 // Sum over this lane's 16 logits of a tile of 2^(y2 - reference), Gumbel adjustment; `base` is the
 // adjustment's constant part less the reference (and the position bias of the lane's first key), rfold the
 // folded row key, kfold the folded key positions of the tile (this lane's: words 8*q4 + 4*half + e).  MASK:
 // keep only the keys up to `room` places behind the lane's first one (the tile crosses the diagonal).
-template <bool BIAS, bool MASK>
+template <bool BIAS, bool MASK, bool TAU1>
 __device__ __forceinline__ float tile_sum(const LogitParams& lp, const f32x16& acc, float base, uint32_t rfold,
                                           const uint32_t* kfold, int half, int room) {
     float ssum = 0.0f;
@@ -239,21 +251,26 @@ __device__ __forceinline__ float tile_sum(const LogitParams& lp, const f32x16& a
     for (int q4 = 0; q4 < 4; ++q4) {
         const uint4 k4 = *(const uint4*)&kfold[q4 * 8 + half * 4];
         const uint32_t ks[4] = {k4.x, k4.y, k4.z, k4.w};
+        float e[4], l2u[4];
 #pragma unroll
         for (int e4 = 0; e4 < 4; ++e4) {
             const int ro = q4 * 8 + e4;
-            const float l2t = hw_log2(neg_log2_uniform(mix32_folded(rfold ^ ks[e4])));
+            l2u[e4] = hw_log2(uniform_of(mix32_folded(rfold ^ ks[e4])));
             // position bias -slope*(dist0 - ro): its dist0 part rides in `base`, the ro part is a literal multiple
-            const float t = fmaf(l2t, -lp.inv_tau, BIAS ? fmaf(lp.slope1, (float)ro, base) : base);
-            const float e = hw_exp2(fmaf(acc[q4 * 4 + e4], lp.sc1, t));
-            ssum += (!MASK || ro <= room) ? e : 0.0f;
+            float t = BIAS ? fmaf(lp.slope1, (float)ro, base) : base;
+            if (!TAU1) t = fmaf(hw_log2(-l2u[e4]), -lp.inv_tau, t);
+            e[e4] = hw_exp2(fmaf(acc[q4 * 4 + e4], lp.sc1, t));
+            if (MASK) e[e4] = ro <= room ? e[e4] : 0.0f;
         }
+        ssum = TAU1 ? add_over_t(e, l2u, ssum) : (((ssum + e[0]) + e[1]) + e[2]) + e[3];
     }
     return ssum;
 }
 
-// GUMBEL: the method's adjustment, trimmed form; otherwise any adjustment, plain form.  BIAS: slopes given.
-template <typename T, int D, bool GUMBEL, bool BIAS>
+// GUMBEL: the method's adjustment, trimmed form; otherwise any adjustment, plain form.  BIAS: slopes given.  TAU1:
+// Gumbel at temperature 1, the method's temperature of the prompt: the adjustment's exponential is a quotient, one
+// logarithm and one multiply-add per logit less against half a reciprocal and three cheaper operations.
+template <typename T, int D, bool GUMBEL, bool BIAS, bool TAU1>
 __global__ void __launch_bounds__(kPrefillThreads, (kPrefillMinWaves<T, D>)) prefill_rowstats_kernel(const PrefillArgs a, int nblk, int64_t units) {
     constexpr int EPV = ElemTraits<T>::kPerVec;
     constexpr int NG = D / (2 * EPV);
@@ -343,9 +360,9 @@ __global__ void __launch_bounds__(kPrefillThreads, (kPrefillMinWaves<T, D>)) pre
                     if (diag) {
                         int room = i - jl;
                         asm volatile("" : "+v"(room));
-                        ssum = tile_sum<BIAS, true>(lp, acc, base, rfold, kfold[cur], half, room);
+                        ssum = tile_sum<BIAS, true, TAU1>(lp, acc, base, rfold, kfold[cur], half, room);
                     } else {
-                        ssum = tile_sum<BIAS, false>(lp, acc, base, rfold, kfold[cur], half, 0);
+                        ssum = tile_sum<BIAS, false, TAU1>(lp, acc, base, rfold, kfold[cur], half, 0);
                     }
                     const float Snew = Ssum + ssum;
                     // a sum beyond fp32 in some lane (a logit 2^120 above its row's reference): that lane raises its
@@ -424,7 +441,7 @@ __global__ void __launch_bounds__(kPrefillThreads, (kPrefillMinWaves<T, D>)) pre
 // Sum of this lane's 16 terms of a tile, a part of its key's column sum.  cs, rs: the tile's row statistics and row noise
 // keys (folded with the Gumbel adjustment); i_first: the lane's first query row.  MASK: the tile crosses the
 // diagonal or the end of the prompt.
-template <bool GUMBEL, bool BIAS, bool MASK>
+template <bool GUMBEL, bool BIAS, bool TAU1, bool MASK>
 __device__ __forceinline__ float column_sum(const LogitParams& lp, const f32x16& acc, const float* cs, const uint32_t* rs,
                                             int i_first, int half, int j, uint32_t kfold, int n) {
     float sum = 0.0f;  // of the tile: a long prompt's column takes n/2 terms, added one by one they would lose 1e-5
@@ -435,28 +452,30 @@ __device__ __forceinline__ float column_sum(const LogitParams& lp, const f32x16&
         const float cv[4] = {c4.x, c4.y, c4.z, c4.w};
         const uint32_t rv[4] = {r4.x, r4.y, r4.z, r4.w};
         const float dist0 = (float)(i_first + q4 * 8 - j);
+        float z[4], l2u[4];
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
             const float x = acc[q4 * 4 + e];
-            float z;
             if constexpr (GUMBEL) {
                 // cv holds (adjustment's constant part - row normaliser): z = 2^(x2 - log2(t)/tau + cv)
-                const float l2t = hw_log2(neg_log2_uniform(mix32_folded(rv[e] ^ kfold)));
-                float t = fmaf(l2t, -lp.inv_tau, cv[e]);
+                l2u[e] = hw_log2(uniform_of(mix32_folded(rv[e] ^ kfold)));
+                float t = cv[e];
+                if (!TAU1) t = fmaf(hw_log2(-l2u[e]), -lp.inv_tau, t);
                 if (BIAS) t = fmaf(dist0 + (float)e, -lp.slope1, t);
-                z = hw_exp2(fmaf(x, lp.sc1, t));
+                z[e] = hw_exp2(fmaf(x, lp.sc1, t));
             } else {
-                z = hw_exp2(logit2_other(lp, x, dist0 + (float)e, rv[e], (uint32_t)j) - cv[e]);
+                z[e] = hw_exp2(logit2_other(lp, x, dist0 + (float)e, rv[e], (uint32_t)j) - cv[e]);
             }
             const int i = i_first + q4 * 8 + e;
-            sum += (!MASK || (i >= j && i < n)) ? z : 0.0f;
+            if (MASK) z[e] = (i >= j && i < n) ? z[e] : 0.0f;
         }
+        sum = TAU1 ? add_over_t(z, l2u, sum) : (((sum + z[0]) + z[1]) + z[2]) + z[3];
     }
     return sum;
 }
 
 // PARTS: the query tiles of a column block are cut into parts, one workgroup each.
-template <typename T, int D, bool GUMBEL, bool BIAS, bool PARTS>
+template <typename T, int D, bool GUMBEL, bool BIAS, bool TAU1, bool PARTS>
 __global__ void __launch_bounds__(kPrefillThreads, (kPrefillMinWaves<T, D>)) prefill_colsum_kernel(const PrefillArgs a, int nblk, int64_t units) {
     constexpr int EPV = ElemTraits<T>::kPerVec;
     constexpr int NG = D / (2 * EPV);
@@ -566,9 +585,9 @@ __global__ void __launch_bounds__(kPrefillThreads, (kPrefillMinWaves<T, D>)) pre
             if (edge) {
                 int first = ib + half * 4;  // (the empty asm keeps the masking compares inside this branch, as in pass 1)
                 asm volatile("" : "+v"(first));
-                colsum += column_sum<GUMBEL, BIAS, true>(lp, acc, cs, rs, first, half, j, kfold, n);
+                colsum += column_sum<GUMBEL, BIAS, TAU1, true>(lp, acc, cs, rs, first, half, j, kfold, n);
             } else {
-                colsum += column_sum<GUMBEL, BIAS, false>(lp, acc, cs, rs, ib + half * 4, half, j, kfold, n);
+                colsum += column_sum<GUMBEL, BIAS, TAU1, false>(lp, acc, cs, rs, ib + half * 4, half, j, kfold, n);
             }
         }
         if (it > it_first) park(cur ^ 1, stage);
@@ -628,26 +647,28 @@ PrefillParts plan_prefill(int64_t U, int32_t n) {
     return {(int32_t)parts, (int32_t)tiles};
 }
 
-template <typename T, int D, bool GUMBEL, bool BIAS>
+template <typename T, int D, bool GUMBEL, bool BIAS, bool TAU1>
 static hipError_t launch_passes(const PrefillArgs& a, int64_t U, hipStream_t st) {
     const int nblk = (a.n + 4 * kTile - 1) / (4 * kTile);
     const int64_t groups = (U + kXcds - 1) / kXcds;  // units are dealt to XCDs in groups of 8
     const dim3 grid((unsigned)(groups * kXcds * nblk * a.parts)), block(kPrefillThreads);
-    hipLaunchKernelGGL((prefill_rowstats_kernel<T, D, GUMBEL, BIAS>), grid, block, 0, st, a, nblk, U);
+    hipLaunchKernelGGL((prefill_rowstats_kernel<T, D, GUMBEL, BIAS, TAU1>), grid, block, 0, st, a, nblk, U);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    if (a.parts > 1) hipLaunchKernelGGL((prefill_colsum_kernel<T, D, GUMBEL, BIAS, true>), grid, block, 0, st, a, nblk, U);
-    else hipLaunchKernelGGL((prefill_colsum_kernel<T, D, GUMBEL, BIAS, false>), grid, block, 0, st, a, nblk, U);
+    if (a.parts > 1) hipLaunchKernelGGL((prefill_colsum_kernel<T, D, GUMBEL, BIAS, TAU1, true>), grid, block, 0, st, a, nblk, U);
+    else hipLaunchKernelGGL((prefill_colsum_kernel<T, D, GUMBEL, BIAS, TAU1, false>), grid, block, 0, st, a, nblk, U);
     return hipGetLastError();
 }
 
 template <typename T, int D>
 static hipError_t launch_prefill_t(const PrefillArgs& a, int64_t U, hipStream_t st) {
-    // four builds of each pass: the Gumbel adjustment in the trimmed form or any adjustment in the plain form,
-    // with or without the position-bias term
-    const bool gum = a.noise == kNoiseGumbel, bias = a.slopes != nullptr;
-    hipError_t e = gum ? (bias ? launch_passes<T, D, true, true>(a, U, st) : launch_passes<T, D, true, false>(a, U, st))
-                       : (bias ? launch_passes<T, D, false, true>(a, U, st) : launch_passes<T, D, false, false>(a, U, st));
+    // six builds of each pass: the Gumbel adjustment in the trimmed form, at temperature 1 or any other, or any
+    // adjustment in the plain form; with or without the position-bias term
+    const bool bias = a.slopes != nullptr;
+    hipError_t e;
+    if (a.noise != kNoiseGumbel) e = bias ? launch_passes<T, D, false, true, false>(a, U, st) : launch_passes<T, D, false, false, false>(a, U, st);
+    else if (a.inv_tau == 1.0f) e = bias ? launch_passes<T, D, true, true, true>(a, U, st) : launch_passes<T, D, true, false, true>(a, U, st);
+    else e = bias ? launch_passes<T, D, true, true, false>(a, U, st) : launch_passes<T, D, true, false, false>(a, U, st);
     if (e != hipSuccess || (a.G == 1 && a.parts == 1)) return e;
     hipLaunchKernelGGL(prefill_group_sum_kernel, dim3((unsigned)(U / a.G), (unsigned)((a.n + 255) / 256)), dim3(256), 0,
                        st, a, U / a.G);
