@@ -456,7 +456,8 @@ __global__ void __launch_bounds__(kWideThreads) shift_chunk_kernel(const SelectA
         fs = (src == bnd) ? a.ws_bscore[(size_t)u * a.nb + c] : fu[src];
         ps = (src == bnd) ? a.ws_bpos[(size_t)u * a.nb + c] : pu[src];
     }
-    __syncthreads();  // (with its wait for the loads) every source of the chunk is in registers
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // (the barrier by itself does not wait for loads)
+    __syncthreads();  // every source of the chunk is in registers
 #pragma unroll
     for (int i = 0; i < kWidePieces; ++i) {
         const int p = tid + i * kWideThreads;
