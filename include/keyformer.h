@@ -143,7 +143,8 @@ uint32_t kf_noise_bits(uint64_t seed, uint32_t layer, uint32_t head, uint32_t q_
 
 /* Bytes of workspace that suffice for any call of this library on this
  * cache, with prompt length up to n_max (pass 0 if kf_prefill_score is not
- * used).  Only the cache's dimensions are read. */
+ * used).  Only the cache's dimensions are read.  A workspace that lacks only the
+ * room for the forms that few units take is accepted and served by the others. */
 size_t kf_workspace_bytes(const kf_cache *c, int32_t n_max);
 
 /* How kf_decode_step would shape its launch for this cache and m_hint (0 = cap):
@@ -249,11 +250,12 @@ kf_status kf_beam_fork(kf_cache *c, const int32_t *parent, void *workspace, size
 /*
  * One whole generation step: kf_decode_step followed by kf_select_evict, with
  * the same arguments, results and error behaviour as the two calls in a row,
- * in as few kernel launches as the shape allows: one in the slot layout when
- * every unit is handled by a single workgroup (that workgroup also evicts and
- * stores the new token straight into the freed slot), else the merge of the
- * decode kernel's split-wise results rides in the selection kernel where that
- * pays.  Algorithm 1, one iteration of the else-branch including the S_w /
+ * in as few kernel launches as the shape allows: one when every unit is handled
+ * by a single workgroup and it is the slot layout (that workgroup also evicts and
+ * stores the new token straight into the freed slot) or a few small units (it
+ * moves the rows itself); two for few units in splits, the second of which
+ * merges, selects and moves the rows; else the merge of the decode kernel's
+ * split-wise results rides in the selection kernel where that pays.  Algorithm 1, one iteration of the else-branch including the S_w /
  * S_key / S_k lines.
  */
 kf_status kf_decode_select_step(kf_cache *c, const void *q, const void *k_new, const void *v_new,
