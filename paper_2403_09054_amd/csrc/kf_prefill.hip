@@ -99,12 +99,14 @@ __device__ __forceinline__ float log2_of_sum(float M, float S) {
     return (M + (float)((int)ex - 127)) + hw_log2(__uint_as_float((b & 0x7FFFFFu) | 0x3F800000u));
 }
 
-// Log2 of a row's normaliser from the partial sums its parts left: sum over p of S_p * 2^(M_p).
+// Log2 of a row's normaliser from the partial sums its parts left: sum over p of S_p * 2^(M_p).  A NaN among the row's
+// logits makes the sum NaN, whichever part met it: it shows in the sum or, where the row's own diagonal term is the
+// NaN, in the reference of every part while the sums are empty.
 __device__ __forceinline__ float merged_normaliser(const float2* rec, size_t stride, int parts) {
     float M = -INFINITY, S = 0.0f;
     for (int p = 0; p < parts; ++p) {
         const float2 r = rec[p * stride];
-        if (!(r.y > 0.0f) && r.y == r.y) continue;  // nothing in this part (a NaN sum is carried on)
+        if (r.y <= 0.0f && r.x == r.x) continue;  // nothing in this part
         const float Mn = fmaxf(M, r.x);
         S = (M > -INFINITY ? S * hw_exp2(M - Mn) : 0.0f) + r.y * hw_exp2(r.x - Mn);
         M = Mn;
@@ -320,7 +322,9 @@ __global__ void __launch_bounds__(kPrefillThreads, (kPrefillMinWaves<T, D>)) pre
         if (threadIdx.x < kTile) kfold[buf][threadIdx.x] = fold16((uint32_t)(jt * kTile + threadIdx.x) * kKposMul);
     };
 
-    float M = -INFINITY, Ssum = 0.0f;
+    // (A part behind the first starts from a finite reference below every logit: with -inf a tile of nothing but
+    // masked logits and NaN would not be told from an empty one.)
+    float M = !GUMBEL && part > 0 ? -0x1p127f : -INFINITY, Ssum = 0.0f;
     if constexpr (GUMBEL) {
         // Reference exponent of the row's sum: its own diagonal term y2_ii, formed here from the query's and the
         // key's elements this lane holds (both halves of the wave added up).  It is a term of the sum, so the

@@ -1405,6 +1405,24 @@ def test_prefill_in_parts_and_whole_match_oracle(dtype, d, G, n, noise, biased):
     run(hi)
 
 
+@pytest.mark.parametrize("noise,tau", [(ko.NOISE_GUMBEL, 1.0), (ko.NOISE_GUMBEL, 1.4), (ko.NOISE_NONE, 1.0),
+                                       (ko.NOISE_GAUSSIAN, 1.4)])
+def test_nan_in_the_last_key_reaches_every_column_in_parts_too(noise, tau):
+    """A NaN logit makes its row's normaliser NaN and with it every column that the row adds to.  The last row is the
+    only one that sees the last key: its own diagonal term, and (n = 3 * 128 + 1) the only key of the row's last part."""
+    rng = np.random.default_rng(385)
+    L, B, H, d, n = 1, 1, 4, 64, 385
+    oc = random_cache(rng, L, B, H, d, n, ko.BF16, 0)
+    oc.K[0, 0, 1, n - 1, 5] = 0x7FC0
+    Q = rnd(rng, (L, B, H, n, d), ko.BF16)
+    gc = upload(oc)
+    kf.kf_prefill_score(gc, dev(Q), n, tau, 0.125, noise, dev(np.array([5], np.uint64)), None, kf.new_workspace(gc, n))
+    torch.cuda.synchronize()
+    nan = np.isnan(host(gc.score))
+    assert nan[0, 0, 1].all()
+    assert not nan[0, 0, [0, 2, 3]].any()
+
+
 @pytest.mark.parametrize("cap,k,w", [(2047, 1000, 200), (2048, 2047, 2047), (2049, 1, 0), (8192, 3000, 0), (8193, 4000, 4000),
                                      (32768, 9830, 1966), (32769, 20000, 100), (64, 10, 9)])
 def test_survivor_lists_at_the_edges_of_their_register_forms(cap, k, w):
