@@ -252,10 +252,12 @@ kf_status kf_beam_fork(kf_cache *c, const int32_t *parent, void *workspace, size
  * the same arguments, results and error behaviour as the two calls in a row,
  * in as few kernel launches as the shape allows: one when every unit is handled
  * by a single workgroup and it is the slot layout (that workgroup also evicts and
- * stores the new token straight into the freed slot) or a few small units (it
- * moves the rows itself); two for few units in splits, the second of which
- * merges, selects and moves the rows; else the merge of the decode kernel's
- * split-wise results rides in the selection kernel where that pays.  Algorithm 1, one iteration of the else-branch including the S_w /
+ * stores the new token straight into the freed slot) or a few small units with
+ * cap == k+1 (it moves the rows itself); two for few units in splits, the second of
+ * which merges, selects and moves the rows, and a third if m_hint (0: cap) is above
+ * k+1, for units that come out more than one token over the budget; else the merge
+ * of the decode kernel's split-wise results rides in the selection kernel where
+ * that pays.  Algorithm 1, one iteration of the else-branch including the S_w /
  * S_key / S_k lines.
  */
 kf_status kf_decode_select_step(kf_cache *c, const void *q, const void *k_new, const void *v_new,

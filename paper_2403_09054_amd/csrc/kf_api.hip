@@ -452,6 +452,7 @@ static kf_status prepare_select(kf_cache* c, int32_t k, int32_t w, int32_t layou
     a->move = 1;
     a->ws_err = (int32_t*)workspace + KF_WS_ERROR_WORD;
     a->step_inc = nullptr;
+    a->rest = 0;
     // Few units, or long ones: one workgroup per unit cannot move the rows of an ordered eviction at the
     // chip's rate, so a second launch spreads every unit's rows over many workgroups.
     a->chunk_rows = kf::wide_chunk_rows(a->row_bytes);
@@ -642,8 +643,10 @@ static kf_status fused_step(kf_cache* c, const void* q, const void* k_new, const
         da.few_brow = sa.ws_brow;
         da.few_bpos = sa.ws_bpos;
         sa.wide = 0;  // of the units that take the general way
+        sa.rest = (m_hint ? m_hint : c->cap) > k + 1;  // a unit may come out more than one token over its budget
         e = kf::launch_decode_split(da, U, c->d, c->dtype, p.lds_bytes, (hipStream_t)stream);
         if (e == hipSuccess) e = kf::launch_step_finish(da, sa, U, c->d, (hipStream_t)stream);
+        if (e == hipSuccess && sa.rest) e = kf::launch_step_rest(da, sa, U, (hipStream_t)stream);
     } else if (da.S > 1 && (int64_t)da.S * da.chunk <= kTailMergeMaxTokens && !sa.presel) {
         // few units in splits: the merge rides in the selection launch, whatever the number of query heads
         if (layout == KF_LAYOUT_SLOT || sa.wide) {

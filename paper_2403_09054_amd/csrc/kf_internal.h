@@ -133,6 +133,7 @@ struct SelectArgs {
     int32_t presel_done;        // the slices' minima are there already (left by the decode merge launch)
     unsigned long long* ws_pmin;  // [U][presel] smallest (score key, tie-break) pack of the slice, ~0 if none
     int32_t* ws_pslot;          // [U][presel] its slot
+    int32_t rest;               // launch_step_finish: units not exactly one token over the budget are left to launch_step_rest
 };
 constexpr int32_t kPreselMaxSlices = 16;
 // rows per workgroup of the wide shift: 2048 16-byte pieces per tensor, i.e. 32 KB of K and 32 KB of V
@@ -175,6 +176,8 @@ hipError_t launch_step_tail(const DecodeArgs& d, const SelectArgs& a, int64_t U,
 // merge + selection + compaction of a small launch, several workgroups per unit (after a FEW split launch with few_f)
 constexpr int32_t kFinishMaxTokens = 4096;
 hipError_t launch_step_finish(const DecodeArgs& d, const SelectArgs& a, int64_t U, int32_t hd, hipStream_t stream);
+// selection and compaction of the units that launch_step_finish left with a.rest set
+hipError_t launch_step_rest(const DecodeArgs& d, const SelectArgs& a, int64_t U, hipStream_t stream);
 // the row-shifting launch of the two-launch eviction (after a selection launch that ran with a.wide set)
 hipError_t launch_shift(const SelectArgs& a, int64_t U, hipStream_t stream);
 // the split kernel alone (no merge launch): first half of a fused step

@@ -711,8 +711,10 @@ __global__ void __launch_bounds__(kFinishThreads) step_finish_kernel(const Decod
     if (m != k + 1) {         // within budget, or far over it: one workgroup does the unit the general way
         if (c < 0) {
             if (m > 0) merge_unit<D, NT, G>(d, u, m - 1, w_p, w_e, 0, m, true);
-            __syncthreads();
-            select_unit<NT>(a, u);
+            if (!a.rest) {
+                __syncthreads();
+                select_unit<NT>(a, u);
+            }
         }
         advance_step(a);  // (the first workgroup of the launch is one of these)
         return;
@@ -875,6 +877,19 @@ hipError_t launch_step_finish(const DecodeArgs& d, const SelectArgs& a, int64_t 
     if (hd == 128) return launch_step_finish_d<128>(d, a, U, stream);
     if (hd == 256) return launch_step_finish_d<256>(d, a, U, stream);
     return hipErrorInvalidValue;
+}
+
+// Where a unit can be further over its budget (the launch above is told by a.rest): those units, by workgroups large
+// enough to move their rows.  The launch above's own 256 threads took 146 us for 16 units of 2047 tokens x 256 cut to
+// 1024 (78 so; 32 x 4095 x 128 to 2048: 161, 94); made of 1024 threads it cost every ordinary step 10 to 20 %.
+// An empty launch otherwise.
+__global__ void __launch_bounds__(kSelectThreads) step_rest_kernel(const int32_t* m, const SelectArgs a) {
+    if (m[blockIdx.x] == a.k + 1) return;
+    select_unit<kSelectThreads>(a, (int64_t)blockIdx.x);
+}
+hipError_t launch_step_rest(const DecodeArgs& d, const SelectArgs& a, int64_t U, hipStream_t stream) {
+    hipLaunchKernelGGL(step_rest_kernel, dim3((unsigned)U), dim3(kSelectThreads), 0, stream, d.ws_m, a);
+    return hipGetLastError();
 }
 
 template <int NT, int G>

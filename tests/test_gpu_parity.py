@@ -939,6 +939,45 @@ def test_step_of_few_units_at_the_edges_of_its_chunks(dtype, d, k, w, G, layout)
         np.testing.assert_allclose(a, b, rtol=2e-5, atol=2e-5 * float(np.abs(b).max()) * 0.05)
 
 
+@pytest.mark.parametrize("over,hint", [(0, 0), (1, 0), (2, 0), (90, 0), (0, 201), (1, 201)])
+def test_step_of_few_units_far_over_the_budget_equals_the_two_calls(over, hint):
+    """The units that the one-launch end of a step of few units leaves to the launch behind it (m_hint says that a unit
+    may be further over its budget): with kept_idx or without, the step number moved on once."""
+    rng = np.random.default_rng(70 + over)
+    L, B, H, d, k, w, cap = 1, 1, 4, 128, 200, 40, 300
+    lens = np.array([k - 1 + over, k, k // 3, k - 1 + over], np.int32).reshape(L, B, H)
+    oc = random_cache(rng, L, B, H, d, cap, ko.BF16, lens)
+    oc.pos[...] = np.arange(cap)
+    q, kn, vn = (rnd(rng, (L, B, H, d), ko.BF16) for _ in range(3))
+    results = []
+    for fused, idx in ((False, True), (True, True), (True, False)):
+        gc = upload(oc)
+        assert kf.kf_decode_launch_shape(gc, hint)[0] > 1
+        ws = kf.new_workspace(gc)
+        out = torch.zeros((L, B, H, d), dtype=torch.float32, device="cuda")
+        kept = torch.full((L, B, H, k), -7, dtype=torch.int32, device="cuda") if idx else None
+        seeds, step = dev(np.array([5], np.uint64)), torch.full((1,), 11, dtype=torch.int32, device="cuda")
+        if fused:
+            kf.kf_decode_select_step_at(gc, dev(q), dev(kn), dev(vn), cap, 32, 1.0, 2.0, step, hint, 0.09, kf.NOISE_GUMBEL,
+                                        seeds, None, out, k=k, w=w, kept_idx=kept, workspace=ws)
+            assert int(step.item()) == 12
+        else:
+            kf.kf_decode_step(gc, dev(q), dev(kn), dev(vn), cap + 10, hint, kf.kf_tau(11, 32), 0.09, kf.NOISE_GUMBEL, seeds,
+                              None, out, ws)
+            kf.kf_select_evict(gc, k, w, kept, ws)
+        torch.cuda.synchronize()
+        assert error_word(ws) == 0
+        lens_now = host(gc.len)
+        live = [host(t).copy() for t in (gc.K, gc.V, gc.score, gc.pos)]
+        for l, b, h in np.ndindex(L, B, H):
+            for t in live:
+                t[l, b, h, int(lens_now[l, b, h]):] = 0
+        results.append([host(out).copy(), lens_now.copy()] + live + ([host(kept).copy()] if idx else []))
+    for r in results[1:]:
+        for a, b in zip(results[0], r):
+            np.testing.assert_array_equal(a, b)
+
+
 @pytest.mark.parametrize("dtype,d,k,w,G", [(ko.F32, 64, 64, 16, 1), (ko.BF16, 128, 127, 127, 2), (ko.BF16, 64, 120, 0, 1),
                                            (ko.F16, 256, 33, 5, 4), (ko.BF16, 256, 1, 0, 1), (ko.F32, 128, 100, 1, 8)])
 def test_small_ordered_step_in_one_launch_equals_the_two_calls(dtype, d, k, w, G):
