@@ -37,11 +37,25 @@ constexpr int64_t kMaxGrid = 0x7fffffff;  // workgroups of a one-dimensional lau
 constexpr int64_t kTailMergeMaxTokens = 4096;
 constexpr int64_t kWideMaxUnits = 256;
 constexpr int32_t kPreselMinTokens = 4096;
-// Bytes of window rows up to which the decode launch of an ordered step leaves them in the caches for the row shift
-// (the chip's memory-side cache holds 256 MB).  Caches of several layers in turn: 2048 heads x 1024 x 128 (215 MB)
-// 276 -> 267 us a step, 1024 x 2048 x 128 (215 MB) 278 -> 264, 448 x 1024 x 256 (94 MB) 140 -> 133, 256 x 2048 x 128
-// 80 -> 76; 8192 x 2048 x 128 (1.7 GB), where they are gone again, 2038 -> 2099.
+// Whether the decode launch of an ordered step leaves the window rows, which the eviction is going to move, in the
+// caches for it (the chip's memory-side cache holds 256 MB), on U units of budget k.  Measured with the same build
+// and the switch on and off, on caches of several layers in turn (the next layer finds nothing of its own in a cache):
+// many units gain where the window is a large share of large units -- up to 11 % where window bytes times its share of
+// the budget reach 16 KB (256 x 1024 x 256 in 16 bits, window 409, 111.0 -> 100.7 us; 1024 x 1024 x 128, 409,
+// 195 -> 182; 2048 x 1024 x 128, 204, 305 -> 303), alike in fp32 and with 2 to 8 query heads per cached head; smaller
+// shares lose up to 3 % (512 x 300 x 256, 60, 57.2 -> 58.3; 1024 x 700 x 128, 70, 107.7 -> 110.5).  A few units only
+// gain with a third of the budget and many bytes (64 x 6000 x 128, window 2400, 93.9 -> 89.2; 16 x 9830 x 256, 3932,
+// 86.6 -> 83.9) and lose below (16 x 6000 x 128, window 1200, 40.7 -> 43.9; 32 x 2048 x 256, 409, 43.9 -> 47.1).
+// Beyond the cache they are gone again (8192 x 2048 x 128, 1.7 GB, 2038 -> 2099).
 constexpr int64_t kKeepMaxBytes = 256ll << 20;
+constexpr int64_t kKeepManyUnits = 128;
+constexpr int64_t kKeepMinShare = 16 << 10;         // many units: window bytes of a unit times w / k
+constexpr int64_t kKeepFewMinBytes = 48ll << 20;    // fewer: of all units
+bool keep_pays(int64_t U, int32_t k, int32_t w, int32_t row_bytes) {
+    const int64_t unit = (int64_t)w * 2 * row_bytes, all = U * unit;
+    if (all > kKeepMaxBytes) return false;
+    return U >= kKeepManyUnits ? unit * w >= kKeepMinShare * k : all >= kKeepFewMinBytes && 3 * (int64_t)w >= k;
+}
 // A step of at most this many units is bound by the chain of memory round trips through its launches, not by bytes:
 // its splits are short, ask for everything at once, and (ordered layout) one launch merges, selects and moves the
 // rows instead of two.  28 layers of 16 heads, d = 256, k = 1024, a call each: 646 -> 466 us per token (slot layout
@@ -614,8 +628,7 @@ static kf_status fused_step(kf_cache* c, const void* q, const void* k_new, const
         sa.step_inc = step;
     }
     const int64_t U = (int64_t)c->L * c->B * c->H;
-    // the rows that the eviction is going to move, if the memory-side cache can hold them until then
-    if (layout == KF_LAYOUT_ORDERED && U * w * 2 * sa.row_bytes <= kKeepMaxBytes) da.keep_w = w;
+    if (layout == KF_LAYOUT_ORDERED && keep_pays(U, k, w, sa.row_bytes)) da.keep_w = w;
     hipError_t e;
     // a few small units: the workgroup that scored one also moves its rows (2 heads x 64 x 64 in fp32, whose two
     // launches were all host and launch time, 17.9 -> 15.7 us a step); cap: no unit is further over its budget

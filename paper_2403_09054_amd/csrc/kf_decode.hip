@@ -291,7 +291,12 @@ __device__ __forceinline__ void close_gap(u32x4_t* Ku, u32x4_t* Vu, const u32x4_
 // asked for at once, before the unit's length is known: its first K and V tiles, the old scores of its tokens and
 // the rows at the chunk boundaries of the eviction that follows (see step_finish_kernel).  Rows past the unit's
 // length are read (they lie in the unit's own cache) and dropped.
-template <typename T, int D, int NT, int G, bool FEW>
+//
+// ORDERED: the form for ordered steps that load the rows which the eviction moves into the caches (keep_w), or evict
+// here (fuse_ordered).  The streaming loops exist twice in it and the row move takes registers; all other launches keep
+// the form without them (one head: 67 to 69 registers, 75 in this one, which is one
+// 4-wave workgroup less per CU).
+template <typename T, int D, int NT, int G, bool FEW, bool ORDERED>
 __device__ __forceinline__ void decode_block(const DecodeArgs& a) {
     constexpr int EPV = ElemTraits<T>::kPerVec;  // elements per 16-byte vector
     constexpr int LPR = D / EPV;                 // lanes that share one row
@@ -409,7 +414,7 @@ __device__ __forceinline__ void decode_block(const DecodeArgs& a) {
                 if (a.fuse_k > 0 && len0 > a.fuse_k + 1) atomicAdd(a.ws_err, 1);
             }
         }
-        if constexpr (!FEW && !BIG) {
+        if constexpr (ORDERED && !BIG) {
             // ordered whole-step launch: the selection evicts from a full unit all the same, by the scores it has
             // (the launch is only made when a unit cannot hold more than one token over its budget)
             if (a.fuse_ordered && len0 < 0 && a.fuse_idx)
@@ -469,7 +474,8 @@ __device__ __forceinline__ void decode_block(const DecodeArgs& a) {
     // Rows from jkeep on are loaded the ordinary way, into the caches: the eviction that follows in the same step
     // moves them and finds them in the memory-side cache.  The others stream past the caches.  (A loop for each kind:
     // with a choice per tile the compiler merges both kinds of load into ordinary ones, or waits for each tile.)
-    const int jkeep = FEW ? 0 : a.keep_w > 0 ? m - a.keep_w : 0x7FFFFFFF;
+    constexpr int kAll = 0x7FFFFFFF;
+    const int jkeep = ORDERED && a.keep_w > 0 ? m - a.keep_w : kAll;
     auto load_plain = [&](auto keep, const char* rows, int base, uint4(&raw)[UNR]) {
         const char* p = rows + (size_t)base * ROWB + lane_off;
 #pragma unroll
@@ -775,7 +781,7 @@ __device__ __forceinline__ void decode_block(const DecodeArgs& a) {
                 }
             };
             if constexpr (!FEW) steady(Flag<false>(), jkeep);
-            steady(Flag<true>(), 0x7FFFFFFF);
+            if constexpr (FEW || ORDERED) steady(Flag<true>(), kAll);
             while (base < j1) {  // the last one or two tiles of the split
                 if (base + TILE < j1) {
                     load_edge(Ku, base + TILE, nxt);
@@ -953,7 +959,7 @@ __device__ __forceinline__ void decode_block(const DecodeArgs& a) {
             }
         };
         if constexpr (!FEW) steady(Flag<false>(), jkeep);
-        steady(Flag<true>(), 0x7FFFFFFF);
+        if constexpr (FEW || ORDERED) steady(Flag<true>(), kAll);
         while (base < j1) {
             if (base + TILE < j1) load_edge(Vu, base + TILE, nxt);
             weigh(base);
@@ -1076,7 +1082,7 @@ __device__ __forceinline__ void decode_block(const DecodeArgs& a) {
             float df = 0.0f;
 #pragma unroll
             for (int g = 0; g < G; ++g) df = fmaf(ys[g * CS + t], inv[g], df);
-            if (!BIG && !FEW && evict_here && a.fuse_ordered) {  // the new scores wait in LDS for their slots
+            if (ORDERED && !BIG && evict_here && a.fuse_ordered) {  // the new scores wait in LDS for their slots
                 const float f_new = t == cnt_c ? df : fu[slot] + df;
                 ys[t] = f_new;
                 if (slot < m - a.fuse_w) {
@@ -1168,7 +1174,7 @@ __device__ __forceinline__ void decode_block(const DecodeArgs& a) {
             }
             return;
         }
-        if (!BIG && !FEW && a.fuse_ordered) {
+        if (ORDERED && !BIG && a.fuse_ordered) {
             for (int i = tid; i < k; i += NT) {
                 fu[i] = ys[i + (i >= e ? 1 : 0)];
                 if (a.fuse_idx) a.fuse_idx[(size_t)u * k + i] = i + (i >= e ? 1 : 0);
@@ -1236,9 +1242,9 @@ __device__ __forceinline__ void decode_block(const DecodeArgs& a) {
 
 // (The 8-wave workgroup is compiled for four waves per SIMD, i.e. two per CU -- at most 128 registers per lane: with a few more its
 // medium-length units lose the second workgroup that overlaps their statistics and folds, 67 -> 48 % of peak.)
-template <typename T, int D, int NT, int G, bool FEW>
+template <typename T, int D, int NT, int G, bool FEW, bool ORDERED>
 __global__ void __launch_bounds__(NT, NT >= 512 ? 4 : 1) decode_kernel(const DecodeArgs a) {
-    decode_block<T, D, NT, G, FEW>(a);
+    decode_block<T, D, NT, G, FEW, ORDERED>(a);
     // Whole-step launch with the step number in device memory: every workgroup read the number when it
     // started, so the one that finishes last may move it on (and clears the ticket counter for the next launch).
     if (a.step_inc && threadIdx.x == 0) {
@@ -1480,7 +1486,8 @@ static hipError_t launch_decode_g(const DecodeArgs& a, int64_t U, size_t lds, hi
         if (logits > big_from) {
             const size_t lds_big = decode_lds_bytes_big(G, a.chunk, D);
             if (lds_big > kDecodeLdsWhole) return hipErrorInvalidValue;
-            hipLaunchKernelGGL((decode_kernel<T, D, kDecodeThreadsBig, G, false>), grid, dim3(kDecodeThreadsBig), lds_big, st, a);
+            if (a.keep_w > 0) hipLaunchKernelGGL((decode_kernel<T, D, kDecodeThreadsBig, G, false, true>), grid, dim3(kDecodeThreadsBig), lds_big, st, a);
+            else hipLaunchKernelGGL((decode_kernel<T, D, kDecodeThreadsBig, G, false, false>), grid, dim3(kDecodeThreadsBig), lds_big, st, a);
             hipError_t e2 = hipGetLastError();
             if (e2 == hipSuccess && a.S > 1 && merge) {
                 const int32_t slices = decode_merge_slices(a.S, a.chunk);
@@ -1495,13 +1502,15 @@ static hipError_t launch_decode_g(const DecodeArgs& a, int64_t U, size_t lds, hi
         if (a.S == 1 && lds > kDecodeLdsPair) {  // a unit too long for two workgroups per CU: one of 8 waves
             const size_t lds_big = decode_lds_bytes_big(G, a.chunk, D);
             if (lds_big > kDecodeLdsWhole) return hipErrorInvalidValue;
-            hipLaunchKernelGGL((decode_kernel<T, D, kDecodeThreadsBig, G, false>), grid, dim3(kDecodeThreadsBig), lds_big, st, a);
+            if (a.keep_w > 0) hipLaunchKernelGGL((decode_kernel<T, D, kDecodeThreadsBig, G, false, true>), grid, dim3(kDecodeThreadsBig), lds_big, st, a);
+            else hipLaunchKernelGGL((decode_kernel<T, D, kDecodeThreadsBig, G, false, false>), grid, dim3(kDecodeThreadsBig), lds_big, st, a);
             return hipGetLastError();
         }
     }
     if (lds > kDecodeLdsPair) return hipErrorInvalidValue;
-    if (a.few) hipLaunchKernelGGL((decode_kernel<T, D, kDecodeThreads, G, true>), grid, block, lds, st, a);
-    else hipLaunchKernelGGL((decode_kernel<T, D, kDecodeThreads, G, false>), grid, block, lds, st, a);
+    if (a.few) hipLaunchKernelGGL((decode_kernel<T, D, kDecodeThreads, G, true, false>), grid, block, lds, st, a);
+    else if (a.keep_w > 0 || a.fuse_ordered) hipLaunchKernelGGL((decode_kernel<T, D, kDecodeThreads, G, false, true>), grid, block, lds, st, a);
+    else hipLaunchKernelGGL((decode_kernel<T, D, kDecodeThreads, G, false, false>), grid, block, lds, st, a);
     hipError_t e = hipGetLastError();
     if (e == hipSuccess && a.S > 1 && merge) {
         const int32_t slices = decode_merge_slices(a.S, a.chunk);

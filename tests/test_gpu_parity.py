@@ -939,6 +939,40 @@ def test_step_of_few_units_at_the_edges_of_its_chunks(dtype, d, k, w, G, layout)
         np.testing.assert_allclose(a, b, rtol=2e-5, atol=2e-5 * float(np.abs(b).max()) * 0.05)
 
 
+@pytest.mark.parametrize("dtype,d,B,k,w,G", [(ko.BF16, 128, 4, 300, 200, 1), (ko.BF16, 128, 10, 150, 100, 1), (ko.F32, 128, 4, 200, 99, 2),
+                                             (ko.F16, 64, 8, 400, 400, 4), (ko.BF16, 128, 8, 260, 130, 8), (ko.F32, 64, 4, 333, 222, 8)])
+def test_ordered_step_that_keeps_the_window_rows_in_the_caches(dtype, d, B, k, w, G):
+    """128 units and more with a large window: the form of the decode launch that loads the rows which the eviction
+    moves the ordinary way, in splits and whole, against the two calls (which have no such rows)."""
+    rng = np.random.default_rng(6100 + k + d)
+    L, H, cap = 1, 32, k + 60
+    assert B * H >= 128 and w * w * 2 * d * (4 if dtype == ko.F32 else 2) >= 16384 * k
+    oc = random_cache(rng, L, B, H, d, cap, dtype, k)
+    oc.len[0, 0, 0], oc.len[0, 1, 1], oc.len[0, 2, 2] = k - 7, k + 9, cap
+    q, kn, vn = rnd(rng, (L, B, H * G, d), dtype), rnd(rng, (L, B, H, d), dtype), rnd(rng, (L, B, H, d), dtype)
+    seeds = dev(np.arange(B).astype(np.uint64))
+    results = []
+    for fused in (False, True):
+        gc = upload(oc, G)
+        ws = kf.new_workspace(gc)
+        out = torch.zeros((L, B, H * G, d), dtype=torch.float32, device="cuda")
+        args = (dev(q), dev(kn), dev(vn), 5 * cap, 0, 1.6, 0.11, kf.NOISE_GUMBEL, seeds, None, out)
+        if fused:
+            kf.kf_decode_select_step(gc, *args, k=k, w=w, workspace=ws)
+        else:
+            kf.kf_decode_step(gc, *args, ws)
+            kf.kf_select_evict(gc, k, w, None, ws)
+        torch.cuda.synchronize()
+        lens_now = host(gc.len)
+        live = [host(t).copy() for t in (gc.K, gc.V, gc.score, gc.pos)]
+        for l, b, h in np.ndindex(L, B, H):
+            for t in live:
+                t[l, b, h, int(lens_now[l, b, h]):] = 0
+        results.append([host(out).copy(), lens_now.copy()] + live)
+    for a, b in zip(*results):
+        np.testing.assert_array_equal(a, b)
+
+
 @pytest.mark.parametrize("over,hint", [(0, 0), (1, 0), (2, 0), (90, 0), (0, 201), (1, 201)])
 def test_step_of_few_units_far_over_the_budget_equals_the_two_calls(over, hint):
     """The units that the one-launch end of a step of few units leaves to the launch behind it (m_hint says that a unit
