@@ -58,11 +58,19 @@ bool keep_pays(int64_t U, int32_t k, int32_t w, int32_t row_bytes) {
 }
 // A step of at most this many units is bound by the chain of memory round trips through its launches, not by bytes:
 // its splits are short, ask for everything at once, and (ordered layout) one launch merges, selects and moves the
-// rows instead of two.  28 layers of 16 heads, d = 256, k = 1024, a call each: 646 -> 466 us per token (slot layout
-// 499 -> 447); 32 heads x 1024 x 128 24 -> 19 us, 64 x 2048 x 128 32.4 -> 28.3;
-// 128 x 2048 x 128, bound by its bytes, 48.5 -> 47.4 and with more units the repeated merging costs what the saved
-// launch gains.
+// rows instead of two.  28 layers of 16 heads, d = 256, k = 1024, a call each: 686 -> 469 us per token.  One ordered
+// step against the launches for more units, caches in turn: 1.04 to 1.5 times as fast at 227 of 228 shapes (32 heads x
+// 1024 x 128 1.21, 128 x 700 x 128 1.31, 64 x 2048 x 128 1.16, 4 query heads 32 x 1024 x 128 1.11; 8 query heads
+// 64 x 300 x 256 0.98).  Longer splits (128 x 2048 x 128) are bound by their bytes: see plan_decode_few.
 constexpr int64_t kFewMaxUnits = 128;
+// Where nothing but a merge follows (kf_decode_step, slot layout, shared score) the splits are the same, for the same
+// results, but the form that asks for everything at once only pays while the launch is a round of workgroups with a
+// compute unit to themselves, or nearly so (the form takes 97 to 156 registers).  kf_decode_step in that form / in the
+// plain one, against the longer splits of more units: 16 x 1024 x 128 (256 splits) 1.08 / 1.05 times as fast,
+// 64 x 300 x 128 (320) 1.03 / 1.01, 64 x 2048 x 128 (512) 0.96 / 1.01, with 2 query heads 16 x 300 (80) 1.05 / 1.03,
+// 32 x 700 (352) 0.95 / 0.99.
+constexpr int64_t kFewAloneMaxWorkgroups = 384;
+constexpr int64_t kFewAloneMaxWorkgroupsGrouped = 256;  // 2 or 4 query heads
 
 bool supported(int32_t dtype, int32_t d) {
     if (dtype == KF_BF16 || dtype == KF_F16) return d == 64 || d == 128 || d == 256;
@@ -176,6 +184,11 @@ WsLayout ws_layout(const kf_cache* c, int32_t n_max, int32_t parts = 1) {
 bool few_plan(const kf_cache* c, const WsLayout& w, size_t workspace_bytes, int32_t m, kf::DecodePlan* plan) {
     if (w.few_bytes == 0 || workspace_bytes - w.few_bytes < w.total || workspace_bytes < w.few_bytes) return false;
     return kf::plan_decode_few((int64_t)c->L * c->B * c->H, m, c->d, c->dtype, group_of(c), plan);
+}
+
+// The form of a few-unit launch that only a merge follows.
+void few_alone(kf::DecodeArgs* a, int64_t U) {
+    if (U * a->S > (a->G == 2 || a->G == 4 ? kFewAloneMaxWorkgroupsGrouped : kFewAloneMaxWorkgroups)) a->few = 0;
 }
 
 // Whether the two-launch ordered eviction is the faster one for U units of budget k.
@@ -502,6 +515,7 @@ kf_status kf_decode_step(kf_cache* c, const void* q, const void* k_new, const vo
     const kf_status st = prepare_decode(c, q, k_new, v_new, q_pos, m_hint, cfg, out, workspace, workspace_bytes, &a, &p);
     if (st != KF_OK) return st;
     const int64_t U = (int64_t)c->L * c->B * c->H;
+    few_alone(&a, U);
     hipError_t e = kf::launch_decode(a, U, c->d, c->dtype, p.lds_bytes, (hipStream_t)stream);
     if (e == hipSuccess && a.shared) e = share_after_decode(c, a, (hipStream_t)stream);
     if (e != hipSuccess) return fail(KF_EDEVICE, "decode launch: %s", hipGetErrorString(e));
@@ -628,6 +642,7 @@ static kf_status fused_step(kf_cache* c, const void* q, const void* k_new, const
         sa.step_inc = step;
     }
     const int64_t U = (int64_t)c->L * c->B * c->H;
+    if (layout != KF_LAYOUT_ORDERED || da.shared) few_alone(&da, U);
     if (layout == KF_LAYOUT_ORDERED && keep_pays(U, k, w, sa.row_bytes)) da.keep_w = w;
     hipError_t e;
     // a few small units: the workgroup that scored one also moves its rows (2 heads x 64 x 64 in fp32, whose two
