@@ -80,14 +80,17 @@ struct Mma<float> {
 // Workgroup -> (unit, block of 128 rows, part of the block's tile walk).  Consecutive workgroup ids are dealt
 // round-robin to the chip's 8 XCDs, each with an L2 of its own; the blocks of
 // one unit re-read the same K / Q rows, so all blocks of a unit are given ids
-// that are equal modulo 8 and therefore share one L2.
+// that are equal modulo 8 and therefore share one L2.  The parts of all blocks follow each other part by part: a
+// block's later parts do not exist where its walk is short, and an XCD deals its workgroups to its shader engines in
+// turn, so with two or four parts of a block in a row some engines would get the empty ones (40 heads x 6340 rows x 128
+// 1850 us so, 1003 part by part, 1129 without parts).
 constexpr int kXcds = 8;
 __device__ __forceinline__ void unit_and_block(int nblk, int parts, int64_t& u, int& blk, int& part) {
     const unsigned xcd = blockIdx.x % kXcds, local = blockIdx.x / kXcds;
     u = (int64_t)(local / (nblk * parts)) * kXcds + xcd;
     const int in_unit = (int)(local % (nblk * parts));
-    blk = in_unit / parts;
-    part = in_unit % parts;
+    part = in_unit / nblk;
+    blk = in_unit % nblk;
 }
 
 // M + log2(S).  The hardware logarithm's error grows with its result and leans to one side: of a sum of 2^8 it

@@ -1478,6 +1478,38 @@ def test_prefill_in_parts_and_whole_match_oracle(dtype, d, G, n, noise, biased):
     run(hi)
 
 
+@pytest.mark.parametrize("U,n,dtype,d", [(16, 5800, ko.BF16, 128), (96, 2100, ko.BF16, 64), (4, 17000, ko.BF16, 64)])
+def test_prefill_in_parts_equals_whole_walks_over_long_prompts(U, n, dtype, d):
+    """Two to many parts, up to the longest that a workgroup walks (64 tiles of 32 rows, its tables of row statistics
+    full): a workspace with room for the parts' records against the smallest that is accepted.  All terms are positive;
+    a term's exponent rounds by half a unit in the last place of the row's normaliser (below 32: 1e-6 twice, times ln 2),
+    a sum of tiles of 16 terms by less."""
+    g = torch.Generator(device="cuda")
+    g.manual_seed(n)
+    gc = kf.Cache.allocate(1, 1, U, d, n, dtype)
+    gc.K.copy_(torch.randn(gc.K.shape, generator=g, device="cuda"))
+    Q = torch.randn((1, 1, U, n, d), generator=g, device="cuda").to(gc.K.dtype)
+    seeds = dev(np.array([7], np.uint64))
+    ws = kf.new_workspace(gc, n)
+
+    def run(nbytes):
+        gc.score.fill_(-1.0)
+        kf.kf_prefill_score(gc, Q, n, 1.0, 0.09, kf.NOISE_GUMBEL, seeds, None, ws[:nbytes])
+        return host(gc.score).astype(np.float64)
+
+    parts = run(ws.numel())
+    lo, hi = 0, ws.numel()
+    while hi - lo > 256:
+        mid = (lo + hi) // 512 * 256
+        try:
+            whole = run(mid)
+            hi = mid
+        except kf.KeyformerError:
+            lo = mid
+    assert hi < ws.numel()
+    np.testing.assert_allclose(parts, whole, rtol=5e-6)
+
+
 @pytest.mark.parametrize("noise,tau", [(ko.NOISE_GUMBEL, 1.0), (ko.NOISE_GUMBEL, 1.4), (ko.NOISE_NONE, 1.0),
                                        (ko.NOISE_GAUSSIAN, 1.4)])
 def test_nan_in_the_last_key_reaches_every_column_in_parts_too(noise, tau):
