@@ -211,6 +211,8 @@ struct PrefillArgs {
 constexpr int32_t kPrefillMaxPartTiles = 64;
 constexpr int32_t kPrefillMaxParts = 32;  // bounds the scratch: 12 bytes per row and part
 constexpr int64_t kPrefillPartsRowLimit = 2 * 1024 * 128;  // U * n from which no prompt is cut
+constexpr int32_t kPrefillPartsMaxRows = 144 * 128;        // n above which none is
+static_assert(kPrefillPartsMaxRows / 32 <= kPrefillMaxParts * kPrefillMaxPartTiles, "the longest cut walk fits the most parts");
 struct PrefillParts {
     int32_t parts, tiles;
 };

@@ -635,22 +635,27 @@ __global__ void __launch_bounds__(256) prefill_group_sum_kernel(const PrefillArg
 // How the tile walks of a launch's 128-row blocks are cut.  A block's walk is serial, up to n/32 tiles, and the
 // blocks of a unit are of all lengths: with few units the launch lasts as long as the longest block while most of
 // the chip has run out of work (16 heads x 2048 tokens: 136 blocks' worth of work in 256 workgroups, 88 us a pass
-// for 10 us of arithmetic).  Below kPrefillPartsRowLimit rows in all the walks are cut
-// into parts of equal length, one workgroup each, so that about kPrefillPartsWanted workgroups have work: 16 heads x
-// 2048 rows x 256 168 -> 98 us (both passes), 16 x 4096 x 128 397 -> 228, 64 x 2048 x 256 359 -> 273; wanting 768 to
-// 3072 workgroups measured within 20 %, fewer or more slower.  Above the limit the longest walk is a small share of
-// the launch and the parts' records would only cost.
+// for 10 us of arithmetic).  Below kPrefillPartsRowLimit rows in all, and kPrefillPartsMaxRows of a unit, the walks are
+// cut into at most kPrefillMaxParts parts of equal length, one workgroup each, so that about kPrefillPartsWanted
+// workgroups have work (wanting 768 to 3072 measured within 20 %, fewer or more slower).  Against uncut walks, both
+// passes, d = 128: 16 heads x 2048 rows 1.7 times as fast, x 4224 1.67, 32 x 3524 1.28, 1 x 8192 1.28, 24 x 6340 1.15,
+// 1 x 16384 1.01; of 858 launches measured 20 below the second limit lost, 1 to 11 % (192 x 580 rows 0.90, one head of
+// d = 256 from 10000 rows on 0.89 to 0.98).  Above the first limit the longest walk is a small share of the launch; above
+// the second a walk has so many parts that putting a row's records together costs what the cut gains (1 x 24000 0.94,
+// 1 x 32768 0.90).
 constexpr int64_t kPrefillPartsWanted = 1536;
 constexpr int64_t kPrefillMinPartTiles = 4;
 PrefillParts plan_prefill(int64_t U, int32_t n) {
     const int64_t nblk = (n + 4 * kTile - 1) / (4 * kTile);
-    if (U * 4 * kTile * nblk >= kPrefillPartsRowLimit) return kPrefillWhole;
+    if (n > kPrefillPartsMaxRows || U * 4 * kTile * nblk >= kPrefillPartsRowLimit) return kPrefillWhole;
     const int64_t steps = U * nblk * (nblk + 1) / 2 * 4;  // tiles walked by all blocks
     int64_t tiles = (steps + kPrefillPartsWanted - 1) / kPrefillPartsWanted;
+    const int64_t least = (nblk * 4 + kPrefillMaxParts - 1) / kPrefillMaxParts;  // of the longest walk
+    if (tiles < least) tiles = least;
     if (tiles < kPrefillMinPartTiles) tiles = kPrefillMinPartTiles;
     if (tiles > kPrefillMaxPartTiles) tiles = kPrefillMaxPartTiles;
     const int64_t parts = (nblk * 4 + tiles - 1) / tiles;
-    if (parts <= 1 || parts > kPrefillMaxParts) return kPrefillWhole;
+    if (parts <= 1) return kPrefillWhole;
     return {(int32_t)parts, (int32_t)tiles};
 }
 

@@ -1478,7 +1478,8 @@ def test_prefill_in_parts_and_whole_match_oracle(dtype, d, G, n, noise, biased):
     run(hi)
 
 
-@pytest.mark.parametrize("U,n,dtype,d", [(16, 5800, ko.BF16, 128), (96, 2100, ko.BF16, 64), (4, 17000, ko.BF16, 64)])
+@pytest.mark.parametrize("U,n,dtype,d", [(16, 5800, ko.BF16, 128), (96, 2100, ko.BF16, 64), (4, 17000, ko.BF16, 64),
+                                          (1, 4200, ko.F32, 64)])
 def test_prefill_in_parts_equals_whole_walks_over_long_prompts(U, n, dtype, d):
     """Two to many parts, up to the longest that a workgroup walks (64 tiles of 32 rows, its tables of row statistics
     full): a workspace with room for the parts' records against the smallest that is accepted.  All terms are positive;

@@ -208,6 +208,23 @@ def test_workspace_for_long_prompts_suffices_for_shorter_ones():
         assert all(a <= b for a, b in zip(sizes, sizes[1:])), (L, B, H, g, sizes)
 
 
+def test_prompts_of_few_units_are_cut_into_parts_without_gaps():
+    # the rule that cuts prompt scoring's tile walks, on the host: every prompt of a few units of more than one block
+    # of 128 rows and up to 18432 is cut, into parts that cover its longest walk and that the kernels' tables hold
+    plan = ctypes.CDLL(kf.lib_path())._ZN2kf12plan_prefillEli
+    plan.argtypes, plan.restype = [ctypes.c_int64, ctypes.c_int32], ctypes.c_uint64
+    for U in (1, 2, 3, 4, 7, 8, 13):
+        for n in list(range(1, 700)) + list(range(700, 20000, 63)):
+            v = plan(U, n)
+            parts, tiles = v & 0xFFFFFFFF, v >> 32
+            blocks = (n + 127) // 128
+            if blocks > 1 and n <= 18432 and U * blocks * 128 < 262144:
+                assert 1 < parts <= 32 and 4 <= tiles <= 64, (U, n, parts, tiles)
+                assert parts * tiles >= 4 * blocks > (parts - 1) * tiles, (U, n, parts, tiles)
+            else:
+                assert parts == 1, (U, n, parts)
+
+
 def test_query_group_validation_and_sizes():
     for g in (3, 5, 16):
         expect(binding.KF_EUNSUPPORTED, kf.kf_select_evict, fake_cache(q_per_kv=g), 8, 2, None, WS, 0)
