@@ -253,18 +253,18 @@ size_t kf_workspace_bytes(const kf_cache* c, int32_t n_max) {
     if (!group_supported(c->q_per_kv)) return 0;
     if (n_max < 0) n_max = 0;
     const WsLayout w0 = ws_layout(c, n_max);
-    size_t total = w0.total + w0.few_bytes;
     // a shorter prompt may be scored in parts and then need more: the most that any length up to n_max takes
-    const int64_t UQ = (int64_t)c->L * c->B * c->H * group_of(c);
-    for (int64_t n = kf::kPrefillRowPad; UQ * n < kf::kPrefillPartsRowLimit; n += kf::kPrefillRowPad) {
-        const int32_t len = n < n_max ? (int32_t)n : n_max;
-        if (len > 0) {
-            const WsLayout w = ws_layout(c, len, kf::plan_prefill(UQ, len).parts);
-            if (w.total > total) total = w.total;
-        }
-        if (n >= n_max) break;
+    const int32_t G = group_of(c);
+    const int64_t UQ = (int64_t)c->L * c->B * c->H * G;
+    const size_t x0 = w0.wide - w0.region;
+    size_t x = x0;
+    const int32_t longest = n_max < kf::kPrefillPartsMaxRows ? n_max : kf::kPrefillPartsMaxRows;
+    for (int32_t n = kf::kPrefillRowPad; n - kf::kPrefillRowPad < longest && UQ * n < kf::kPrefillPartsRowLimit; n += kf::kPrefillRowPad) {
+        const size_t pre = prefill_region(UQ, (size_t)n, G, kf::plan_prefill(UQ, n < n_max ? n : n_max).parts);
+        if (pre > x) x = pre;
     }
-    return total;
+    const size_t total = w0.total + (x - x0), with_few = w0.total + w0.few_bytes;
+    return total > with_few ? total : with_few;
 }
 
 kf_status kf_decode_launch_shape(const kf_cache* c, int32_t m_hint, int32_t* splits, int32_t* chunk) {
