@@ -175,6 +175,7 @@ WsLayout ws_layout(const kf_cache* c, int32_t n_max, int32_t parts = 1) {
               2 * wide_part((size_t)U * w.nb * 4) + wide_part((size_t)U * kf::kPreselMaxSlices * 8) +
               wide_part((size_t)U * kf::kPreselMaxSlices * 4);
     w.few_bytes = 0;
+    static_assert(kPreselMinTokens <= kf::kFinishMaxTokens, "the joint end holds the scores of a unit of few");
     if (U <= kFewMaxUnits && c->cap < kPreselMinTokens)
         w.few_bytes = few_records(U, c) + wide_part((size_t)U * c->cap * 4);
     return w;

@@ -1446,6 +1446,8 @@ DecodePlan plan_decode(int64_t U, int32_t m, int32_t d, int32_t dtype, int32_t G
     return p;
 }
 
+static_assert(kFewMaxChunk <= kFewTokens * kDecodeThreads, "a thread holds the old scores of its tokens of a split");
+static_assert(kFewChunkBytes / kWideChunkBytes * 2 * kFewMaxRowPieces <= kFewPieces * kDecodeThreads, "and its pieces of the boundary rows");
 // Not for splits that are long all the same (the launch is then bound by bytes and wants its workgroups spread evenly),
 // nor for many query heads with more than a few splits of them (a record and a pass over them per head and split).
 int32_t few_max_splits(int64_t U, int32_t G) {

@@ -41,10 +41,10 @@ struct DecodeArgs {
     // Per-sequence query position / temperature (either may be NULL): [B], override the above.
     const int32_t* seq_q_pos;
     const float* seq_tau;
-    // Whole step in this launch (single split, slot layout): after the scores are updated the workgroup
-    // evicts for its unit and stores the new token straight into the freed slot.  fuse_k = 0: off.
+    // Whole step in this launch (single split): after the scores are updated the workgroup
+    // evicts for its unit.  Slot layout: it stores the new token straight into the freed slot.  fuse_k = 0: off.
     int32_t fuse_k, fuse_w;
-    int32_t fuse_ordered;  // ... or, ordered layout, a small unit: moves the rows behind the evicted slot down itself
+    int32_t fuse_ordered;  // ordered layout (a few small units, cap == k + 1): it moves the rows behind the evicted slot down itself
     int32_t* fuse_idx;  // NULL, or [U][k] survivor list as the selection kernel writes it
     int32_t* step_inc;   // NULL, or the device step counter the launch's last workgroup advances (whole-step launch)
     int32_t* ws_ticket;  // [1] workgroups of this launch that are done (zero between launches)
@@ -68,14 +68,19 @@ struct DecodeArgs {
 };
 constexpr int32_t kFuseOrderedBytes = 64 * 1024;  // of K, and as much of V, that the workgroup of a unit moves itself
 
-// Limits of the FEW form: tokens per split (old scores and boundary rows are held in registers) and splits.
+// Limits of the FEW form: tokens per split (old scores and boundary rows are held in registers) and splits.  The ordered
+// step at other values, up to 130 shapes each, of the speed at these: 256 workgroups 0.75 to 1.09, 1024 0.80 to 1.08
+// (1.24 where only they bring a split below its limit), 32 KB 0.75 to 0.92, 128 KB 0.96 to 1.05 (1.21 likewise), 64 rows
+// with 4 or 8 heads 0.75 to 0.94, 256 rows 0.88 to 1.15, 32 splits 0.87 to 1.08.
 constexpr int32_t kFewTokens = 2;    // per thread of 256
 constexpr int32_t kFewPieces = 2;    // 16-byte pieces of boundary rows per thread
 constexpr int32_t kFewMaxChunk = 512;
 constexpr int32_t kFewMaxChunkGrouped = 128;     // with 4 or 8 query heads
 constexpr int32_t kFewChunkBytes = 64 * 1024;    // of K, and as much of V
 constexpr int32_t kFewWorkgroups = 512;          // splits of all units together
-constexpr int32_t kFewMaxSplits = 64;
+constexpr int32_t kFewMaxSplits = 64;            // of a unit, times its query heads
+constexpr int32_t kFewMaxRowPieces = 32;         // 16-byte pieces of the longest row
+constexpr int32_t kWideChunkBytes = 32 * 1024;   // see wide_chunk_rows
 
 // Launch shape of the decode kernel for U units of up to m tokens.
 struct DecodePlan {
@@ -137,7 +142,7 @@ struct SelectArgs {
 };
 constexpr int32_t kPreselMaxSlices = 16;
 // rows per workgroup of the wide shift: 2048 16-byte pieces per tensor, i.e. 32 KB of K and 32 KB of V
-inline int32_t wide_chunk_rows(int32_t row_bytes) { return 2048 / (row_bytes >> 4); }
+inline int32_t wide_chunk_rows(int32_t row_bytes) { return kWideChunkBytes / row_bytes; }
 hipError_t launch_select(const SelectArgs& a, int64_t U, hipStream_t stream);
 // the survivor lists alone (a.move == 0)
 hipError_t launch_select_list(const SelectArgs& a, int64_t U, hipStream_t stream);

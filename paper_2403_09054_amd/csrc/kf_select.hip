@@ -873,6 +873,8 @@ static hipError_t launch_step_finish_d(const DecodeArgs& d, const SelectArgs& a,
 }
 
 hipError_t launch_step_finish(const DecodeArgs& d, const SelectArgs& a, int64_t U, int32_t hd, hipStream_t stream) {
+    // what the kernel's tables hold
+    if (a.k > kFinishMaxTokens || d.S > kWave || d.S > kFewMaxSplits || a.chunk_rows > kFinishThreads) return hipErrorInvalidValue;
     if (hd == 64) return launch_step_finish_d<64>(d, a, U, stream);
     if (hd == 128) return launch_step_finish_d<128>(d, a, U, stream);
     if (hd == 256) return launch_step_finish_d<256>(d, a, U, stream);
