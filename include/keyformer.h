@@ -144,13 +144,18 @@ uint32_t kf_noise_bits(uint64_t seed, uint32_t layer, uint32_t head, uint32_t q_
 /* Bytes of workspace that suffice for any call of this library on this
  * cache, with prompt length up to n_max (pass 0 if kf_prefill_score is not
  * used).  Only the cache's dimensions are read.  A workspace that lacks only the
- * room for the forms that few units take is accepted and served by the others. */
+ * room for the forms that few units take is accepted and served by the others,
+ * with the same results up to the order of their sums.  Those forms: the short
+ * splits of a step of at most 128 units (up to 7 MB), and prompt scoring in parts
+ * of fewer than 262144 prompt rows over all query heads (up to 30 MB; 16 heads x
+ * 2048 rows 4.8 MB, 1 x 8192 3.2 MB, where 8 bytes a row would do). */
 size_t kf_workspace_bytes(const kf_cache *c, int32_t n_max);
 
 /* How kf_decode_step would shape its launch for this cache and m_hint (0 = cap):
  * *splits = workgroups per unit, *chunk = cache rows per workgroup.  Host only;
- * for callers that want to reason about occupancy.  Returns KF_EINVAL /
- * KF_EUNSUPPORTED like the hot calls. */
+ * for callers that want to reason about occupancy.  The shape is that with a workspace
+ * of kf_workspace_bytes(); a smaller one that is accepted may launch another.
+ * Returns KF_EINVAL / KF_EUNSUPPORTED like the hot calls. */
 kf_status kf_decode_launch_shape(const kf_cache *c, int32_t m_hint, int32_t *splits, int32_t *chunk);
 
 /* Device-side error counter: the first int32 of the workspace counts units a
@@ -312,7 +317,8 @@ kf_status kf_decode_select_step_at(kf_cache *c, const void *q, const void *k_new
  *  - The first call on a device looks up the buffer's device address
  *    (hipGetSymbolAddress); make that call outside a stream capture.
  * Errors: as kf_decode_select_step; KF_EWORKSPACE if the cache's shape needs
- * more than KF_NOALLOC_SCRATCH_BYTES of scratch (kf_workspace_bytes(c, 0) tells);
+ * more than KF_NOALLOC_SCRATCH_BYTES of scratch (never if kf_workspace_bytes(c, 0)
+ * is within it; that counts room the call can do without, at most 7 MB);
  * KF_EDEVICE if the buffer's address cannot be resolved.
  */
 #define KF_NOALLOC_SCRATCH_BYTES (32u << 20)
