@@ -1052,6 +1052,40 @@ def test_small_ordered_step_in_one_launch_equals_the_two_calls(dtype, d, k, w, G
         np.testing.assert_array_equal(a, b)
 
 
+@pytest.mark.parametrize("dtype,d,k,w,G", [(ko.BF16, 64, 512, 102, 4), (ko.F32, 128, 128, 128, 1)])
+def test_small_ordered_step_in_one_launch_at_its_largest(dtype, d, k, w, G):
+    """256 units of 64 KB of keys, the most that the one-launch ordered step takes, with the step number in device memory
+    (the last workgroup moves it on): two steps in a row against the two calls."""
+    rng = np.random.default_rng(4700 + k)
+    L, B, H, cap = 1, 8, 32, k + 1
+    oc = random_cache(rng, L, B, H, d, cap, dtype, k)
+    oc.len[0, 0, 0], oc.len[0, 3, 5] = k - 1, cap
+    q, kn, vn = rnd(rng, (L, B, H * G, d), dtype), rnd(rng, (L, B, H, d), dtype), rnd(rng, (L, B, H, d), dtype)
+    seeds = dev(np.arange(B).astype(np.uint64))
+    results = []
+    for fused in (False, True):
+        gc = upload(oc, G)
+        assert kf.kf_decode_launch_shape(gc, cap)[0] == 1
+        ws = kf.new_workspace(gc)
+        out = torch.zeros((L, B, H * G, d), dtype=torch.float32, device="cuda")
+        step = torch.full((1,), 5, dtype=torch.int32, device="cuda")
+        for t in (5, 6):
+            if fused:
+                kf.kf_decode_select_step_at(gc, dev(q), dev(kn), dev(vn), 4 * cap, 32, 1.0, 2.0, step, 0, 0.11, kf.NOISE_GUMBEL,
+                                            seeds, None, out, k=k, w=w, workspace=ws)
+                assert int(step.item()) == t + 1
+            else:
+                kf.kf_decode_step(gc, dev(q), dev(kn), dev(vn), 4 * cap + t - 1, 0, kf.kf_tau(t, 32), 0.11, kf.NOISE_GUMBEL,
+                                  seeds, None, out, ws)
+                kf.kf_select_evict(gc, k, w, None, ws)
+        torch.cuda.synchronize()
+        assert error_word(ws) == 1
+        assert (host(gc.len) == k).all()
+        results.append([host(out).copy()] + [host(t)[:, :, :, :k].copy() for t in (gc.K, gc.V, gc.score, gc.pos)])
+    for a, b in zip(*results):
+        np.testing.assert_array_equal(a, b)
+
+
 @pytest.mark.parametrize("sweep_seed", SWEEP_SEEDS)
 def test_fused_step_on_random_shapes_equals_the_two_calls(sweep_seed):
     """Seeded sweep: kf_decode_select_step against kf_decode_step + kf_select_evict, bit for bit, over element
