@@ -80,17 +80,18 @@ struct Mma<float> {
 // Workgroup -> (unit, block of 128 rows, part of the block's tile walk).  Consecutive workgroup ids are dealt
 // round-robin to the chip's 8 XCDs, each with an L2 of its own; the blocks of
 // one unit re-read the same K / Q rows, so all blocks of a unit are given ids
-// that are equal modulo 8 and therefore share one L2.  The parts of all blocks follow each other part by part: a
-// block's later parts do not exist where its walk is short, and an XCD deals its workgroups to its shader engines in
-// turn, so with two or four parts of a block in a row some engines would get the empty ones (40 heads x 6340 rows x 128
-// 1850 us so, 1003 part by part, 1129 without parts).
+// that are equal modulo 8 and therefore share one L2.  A block's later parts
+// do not exist where its walk is short, and an XCD deals its workgroups to its shader engines in turn: with an even number
+// of parts of a block in a row some engines would get the empty ones (40 heads x 6340 rows x 128, four parts, 1850 us;
+// without parts 1129).  So an even number goes part by part (1003 us; 0.99 to 1.6 times as fast over 200 launches),
+// an odd one block by block (0.98 to 1.09 times as fast as part by part; 16 x 2048 x 256, eleven parts, 95 against 103).
 constexpr int kXcds = 8;
 __device__ __forceinline__ void unit_and_block(int nblk, int parts, int64_t& u, int& blk, int& part) {
     const unsigned xcd = blockIdx.x % kXcds, local = blockIdx.x / kXcds;
     u = (int64_t)(local / (nblk * parts)) * kXcds + xcd;
     const int in_unit = (int)(local % (nblk * parts));
-    part = in_unit / nblk;
-    blk = in_unit % nblk;
+    blk = parts % 2 ? in_unit / parts : in_unit % nblk;
+    part = parts % 2 ? in_unit % parts : in_unit / nblk;
 }
 
 // M + log2(S).  The hardware logarithm's error grows with its result and leans to one side: of a sum of 2^8 it
