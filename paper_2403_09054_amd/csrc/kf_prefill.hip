@@ -15,21 +15,28 @@
 //   pass 2  (column sums)     computes Q_tile * K_tile^T so that a lane owns ONE
 //           key and sees 16 of the tile's 32 queries: z_ij = 2^(y2_ij - c_i) is
 //           added into the lane's column sum.
-// Per logit the work is one 32-bit hash, two logarithms and one exponential;
-// that, not the MFMA rate, bounds the kernel (vector pipe 97 % busy, 1.9 T logit
-// evaluations per second and pass at d = 128, 32768 rows), so the per-logit
-// instruction count is what is trimmed: 16.7 a pass (20.5 and 17.6 before the
-// hash's first step left the loop, the masking compares moved into the edge
-// tiles' branch and the accumulators into ordinary registers: 32 heads x 32768
-// rows 20.3 -> 18.4 ms, 256 x 4096 with position bias 3.13 -> 2.81 ms), and at
-// temperature 1, where the adjustment is a quotient, 16 (17.5 and 2.59 ms).  With the Gumbel adjustment (the method; the other
-// adjustments keep the plain form): pass 1 sums every term against a reference
-// exponent instead of searching each tile's maximum first -- the reference
-// starts at the row's own diagonal term (so the sum cannot vanish), follows the
-// sum's exponent upwards tile by tile, and a tile whose sum overflows is summed
-// again against a higher reference; pass 1 leaves the row normaliser already
-// combined with the adjustment's constant part; kernels built for "no position
-// bias" drop that term.
+// Per logit the work is one 32-bit hash, two logarithms and one exponential; at
+// temperature 1 (the method's in the prompt) the adjustment is a quotient, one
+// logarithm and half a reciprocal instead.  That, not the MFMA rate, bounds the
+// kernel (vector pipe 97 % busy, 1.9 T logit evaluations per second and pass at
+// d = 128, 32768 rows), so the per-logit instruction count is what is trimmed:
+// 16.7 a pass, 16 at temperature 1 (20.5 and 17.6 before the hash's first step
+// left the loop, the masking compares moved into the edge tiles' branch and the
+// accumulators into ordinary registers).  At temperature 1, 32 heads x 32768 rows
+// 20.3 -> 17.0 to 17.9 ms from box to box, 256 x 4096 with position bias
+// 3.13 -> 2.56 to 2.71.
+//
+// With the Gumbel adjustment (the method; the others keep the plain form) pass 1
+// sums every term against a reference exponent instead of searching each tile's
+// maximum first: it starts at the row's own diagonal term (so the sum cannot
+// vanish) and follows the sum's exponent upwards tile by tile; a tile whose sum
+// overflows is summed again against a higher one.  Pass 1 leaves the row
+// normaliser already combined with the adjustment's constant part; kernels built
+// for "no position bias" drop that term.
+//
+// Few units: the walks are cut into parts (plan_prefill).  Pass 1 then leaves a
+// row's (reference, sum) per part, pass 2 puts them together while it loads, and a
+// small launch adds the parts' column sums.
 #include "kf_device.h"
 #include "kf_internal.h"
 
