@@ -1487,7 +1487,7 @@ static hipError_t launch_decode_g(const DecodeArgs& a, int64_t U, size_t lds, hi
         const size_t big_from = a.few ? (size_t)-1 : a.S > 1 ? kDecodeBigMinLogitsSplit : (G == 8 ? kDecodeBigMinLogits8 : kDecodeBigMinLogits4);
         if (logits > big_from) {
             const size_t lds_big = decode_lds_bytes_big(G, a.chunk, D);
-            if (lds_big > kDecodeLdsWhole) return hipErrorInvalidValue;
+            if (lds_big > kDecodeLdsWhole || a.fuse_ordered) return hipErrorInvalidValue;  // (only the 4-wave form moves rows)
             if (a.keep_w > 0) hipLaunchKernelGGL((decode_kernel<T, D, kDecodeThreadsBig, G, false, true>), grid, dim3(kDecodeThreadsBig), lds_big, st, a);
             else hipLaunchKernelGGL((decode_kernel<T, D, kDecodeThreadsBig, G, false, false>), grid, dim3(kDecodeThreadsBig), lds_big, st, a);
             hipError_t e2 = hipGetLastError();
@@ -1503,7 +1503,7 @@ static hipError_t launch_decode_g(const DecodeArgs& a, int64_t U, size_t lds, hi
     if constexpr (G <= 2) {
         if (a.S == 1 && lds > kDecodeLdsPair) {  // a unit too long for two workgroups per CU: one of 8 waves
             const size_t lds_big = decode_lds_bytes_big(G, a.chunk, D);
-            if (lds_big > kDecodeLdsWhole) return hipErrorInvalidValue;
+            if (lds_big > kDecodeLdsWhole || a.fuse_ordered) return hipErrorInvalidValue;  // (only the 4-wave form moves rows)
             if (a.keep_w > 0) hipLaunchKernelGGL((decode_kernel<T, D, kDecodeThreadsBig, G, false, true>), grid, dim3(kDecodeThreadsBig), lds_big, st, a);
             else hipLaunchKernelGGL((decode_kernel<T, D, kDecodeThreadsBig, G, false, false>), grid, dim3(kDecodeThreadsBig), lds_big, st, a);
             return hipGetLastError();
