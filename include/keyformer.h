@@ -144,11 +144,12 @@ uint32_t kf_noise_bits(uint64_t seed, uint32_t layer, uint32_t head, uint32_t q_
 /* Bytes of workspace that suffice for any call of this library on this
  * cache, with prompt length up to n_max (pass 0 if kf_prefill_score is not
  * used).  Only the cache's dimensions are read.  A workspace that lacks only the
- * room for the forms that few units take is accepted and served by the others,
- * with the same results up to the order of their sums.  Those forms: the short
- * splits of a step of at most 128 units (up to 7 MB), and prompt scoring in parts
- * of fewer than 262144 prompt rows over all query heads (up to 30 MB; 16 heads x
- * 2048 rows 4.8 MB, 1 x 8192 3.2 MB, where 8 bytes a row would do). */
+ * room for these is accepted and served without them, with the same results up to
+ * the rounding and the order of their sums: the short splits of a step of at most 128
+ * units (up to 7 MB), prompt scoring in parts of fewer than 262144 prompt rows over
+ * all query heads (up to 30 MB; 16 heads x 2048 rows 4.8 MB, 1 x 8192 3.2 MB, where
+ * 8 bytes a row would do), and the bounds that tell which tiles of a prompt with a
+ * position bias cannot matter (0.6 bytes a row). */
 size_t kf_workspace_bytes(const kf_cache *c, int32_t n_max);
 
 /* How kf_decode_step would shape its launch for this cache and m_hint (0 = cap):

@@ -153,6 +153,14 @@ size_t prefill_region(int64_t UQ, size_t n_pad, int32_t G, int32_t parts) {
     return 2 * row + ((G > 1 || parts > 1) ? (size_t)parts * row : 0) + (parts > 1 ? (size_t)parts * 2 * row : 0);
 }
 
+// Per-tile bounds of a prompt with a position bias, behind everything else; a workspace without them is served by walks
+// over all tiles.
+size_t prefill_bounds(int64_t UQ, int32_t n, int32_t G) {
+    if (n < kf::kPrefillSkipMinRows || UQ * n < kf::kPrefillSkipMinAllRows) return 0;
+    const size_t tiles = align_up((size_t)n, kf::kPrefillRowPad) / 32;
+    return align_up((size_t)UQ * tiles * sizeof(float4), 256) + align_up((size_t)(UQ / G) * tiles * sizeof(float), 256);
+}
+
 // parts: of prompt scoring's tile walks (1: whole, what a prompt of n_max rows needs at least)
 WsLayout ws_layout(const kf_cache* c, int32_t n_max, int32_t parts = 1) {
     const int64_t U = (int64_t)c->L * c->B * c->H;
@@ -264,7 +272,8 @@ size_t kf_workspace_bytes(const kf_cache* c, int32_t n_max) {
         const size_t pre = prefill_region(UQ, (size_t)n, G, kf::plan_prefill(UQ, n < n_max ? n : n_max).parts);
         if (pre > x) x = pre;
     }
-    const size_t total = w0.total + (x - x0), with_few = w0.total + w0.few_bytes;
+    const size_t bounds = prefill_bounds(UQ, n_max, G);
+    const size_t total = w0.total + (x - x0) + bounds, with_few = w0.total + w0.few_bytes;
     return total > with_few ? total : with_few;
 }
 
@@ -325,6 +334,10 @@ kf_status kf_prefill_score(const kf_cache* c, const void* Q, int32_t n, const kf
     a.ws_part = (float2*)((char*)workspace + w.region + (2 + (size_t)parts.parts) * row);
     a.parts = parts.parts;
     a.part_tiles = parts.tiles;
+    const size_t bounds = cfg->alibi_slopes ? prefill_bounds(U, n, G) : 0;
+    const bool skips = bounds > 0 && workspace_bytes - w.total >= bounds;
+    a.ws_tile = skips ? (float4*)((char*)workspace + w.total) : nullptr;
+    a.ws_kn = skips ? (float*)((char*)a.ws_tile + align_up((size_t)U * (n_pad / 32) * sizeof(float4), 256)) : nullptr;
     a.G = G;
     a.B = c->B;
     a.H = c->H * G;

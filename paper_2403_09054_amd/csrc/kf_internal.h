@@ -204,6 +204,8 @@ struct PrefillArgs {
     uint32_t* ws_r;     // [U][n_pad] per-row noise key
     float* ws_f;        // [U][parts][n_pad] column sums per query head and part (G > 1 or parts > 1 only)
     float2* ws_part;    // [U][parts][n_pad] reference exponent and sum of a row's parts (parts > 1 only)
+    float* ws_kn;       // NULL, or [U/G][n_pad/32] largest key norm of a tile: far tiles are left out with a position bias
+    float4* ws_tile;    // [U][n_pad/32] bounds of a tile's query rows (with ws_kn)
     int32_t B, H, cap, layer0, n, n_pad;  // H counts QUERY heads; the caches hold H/G heads
     int32_t G;          // query heads per cached head
     int32_t parts;      // workgroups that share the tile walk of a 128-row block, at most ...
@@ -225,6 +227,13 @@ constexpr PrefillParts kPrefillWhole{1, 1 << 26};
 PrefillParts plan_prefill(int64_t U, int32_t n);
 hipError_t launch_prefill(const PrefillArgs& a, int64_t U, int32_t d, int32_t dtype, hipStream_t stream);
 
+// Prompts with a position bias whose far tiles are looked for (see kf_prefill.hip): the search takes a launch and a trip to
+// memory ahead of each walk.  Slopes 2^(-8h/H), d = 128, against walks over all tiles: 32 x 2048 rows 1.07 to 1.1 times as
+// fast, 16 x 4096 1.2, 128 x 1300 1.06, 32 x 4096 1.3, 256 x 2048 1.27 to 1.3, 128 x 4096 1.5; below these limits 32 x 1300
+// 0.96, 8 x 4096 0.94 to 0.98, 128 x 1000 0.98 to 1.  Slopes too flat for anything to be left out cost 0.5 % at 256 x 2048
+// and 3 % (a launch) at 32 x 2048.
+constexpr int32_t kPrefillSkipMinRows = 1025;
+constexpr int64_t kPrefillSkipMinAllRows = 65536;
 constexpr int32_t kPrefillRowPad = 128;  // n is padded to this for the row-statistics arrays
 
 }  // namespace kf

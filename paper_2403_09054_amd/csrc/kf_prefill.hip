@@ -92,10 +92,13 @@ struct Mma<float> {
 // of parts of a block in a row some engines would get the empty ones (40 heads x 6340 rows x 128, four parts, 1850 us;
 // without parts 1129).  So an even number goes part by part (1003 us; 0.99 to 1.6 times as fast over 200 launches),
 // an odd one block by block (0.98 to 1.09 times as fast as part by part; 16 x 2048 x 256, eleven parts, 95 against 103).
+// A group of 8 units starts at the next XCD each time: with a position bias a head's work falls with its slope, and with
+// equal ids modulo 8 one XCD would get the flattest slope of every 8 heads.
 constexpr int kXcds = 8;
 __device__ __forceinline__ void unit_and_block(int nblk, int parts, int64_t& u, int& blk, int& part) {
     const unsigned xcd = blockIdx.x % kXcds, local = blockIdx.x / kXcds;
-    u = (int64_t)(local / (nblk * parts)) * kXcds + xcd;
+    const unsigned group = local / (nblk * parts);
+    u = (int64_t)group * kXcds + (xcd + group) % kXcds;
     const int in_unit = (int)(local % (nblk * parts));
     blk = parts % 2 ? in_unit / parts : in_unit % nblk;
     part = parts % 2 ? in_unit % parts : in_unit / nblk;
@@ -222,6 +225,36 @@ struct TileStage {
     }
 };
 
+// ------------------------------------------------------------------ tiles that a position bias rules out
+// With a position bias of positive slope the far tiles of a walk cannot matter: by Cauchy-Schwarz
+//     y2_ij <= |q_i| |k_j| scale log2(e)/tau + (largest adjustment) - slope log2(e)/tau (i - j)
+// for every finite input, and both softmaxes have a term to compare with, the row's own diagonal one.  Pass 1 leaves
+// out the leading tiles of a walk whose terms stay below 2^-(28 + log2 n) of the diagonal term of each of the block's
+// rows: all of them together change a row's sum by less than 2^-28.  Pass 2 leaves out the trailing query tiles whose
+// terms stay below 2^-(28 + log2 n) of each of the block's columns' own diagonal term, which is part of the column's sum.
+// Both are less than a rounding of the result.  The bounds are taken from the data (norms, diagonal terms and
+// normalisers per tile); a NaN or an infinity in any of them makes every comparison below fail, and the tile is walked.
+// One layer of 8 x 32 heads x 4096 rows with slopes 2^(-h/4), h = 1..32: 2676 -> 1678 us.  A unit whose largest possible bias
+// cannot outweigh the constants takes none of this (skip_reach).
+constexpr float kSkipBits = 29.0f;  // 28, and one for the rounding of the bound itself
+
+// Largest adjustment zeta log2(e) that the generator can produce (Gumbel: -ln(-ln(1 - 2^-24)) log2(e) = 24; Gaussian: radius
+// sqrt(2 ln 2^24)).
+__device__ __forceinline__ float largest_adjustment(int noise) {
+    return noise == kNoiseGumbel ? 24.01f : noise == kNoiseGaussian ? (kAdjMean + kAdjStd * 5.77f) * 1.4427f + 0.01f
+         : noise == kNoiseConstant ? kAdjMean * 1.4427f + 0.01f : 0.0f;
+}
+// What the bias has to outweigh, for vectors of no length: a walk whose bias stays below it is not searched (the search is
+// a trip to memory ahead of the walk, 1 to 3 us of a launch).
+__device__ __forceinline__ float skip_reach(int noise, float inv_tau, int n) {
+    return largest_adjustment(noise) * inv_tau + kSkipBits + hw_log2((float)n);
+}
+__device__ __forceinline__ float not_below(float x) { return x < INFINITY ? x : INFINITY; }    // upper bound: NaN is none
+__device__ __forceinline__ float not_above(float x) { return x > -INFINITY ? x : -INFINITY; }  // lower bound: NaN is none
+__device__ __forceinline__ float wave_min(float v) { return -wave_max(-v); }
+// Norm from its square, never too small (a square that underflowed).
+__device__ __forceinline__ float norm_bound(float sq) { return not_below(sqrtf(fmaxf(sq, 1e-36f)) * 1.0001f); }
+
 // ------------------------------------------------------------------ pass 1
 // <q, k> over the elements of the 16-byte pieces x and y
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
@@ -239,6 +272,36 @@ __device__ __forceinline__ float dot_piece(const uint4& x, const uint4& y, float
             d = __builtin_amdgcn_fdot2(__builtin_bit_cast(f16x2, xs[e]), __builtin_bit_cast(f16x2, ys[e]), d, false);
     }
     return d;
+}
+
+// Largest |k| of every 32-row tile of a cached head, for the bound above: a wave a tile, one read of K.
+constexpr int kNormWaves = 4;
+template <typename T, int D>
+__global__ void __launch_bounds__(kNormWaves * kWave) prefill_key_norms_kernel(const PrefillArgs a, int64_t kv_units) {
+    constexpr int LPR = D * (int)sizeof(T) / 16, RPL = kWave / LPR, NL = kTile / RPL;  // lanes a row, rows a load, loads a tile
+    const int64_t u = blockIdx.x;
+    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, jt = blockIdx.y * kNormWaves + wv;
+    if (u >= kv_units) return;
+    const int n = a.seq_n ? a.seq_n[(u / (a.H / a.G)) % a.B] : a.n;
+    if (n < 1 || n > a.n || jt * kTile >= n) return;
+    float slope = 0.0f;
+    for (int g = 0; g < a.G; ++g) slope = fmaxf(slope, a.slopes[(u * a.G + g) % a.H]);
+    if (!(slope * a.inv_tau * kLog2e * (float)n > skip_reach(a.noise, a.inv_tau, n))) return;  // none of the heads looks
+    const char* Ku = (const char*)a.K + (size_t)u * a.cap * D * sizeof(T);
+    uint4 r[NL];
+#pragma unroll
+    for (int i = 0; i < NL; ++i)
+        r[i] = *(const uint4*)(Ku + (size_t)min(jt * kTile + i * RPL + lane / LPR, n - 1) * D * sizeof(T) + (lane % LPR) * 16);
+    float most = 0.0f;
+#pragma unroll
+    for (int i = 0; i < NL; ++i) {
+        float sq = dot_piece<T>(r[i], r[i], 0.0f);
+#pragma unroll
+        for (int o = 1; o < LPR; o <<= 1) sq += __shfl_xor(sq, o, kWave);
+        most = fmaxf(most, norm_bound(sq));
+    }
+    most = wave_max(most);
+    if (lane == 0) a.ws_kn[(size_t)u * (a.n_pad / kTile) + jt] = most;
 }
 
 // s + sum of e[i]/t[i], t = -l2u: the Gumbel factor (-ln u)^(-1/tau) at temperature 1 (its ln 2 rides in the
@@ -290,6 +353,8 @@ __global__ void __launch_bounds__(kPrefillThreads, (kPrefillMinWaves<T, D>)) pre
     using Stage = TileStage<T, D>;
     __shared__ __attribute__((aligned(16))) char kbuf[2][Stage::kBufBytes];
     __shared__ __attribute__((aligned(16))) uint32_t kfold[2][kTile];  // folded positions of the tile's keys
+    __shared__ float2 wstat[kPrefillThreads / kWave];  // of a wave's rows: largest norm, smallest diagonal term
+    __shared__ int tile_s;
     const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int n0 = lane & 31, half = lane >> 5;
     int64_t u;
@@ -302,7 +367,7 @@ __global__ void __launch_bounds__(kPrefillThreads, (kPrefillMinWaves<T, D>)) pre
     // workgroup-uniform exits: a length out of range (the second pass reports it), a block inside the padding
     if (n < 1 || n > a.n || rb * (4 * kTile) >= n) return;
     // this workgroup's tiles [jt_first, jt_last] of the block's walk
-    const int jt_first = part * a.part_tiles;
+    int jt_first = part * a.part_tiles;
     const int jt_last = min(min(rb * (4 * kTile) + 4 * kTile - 1, n - 1) / kTile, jt_first + a.part_tiles - 1);
     if (jt_first > jt_last) return;  // workgroup-uniform: the block has fewer parts
     const int i0 = rb * (4 * kTile) + wv * kTile;
@@ -336,7 +401,10 @@ __global__ void __launch_bounds__(kPrefillThreads, (kPrefillMinWaves<T, D>)) pre
     // (A part behind the first starts from a finite reference below every logit: with -inf a tile of nothing but
     // masked logits and NaN would not be told from an empty one.)
     float M = !GUMBEL && part > 0 ? -0x1p127f : -INFINITY, Ssum = 0.0f;
-    if constexpr (GUMBEL) {
+    const float reach = BIAS ? skip_reach(a.noise, a.inv_tau, n) : 0.0f;
+    const bool skips = BIAS && a.ws_kn && lp.slope1 * (float)n > reach;  // of the unit
+    float own = -INFINITY, qnorm = 0.0f;                     // the row's diagonal term, the norm of its query
+    if (GUMBEL || skips) {
         // Reference exponent of the row's sum: its own diagonal term y2_ii, formed here from the query's and the
         // key's elements this lane holds (both halves of the wave added up).  It is a term of the sum, so the
         // sum against it cannot vanish however far below it the others lie.
@@ -345,10 +413,41 @@ __global__ void __launch_bounds__(kPrefillThreads, (kPrefillMinWaves<T, D>)) pre
 #pragma unroll
         for (int g = 0; g < NG; ++g) dot = dot_piece<T>(bq[g], *(const uint4*)(krow + g * 2 * EPV), dot);
         dot += __shfl_xor(dot, 32, kWave);
-        M = logit2_gumbel(lp, dot, 0.0f, rfold ^ fold16((uint32_t)i * kKposMul));
+        own = GUMBEL ? logit2_gumbel(lp, dot, 0.0f, rfold ^ fold16((uint32_t)i * kKposMul)) : logit2_other(lp, dot, 0.0f, rkey, (uint32_t)i);
+        if (GUMBEL) M = own;
+    }
+    if (skips) {
+        float sq = 0.0f;
+#pragma unroll
+        for (int g = 0; g < NG; ++g) sq = dot_piece<T>(bq[g], bq[g], sq);
+        qnorm = wave_max(norm_bound(sq + __shfl_xor(sq, 32, kWave)));
+        const float least = wave_min(not_above(own));
+        if (lane == 0) wstat[wv] = make_float2(qnorm, least);
+        if (lane == 0 && active && part == 0 && a.parts > 1) a.ws_tile[(size_t)u * (a.n_pad / kTile) + i0 / kTile] = make_float4(qnorm, least, 0.0f, 0.0f);
+        const int limit = min(rb * 4, jt_last + 1);  // the block's own tiles are walked in any case
+        if (lp.slope1 * (float)((rb * 4 - jt_first) * kTile) > reach) {  // workgroup-uniform
+            if (threadIdx.x == 0) tile_s = max(limit, jt_first);
+            __syncthreads();
+            const float* kn = a.ws_kn + (size_t)(u / a.G) * (a.n_pad / kTile);
+            for (int jt = jt_first + (int)threadIdx.x; jt < limit; jt += kPrefillThreads) {
+                bool none = true;
+                for (int v = 0; v < kPrefillThreads / kWave; ++v) {
+                    const int first = rb * (4 * kTile) + v * kTile;  // the wave's first row
+                    if (first >= n) break;
+                    const float bias = lp.slope1 * (float)(first - (jt * kTile + kTile - 1));
+                    none = none && wstat[v].x * kn[jt] * fabsf(lp.sc1) + reach - bias < wstat[v].y;
+                }
+                if (!none) {
+                    atomicMin(&tile_s, jt);
+                    break;
+                }
+            }
+            __syncthreads();
+            jt_first = __builtin_amdgcn_readfirstlane(tile_s);  // behind jt_last: nothing is left of the part
+        }
     }
     const int jt_end = min(i0 + kTile - 1, n - 1) / kTile;  // this wave's last key tile
-    typename Stage::Regs stage = Stage::fetch(Ku, jt_first * kTile, n);
+    typename Stage::Regs stage = Stage::fetch(Ku, min(jt_first, jt_last) * kTile, n);
     Stage::park(kbuf[0], stage);
     if constexpr (GUMBEL) park_keys(0, jt_first);
     __syncthreads();
@@ -450,6 +549,11 @@ __global__ void __launch_bounds__(kPrefillThreads, (kPrefillMinWaves<T, D>)) pre
         a.ws_c[(size_t)u * a.n_pad + i] = GUMBEL ? lp.gz - c : c;
         a.ws_r[(size_t)u * a.n_pad + i] = GUMBEL ? rfold : rkey;
     }
+    if (skips && a.parts == 1) {  // of the wave's rows: norm, smallest normaliser, smallest share of the diagonal term
+        const float c = log2_of_sum(Mt, St);
+        const float cmin = wave_min(i < n ? not_above(c) : INFINITY), dmin = wave_min(i < n ? not_above(own - c) : INFINITY);
+        if (lane == 0) a.ws_tile[(size_t)u * (a.n_pad / kTile) + i0 / kTile] = make_float4(qnorm, cmin, dmin, 0.0f);
+    }
 }
 
 // ------------------------------------------------------------------ pass 2
@@ -500,6 +604,8 @@ __global__ void __launch_bounds__(kPrefillThreads, (kPrefillMinWaves<T, D>)) pre
     __shared__ __attribute__((aligned(16))) uint32_t rbuf[2][kTile];  // ... and row noise keys
     __shared__ __attribute__((aligned(16))) float call[PARTS ? kPrefillMaxPartTiles * kTile : 4];     // all tiles'
     __shared__ __attribute__((aligned(16))) uint32_t rall[PARTS ? kPrefillMaxPartTiles * kTile : 4];  // (PARTS)
+    __shared__ float share_s[2];
+    __shared__ int tile_s;
     const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int n0 = lane & 31, half = lane >> 5;
     int64_t u;
@@ -516,7 +622,7 @@ __global__ void __launch_bounds__(kPrefillThreads, (kPrefillMinWaves<T, D>)) pre
     if (cb == 0 && threadIdx.x == 0 && first_of_group) a.len[u / a.G] = n;
     if (cb * (4 * kTile) >= n) return;  // workgroup-uniform: the block lies in the padding
     // this workgroup's query tiles it_end, it_end-1, .. it_first
-    const int it_end = (n - 1) / kTile - (PARTS ? part * a.part_tiles : 0);
+    int it_end = (n - 1) / kTile - (PARTS ? part * a.part_tiles : 0);
     const int it_first = PARTS ? max(cb * 4, it_end - a.part_tiles + 1) : cb * 4;
     if (it_end < it_first) return;  // workgroup-uniform: the block has fewer parts
     const int j0 = cb * (4 * kTile) + wv * kTile;
@@ -561,6 +667,48 @@ __global__ void __launch_bounds__(kPrefillThreads, (kPrefillMinWaves<T, D>)) pre
             rall[r] = i < n ? wr[i] : 0u;
         }
     }
+    const float reach = BIAS ? skip_reach(a.noise, a.inv_tau, n) : 0.0f;
+    if (BIAS && a.ws_kn && lp.slope1 * (float)n > reach && lp.slope1 * (float)((it_end - cb * 4) * kTile) > reach) {
+        // workgroup-uniform: the unit's bounds are there, and the last tile may be ruled out
+        const size_t nt = a.n_pad / kTile;
+        const float4* tiles = a.ws_tile + (size_t)u * nt;
+        const int own_last = min(cb * 4 + 3, (n - 1) / kTile);  // the block's own tiles are walked in any case
+        const int limit = max(own_last + 1, it_first);
+        // the block's columns: smallest share of a diagonal term in its row, largest key
+        float share = INFINITY;
+        if constexpr (PARTS) {
+            const int i = cb * (4 * kTile) + (int)threadIdx.x;
+            if (threadIdx.x < 4 * kTile && i < n)
+                share = not_above(tiles[i / kTile].y - merged_normaliser(a.ws_part + (size_t)u * a.parts * a.n_pad + i, a.n_pad, (i / kTile) / a.part_tiles + 1));
+            share = wave_min(share);
+            if (lane == 0 && wv < 2) share_s[wv] = share;
+        }
+        if (threadIdx.x == 0) tile_s = limit - 1;
+        __syncthreads();  // (and the normalisers of this workgroup's rows are complete)
+        float kmax = 0.0f;
+        if constexpr (PARTS) share = fminf(share_s[0], share_s[1]);
+        for (int t = cb * 4; t <= own_last; ++t) {
+            if constexpr (!PARTS) share = fminf(share, tiles[t].z);
+            kmax = fmaxf(kmax, a.ws_kn[(size_t)(u / a.G) * nt + t]);
+        }
+        for (int it = it_end - (int)threadIdx.x; it >= limit; it -= kPrefillThreads) {
+            float c = PARTS ? INFINITY : tiles[it].y;  // smallest normaliser of the tile's rows
+            if constexpr (PARTS) {
+                for (int r = 0; r < kTile; ++r)
+                    if (it * kTile + r < n) {
+                        const float v = call[(it - it_first) * kTile + r];
+                        c = fminf(c, not_above(GUMBEL ? lp.gz - v : v));
+                    }
+            }
+            const float bias = lp.slope1 * (float)(it * kTile - (cb * (4 * kTile) + 4 * kTile - 1));
+            if (!(tiles[it].x * kmax * fabsf(lp.sc1) + reach - bias - c < share)) {
+                atomicMax(&tile_s, it);
+                break;
+            }
+        }
+        __syncthreads();
+        it_end = min(it_end, __builtin_amdgcn_readfirstlane(tile_s));  // before it_first: nothing is left of the part
+    }
     auto fetch = [&](int it) {
         Staged s;
         s.rows = Stage::fetch(Qu, it * kTile, n);
@@ -583,7 +731,7 @@ __global__ void __launch_bounds__(kPrefillThreads, (kPrefillMinWaves<T, D>)) pre
     // tile and the blocks, which run at the same time on one XCD, ask its L2 for the same rows at about the
     // same time (walking up, each block starts at its own diagonal and the L2 sees 16 unrelated streams:
     // 2.7 GB instead of 1.0 GB fetched on the GPT-J-shaped workload).
-    Staged stage = fetch(it_end);
+    Staged stage = fetch(max(it_end, it_first));
     park(0, stage);
     __syncthreads();
     for (int it = it_end; it >= it_first; --it) {
@@ -672,8 +820,15 @@ static hipError_t launch_passes(const PrefillArgs& a, int64_t U, hipStream_t st)
     const int nblk = (a.n + 4 * kTile - 1) / (4 * kTile);
     const int64_t groups = (U + kXcds - 1) / kXcds;  // units are dealt to XCDs in groups of 8
     const dim3 grid((unsigned)(groups * kXcds * nblk * a.parts)), block(kPrefillThreads);
+    hipError_t e;
+    if (BIAS && a.ws_kn) {
+        const dim3 tiles((unsigned)(U / a.G), (unsigned)((a.n + kNormWaves * kTile - 1) / (kNormWaves * kTile)));
+        hipLaunchKernelGGL((prefill_key_norms_kernel<T, D>), tiles, dim3(kNormWaves * kWave), 0, st, a, U / a.G);
+        e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
     hipLaunchKernelGGL((prefill_rowstats_kernel<T, D, GUMBEL, BIAS, TAU1>), grid, block, 0, st, a, nblk, U);
-    hipError_t e = hipGetLastError();
+    e = hipGetLastError();
     if (e != hipSuccess) return e;
     if (a.parts > 1) hipLaunchKernelGGL((prefill_colsum_kernel<T, D, GUMBEL, BIAS, TAU1, true>), grid, block, 0, st, a, nblk, U);
     else hipLaunchKernelGGL((prefill_colsum_kernel<T, D, GUMBEL, BIAS, TAU1, false>), grid, block, 0, st, a, nblk, U);

@@ -1545,6 +1545,57 @@ def test_prefill_in_parts_equals_whole_walks_over_long_prompts(U, n, dtype, d):
     np.testing.assert_allclose(parts, whole, rtol=5e-6)
 
 
+@pytest.mark.parametrize("B,H,G,n,dtype,d,noise,tau,steep", [
+    (8, 8, 1, 1025, ko.BF16, 64, ko.NOISE_GUMBEL, 1.0, 4.0), (2, 16, 1, 2305, ko.F16, 128, ko.NOISE_GAUSSIAN, 1.0, 1.0),
+    (16, 16, 1, 1025, ko.BF16, 128, ko.NOISE_GUMBEL, 1.0, 1.0), (3, 40, 2, 1200, ko.BF16, 64, ko.NOISE_NONE, 0.7, 2.0),
+    (32, 8, 1, 1100, ko.F32, 64, ko.NOISE_GUMBEL, 1.5, 1.0), (4, 1, 4, 4200, ko.BF16, 256, ko.NOISE_CONSTANT, 1.0, 1.0)])
+def test_tiles_ruled_out_by_the_position_bias_change_nothing(B, H, G, n, dtype, d, noise, tau, steep):
+    """A workspace with room for the tiles' bounds against the smallest that is accepted, whose walks take every tile; whole
+    walks and walks in parts; prompts of different lengths; slopes from steep to flat, zero, negative and NaN; large keys, an
+    infinite one and NaN queries far behind the diagonal.  Left out are terms below 2^-28 of a sum; the normaliser's rounding
+    (half a unit below 32, 1e-6, on either side) and the order of the parts are what the two may differ by."""
+    rng = np.random.default_rng(n + d)
+    L = 1
+    oc = random_cache(rng, L, B, H, d, n + 5, dtype, 0)
+    gc = upload(oc, G)
+    far = torch.rand(gc.K.shape[:-1], device="cuda") < 0.002
+    gc.K.mul_(torch.where(far, 4.0, 1.0).to(gc.K.dtype).unsqueeze(-1))
+    Q = dev(rnd(rng, (L, B, H * G, n, d), dtype))
+    slopes = steep * 2.0 ** (-8.0 * np.arange(1, H * G + 1) / (H * G))
+    if H * G > 4:
+        slopes[-3:] = 0.0, -0.01, np.nan
+    slopes[0] = 0.8
+    if H > 1:
+        gc.K[0, 0, 1, 3, 5] = np.inf     # a steep head: an infinite logit far from every late row
+        Q[0, 0, 0, n - 1, 2] = np.nan    # a row that makes every column NaN
+    dslopes = dev(slopes.astype(np.float32))
+    seeds = dev(np.arange(5, 5 + B).astype(np.uint64))
+    lens = np.maximum(1, n - 97 * np.arange(B)).astype(np.int32)
+    assert B * H * G * n >= 65536 and n > 1024, "bounds are looked for"
+    ws = kf.new_workspace(gc, n)
+
+    def run(nbytes):
+        gc.score.fill_(-1.0)
+        kf.kf_prefill_score(gc, Q, n, tau, float(d) ** -0.5, noise, seeds, dslopes, ws[:nbytes], seq_n=dev(lens))
+        return host(gc.score).astype(np.float64), host(gc.len)
+
+    got, glen = run(ws.numel())
+    lo, hi = 0, ws.numel()
+    while hi - lo > 256:
+        mid = (lo + hi) // 512 * 256
+        try:
+            want, wlen = run(mid)
+            hi = mid
+        except kf.KeyformerError:
+            lo = mid
+    assert hi < ws.numel()
+    np.testing.assert_array_equal(glen, wlen)
+    np.testing.assert_array_equal(np.isnan(got), np.isnan(want))
+    np.testing.assert_allclose(got, want, rtol=5e-6, atol=0)
+    if H > 1:
+        assert np.isnan(got[0, 0, 0, :n]).all()
+
+
 @pytest.mark.parametrize("noise,tau", [(ko.NOISE_GUMBEL, 1.0), (ko.NOISE_GUMBEL, 1.4), (ko.NOISE_NONE, 1.0),
                                        (ko.NOISE_GAUSSIAN, 1.4)])
 def test_nan_in_the_last_key_reaches_every_column_in_parts_too(noise, tau):
