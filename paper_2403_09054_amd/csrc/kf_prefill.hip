@@ -286,7 +286,8 @@ __global__ void __launch_bounds__(kNormWaves * kWave) prefill_key_norms_kernel(c
     if (n < 1 || n > a.n || jt * kTile >= n) return;
     float slope = 0.0f;
     for (int g = 0; g < a.G; ++g) slope = fmaxf(slope, a.slopes[(u * a.G + g) % a.H]);
-    if (!(slope * a.inv_tau * kLog2e * (float)n > skip_reach(a.noise, a.inv_tau, n))) return;  // none of the heads looks
+    // none of the heads looks (the product in the order of the passes': the two sides of the limit must be the same there)
+    if (!(slope * (a.inv_tau * kLog2e) * (float)n > skip_reach(a.noise, a.inv_tau, n))) return;
     const char* Ku = (const char*)a.K + (size_t)u * a.cap * D * sizeof(T);
     uint4 r[NL];
 #pragma unroll
@@ -414,7 +415,7 @@ __global__ void __launch_bounds__(kPrefillThreads, (kPrefillMinWaves<T, D>)) pre
         for (int g = 0; g < NG; ++g) dot = dot_piece<T>(bq[g], *(const uint4*)(krow + g * 2 * EPV), dot);
         dot += __shfl_xor(dot, 32, kWave);
         own = GUMBEL ? logit2_gumbel(lp, dot, 0.0f, rfold ^ fold16((uint32_t)i * kKposMul)) : logit2_other(lp, dot, 0.0f, rkey, (uint32_t)i);
-        if (GUMBEL) M = own;
+        if (GUMBEL) M = own > -INFINITY || own != own ? own : 0.0f;  // (no reference: every other term would be infinite)
     }
     if (skips) {
         float sq = 0.0f;
