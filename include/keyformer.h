@@ -148,8 +148,10 @@ uint32_t kf_noise_bits(uint64_t seed, uint32_t layer, uint32_t head, uint32_t q_
  * the rounding and the order of their sums: the short splits of a step of at most 128
  * units (up to 7 MB), prompt scoring in parts of fewer than 262144 prompt rows over
  * all query heads (up to 30 MB; 16 heads x 2048 rows 4.8 MB, 1 x 8192 3.2 MB, where
- * 8 bytes a row would do), and the bounds that tell which tiles of a prompt with a
- * position bias cannot matter (0.6 bytes a row). */
+ * 8 bytes a row would do), prompt scoring of up to 2048 rows in strips (4 bytes a row
+ * and workgroup of a query unit: 256 heads x 2048 rows x 128 make the whole
+ * workspace 22 MB), and the bounds that tell which tiles of a prompt with a position
+ * bias cannot matter (0.6 bytes a row). */
 size_t kf_workspace_bytes(const kf_cache *c, int32_t n_max);
 
 /* How kf_decode_step would shape its launch for this cache and m_hint (0 = cap):

@@ -8,8 +8,8 @@ import sys
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libkeyformer.so")
-SOURCES = ["kf_api.hip", "kf_decode.hip", "kf_select.hip", "kf_prefill.hip"]
-HEADERS = ["kf_device.h", "kf_internal.h", "kf_merge.h", os.path.join("..", "..", "include", "keyformer.h")]
+SOURCES = ["kf_api.hip", "kf_decode.hip", "kf_select.hip", "kf_prefill.hip", "kf_strips.hip"]
+HEADERS = ["kf_device.h", "kf_internal.h", "kf_merge.h", "kf_prefill.h", os.path.join("..", "..", "include", "keyformer.h")]
 EXAMPLE_SRC = os.path.join(HERE, "examples", "generate_loop.cpp")
 EXAMPLE_BIN = os.path.join(HERE, "examples", "generate_loop")
 

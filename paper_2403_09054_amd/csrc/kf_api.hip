@@ -153,6 +153,11 @@ size_t prefill_region(int64_t UQ, size_t n_pad, int32_t G, int32_t parts) {
     return 2 * row + ((G > 1 || parts > 1) ? (size_t)parts * row : 0) + (parts > 1 ? (size_t)parts * 2 * row : 0);
 }
 
+// Column sums of a prompt whose logits are evaluated once, by `walkers` workgroups a unit.
+size_t strips_region(int64_t UQ, size_t n_pad, int32_t G, int32_t walkers) {
+    return G > 1 || walkers > 1 ? (size_t)walkers * align_up((size_t)UQ * n_pad * sizeof(float), 256) : 0;
+}
+
 // Per-tile bounds of a prompt with a position bias, behind everything else; a workspace without them is served by walks
 // over all tiles.
 size_t prefill_bounds(int64_t UQ, int32_t n, int32_t G) {
@@ -161,8 +166,8 @@ size_t prefill_bounds(int64_t UQ, int32_t n, int32_t G) {
     return align_up((size_t)UQ * tiles * sizeof(float4), 256) + align_up((size_t)(UQ / G) * tiles * sizeof(float), 256);
 }
 
-// parts: of prompt scoring's tile walks (1: whole, what a prompt of n_max rows needs at least)
-WsLayout ws_layout(const kf_cache* c, int32_t n_max, int32_t parts = 1) {
+// parts: of prompt scoring's tile walks (1: whole, what a prompt of n_max rows needs at least); walkers: evaluated once
+WsLayout ws_layout(const kf_cache* c, int32_t n_max, int32_t parts = 1, int32_t walkers = 0) {
     const int64_t U = (int64_t)c->L * c->B * c->H;
     WsLayout w;
     w.region = 256;
@@ -173,7 +178,7 @@ WsLayout ws_layout(const kf_cache* c, int32_t n_max, int32_t parts = 1) {
     if (n_max > 0) {
         const size_t n_pad = align_up((size_t)n_max, kf::kPrefillRowPad);
         const int32_t G = group_of(c);
-        const size_t pre = prefill_region(U * G, n_pad, G, parts);
+        const size_t pre = walkers ? strips_region(U * G, n_pad, G, walkers) : prefill_region(U * G, n_pad, G, parts);
         if (pre > x) x = pre;
     }
     w.wide = w.region + x;
@@ -272,6 +277,10 @@ size_t kf_workspace_bytes(const kf_cache* c, int32_t n_max) {
         const size_t pre = prefill_region(UQ, (size_t)n, G, kf::plan_prefill(UQ, n < n_max ? n : n_max).parts);
         if (pre > x) x = pre;
     }
+    for (int32_t n = kf::kPrefillRowPad; n - kf::kPrefillRowPad < n_max && n <= kf::kStripMaxRows; n += kf::kPrefillRowPad) {
+        const size_t pre = strips_region(UQ, (size_t)n, G, kf::plan_strips(UQ, n < n_max ? n : n_max, c->d, c->dtype, false));
+        if (pre > x) x = pre;
+    }
     const size_t bounds = prefill_bounds(UQ, n_max, G);
     const size_t total = w0.total + (x - x0) + bounds, with_few = w0.total + w0.few_bytes;
     return total > with_few ? total : with_few;
@@ -305,17 +314,24 @@ kf_status kf_prefill_score(const kf_cache* c, const void* Q, int32_t n, const kf
     if (n < 1 || n > c->cap) return fail(KF_EINVAL, "prompt length %d outside [1, cap=%d]", n, c->cap);
     const int32_t G = group_of(c);
     const int64_t U = (int64_t)c->L * c->B * c->H * G;  // query units
-    kf::PrefillParts parts = kf::plan_prefill(U, n);
-    WsLayout w = ws_layout(c, n, parts.parts);
-    if (parts.parts > 1 && workspace_bytes < w.total) {  // no room for the parts' records: whole walks
-        parts = kf::kPrefillWhole;
-        w = ws_layout(c, n);
-    }
-    st = check_ws(workspace, workspace_bytes, w.total);
+    st = check_ws(workspace, workspace_bytes, ws_layout(c, n).total);  // the least that any form needs
     if (st != KF_OK) return st;
 
     if ((U + 7) / 8 * 8 * ((n + 127) / 128) > kMaxGrid)  // one workgroup per 128 prompt rows of a unit
         return fail(KF_EUNSUPPORTED, "%lld query units of %d prompt rows exceed the largest launch", (long long)U, n);
+    int32_t walkers = cfg->noise == KF_NOISE_GUMBEL ? kf::plan_strips(U, n, c->d, c->dtype, cfg->alibi_slopes != nullptr) : 0;
+    if ((U + 7) / 8 * 8 * walkers > kMaxGrid) walkers = 0;
+    kf::PrefillParts parts = kf::kPrefillWhole;
+    WsLayout w = ws_layout(c, n, 1, walkers);
+    if (walkers && workspace_bytes < w.total) walkers = 0;  // no room for the walkers' sums: two passes
+    if (!walkers) {
+        parts = kf::plan_prefill(U, n);
+        w = ws_layout(c, n, parts.parts);
+        if (parts.parts > 1 && workspace_bytes < w.total) {  // no room for the parts' records: whole walks
+            parts = kf::kPrefillWhole;
+            w = ws_layout(c, n);
+        }
+    }
     const size_t n_pad = align_up((size_t)n, kf::kPrefillRowPad);
     kf::PrefillArgs a;
     a.Q = Q;
@@ -348,7 +364,14 @@ kf_status kf_prefill_score(const kf_cache* c, const void* Q, int32_t n, const kf
     a.noise = cfg->noise;
     a.inv_tau = 1.0f / cfg->tau;
     a.scale = cfg->scale;
-    hipError_t e = kf::launch_prefill(a, U, c->d, c->dtype, (hipStream_t)stream);
+    hipError_t e;
+    if (walkers) {
+        a.parts = walkers;
+        a.ws_f = G > 1 || walkers > 1 ? (float*)((char*)workspace + w.region) : nullptr;
+        e = kf::launch_strips(a, U, c->d, c->dtype, (hipStream_t)stream);
+    } else {
+        e = kf::launch_prefill(a, U, c->d, c->dtype, (hipStream_t)stream);
+    }
     if (e == hipSuccess && cfg->score_mode == KF_SCORE_SHARED) {
         kf::ShareArgs sh;
         sh.score = c->score;

@@ -236,4 +236,12 @@ constexpr int32_t kPrefillSkipMinRows = 1025;
 constexpr int64_t kPrefillSkipMinAllRows = 65536;
 constexpr int32_t kPrefillRowPad = 128;  // n is padded to this for the row-statistics arrays
 
+// Prompts whose logits are evaluated once (kf_strips.hip): Gumbel adjustment.
+constexpr int32_t kStripSmallRows = 1024;  // up to here workgroups of 4 waves
+constexpr int32_t kStripMaxRows = 2048;
+// Workgroups per query unit (their column sums take as many floats a row, ws_f; one alone of an ungrouped head writes the
+// score itself), or 0: not this way.
+int32_t plan_strips(int64_t U, int32_t n, int32_t d, int32_t dtype, bool bias);
+hipError_t launch_strips(const PrefillArgs& a, int64_t U, int32_t d, int32_t dtype, hipStream_t stream);
+
 }  // namespace kf

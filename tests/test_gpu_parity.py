@@ -1545,10 +1545,41 @@ def test_prefill_in_parts_equals_whole_walks_over_long_prompts(U, n, dtype, d):
     np.testing.assert_allclose(parts, whole, rtol=5e-6)
 
 
+@pytest.mark.parametrize("dtype,d,G,B,H,n,tau,biased,factor", [
+    (ko.BF16, 128, 1, 1, 1, 1, 1.0, False, 1.0), (ko.BF16, 64, 1, 2, 2, 31, 1.7, True, 1.0), (ko.F16, 128, 2, 1, 2, 33, 1.0, True, 1.0),
+    (ko.F32, 64, 1, 1, 3, 1024, 1.0, False, 1.0), (ko.F16, 64, 1, 3, 9, 257, 1.0, False, 1.0), (ko.BF16, 256, 1, 1, 2, 1025, 1.0, False, 1.0),
+    (ko.F32, 128, 1, 2, 1, 1057, 1.3, True, 1.0), (ko.BF16, 128, 1, 1, 2, 2048, 1.0, True, 1.0), (ko.BF16, 64, 4, 2, 1, 2047, 1.0, False, 1.0),
+    (ko.BF16, 128, 1, 1, 2, 1100, 1.0, False, 60.0), (ko.F32, 64, 1, 2, 2, 300, 1.0, True, 60.0)])
+def test_prompt_whose_logits_are_evaluated_once_matches_oracle(dtype, d, G, B, H, n, tau, biased, factor):
+    """Up to 2048 rows, Gumbel: strips of 32 rows by workgroups of 4 and (from 1025 rows or with 512-byte rows) 8 waves, one to
+    many of them a unit, next to the edges of strips and tiles, sequences of different lengths; logits far beyond the range
+    of the exponential, which take every row against its maximum.  A workspace without room for the walkers' sums is served
+    by the two passes (covered by the tests of parts and whole walks)."""
+    rng = np.random.default_rng(9700 + d + n)
+    oc = random_cache(rng, 1, B, H, d, n + 3, dtype, 0)
+    Q = rnd(rng, (1, B, H * G, n, d), dtype)
+    seeds = np.arange(3, 3 + B).astype(np.uint64)
+    slopes = (0.5 ** np.arange(1, H * G + 1)).astype(np.float32) if biased else None
+    n_seq = np.maximum(1, n - 70 * np.arange(B)).astype(np.int32)
+    scale = float(np.float32(factor) / np.sqrt(np.float32(d)))
+    gc = upload(oc, G)
+    ws = kf.new_workspace(gc, n)
+    gc.score.fill_(-1.0)
+    kf.kf_prefill_score(gc, dev(Q), n, tau, scale, kf.NOISE_GUMBEL, dev(seeds), dev(slopes) if biased else None, ws, seq_n=dev(n_seq))
+    torch.cuda.synchronize()
+    oc.prefill_score(Q, n, tau, scale, ko.NOISE_GUMBEL, seeds, slopes, q_per_kv=G, n_seq=n_seq)
+    np.testing.assert_array_equal(host(gc.len), oc.len)
+    for b in range(B):
+        np.testing.assert_array_equal(host(gc.pos)[0, b, :, :n_seq[b]], oc.pos[0, b, :, :n_seq[b]])
+        assert (host(gc.score)[0, b, :, n_seq[b]:] == -1.0).all()
+    assert_close_score(host(gc.score), oc.score, oc.len, "prompt evaluated once", rtol=SCORE_RTOL_PREFILL)
+
+
 @pytest.mark.parametrize("B,H,G,n,dtype,d,noise,tau,steep", [
     (8, 8, 1, 1025, ko.BF16, 64, ko.NOISE_GUMBEL, 1.0, 4.0), (2, 16, 1, 2305, ko.F16, 128, ko.NOISE_GAUSSIAN, 1.0, 1.0),
     (16, 16, 1, 1025, ko.BF16, 128, ko.NOISE_GUMBEL, 1.0, 1.0), (3, 40, 2, 1200, ko.BF16, 64, ko.NOISE_NONE, 0.7, 2.0),
-    (32, 8, 1, 1100, ko.F32, 64, ko.NOISE_GUMBEL, 1.5, 1.0), (4, 1, 4, 4200, ko.BF16, 256, ko.NOISE_CONSTANT, 1.0, 1.0)])
+    (32, 8, 1, 1100, ko.F32, 64, ko.NOISE_GUMBEL, 1.5, 1.0), (4, 1, 4, 4200, ko.BF16, 256, ko.NOISE_CONSTANT, 1.0, 1.0),
+    (2, 20, 1, 2100, ko.BF16, 128, ko.NOISE_GUMBEL, 1.0, 2.0), (1, 32, 1, 2177, ko.F16, 64, ko.NOISE_GUMBEL, 1.5, 1.0)])
 def test_tiles_ruled_out_by_the_position_bias_change_nothing(B, H, G, n, dtype, d, noise, tau, steep):
     """A workspace with room for the tiles' bounds against the smallest that is accepted, whose walks take every tile; whole
     walks and walks in parts; prompts of different lengths; slopes from steep to flat, zero, negative and NaN; large keys, an
