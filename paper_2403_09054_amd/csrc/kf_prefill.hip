@@ -58,12 +58,13 @@ constexpr int kPrefillMinWaves = D * sizeof(T) >= 512 ? 3 : 4;
 // of parts of a block in a row some engines would get the empty ones (40 heads x 6340 rows x 128, four parts, 1850 us;
 // without parts 1129).  So an even number goes part by part (1003 us; 0.99 to 1.6 times as fast over 200 launches),
 // an odd one block by block (0.98 to 1.09 times as fast as part by part; 16 x 2048 x 256, eleven parts, 95 against 103).
-// A group of 8 units starts at the next XCD each time: with a position bias a head's work falls with its slope, and with
+// With a position bias a group of 8 units starts at the next XCD each time: a head's work falls with its slope, and with
 // equal ids modulo 8 one XCD would get the flattest slope of every 8 heads.
+template <bool BIAS>
 __device__ __forceinline__ void unit_and_block(int nblk, int parts, int64_t& u, int& blk, int& part) {
     const unsigned xcd = blockIdx.x % kXcds, local = blockIdx.x / kXcds;
     const unsigned group = local / (nblk * parts);
-    u = (int64_t)group * kXcds + (xcd + group) % kXcds;
+    u = (int64_t)group * kXcds + (BIAS ? (xcd + group) % kXcds : xcd);
     const int in_unit = (int)(local % (nblk * parts));
     blk = parts % 2 ? in_unit / parts : in_unit % nblk;
     part = parts % 2 ? in_unit % parts : in_unit / nblk;
@@ -283,7 +284,7 @@ __global__ void __launch_bounds__(kPrefillThreads, (kPrefillMinWaves<T, D>)) pre
     const int n0 = lane & 31, half = lane >> 5;
     int64_t u;
     int blk, part;
-    unit_and_block(nblk, a.parts, u, blk, part);
+    unit_and_block<BIAS>(nblk, a.parts, u, blk, part);
     if (u >= units) return;  // workgroup-uniform
     const int rb = nblk - 1 - blk;  // longest rows first
     const int h = (int)(u % a.H), b = (int)((u / a.H) % a.B), l = a.layer0 + (int)(u / ((int64_t)a.H * a.B));
@@ -534,7 +535,7 @@ __global__ void __launch_bounds__(kPrefillThreads, (kPrefillMinWaves<T, D>)) pre
     const int n0 = lane & 31, half = lane >> 5;
     int64_t u;
     int cb, part;  // longest columns (lowest keys) first
-    unit_and_block(nblk, PARTS ? a.parts : 1, u, cb, part);
+    unit_and_block<BIAS>(nblk, PARTS ? a.parts : 1, u, cb, part);
     if (u >= units) return;  // workgroup-uniform
     const int h = (int)(u % a.H), b = (int)((u / a.H) % a.B);
     const int n = a.seq_n ? a.seq_n[b] : a.n;  // this sequence's prompt length; rows n..a.n-1 are padding

@@ -11,6 +11,8 @@
 //   * each term times its row's 1/sum goes into the lane's column sums, which stay in registers over all strips that
 //     the workgroup walks, and are written once.
 // Two waves per SIMD at 256 registers a lane: 8 waves (2048 keys), or two workgroups of 4 waves (1024 keys) on a CU.
+// (Two of those fit with 512-byte rows since their keys go through LDS in quarters: 64 heads x 1024 x 256 73 -> 55 us, 256 x
+// 1024 fp32 x 128 515 -> 442 against 8 waves.)
 // With so few waves a wave has to cover its own round trips: while the vector units work on a tile, its next one's
 // products are formed in batches of two MFMAs, and the keys of the one after are on their way from memory; the strip's
 // query rows lie in LDS, asked for two strips ahead.
@@ -25,7 +27,7 @@
 namespace kf {
 
 constexpr int kStripTiles = 8;         // key tiles of a wave
-constexpr int strip_waves(int n, int row_bytes) { return n > kStripSmallRows || row_bytes > 256 ? 8 : 4; }
+constexpr int strip_waves(int n) { return n > kStripSmallRows ? 8 : 4; }
 constexpr float kStripTop = 110.0f;    // largest exponent of a term: 2048 of them stay finite
 constexpr float kStripLeast = 1e-30f;  // a row's sum below it (its terms lose bits) is taken against the row's maximum instead
 
@@ -64,7 +66,7 @@ template <typename T, int D, bool BIAS, int W>
 __global__ void __launch_bounds__(W * kWave, 2) prefill_strips_kernel(const PrefillArgs a, int64_t units, int grouped) {
     constexpr int NT = W * kWave, RB = D * (int)sizeof(T), NG = RB / 32, PITCH = RB + 16;
     constexpr int PPR = RB / 16, TPR = NT / kTile, PT = (PPR + TPR - 1) / TPR;  // 16-byte pieces a row, threads a row, pieces a thread
-    constexpr int HB = RB < 256 ? RB : 256, NGA = HB / 32, HPR = HB / 16, KPITCH = HB + 16;  // key rows, half by half
+    constexpr int HB = RB < 256 ? RB : W == 4 && RB > 256 ? 128 : 256, NGA = HB / 32, HPR = HB / 16, KPITCH = HB + 16;  // key rows, part by part
     constexpr int QB = 2, NB = NG / QB, NS = 8 / NB;  // products a batch, batches a tile, pairs of logits a batch
     __shared__ __attribute__((aligned(16))) char qbuf[3][kTile * PITCH];
     __shared__ __attribute__((aligned(16))) char kbuf[W][kTile * KPITCH];
@@ -143,7 +145,7 @@ __global__ void __launch_bounds__(W * kWave, 2) prefill_strips_kernel(const Pref
             if (col + x * TPR < PPR) *(u32x4_t*)(qbuf[buf] + row * PITCH + (col + x * TPR) * 16) = r.q[x];
         if (t < kTile) fold_s[buf][t] = fold16(row_key(ukey, (uint32_t)(s * kTile) + t));
     };
-    // The wave's next key tile, in whole lines, 16-byte pieces of 256-byte rows (a tile of 512-byte rows in two halves): asked
+    // The wave's next key tile, in whole lines, 16-byte pieces of up to 256-byte rows (512-byte rows in halves or quarters): asked
     // for while the piece of work before is under way, then by way of the wave's own LDS into the operand's layout.  (Asked
     // for in that layout, 32 rows an instruction, a tile of 256-byte rows kept the CU's address unit busy for 500 cycles.
     // The empty asm keeps addresses of all tiles from being formed ahead and held in registers.)
@@ -159,8 +161,8 @@ __global__ void __launch_bounds__(W * kWave, 2) prefill_strips_kernel(const Pref
     };
     char* const kb = kbuf[wv];
     const char* const kp = kb + n0 * KPITCH + half * 16;
-    // operands of QB products, batch x of a tile: key tile jt (at the head of a half: parked here, and the next one, of tile
-    // `after` behind the last half, asked for), query rows at q
+    // operands of QB products, batch x of a tile: key tile jt (at the head of a part: parked here, and the next one, of tile
+    // `after` behind the last part, asked for), query rows at q
     struct Batch {
         uint4 q[QB], k[QB];
     };
@@ -172,7 +174,9 @@ __global__ void __launch_bounds__(W * kWave, 2) prefill_strips_kernel(const Pref
                 *(u32x4_t*)(kb + (klane + g * (kWave / HPR)) * KPITCH + kcol) = key[g];
             }
             wave_sync();
-            if ((x + 1) * QB + NGA - QB < NG) load_keys(jt, 1);
+            constexpr int chunks = NG / NGA;
+            const int c = x * QB / NGA + 1;
+            if (c < chunks) load_keys(jt, c);
             else load_keys(after, 0);
         }
         Batch o;
@@ -412,16 +416,21 @@ __global__ void __launch_bounds__(256) strips_sum_kernel(const PrefillArgs a, in
     a.score[(size_t)u * a.cap + j] = s;
 }
 
-// Which prompts are scored this way.  Against the two passes (both ways' calls, d = 64 to 256, 2 to 2048 units): few units
-// 1.2 to 2.4 times as fast from 128 rows on (16 heads x 2048 x 256 105 -> 63 us, 32 x 2048 x 128 127 -> 80, 32 x 1024
-// 54 -> 26), the same below; 256 units 1.1 to 1.9 (256 x 2048 x 128 731 -> 553 us, fp32 1.9).  With more units the passes
-// fill the chip by themselves, and a short strip's sums and barrier weigh more than its logits: 1024 units 0.78 to 1.1 below
-// 400 rows, then 1.07 to 1.6; just above 1024 rows, where every strip goes to 8 waves, 0.91; 16-bit rows of 512 bytes,
-// whose registers leave the workgroup of 4 waves no room beside another, 0.5 to 0.9 below 1280 rows, then 1.1 to 1.2.
-// With a position bias the passes leave out tiles from 1025 rows on: 1024 units 0.95, up to 256 1.1 to 1.8.
-constexpr int64_t kStripAnyUnits = 256;
-constexpr int32_t kStripManyRows = 400;
-constexpr int32_t kStripLongRows = 1280;
+// Which prompts are scored this way.  Against the two passes (whole calls, 1.0 = the same time; d = 64 to 256, 2 to 2048
+// units): few units 1.2 to 2.5 from 128 rows on (16 heads x 2048 x 256 95 -> 55 us, 32 x 2048 x 128 127 -> 80, 32 x 1024
+// 54 -> 26), the same below; 256 units 1.1 to 1.9 (x 2048 x 128 731 -> 553 us; fp32, whose products take the time, 1.9).  With
+// more units the passes fill the chip by themselves, and a short strip's sums and barrier weigh more than its logits:
+// 512 units 0.91 to 1.2 below 200 rows, 1.2 to 1.6 at 256; 1024 units 0.86 to 1.03 below 200 rows, 0.97 to 1.4 at 256; 2048 units
+// 0.89 to 1.3 at 256, 0.98 to 1.7 at 400, 1.16 to 2 at 512.  Just above 1024 rows, where every strip goes to 8 waves, 16-bit
+// rows 1.03 to 1.08 with 160 units, 0.92 to 1.07 with 256, 0.87 with 512; from 1280 rows on 1.0 to 1.3.  With a position bias
+// the passes leave out tiles from 1025 rows on: 1024 units 0.95, up to 256 1.1 to 1.8.
+static int64_t most_strip_units(int32_t n, int32_t dtype, int32_t row_bytes, bool bias) {
+    const bool narrow = dtype != KF_F32;
+    int64_t most = n < 256 ? 320 : n < (narrow && row_bytes > 256 ? 512 : 400) ? 512 : INT64_MAX;
+    if (bias && n >= kPrefillSkipMinRows && most > 256) most = 256;
+    if (narrow && n > kStripSmallRows && n < 1280) most = 160;
+    return most;
+}
 
 // Workgroups that share a unit's strips.  A round of workgroups fills the chip (one of 8 waves on a CU, or two of 4); the
 // cost of a choice is its rounds times the longest workgroup's walk, in tiles of a wave: half the longest strip's for each
@@ -432,13 +441,9 @@ constexpr int64_t kStripL2Bytes = 2500000;
 int32_t plan_strips(int64_t U, int32_t n, int32_t d, int32_t dtype, bool bias) {
     if (n > kStripMaxRows) return 0;
     const int32_t row_bytes = d * (dtype == KF_F32 ? 4 : 2);
-    if (U > kStripAnyUnits || (U > kStripAnyUnits / 2 && dtype != KF_F32 && row_bytes > 256)) {
-        if (dtype != KF_F32 && row_bytes > 256 && n < kStripLongRows) return 0;
-        if (dtype != KF_F32 && n > kStripSmallRows && n < kStripLongRows) return 0;
-        if (n < kStripManyRows || (bias && n >= kPrefillSkipMinRows)) return 0;
-    }
+    if (U > most_strip_units(n, dtype, row_bytes, bias)) return 0;
     const int64_t padded = (n + kPrefillRowPad - 1) / kPrefillRowPad * kPrefillRowPad, strips = padded / kTile;
-    const int waves = strip_waves(n, row_bytes);
+    const int waves = strip_waves(n);
     const int64_t slots = waves == 8 ? 256 : 512;
     const int64_t most = strips < kStripMaxWalkers ? strips : kStripMaxWalkers;
     int64_t least = 1;
@@ -457,15 +462,14 @@ int32_t plan_strips(int64_t U, int32_t n, int32_t d, int32_t dtype, bool bias) {
 
 template <typename T, int D>
 static hipError_t launch_strips_t(const PrefillArgs& a, int64_t U, hipStream_t st) {
-    constexpr int RB = D * (int)sizeof(T);
     const int grouped = U % kXcds == 0 || U >= 8 * kXcds;
     const int64_t all = (grouped ? (U + kXcds - 1) / kXcds * kXcds : U) * a.parts;
     const dim3 grid((unsigned)all);
     const bool bias = a.slopes != nullptr;
-    if (strip_waves(a.n, RB) == 8) {
+    if (strip_waves(a.n) == 8) {
         if (bias) hipLaunchKernelGGL((prefill_strips_kernel<T, D, true, 8>), grid, dim3(8 * kWave), 0, st, a, U, grouped);
         else hipLaunchKernelGGL((prefill_strips_kernel<T, D, false, 8>), grid, dim3(8 * kWave), 0, st, a, U, grouped);
-    } else if constexpr (RB <= 256) {
+    } else {
         if (bias) hipLaunchKernelGGL((prefill_strips_kernel<T, D, true, 4>), grid, dim3(4 * kWave), 0, st, a, U, grouped);
         else hipLaunchKernelGGL((prefill_strips_kernel<T, D, false, 4>), grid, dim3(4 * kWave), 0, st, a, U, grouped);
     }
