@@ -11,8 +11,9 @@
 //   * each term times its row's 1/sum goes into the lane's column sums, which stay in registers over all strips that
 //     the workgroup walks, and are written once.
 // Two waves per SIMD at 256 registers a lane: 8 waves (2048 keys), or two workgroups of 4 waves (1024 keys) on a CU.
-// (Two of those fit with 512-byte rows since their keys go through LDS in quarters: 64 heads x 1024 x 256 73 -> 55 us, 256 x
-// 1024 fp32 x 128 515 -> 442 against 8 waves.)
+// Keys go through LDS in parts of 128 bytes a row: two workgroups of 4 waves fit also with 512-byte rows (64 heads x 1024 x
+// 256 73 -> 55 us, 256 x 1024 fp32 x 128 515 -> 442 against 8 waves), and nothing is spilled (against parts of 256 bytes 16 x
+// 2048 x 256 64 -> 59 us, 256 x 2048 x 128 595 -> 581, 512 x 1024 x 128 312 -> 298).
 // With so few waves a wave has to cover its own round trips: while the vector units work on a tile, its next one's
 // products are formed in batches of two MFMAs, and the keys of the one after are on their way from memory; the strip's
 // query rows lie in LDS, asked for two strips ahead.
@@ -66,7 +67,7 @@ template <typename T, int D, bool BIAS, int W>
 __global__ void __launch_bounds__(W * kWave, 2) prefill_strips_kernel(const PrefillArgs a, int64_t units, int grouped) {
     constexpr int NT = W * kWave, RB = D * (int)sizeof(T), NG = RB / 32, PITCH = RB + 16;
     constexpr int PPR = RB / 16, TPR = NT / kTile, PT = (PPR + TPR - 1) / TPR;  // 16-byte pieces a row, threads a row, pieces a thread
-    constexpr int HB = RB < 256 ? RB : W == 4 && RB > 256 ? 128 : 256, NGA = HB / 32, HPR = HB / 16, KPITCH = HB + 16;  // key rows, part by part
+    constexpr int HB = 128, NGA = HB / 32, HPR = HB / 16, KPITCH = HB + 16;  // key rows, part by part
     constexpr int QB = 2, NB = NG / QB, NS = 8 / NB;  // products a batch, batches a tile, pairs of logits a batch
     __shared__ __attribute__((aligned(16))) char qbuf[3][kTile * PITCH];
     __shared__ __attribute__((aligned(16))) char kbuf[W][kTile * KPITCH];
@@ -145,7 +146,7 @@ __global__ void __launch_bounds__(W * kWave, 2) prefill_strips_kernel(const Pref
             if (col + x * TPR < PPR) *(u32x4_t*)(qbuf[buf] + row * PITCH + (col + x * TPR) * 16) = r.q[x];
         if (t < kTile) fold_s[buf][t] = fold16(row_key(ukey, (uint32_t)(s * kTile) + t));
     };
-    // The wave's next key tile, in whole lines, 16-byte pieces of up to 256-byte rows (512-byte rows in halves or quarters): asked
+    // The wave's next key tile, in whole lines, 16-byte pieces of 128-byte parts of its rows: asked
     // for while the piece of work before is under way, then by way of the wave's own LDS into the operand's layout.  (Asked
     // for in that layout, 32 rows an instruction, a tile of 256-byte rows kept the CU's address unit busy for 500 cycles.
     // The empty asm keeps addresses of all tiles from being formed ahead and held in registers.)
@@ -417,7 +418,7 @@ __global__ void __launch_bounds__(256) strips_sum_kernel(const PrefillArgs a, in
 }
 
 // Which prompts are scored this way.  Against the two passes (whole calls, 1.0 = the same time; d = 64 to 256, 2 to 2048
-// units): few units 1.2 to 2.5 from 128 rows on (16 heads x 2048 x 256 95 -> 55 us, 32 x 2048 x 128 127 -> 80, 32 x 1024
+// units): few units 1.2 to 2.5 from 128 rows on (16 heads x 2048 x 256 95 -> 52 us, 32 x 2048 x 128 127 -> 80, 32 x 1024
 // 54 -> 26), the same below; 256 units 1.1 to 1.9 (x 2048 x 128 731 -> 553 us; fp32, whose products take the time, 1.9).  With
 // more units the passes fill the chip by themselves, and a short strip's sums and barrier weigh more than its logits:
 // 512 units 0.91 to 1.2 below 200 rows, 1.2 to 1.6 at 256; 1024 units 0.86 to 1.03 below 200 rows, 0.97 to 1.4 at 256; 2048 units
