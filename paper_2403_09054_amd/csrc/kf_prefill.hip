@@ -191,11 +191,11 @@ __device__ __forceinline__ float largest_adjustment(int noise) {
 __device__ __forceinline__ float skip_reach(int noise, float inv_tau, int n) {
     return largest_adjustment(noise) * inv_tau + kSkipBits + hw_log2((float)n);
 }
-__device__ __forceinline__ float not_below(float x) { return x < INFINITY ? x : INFINITY; }    // upper bound: NaN is none
 __device__ __forceinline__ float not_above(float x) { return x > -INFINITY ? x : -INFINITY; }  // lower bound: NaN is none
 __device__ __forceinline__ float wave_min(float v) { return -wave_max(-v); }
-// Norm from its square, never too small (a square that underflowed).
-__device__ __forceinline__ float norm_bound(float sq) { return not_below(sqrtf(fmaxf(sq, 1e-36f)) * 1.0001f); }
+// Norm from its square: never too small (256 squares that underflowed are 3e-36 together), infinite where the square is no
+// number (every maximum that follows would pass a NaN over).
+__device__ __forceinline__ float norm_bound(float sq) { return sq < INFINITY ? sqrtf(fmaxf(sq, 4e-36f)) * 1.0001f : INFINITY; }
 
 // ------------------------------------------------------------------ pass 1
 // Largest |k| of every 32-row tile of a cached head, for the bound above: a wave a tile, one read of K.

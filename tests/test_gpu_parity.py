@@ -1627,6 +1627,27 @@ def test_tiles_ruled_out_by_the_position_bias_change_nothing(B, H, G, n, dtype, 
         assert np.isnan(got[0, 0, 0, :n]).all()
 
 
+@pytest.mark.parametrize("B,H,G,n,dtype,d,noise", [
+    (4, 32, 1, 2100, ko.BF16, 64, ko.NOISE_GUMBEL), (1, 32, 1, 2177, ko.F16, 128, ko.NOISE_GUMBEL),
+    (16, 8, 2, 1100, ko.F32, 64, ko.NOISE_GAUSSIAN), (1, 16, 4, 1100, ko.BF16, 64, ko.NOISE_NONE)])
+def test_a_nan_key_reaches_every_row_behind_it_however_steep_the_position_bias(B, H, G, n, dtype, d, noise):
+    """A NaN key, early in a prompt whose position bias rules out all but the near tiles: every later row's softmax is NaN, and
+    with the last row's every column, however large a workspace allows tiles to be left out; the other heads stay finite.
+    Whole walks and walks in parts."""
+    assert B * H * G * n >= 65536 and n > 1024, "bounds are looked for"
+    oc = random_cache(np.random.default_rng(n + d), 1, B, H, d, n, dtype, 0)
+    gc = upload(oc, G)
+    gc.K[0, B - 1, 1, 3, 5] = np.nan
+    Q = dev(rnd(np.random.default_rng(n), (1, B, H * G, n, d), dtype))
+    ws = kf.new_workspace(gc, n)
+    kf.kf_prefill_score(gc, Q, n, 1.0, float(d) ** -0.5, noise, dev(np.arange(B).astype(np.uint64)),
+                        dev(np.full(H * G, 0.8, np.float32)), ws)
+    nan = np.isnan(host(gc.score))
+    assert nan[0, B - 1, 1].all()
+    nan[0, B - 1, 1] = False
+    assert not nan.any()
+
+
 @pytest.mark.parametrize("noise,tau", [(ko.NOISE_GUMBEL, 1.0), (ko.NOISE_GUMBEL, 1.4), (ko.NOISE_NONE, 1.0),
                                        (ko.NOISE_GAUSSIAN, 1.4)])
 def test_nan_in_the_last_key_reaches_every_column_in_parts_too(noise, tau):
