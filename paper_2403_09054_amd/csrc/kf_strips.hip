@@ -324,12 +324,23 @@ __global__ void __launch_bounds__(W * kWave, 2) prefill_strips_kernel(const Pref
 #pragma unroll
                 for (int w = 0; w < W; ++w) most = fmaxf(most, part_s[par][w][n0]);
                 par ^= 1;
-                spread(fminf(most, 0x1.fffffep127f), v);  // (against an infinite logit all others vanish, and it stays infinite)
+                // Against an infinite logit all others vanish, and it stays infinite.  The last strip's rows behind the prompt's end
+                // repeat its last row: only here can a term of theirs be infinite (which times their factor of 0 would be no
+                // number in the column), so here their logits become 0.  (By masks of bits: compares held over the tiles made the
+                // compiler spill scalar registers, which cost the whole kernel 1 to 4 %.)
+                const int left = n - s * kTile;
+                spread((int)(thread_here() & 31) < left ? fminf(most, 0x1.fffffep127f) : 0.0f, v);
+                const uint32_t inside = left < kTile ? (1u << left) - 1u : ~0u;  // by rows of the strip
 #pragma unroll
                 for (int t = 0; t < kStripTiles; ++t)
-                    if (t < tiles)
+                    if (t < tiles) {
+                        const uint32_t mine = inside >> (thread_here() >> 5 & 1) * 4;
 #pragma unroll
-                        for (int r = 0; r < 16; ++r) y[t][r] -= v[r];
+                        for (int r = 0; r < 16; ++r) {
+                            const int keep = __builtin_amdgcn_sbfe((int)mine, (r >> 2) * 8 + (r & 3), 1);  // all bits or none
+                            y[t][r] = __uint_as_float(__float_as_uint(y[t][r]) & (uint32_t)keep) - v[r];
+                        }
+                    }
             }
             // ---- terms and row sums; the rows of the strip after the next
             {

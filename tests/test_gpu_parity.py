@@ -1648,6 +1648,42 @@ def test_a_nan_key_reaches_every_row_behind_it_however_steep_the_position_bias(B
     assert not nan.any()
 
 
+@pytest.mark.parametrize("n,dtype,d", [(33, ko.F32, 64), (64, ko.BF16, 64), (95, ko.F16, 256), (1057, ko.BF16, 128), (2047, ko.BF16, 64)])
+def test_an_infinite_logit_makes_its_column_infinite_at_every_prompt_length(n, dtype, d):
+    """An infinite key element that every later query meets with a positive one, its own with a negative one: the column is
+    infinite, the columns behind it get nothing, those before it what the rows up to it add.  With a full workspace (every
+    logit evaluated once) and with the smallest (two passes), also where the last strip of rows is not full."""
+    rng = np.random.default_rng(n + d)
+    oc = random_cache(rng, 1, 1, 2, d, n, dtype, 0)
+    Q = rnd(rng, (1, 1, 2, n, d), dtype)
+    gc, gQ = upload(oc), dev(Q)
+    gQ[..., 2].abs_().add_(0.1)
+    gQ[0, 0, 1, 5, 2] = -1.0
+    gc.K[0, 0, 1, 5, 2] = np.inf
+    ws = kf.new_workspace(gc, n)
+
+    def run(nbytes):
+        gc.score.fill_(-1.0)
+        kf.kf_prefill_score(gc, gQ, n, 1.0, 0.125, kf.NOISE_GUMBEL, dev(np.array([9], np.uint64)), None, ws[:nbytes])
+        return host(gc.score).astype(np.float64)
+
+    once = run(ws.numel())
+    lo, hi = 0, ws.numel()
+    while hi - lo > 256:
+        mid = (lo + hi) // 512 * 256
+        try:
+            passes = run(mid)
+            hi = mid
+        except kf.KeyformerError:
+            lo = mid
+    assert hi < ws.numel()
+    for got in (once, passes):
+        assert got[0, 0, 1, 5] == np.inf and (got[0, 0, 1, 6:] == 0.0).all()
+        assert np.isfinite(got[0, 0, 0]).all() and np.isfinite(got[0, 0, 1, :5]).all()
+    sel = np.isfinite(once)
+    np.testing.assert_allclose(once[sel], passes[sel], rtol=5e-6, atol=0)
+
+
 @pytest.mark.parametrize("noise,tau", [(ko.NOISE_GUMBEL, 1.0), (ko.NOISE_GUMBEL, 1.4), (ko.NOISE_NONE, 1.0),
                                        (ko.NOISE_GAUSSIAN, 1.4)])
 def test_nan_in_the_last_key_reaches_every_column_in_parts_too(noise, tau):
