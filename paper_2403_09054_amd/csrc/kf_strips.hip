@@ -7,7 +7,9 @@
 //     lane owns one key and 16 of the strip's rows) and stay in the lane, 16 registers a tile, at most 8 tiles;
 //   * all exponentials, row sums over lanes and waves, one barrier.  The exponentials are taken as they are: a softmax
 //     needs a row's maximum only where a term leaves the range of fp32 or all of them vanish, and then the strip is
-//     evaluated again and every row taken against its maximum;
+//     evaluated again and every row taken against its maximum, and so are the next ones, at once, while their maxima ask
+//     for it (all logits beyond the range: 256 x 2048 x 128 740 us, 1024 x 512 x 128 273, 300 x 100 x 64 22; every strip twice
+//     1183, 392, 29; two passes 795, 334, 24);
 //   * each term times its row's 1/sum goes into the lane's column sums, which stay in registers over all strips that
 //     the workgroup walks, and are written once.
 // Two waves per SIMD at 256 registers a lane: 8 waves (2048 keys), or two workgroups of 4 waves (1024 keys) on a CU.
@@ -30,6 +32,7 @@ namespace kf {
 constexpr int kStripTiles = 8;         // key tiles of a wave
 constexpr int strip_waves(int n) { return n > kStripSmallRows ? 8 : 4; }
 constexpr float kStripTop = 110.0f;    // largest exponent of a term: 2048 of them stay finite
+constexpr float kStripBottom = -99.0f; // rows whose largest exponent lies from here to the top have a sum that is taken as it is
 constexpr float kStripLeast = 1e-30f;  // a row's sum below it (its terms lose bits) is taken against the row's maximum instead
 
 // Folds 16 values per lane over the 32 lanes of each half: lanes 0-15 of a half get the results of values 0-7, lanes 16-31
@@ -231,6 +234,7 @@ __global__ void __launch_bounds__(W * kWave, 2) prefill_strips_kernel(const Pref
 
     f32x16 acc;          // products of the wave's first tile of the strip, if ready
     bool ready = false;
+    int start = 0;       // how the next strip is begun: 0 plainly, 2 against its rows' maxima, as the strip before had to be
     park_strip(p, 0, fetch_strip(p));
     park_strip(strip_of(1), 1, fetch_strip(strip_of(1)));
     __syncthreads();
@@ -240,7 +244,7 @@ __global__ void __launch_bounds__(W * kWave, 2) prefill_strips_kernel(const Pref
         const int coming = strip_of(k + 2);  // (behind the last strip: the last row again)
         const Rows rows = fetch_strip(coming);
 #pragma clang loop unroll(disable)
-        for (int mode = 0;; ++mode) {
+        for (int mode = start;; mode = 1) {  // 1: again, against the rows' maxima
             // ---- logits (log2).  While the vector units work on a tile, the matrix cores form the next one's products (behind
             // the last tile: of the next strip's first).
             if (!ready && wv <= s) {
@@ -308,7 +312,8 @@ __global__ void __launch_bounds__(W * kWave, 2) prefill_strips_kernel(const Pref
             }
             ready = wv <= s;
             if (mode > 0) {
-                // the rare way: a term too large, or a row without a term that counts: every row against its maximum
+                // the rare way: a term too large, or a row without a term that counts: every row against its maximum (which
+                // tells whether the next strip is likely to need it too; the same in every wave)
                 float v[16];
                 const int tiles = tiles_of(s);
 #pragma unroll
@@ -329,7 +334,9 @@ __global__ void __launch_bounds__(W * kWave, 2) prefill_strips_kernel(const Pref
                 // number in the column), so here their logits become 0.  (By masks of bits: compares held over the tiles made the
                 // compiler spill scalar registers, which cost the whole kernel 1 to 4 %.)
                 const int left = n - s * kTile;
-                spread((int)(thread_here() & 31) < left ? fminf(most, 0x1.fffffep127f) : 0.0f, v);
+                const bool row = (int)(thread_here() & 31) < left;
+                start = __any(row && !(most >= kStripBottom && most < kStripTop)) ? 2 : 0;
+                spread(row ? fminf(most, 0x1.fffffep127f) : 0.0f, v);
                 const uint32_t inside = left < kTile ? (1u << left) - 1u : ~0u;  // by rows of the strip
 #pragma unroll
                 for (int t = 0; t < kStripTiles; ++t)
@@ -357,7 +364,7 @@ __global__ void __launch_bounds__(W * kWave, 2) prefill_strips_kernel(const Pref
                             v[r] += y[t][r];
                         }
                 leave_rows(v, [](float x, float z) { return x + z; });
-                if (mode == 0) park_strip(coming, (k + 2) % 3, rows);
+                if (mode != 1) park_strip(coming, (k + 2) % 3, rows);
             }
             const bool over = __any(top >= kStripTop);
             if (lane == 0) over_s[par][wv] = over;

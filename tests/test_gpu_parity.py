@@ -1684,6 +1684,23 @@ def test_an_infinite_logit_makes_its_column_infinite_at_every_prompt_length(n, d
     np.testing.assert_allclose(once[sel], passes[sel], rtol=5e-6, atol=0)
 
 
+@pytest.mark.parametrize("B,H,G,n,dtype,d,rows", [(15, 20, 1, 100, ko.BF16, 64, 32), (11, 5, 2, 130, ko.F32, 64, 32),
+                                                  (2, 50, 1, 1100, ko.F16, 64, 96)])
+def test_prompt_with_logits_beyond_the_exponentials_range_in_some_strips_only(B, H, G, n, dtype, d, rows):
+    """Every other block of rows has logits far beyond the exponential's range: a workgroup's strips go from being taken as
+    they are to being taken against their rows' maxima and back.  (Logits of several hundred, in fp32: 1e-5 of a term.)"""
+    rng = np.random.default_rng(n + d)
+    oc = random_cache(rng, 1, B, H, d, n, dtype, 0)
+    Q = rng.standard_normal((1, B, H * G, n, d)).astype(np.float32)
+    Q *= np.where(np.arange(n) // rows % 2, 60.0, 1.0).astype(np.float32)[:, None]
+    Q = Q.astype(np.float16) if dtype == ko.F16 else bf16_round(Q) if dtype == ko.BF16 else Q
+    seeds = np.arange(3, 3 + B).astype(np.uint64)
+    gc = upload(oc, G)
+    kf.kf_prefill_score(gc, dev(Q), n, 1.0, float(d) ** -0.5, kf.NOISE_GUMBEL, dev(seeds), None, kf.new_workspace(gc, n))
+    oc.prefill_score(Q, n, 1.0, float(d) ** -0.5, ko.NOISE_GUMBEL, seeds, None, q_per_kv=G)
+    assert_close_score(host(gc.score), oc.score, oc.len, "some strips far", rtol=SCORE_RTOL_PREFILL)
+
+
 @pytest.mark.parametrize("noise,tau", [(ko.NOISE_GUMBEL, 1.0), (ko.NOISE_GUMBEL, 1.4), (ko.NOISE_NONE, 1.0),
                                        (ko.NOISE_GAUSSIAN, 1.4)])
 def test_nan_in_the_last_key_reaches_every_column_in_parts_too(noise, tau):
