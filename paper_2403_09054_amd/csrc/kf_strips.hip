@@ -32,8 +32,10 @@ namespace kf {
 constexpr int kStripTiles = 8;         // key tiles of a wave
 constexpr int strip_waves(int n) { return n > kStripSmallRows ? 8 : 4; }
 constexpr float kStripTop = 110.0f;    // largest exponent of a term: 2048 of them stay finite
-constexpr float kStripBottom = -99.0f; // rows whose largest exponent lies from here to the top have a sum that is taken as it is
-constexpr float kStripLeast = 1e-30f;  // a row's sum below it (its terms lose bits) is taken against the row's maximum instead
+// A row whose sum is smaller is taken against its maximum: a term is kept down to 2^-126, the hardware's smallest, so down to
+// 2^-86 of its row's sum.  (At 2^-100, a term 2^-26 of its row could vanish, and a column of such terms with it.)
+constexpr float kStripLeast = 0x1p-40f;
+constexpr float kStripBottom = -40.0f; // rows whose largest exponent lies from here to the top are taken as they are for certain
 
 // Folds 16 values per lane over the 32 lanes of each half: lanes 0-15 of a half get the results of values 0-7, lanes 16-31
 // those of values 8-15.  One exchange of rows of 16 lanes folds two values at a time, rotations inside the rows do the rest

@@ -1701,6 +1701,29 @@ def test_prompt_with_logits_beyond_the_exponentials_range_in_some_strips_only(B,
     assert_close_score(host(gc.score), oc.score, oc.len, "some strips far", rtol=SCORE_RTOL_PREFILL)
 
 
+@pytest.mark.parametrize("n,dtype,d", [(300, ko.F32, 64), (1100, ko.BF16, 128)])
+def test_prompt_whose_logits_all_lie_far_below_zero_keeps_its_small_columns(n, dtype, d):
+    """All logits at about -62, one key's at -95: its terms, below the smallest fp32 number as they are, are 1e-15 of their
+    rows' sums and have to show in its column.  (Products of about 500 and 760 accumulated in fp32, times 1/8: 3e-5 at most
+    of a term; SCORE_RTOL_PREFILL allows 1e-4 of a column.)"""
+    rng = np.random.default_rng(n)
+    oc = random_cache(rng, 1, 1, 2, d, n, ko.F32, 0)
+    Q = rng.standard_normal((1, 1, 2, n, d)).astype(np.float32) * np.float32(8.0 / np.sqrt(d))
+    oc.K[..., 0] = -62.0
+    oc.K[0, 0, 1, 7, 0] = -95.0
+    Q[..., 0] = 8.0
+    if dtype == ko.BF16:
+        K32 = oc.K
+        oc = ko.OracleCache(1, 1, 2, d, n, dtype)
+        oc.K[...], Q = bf16_round(K32), bf16_round(Q)
+    seeds = np.array([5], np.uint64)
+    gc = upload(oc)
+    kf.kf_prefill_score(gc, dev(Q), n, 1.0, 0.125, kf.NOISE_GUMBEL, dev(seeds), None, kf.new_workspace(gc, n))
+    oc.prefill_score(Q, n, 1.0, 0.125, ko.NOISE_GUMBEL, seeds, None)
+    assert 0.0 < oc.score[0, 0, 1, 7] < 1e-9
+    assert_close_score(host(gc.score), oc.score, oc.len, "far below zero", rtol=SCORE_RTOL_PREFILL)
+
+
 @pytest.mark.parametrize("noise,tau", [(ko.NOISE_GUMBEL, 1.0), (ko.NOISE_GUMBEL, 1.4), (ko.NOISE_NONE, 1.0),
                                        (ko.NOISE_GAUSSIAN, 1.4)])
 def test_nan_in_the_last_key_reaches_every_column_in_parts_too(noise, tau):
