@@ -225,6 +225,22 @@ def test_prompts_of_few_units_are_cut_into_parts_without_gaps():
                 assert parts == 1, (U, n, parts)
 
 
+def test_prompts_evaluated_once_have_one_to_many_workgroups_a_unit():
+    # the rule that gives a unit's strips of 32 prompt rows to workgroups, on the host; among its forms one workgroup a
+    # unit, whose column sums are the score, and with grouped queries one whose sums are added up
+    plan = ctypes.CDLL(kf.lib_path())._ZN2kf11plan_stripsEliiib
+    plan.argtypes, plan.restype = [ctypes.c_int64] + [ctypes.c_int32] * 3 + [ctypes.c_bool], ctypes.c_int32
+    for U in (1, 2, 16, 63, 64, 65, 160, 256, 300, 320, 1024):
+        for n in list(range(1, 140)) + list(range(140, 2050, 37)) + [2047, 2048]:
+            for d, dt in ((64, kf.F32), (128, kf.BF16), (256, kf.F16)):
+                P, biased = plan(U, n, d, dt, False), plan(U, n, d, dt, True)
+                assert 0 <= P <= min(64, (n + 127) // 128 * 4) and biased in (0, P), (U, n, d, dt, P, biased)
+                assert P > 0 or U > 160, (U, n, d, dt)
+    assert plan(1, 2049, 64, kf.BF16, False) == 0
+    assert plan(300, 100, 64, kf.BF16, False) == 1 and plan(306, 130, 64, kf.F32, True) == 3
+    assert plan(16, 2048, 256, kf.BF16, False) > 1
+
+
 def test_query_group_validation_and_sizes():
     for g in (3, 5, 16):
         expect(binding.KF_EUNSUPPORTED, kf.kf_select_evict, fake_cache(q_per_kv=g), 8, 2, None, WS, 0)
