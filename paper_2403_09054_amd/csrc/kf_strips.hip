@@ -13,18 +13,20 @@
 //   * each term times its row's 1/sum goes into the lane's column sums, which stay in registers over all strips that
 //     the workgroup walks, and are written once.
 // Two waves per SIMD at 256 registers a lane: 8 waves (2048 keys), or two workgroups of 4 waves (1024 keys) on a CU.
-// Keys go through LDS in parts of 128 bytes a row: two workgroups of 4 waves fit also with 512-byte rows (64 heads x 1024 x
-// 256 73 -> 55 us, 256 x 1024 fp32 x 128 515 -> 442 against 8 waves), and nothing is spilled (against parts of 256 bytes 16 x
-// 2048 x 256 64 -> 59 us, 256 x 2048 x 128 595 -> 581, 512 x 1024 x 128 312 -> 298).
+// Keys go through LDS in parts of 128 bytes a row: two workgroups of 4 waves fit also with 512-byte rows (against 8 waves 64
+// heads x 1024 x 256 72 -> 53 us, 256 x 1024 x 128 fp32 525 -> 441), and only the form for fp32, d = 128 and 4 waves spills, 4
+// registers (against parts of 256 bytes 16 x 2048 x 256 62 -> 57 us, 256 x 2048 x 128 577 -> 569, 512 x 1024 x 128 299 -> 290; all
+// on one box).
 // With so few waves a wave has to cover its own round trips: while the vector units work on a tile, its next one's
 // products are formed in batches of two MFMAs, and the keys of the one after are on their way from memory; the strip's
 // query rows lie in LDS, asked for two strips ahead.
 //
-// What bounds it: the vector pipe (17 instructions a logit instead of 32) at about 60 % of its rate; the rest is the
-// strips' ends, where a workgroup's waves wait for each other.  Of 8 x 32 heads x 2048 x 128 (two passes 731 us): 672 us with
-// the key rows read from memory as operands, 664 by way of LDS (512-byte rows 1.3 times as fast), 595 with products
-// ahead, 552 without row references formed ahead of a strip and with row sums folded inside the lanes' rows.  Against float64
-// 0.7e-7 to 1.1e-7 relative (the passes 1.1e-7 to 2.5e-7): numerator and sum hold the same rounded term.
+// What bounds it: the vector pipe, 22 instructions a logit in all where the two passes take 32 (8 x 32 heads x 2048 x 128, pipe
+// busy 58 % of the time; 16 x 2048 x 256 24 where they take 38, 41 %); the rest is the strips' ends, where a workgroup's waves
+// wait for each other.  8 x 32 heads x 2048 x 128 take 569 us, the two passes 731 on the same box.  On the way, on a box where the
+// last of these took 552: 672 us with the key rows read from memory as operands, 664 by way of LDS (512-byte rows 1.3 times as
+// fast), 595 with products ahead, 552 without row references formed ahead of a strip and with row sums folded inside the lanes'
+// rows.  Against float64 0.7e-7 to 1.1e-7 relative (the passes 1.1e-7 to 2.5e-7): numerator and sum hold the same rounded term.
 #include "kf_prefill.h"
 
 namespace kf {
@@ -438,8 +440,8 @@ __global__ void __launch_bounds__(256) strips_sum_kernel(const PrefillArgs a, in
 }
 
 // Which prompts are scored this way.  Against the two passes (whole calls, 1.0 = the same time; d = 64 to 256, 2 to 2048
-// units): few units 1.2 to 2.5 from 128 rows on (16 heads x 2048 x 256 95 -> 52 us, 32 x 2048 x 128 127 -> 80, 32 x 1024
-// 54 -> 26), the same below; 256 units 1.1 to 1.9 (x 2048 x 128 731 -> 553 us; fp32, whose products take the time, 1.9).  With
+// units): few units 1.2 to 2.5 from 128 rows on (16 heads x 2048 x 256 95 -> 52 us, 32 x 2048 x 128 121 -> 73, 32 x 1024
+// 53 -> 25), the same below; 256 units 1.1 to 1.9 (x 2048 x 128 731 -> 569 us; fp32, whose products take the time, 1.9).  With
 // more units the passes fill the chip by themselves, and a short strip's sums and barrier weigh more than its logits:
 // 512 units 0.91 to 1.2 below 200 rows, 1.2 to 1.6 at 256; 1024 units 0.86 to 1.03 below 200 rows, 0.97 to 1.4 at 256; 2048 units
 // 0.89 to 1.3 at 256, 0.98 to 1.7 at 400, 1.16 to 2 at 512.  Just above 1024 rows, where every strip goes to 8 waves, 16-bit
