@@ -24,7 +24,11 @@
 // left the loop, the masking compares moved into the edge tiles' branch and the
 // accumulators into ordinary registers).  At temperature 1, 32 heads x 32768 rows
 // 20.3 -> 17.0 to 17.9 ms from box to box, 256 x 4096 with position bias
-// 3.13 -> 2.56 to 2.71.
+// 3.13 -> 2.56 to 2.71.  With a logit's work in two phases, the second at a raised
+// issue priority (wave_priority), on one box 17.05 -> 16.47 ms and, with the tiles
+// that the bias leaves, 1667 -> 1559 us, the same results.  (Four waves per SIMD;
+// three cost 2 % of the per-logit work, five and six spill.  The first of these
+// two runs at 2.07 GHz, the second at 2.23: the chip's power, not only its issue.)
 //
 // With the Gumbel adjustment (the method; the others keep the plain form) pass 1
 // sums every term against a reference exponent instead of searching each tile's
@@ -253,10 +257,15 @@ __device__ __forceinline__ float tile_sum(const LogitParams& lp, const f32x16& a
         const uint4 k4 = *(const uint4*)&kfold[q4 * 8 + half * 4];
         const uint32_t ks[4] = {k4.x, k4.y, k4.z, k4.w};
         float e[4], l2u[4];
+        uint32_t bits[4];
+#pragma unroll
+        for (int e4 = 0; e4 < 4; ++e4) bits[e4] = mix32_folded(rfold ^ ks[e4]);
+        wave_priority<1>();
+#pragma unroll
+        for (int e4 = 0; e4 < 4; ++e4) l2u[e4] = hw_log2(uniform_of(bits[e4]));
 #pragma unroll
         for (int e4 = 0; e4 < 4; ++e4) {
             const int ro = q4 * 8 + e4;
-            l2u[e4] = hw_log2(uniform_of(mix32_folded(rfold ^ ks[e4])));
             // position bias -slope*(dist0 - ro): its dist0 part rides in `base`, the ro part is a literal multiple
             float t = BIAS ? fmaf(lp.slope1, (float)ro, base) : base;
             if (!TAU1) t = fmaf(hw_log2(-l2u[e4]), -lp.inv_tau, t);
@@ -264,6 +273,7 @@ __device__ __forceinline__ float tile_sum(const LogitParams& lp, const f32x16& a
             if (MASK) e[e4] = ro <= room ? e[e4] : 0.0f;
         }
         ssum = TAU1 ? add_over_t(e, l2u, ssum) : (((ssum + e[0]) + e[1]) + e[2]) + e[3];
+        wave_priority<0>();
     }
     return ssum;
 }
@@ -497,12 +507,19 @@ __device__ __forceinline__ float column_sum(const LogitParams& lp, const f32x16&
         const uint32_t rv[4] = {r4.x, r4.y, r4.z, r4.w};
         const float dist0 = (float)(i_first + q4 * 8 - j);
         float z[4], l2u[4];
+        if constexpr (GUMBEL) {
+            uint32_t bits[4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) bits[e] = mix32_folded(rv[e] ^ kfold);
+            wave_priority<1>();
+#pragma unroll
+            for (int e = 0; e < 4; ++e) l2u[e] = hw_log2(uniform_of(bits[e]));
+        }
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
             const float x = acc[q4 * 4 + e];
             if constexpr (GUMBEL) {
                 // cv holds (adjustment's constant part - row normaliser): z = 2^(x2 - log2(t)/tau + cv)
-                l2u[e] = hw_log2(uniform_of(mix32_folded(rv[e] ^ kfold)));
                 float t = cv[e];
                 if (!TAU1) t = fmaf(hw_log2(-l2u[e]), -lp.inv_tau, t);
                 if (BIAS) t = fmaf(dist0 + (float)e, -lp.slope1, t);
@@ -514,6 +531,7 @@ __device__ __forceinline__ float column_sum(const LogitParams& lp, const f32x16&
             if (MASK) z[e] = (i >= j && i < n) ? z[e] : 0.0f;
         }
         sum = TAU1 ? add_over_t(z, l2u, sum) : (((sum + z[0]) + z[1]) + z[2]) + z[3];
+        if (GUMBEL) wave_priority<0>();
     }
     return sum;
 }
