@@ -21,9 +21,16 @@
 // products are formed in batches of two MFMAs, and the keys of the one after are on their way from memory; the strip's
 // query rows lie in LDS, asked for two strips ahead.
 //
+// A batch asks the LDS for its rows' noise keys before its operands, so that its hashes do not wait for those, and the logarithms
+// run at a raised issue priority (wave_priority): with the terms' range told from the sums, 8 x 32 heads x 2048 x 128 567 -> 513 us, 32
+// x 2048 x 128 72.4 -> 66.2, with position bias 74.4 -> 66.9, 16 x 2048 x 256 49.5 -> 47.7, 32 x 1024 x 128 24.4 -> 22.7, fp32 64 x
+// 2000 x 128 405 -> 398 (one box).  Measured and left: keys by direct loads to LDS (asked for 4 to 8 logits ahead, no key registers):
+// 530, 68.4, 48.5 and, 64 x 1024 x 256, 52 -> 56; noise keys asked for a batch ahead: the same, 5 to 13 registers spilled.  With
+// 512-byte rows the keys alone, 16 KB a tile, take 33 of 105 thousand cycles of a CU's way from its L2 at 64 bytes each.
+//
 // What bounds it: the vector pipe, 22 instructions a logit in all where the two passes take 32 (8 x 32 heads x 2048 x 128, pipe
-// busy 58 % of the time; 16 x 2048 x 256 24 where they take 38, 41 %); the rest is the strips' ends, where a workgroup's waves
-// wait for each other.  8 x 32 heads x 2048 x 128 take 569 us, the two passes 731 on the same box.  On the way, on a box where the
+// busy 58 % of the time; 16 x 2048 x 256 24 where they take 38, 41 %, before the order above); the rest is the strips' ends, where
+// a workgroup's waves wait for each other.  8 x 32 heads x 2048 x 128 take 569 us, the two passes 731 on the same box.  On the way, on a box where the
 // last of these took 552: 672 us with the key rows read from memory as operands, 664 by way of LDS (512-byte rows 1.3 times as
 // fast), 595 with products ahead, 552 without row references formed ahead of a strip and with row sums folded inside the lanes'
 // rows.  Against float64 0.7e-7 to 1.1e-7 relative (the passes 1.1e-7 to 2.5e-7): numerator and sum hold the same rounded term.
@@ -33,7 +40,10 @@ namespace kf {
 
 constexpr int kStripTiles = 8;         // key tiles of a wave
 constexpr int strip_waves(int n) { return n > kStripSmallRows ? 8 : 4; }
-constexpr float kStripTop = 110.0f;    // largest exponent of a term: 2048 of them stay finite
+// A row whose sum is larger, or infinite, is taken against its maximum; below, the sum has a reciprocal that is no denormal.  (The
+// sums tell of a term too large; a running maximum of the terms would take an instruction a logit for it.)
+constexpr float kStripMost = 0x1p118f;
+constexpr float kStripTop = 107.0f;    // 2048 terms of this exponent stay below that
 // A row whose sum is smaller is taken against its maximum: a term is kept down to 2^-126, the hardware's smallest, so down to
 // 2^-86 of its row's sum.  (At 2^-100, a term 2^-26 of its row could vanish, and a column of such terms with it.)
 constexpr float kStripLeast = 0x1p-40f;
@@ -80,7 +90,6 @@ __global__ void __launch_bounds__(W * kWave, 2) prefill_strips_kernel(const Pref
     __shared__ __attribute__((aligned(16))) char kbuf[W][kTile * KPITCH];
     __shared__ __attribute__((aligned(16))) uint32_t fold_s[3][kTile];  // folded noise keys of the rows
     __shared__ __attribute__((aligned(16))) float part_s[2][W][kTile];  // what each wave has of the rows' sums
-    __shared__ int over_s[2][W];
     __shared__ __attribute__((aligned(16))) float own_s[W][kTile];      // a wave's own copy of the rows' factors
     const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int n0 = lane & 31, half = lane >> 5;
@@ -219,7 +228,7 @@ __global__ void __launch_bounds__(W * kWave, 2) prefill_strips_kernel(const Pref
         wave_sync();
     };
 
-    int par = 0;  // of part_s and over_s: a value written before a barrier is read before the next one
+    int par = 0;  // of part_s: a value written before a barrier is read before the next one
     // what the wave has of the rows' sums (or maxima) to the other waves
     auto leave_rows = [&](const float (&v)[16], auto op) {
         float f[8];
@@ -259,7 +268,6 @@ __global__ void __launch_bounds__(W * kWave, 2) prefill_strips_kernel(const Pref
                 for (int x = 0; x < NB; ++x)
                     acc = multiply(operands(x, wv, wv + W <= s ? wv + W : wv, qbuf[cur] + n0 * PITCH + half * 16), acc);
             }
-            float top = -INFINITY;
 #pragma unroll
             for (int t = 0; t < kStripTiles; ++t) {
                 int jt = wv + W * t, end = s;
@@ -278,24 +286,32 @@ __global__ void __launch_bounds__(W * kWave, 2) prefill_strips_kernel(const Pref
                     asm volatile("" : "+v"(j));  // (keeps the eight tiles' positions from being formed ahead and held)
                     uint32_t kfold = fold16((uint32_t)j * kKposMul);
                     asm volatile("" : "+v"(kfold));  // (else its two halves go into every logit apart)
+                    auto folds = [&](int r) { return *(const uint2*)&fold_s[cur][(r >> 2) * 8 + half * 4 + (r & 3)]; };
                     // position bias -slope*(i - j): the lane's part here, that of its 16 rows as literal multiples
                     const float back = BIAS ? fmaf(lp.slope1, (float)(j - end * kTile - half * 4), lp.gz) : lp.gz;
 #pragma unroll
                     for (int x = 0; x < NB; ++x) {
+                        uint2 fold[NS];  // (ahead of the operands: the LDS answers in order)
+#pragma unroll
+                        for (int i = 0; i < NS; ++i) fold[i] = folds(x * NS * 2 + 2 * i);
+                        __builtin_amdgcn_sched_barrier(0);
                         const Batch o = operands(x, coming, after, qp);
                         __builtin_amdgcn_sched_barrier(0);
+                        uint32_t bits[2 * NS];
 #pragma unroll
-                        for (int r = x * NS * 2; r < (x + 1) * NS * 2; r += 2) {  // two rows
-                            const uint2 f2 = *(const uint2*)&fold_s[cur][(r >> 2) * 8 + half * 4 + (r & 3)];
-                            const uint32_t rv[2] = {f2.x, f2.y};
-#pragma unroll
-                            for (int e = 0; e < 2; ++e) {
-                                const float l2u = hw_log2(uniform_of(mix32_folded(rv[e] ^ kfold)));
-                                const float c = BIAS ? fmaf(lp.slope1, -(float)((r >> 2) * 8 + (r & 3) + e), back) : back;
-                                y[t][r + e] = fmaf(acc[r + e], lp.sc1, fmaf(hw_log2(-l2u), -lp.inv_tau, c));
-                            }
+                        for (int i = 0; i < NS; ++i) {  // two rows
+                            bits[2 * i] = mix32_folded(fold[i].x ^ kfold);
+                            bits[2 * i + 1] = mix32_folded(fold[i].y ^ kfold);
                         }
-                        __builtin_amdgcn_sched_barrier(0);
+                        wave_priority<1>();
+#pragma unroll
+                        for (int i = 0; i < 2 * NS; ++i) {
+                            const int r = x * NS * 2 + i;
+                            const float l2u = hw_log2(uniform_of(bits[i]));
+                            const float c = BIAS ? fmaf(lp.slope1, -(float)((r >> 2) * 8 + (r & 3)), back) : back;
+                            y[t][r] = fmaf(acc[r], lp.sc1, fmaf(hw_log2(-l2u), -lp.inv_tau, c));
+                        }
+                        wave_priority<0>();
                         ahead = multiply(o, ahead);
                     }
                     if (jt == end) {  // crosses the diagonal (the empty asm keeps the compares inside this branch)
@@ -309,8 +325,6 @@ __global__ void __launch_bounds__(W * kWave, 2) prefill_strips_kernel(const Pref
                             y[t][r] = past >= 0 ? x : -INFINITY;
                         }
                     }
-#pragma unroll
-                    for (int r = 0; r < 16; ++r) top = fmaxf(top, y[t][r]);
                     acc = ahead;
                 }
             }
@@ -370,20 +384,15 @@ __global__ void __launch_bounds__(W * kWave, 2) prefill_strips_kernel(const Pref
                 leave_rows(v, [](float x, float z) { return x + z; });
                 if (mode != 1) park_strip(coming, (k + 2) % 3, rows);
             }
-            const bool over = __any(top >= kStripTop);
-            if (lane == 0) over_s[par][wv] = over;
             __syncthreads();
             float sum = 0.0f;
-            int again = 0;
 #pragma unroll
-            for (int w = 0; w < W; ++w) {
-                sum += part_s[par][w][n0];
-                again |= over_s[par][w];
-            }
+            for (int w = 0; w < W; ++w) sum += part_s[par][w][n0];
             par ^= 1;
             const bool row = s * kTile + (int)(thread_here() & 31) < n;
-            // (the same in every wave: all read the same sums)
-            if (mode == 0 && (__builtin_amdgcn_readfirstlane(again) || __any(row && sum < kStripLeast))) {
+            // (the same in every wave: all read the same sums.  Also a sum of a row behind the prompt's end: an infinite term of its
+            // times the row's factor of 0 would be no number.)
+            if (mode == 0 && __any(sum >= kStripMost || (row && sum < kStripLeast))) {
                 ready = false;
                 continue;
             }

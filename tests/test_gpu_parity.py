@@ -1738,6 +1738,28 @@ def test_prompt_whose_logits_all_lie_far_below_zero_keeps_its_small_columns(n, d
     assert_close_score(host(gc.score), oc.score, oc.len, "far below zero", rtol=SCORE_RTOL_PREFILL)
 
 
+@pytest.mark.parametrize("level", [74.0, 78.0, 80.0, 82.0, 86.0, 90.0])
+@pytest.mark.parametrize("n,dtype,d", [(300, ko.F32, 64), (1300, ko.BF16, 128)])
+def test_prompt_with_row_sums_around_the_largest_taken_as_they_are(n, dtype, d, level):
+    """All logits at about `level`: rows whose sums of terms (up to n times e^level times a few) end below, around and above 2^118,
+    where a strip is evaluated against its rows' maxima instead, and beyond fp32.  (Products of at most 8 * 90 accumulated in
+    fp32, times 1/8: 3e-5 at most of a term; SCORE_RTOL_PREFILL allows 1e-4 of a column.)"""
+    rng = np.random.default_rng(n)
+    oc = random_cache(rng, 1, 1, 2, d, n, ko.F32, 0)
+    Q = rng.standard_normal((1, 1, 2, n, d)).astype(np.float32) * np.float32(8.0 / np.sqrt(d))
+    oc.K[..., 0] = level
+    Q[..., 0] = 8.0
+    if dtype == ko.BF16:
+        K32 = oc.K
+        oc = ko.OracleCache(1, 1, 2, d, n, dtype)
+        oc.K[...], Q = bf16_round(K32), bf16_round(Q)
+    seeds = np.array([5], np.uint64)
+    gc = upload(oc)
+    kf.kf_prefill_score(gc, dev(Q), n, 1.0, 0.125, kf.NOISE_GUMBEL, dev(seeds), None, kf.new_workspace(gc, n))
+    oc.prefill_score(Q, n, 1.0, 0.125, ko.NOISE_GUMBEL, seeds, None)
+    assert_close_score(host(gc.score), oc.score, oc.len, "large sums", rtol=SCORE_RTOL_PREFILL)
+
+
 @pytest.mark.parametrize("n,noise,tau", [(300, ko.NOISE_GUMBEL, 1.0), (2100, ko.NOISE_GUMBEL, 1.0), (2100, ko.NOISE_GUMBEL, 1.4),
                                          (300, ko.NOISE_NONE, 1.0)])
 def test_a_row_whose_own_logit_is_minus_infinity_is_scored_by_its_others(n, noise, tau):
