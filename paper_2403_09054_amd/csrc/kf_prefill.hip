@@ -174,14 +174,18 @@ struct TileStage {
 // ------------------------------------------------------------------ tiles that a position bias rules out
 // With a position bias of positive slope the far tiles of a walk cannot matter: by Cauchy-Schwarz
 //     y2_ij <= |q_i| |k_j| scale log2(e)/tau + (largest adjustment) - slope log2(e)/tau (i - j)
-// for every finite input, and both softmaxes have a term to compare with, the row's own diagonal one.  Pass 1 leaves
-// out the leading tiles of a walk whose terms stay below 2^-(28 + log2 n) of the diagonal term of each of the block's
-// rows: all of them together change a row's sum by less than 2^-28.  Pass 2 leaves out the trailing query tiles whose
-// terms stay below 2^-(28 + log2 n) of each of the block's columns' own diagonal term, which is part of the column's sum.
-// Both are less than a rounding of the result.  The bounds are taken from the data (norms, diagonal terms and
-// normalisers per tile); a NaN or an infinity in any of them makes every comparison below fail, and the tile is walked.
-// One layer of 8 x 32 heads x 4096 rows with slopes 2^(-h/4), h = 1..32: 2676 -> 1678 us.  A unit whose largest possible bias
-// cannot outweigh the constants takes none of this (skip_reach).
+// for every finite input.  A walk that is not cut into parts begins at the diagonal.  kSkipAhead tiles behind the block's own
+// it looks at what its rows (pass 2: columns) have gathered so far, and leaves out the tiles at the far end whose terms, by
+// that bound, all together stay below 2^-28 of it: less than a rounding of the result.  (Against what has been gathered, not
+// against the diagonal term alone, which is 2^15 smaller in the rows that decide; and the terms' bounds added up tile by
+// tile, the far ones being smaller by the bias, instead of n times the largest: 22 of 95 bits that the bias has to outweigh.
+// One layer of 8 x 32 heads x 4096 rows with slopes 2^(-h/4), h = 1..32, 2676 us with all tiles: 1678 against the diagonal terms;
+// 1556 so, later, and 1470 against the sums on the same box, the error against float64 unchanged.)
+// A part of a walk does not have the others' sums: pass 1 takes the diagonal term instead, and so does pass 2, there with n
+// times the largest term for the sum over the tiles, whose normalisers it has not.
+// The bounds are taken from the data (norms, sums and normalisers per tile); a NaN or an infinity in any of them makes every
+// comparison below fail, and the tile is walked.  A unit whose largest possible bias cannot outweigh the constants takes none
+// of this (skip_reach).
 constexpr float kSkipBits = 29.0f;  // 28, and one for the rounding of the bound itself
 
 // Largest adjustment zeta log2(e) that the generator can produce (Gumbel: -ln(-ln(1 - 2^-24)) log2(e) = 24; Gaussian: radius
@@ -195,8 +199,29 @@ __device__ __forceinline__ float largest_adjustment(int noise) {
 __device__ __forceinline__ float skip_reach(int noise, float inv_tau, int n) {
     return largest_adjustment(noise) * inv_tau + kSkipBits + hw_log2((float)n);
 }
+constexpr int kSkipAhead = 2;
+constexpr float kSkipTileBits = kSkipBits + 5.0f;  // a tile's terms of a row (or column): 32 of the bound each
 __device__ __forceinline__ float not_above(float x) { return x > -INFINITY ? x : -INFINITY; }  // lower bound: NaN is none
 __device__ __forceinline__ float wave_min(float v) { return -wave_max(-v); }
+// Of `count` tiles in the order of a walk's far end: how many of the first ones may be left out, all together.  term(x): what
+// tile x can add to the most affected row, of what the row may lose.  The same in every wave that asks.
+template <typename F>
+__device__ __forceinline__ int tiles_ruled_out(int count, F term) {
+    const int lane = threadIdx.x & 63;
+    float before = 0.0f;
+    for (int x0 = 0; x0 < count; x0 += kWave) {
+        float e = x0 + lane < count ? term(x0 + lane) : INFINITY;
+#pragma unroll
+        for (int o = 1; o < kWave; o <<= 1) {
+            const float t = __shfl_up(e, o, kWave);
+            if (lane >= o) e += t;
+        }
+        const unsigned long long most = __ballot(!(before + e <= 1.0f));
+        if (most) return x0 + __ffsll((long long)most) - 1;
+        before += __shfl(e, kWave - 1, kWave);
+    }
+    return count;
+}
 // Norm from its square: never too small (256 squares that underflowed are 3e-36 together), infinite where the square is no
 // number (every maximum that follows would pass a NaN over).
 __device__ __forceinline__ float norm_bound(float sq) { return sq < INFINITY ? sqrtf(fmaxf(sq, 4e-36f)) * 1.0001f : INFINITY; }
@@ -288,8 +313,7 @@ __global__ void __launch_bounds__(kPrefillThreads, (kPrefillMinWaves<T, D>)) pre
     using Stage = TileStage<T, D>;
     __shared__ __attribute__((aligned(16))) char kbuf[2][Stage::kBufBytes];
     __shared__ __attribute__((aligned(16))) uint32_t kfold[2][kTile];  // folded positions of the tile's keys
-    __shared__ float2 wstat[kPrefillThreads / kWave];  // of a wave's rows: largest norm, smallest diagonal term
-    __shared__ int tile_s;
+    __shared__ float2 wstat[kPrefillThreads / kWave];  // of a wave's rows: largest norm, smallest sum so far (or diagonal term)
     const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int n0 = lane & 31, half = lane >> 5;
     int64_t u;
@@ -336,9 +360,24 @@ __global__ void __launch_bounds__(kPrefillThreads, (kPrefillMinWaves<T, D>)) pre
     // (A part behind the first starts from a finite reference below every logit: with -inf a tile of nothing but
     // masked logits and NaN would not be told from an empty one.)
     float M = !GUMBEL && part > 0 ? -0x1p127f : -INFINITY, Ssum = 0.0f;
-    const float reach = BIAS ? skip_reach(a.noise, a.inv_tau, n) : 0.0f;
-    const bool skips = BIAS && a.ws_kn && lp.slope1 * (float)n > reach;  // of the unit
+    const bool skips = BIAS && a.ws_kn && lp.slope1 * (float)n > skip_reach(a.noise, a.inv_tau, n);  // of the unit
     float own = -INFINITY, qnorm = 0.0f;                     // the row's diagonal term, the norm of its query
+    // how many of the walk's first `count` tiles do not matter to the block's rows (wstat is there)
+    auto ruled_out = [&](int count) {
+        const float* kn = a.ws_kn + (size_t)(u / a.G) * (a.n_pad / kTile);
+        const float most = largest_adjustment(a.noise) * a.inv_tau + kSkipTileBits;
+        return __builtin_amdgcn_readfirstlane(tiles_ruled_out(count, [&](int jt) {
+            const float norm = kn[jt] * fabsf(lp.sc1);
+            float e = 0.0f;
+            for (int v = 0; v < kPrefillThreads / kWave; ++v) {
+                const int first = rb * (4 * kTile) + v * kTile;  // the wave's first row
+                if (first >= n) break;
+                const float bias = lp.slope1 * (float)(first - (jt * kTile + kTile - 1));
+                e += hw_exp2(wstat[v].x * norm + most - bias - wstat[v].y);
+            }
+            return e;
+        }));
+    };
     if (GUMBEL || skips) {
         // Reference exponent of the row's sum: its own diagonal term y2_ii, formed here from the query's and the
         // key's elements this lane holds (both halves of the wave added up).  It is a term of the sum, so the
@@ -356,41 +395,29 @@ __global__ void __launch_bounds__(kPrefillThreads, (kPrefillMinWaves<T, D>)) pre
 #pragma unroll
         for (int g = 0; g < NG; ++g) sq = dot_piece<T>(bq[g], bq[g], sq);
         qnorm = wave_max(norm_bound(sq + __shfl_xor(sq, 32, kWave)));
-        const float least = wave_min(not_above(own));
-        if (lane == 0) wstat[wv] = make_float2(qnorm, least);
-        if (lane == 0 && active && part == 0 && a.parts > 1) a.ws_tile[(size_t)u * (a.n_pad / kTile) + i0 / kTile] = make_float4(qnorm, least, 0.0f, 0.0f);
-        const int limit = min(rb * 4, jt_last + 1);  // the block's own tiles are walked in any case
-        if (lp.slope1 * (float)((rb * 4 - jt_first) * kTile) > reach) {  // workgroup-uniform
-            if (threadIdx.x == 0) tile_s = max(limit, jt_first);
+        if (a.parts > 1) {
+            const float least = wave_min(not_above(own));
+            if (lane == 0) wstat[wv] = make_float2(qnorm, least);
+            if (lane == 0 && active && part == 0) a.ws_tile[(size_t)u * (a.n_pad / kTile) + i0 / kTile] = make_float4(qnorm, least, 0.0f, 0.0f);
             __syncthreads();
-            const float* kn = a.ws_kn + (size_t)(u / a.G) * (a.n_pad / kTile);
-            for (int jt = jt_first + (int)threadIdx.x; jt < limit; jt += kPrefillThreads) {
-                bool none = true;
-                for (int v = 0; v < kPrefillThreads / kWave; ++v) {
-                    const int first = rb * (4 * kTile) + v * kTile;  // the wave's first row
-                    if (first >= n) break;
-                    const float bias = lp.slope1 * (float)(first - (jt * kTile + kTile - 1));
-                    none = none && wstat[v].x * kn[jt] * fabsf(lp.sc1) + reach - bias < wstat[v].y;
-                }
-                if (!none) {
-                    atomicMin(&tile_s, jt);
-                    break;
-                }
-            }
-            __syncthreads();
-            jt_first = __builtin_amdgcn_readfirstlane(tile_s);  // behind jt_last: nothing is left of the part
+            jt_first = max(jt_first, ruled_out(min(rb * 4, jt_last + 1)));  // behind jt_last: nothing is left of the part
         }
     }
     const int jt_end = min(i0 + kTile - 1, n - 1) / kTile;  // this wave's last key tile
-    typename Stage::Regs stage = Stage::fetch(Ku, min(jt_first, jt_last) * kTile, n);
+    // What rounding has added to the sum so far: from the diagonal down the largest tiles come first, and the others would each
+    // lose half a unit of the whole sum's last place (2.2e-7 of a score instead of 2.0e-7, 256 x 4096).
+    float lost = 0.0f;
+    // the walk: upwards, or with a position bias from the diagonal down
+    const int jt_begin = BIAS ? max(jt_last, jt_first) : min(jt_first, jt_last), looks_at = skips && a.parts == 1 ? rb * 4 - kSkipAhead : -1;
+    typename Stage::Regs stage = Stage::fetch(Ku, min(jt_begin, jt_last) * kTile, n);
     Stage::park(kbuf[0], stage);
-    if constexpr (GUMBEL) park_keys(0, jt_first);
+    if constexpr (GUMBEL) park_keys(0, jt_begin);
     __syncthreads();
-    for (int jt = jt_first; jt <= jt_last; ++jt) {
-        const int cur = (jt - jt_first) & 1;
+    for (int jt = BIAS ? jt_last : jt_first, cur = 0; BIAS ? jt >= jt_first : jt <= jt_last; jt += BIAS ? -1 : 1, cur ^= 1) {
         // the next tile (the last one again at the end: rows stay in range), in flight during this tile's work;
         // asking two tiles ahead measured the same
-        stage = Stage::fetch(Ku, min(jt + 1, jt_last) * kTile, n);
+        const int jt_next = BIAS ? max(jt - 1, jt_first) : min(jt + 1, jt_last);
+        stage = Stage::fetch(Ku, jt_next * kTile, n);
         if (active && jt <= jt_end) {
             const char* kb = kbuf[cur];
             const f32x16 acc = Stage::products(kb, n0, half, bq);
@@ -413,7 +440,8 @@ __global__ void __launch_bounds__(kPrefillThreads, (kPrefillMinWaves<T, D>)) pre
                     } else {
                         ssum = tile_sum<BIAS, false, TAU1>(lp, acc, base, rfold, kfold[cur], half, 0);
                     }
-                    const float Snew = Ssum + ssum;
+                    const float add = BIAS ? ssum - lost : ssum;
+                    const float Snew = Ssum + add;
                     // a sum beyond fp32 in some lane (a logit 2^120 above its row's reference): that lane raises its
                     // reference and the wave sums the tile again (the other lanes arrive at the same sums as
                     // before); bounded, so that NaN inputs end as NaN
@@ -422,9 +450,11 @@ __global__ void __launch_bounds__(kPrefillThreads, (kPrefillMinWaves<T, D>)) pre
                         if (over) {
                             M += 100.0f;
                             Ssum *= 0x1p-100f;
+                            lost *= 0x1p-100f;
                         }
                         continue;
                     }
+                    if (BIAS) lost = Snew < INFINITY ? (Snew - Ssum) - add : 0.0f;
                     Ssum = Snew;
                     break;
                 }
@@ -433,6 +463,7 @@ __global__ void __launch_bounds__(kPrefillThreads, (kPrefillMinWaves<T, D>)) pre
                     const int sh = (int)(__float_as_uint(Ssum) >> 23) - 127;
                     M += (float)sh;
                     Ssum = __uint_as_float(__float_as_uint(Ssum) - ((uint32_t)sh << 23));
+                    if (BIAS) lost *= __uint_as_float((uint32_t)(127 - min(sh, 126)) << 23);
                 }
             } else {
             float y2[16];
@@ -461,11 +492,19 @@ __global__ void __launch_bounds__(kPrefillThreads, (kPrefillMinWaves<T, D>)) pre
             }
             }
         }
-        if (jt < jt_last) {
+        if (jt != jt_next) {
             Stage::park(kbuf[cur ^ 1], stage);
-            if constexpr (GUMBEL) park_keys(cur ^ 1, jt + 1);
+            if constexpr (GUMBEL) park_keys(cur ^ 1, jt_next);
+        }
+        const bool looks = BIAS && jt == looks_at;  // workgroup-uniform
+        if (looks) {
+            const float M2 = __shfl_xor(M, 32, kWave), S2 = __shfl_xor(Ssum, 32, kWave), Mt = fmaxf(M, M2);
+            const float c = log2_of_sum(Mt, (M > -INFINITY ? Ssum * hw_exp2(M - Mt) : 0.0f) + (M2 > -INFINITY ? S2 * hw_exp2(M2 - Mt) : 0.0f));
+            const float least = wave_min(i < n ? not_above(c) : INFINITY);
+            if (lane == 0) wstat[wv] = make_float2(qnorm, least);
         }
         __syncthreads();
+        if (looks) jt_first = ruled_out(jt);
     }
     if (!active) return;
     // the two halves of the wave hold disjoint key subsets of the same query
@@ -484,10 +523,9 @@ __global__ void __launch_bounds__(kPrefillThreads, (kPrefillMinWaves<T, D>)) pre
         a.ws_c[(size_t)u * a.n_pad + i] = GUMBEL ? lp.gz - c : c;
         a.ws_r[(size_t)u * a.n_pad + i] = GUMBEL ? rfold : rkey;
     }
-    if (skips && a.parts == 1) {  // of the wave's rows: norm, smallest normaliser, smallest share of the diagonal term
-        const float c = log2_of_sum(Mt, St);
-        const float cmin = wave_min(i < n ? not_above(c) : INFINITY), dmin = wave_min(i < n ? not_above(own - c) : INFINITY);
-        if (lane == 0) a.ws_tile[(size_t)u * (a.n_pad / kTile) + i0 / kTile] = make_float4(qnorm, cmin, dmin, 0.0f);
+    if (skips && a.parts == 1) {  // of the wave's rows: norm, smallest normaliser
+        const float cmin = wave_min(i < n ? not_above(log2_of_sum(Mt, St)) : INFINITY);
+        if (lane == 0) a.ws_tile[(size_t)u * (a.n_pad / kTile) + i0 / kTile] = make_float4(qnorm, cmin, 0.0f, 0.0f);
     }
 }
 
@@ -549,6 +587,7 @@ __global__ void __launch_bounds__(kPrefillThreads, (kPrefillMinWaves<T, D>)) pre
     __shared__ __attribute__((aligned(16))) uint32_t rall[PARTS ? kPrefillMaxPartTiles * kTile : 4];  // (PARTS)
     __shared__ float share_s[2];
     __shared__ int tile_s;
+    __shared__ float2 wstat[kPrefillThreads / kWave];  // of a wave's columns: largest norm, smallest sum so far
     const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int n0 = lane & 31, half = lane >> 5;
     int64_t u;
@@ -591,7 +630,7 @@ __global__ void __launch_bounds__(kPrefillThreads, (kPrefillMinWaves<T, D>)) pre
     const float* wc = a.ws_c + (size_t)u * a.n_pad;
     const uint32_t* wr = a.ws_r + (size_t)u * a.n_pad;
 
-    float colsum = 0.0f;
+    float colsum = 0.0f, lost = 0.0f;  // lost: what rounding has added to it (UP, as in pass 1)
     const int it_begin = j0 / kTile;                    // this wave's first query tile (the diagonal one)
     // a tile's 32 row statistics ride with the tile: one wave fetches them (n_pad covers whole tiles)
     struct Staged {
@@ -611,38 +650,32 @@ __global__ void __launch_bounds__(kPrefillThreads, (kPrefillMinWaves<T, D>)) pre
         }
     }
     const float reach = BIAS ? skip_reach(a.noise, a.inv_tau, n) : 0.0f;
-    if (BIAS && a.ws_kn && lp.slope1 * (float)n > reach && lp.slope1 * (float)((it_end - cb * 4) * kTile) > reach) {
-        // workgroup-uniform: the unit's bounds are there, and the last tile may be ruled out
-        const size_t nt = a.n_pad / kTile;
-        const float4* tiles = a.ws_tile + (size_t)u * nt;
+    const bool skips = BIAS && a.ws_kn && lp.slope1 * (float)n > reach;  // of the unit: its bounds are there
+    const float4* tiles = a.ws_tile + (size_t)u * (a.n_pad / kTile);
+    const float* kn = a.ws_kn + (size_t)(u / a.G) * (a.n_pad / kTile);
+    if (PARTS && skips && lp.slope1 * (float)((it_end - cb * 4) * kTile) > reach) {
+        // workgroup-uniform: the last tile may be ruled out
         const int own_last = min(cb * 4 + 3, (n - 1) / kTile);  // the block's own tiles are walked in any case
         const int limit = max(own_last + 1, it_first);
         // the block's columns: smallest share of a diagonal term in its row, largest key
+        const int i = cb * (4 * kTile) + (int)threadIdx.x;
         float share = INFINITY;
-        if constexpr (PARTS) {
-            const int i = cb * (4 * kTile) + (int)threadIdx.x;
-            if (threadIdx.x < 4 * kTile && i < n)
-                share = not_above(tiles[i / kTile].y - merged_normaliser(a.ws_part + (size_t)u * a.parts * a.n_pad + i, a.n_pad, (i / kTile) / a.part_tiles + 1));
-            share = wave_min(share);
-            if (lane == 0 && wv < 2) share_s[wv] = share;
-        }
+        if (threadIdx.x < 4 * kTile && i < n)
+            share = not_above(tiles[i / kTile].y - merged_normaliser(a.ws_part + (size_t)u * a.parts * a.n_pad + i, a.n_pad, (i / kTile) / a.part_tiles + 1));
+        share = wave_min(share);
+        if (lane == 0 && wv < 2) share_s[wv] = share;
         if (threadIdx.x == 0) tile_s = limit - 1;
         __syncthreads();  // (and the normalisers of this workgroup's rows are complete)
+        share = fminf(share_s[0], share_s[1]);
         float kmax = 0.0f;
-        if constexpr (PARTS) share = fminf(share_s[0], share_s[1]);
-        for (int t = cb * 4; t <= own_last; ++t) {
-            if constexpr (!PARTS) share = fminf(share, tiles[t].z);
-            kmax = fmaxf(kmax, a.ws_kn[(size_t)(u / a.G) * nt + t]);
-        }
+        for (int t = cb * 4; t <= own_last; ++t) kmax = fmaxf(kmax, kn[t]);
         for (int it = it_end - (int)threadIdx.x; it >= limit; it -= kPrefillThreads) {
-            float c = PARTS ? INFINITY : tiles[it].y;  // smallest normaliser of the tile's rows
-            if constexpr (PARTS) {
-                for (int r = 0; r < kTile; ++r)
-                    if (it * kTile + r < n) {
-                        const float v = call[(it - it_first) * kTile + r];
-                        c = fminf(c, not_above(GUMBEL ? lp.gz - v : v));
-                    }
-            }
+            float c = INFINITY;  // smallest normaliser of the tile's rows
+            for (int r = 0; r < kTile; ++r)
+                if (it * kTile + r < n) {
+                    const float v = call[(it - it_first) * kTile + r];
+                    c = fminf(c, not_above(GUMBEL ? lp.gz - v : v));
+                }
             const float bias = lp.slope1 * (float)(it * kTile - (cb * (4 * kTile) + 4 * kTile - 1));
             if (!(tiles[it].x * kmax * fabsf(lp.sc1) + reach - bias - c < share)) {
                 atomicMax(&tile_s, it);
@@ -673,14 +706,17 @@ __global__ void __launch_bounds__(kPrefillThreads, (kPrefillMinWaves<T, D>)) pre
     // The query tiles are walked from the LAST one down: every column block of a unit then starts at the same
     // tile and the blocks, which run at the same time on one XCD, ask its L2 for the same rows at about the
     // same time (walking up, each block starts at its own diagonal and the L2 sees 16 unrelated streams:
-    // 2.7 GB instead of 1.0 GB fetched on the GPT-J-shaped workload).
-    Staged stage = fetch(max(it_end, it_first));
+    // 2.7 GB instead of 1.0 GB fetched on the GPT-J-shaped workload).  With a position bias the far end may not matter, and
+    // the walk goes up from the diagonal.
+    constexpr bool UP = BIAS && !PARTS;
+    const int looks_at = UP && skips && it_end > it_first + 3 + kSkipAhead ? it_first + 3 + kSkipAhead : -1;
+    Staged stage = fetch(UP ? it_first : max(it_end, it_first));
     park(0, stage);
     __syncthreads();
-    for (int it = it_end; it >= it_first; --it) {
-        const int cur = (it_end - it) & 1;
-        // the next tile (the first one again at the end: rows stay in range), in flight during this tile's work
-        stage = fetch(max(it - 1, it_first));
+    for (int it = UP ? it_first : it_end, cur = 0; UP ? it <= it_end : it >= it_first; it += UP ? 1 : -1, cur ^= 1) {
+        // the next tile (the last one again at the end: rows stay in range), in flight during this tile's work
+        const int it_next = UP ? min(it + 1, it_end) : max(it - 1, it_first);
+        stage = fetch(it_next);
         if (active && it >= it_begin) {
             const char* qb = qbuf[cur];
             const f32x16 acc = Stage::products(qb, n0, half, bk);
@@ -688,16 +724,42 @@ __global__ void __launch_bounds__(kPrefillThreads, (kPrefillMinWaves<T, D>)) pre
             const float* cs = PARTS ? call + (it - it_first) * kTile : cbuf[cur];
             const uint32_t* rs = PARTS ? rall + (it - it_first) * kTile : rbuf[cur];
             const bool edge = (ib < j0 + kTile) || (ib + kTile > n);  // crosses the diagonal or the end of the prompt
+            float add;
             if (edge) {
                 int first = ib + half * 4;  // (the empty asm keeps the masking compares inside this branch, as in pass 1)
                 asm volatile("" : "+v"(first));
-                colsum += column_sum<GUMBEL, BIAS, TAU1, true>(lp, acc, cs, rs, first, half, j, kfold, n);
+                add = column_sum<GUMBEL, BIAS, TAU1, true>(lp, acc, cs, rs, first, half, j, kfold, n);
             } else {
-                colsum += column_sum<GUMBEL, BIAS, TAU1, false>(lp, acc, cs, rs, ib + half * 4, half, j, kfold, n);
+                add = column_sum<GUMBEL, BIAS, TAU1, false>(lp, acc, cs, rs, ib + half * 4, half, j, kfold, n);
             }
+            if (UP) add -= lost;
+            const float sum = colsum + add;
+            if (UP) lost = fabsf(sum) < INFINITY ? (sum - colsum) - add : 0.0f;
+            colsum = sum;
         }
-        if (it > it_first) park(cur ^ 1, stage);
+        if (it != it_next) park(cur ^ 1, stage);
+        const bool looks = UP && it == looks_at;  // workgroup-uniform
+        if (looks) {
+            const float sum = colsum + __shfl_xor(colsum, 32, kWave);
+            const float least = wave_min(j < n ? not_above(hw_log2(sum)) : INFINITY);
+            if (lane == 0) wstat[wv] = make_float2(active ? kn[j0 / kTile] : 0.0f, least);
+        }
         __syncthreads();
+        if (looks) {
+            const float most = largest_adjustment(a.noise) * a.inv_tau + kSkipTileBits;
+            it_end -= __builtin_amdgcn_readfirstlane(tiles_ruled_out(it_end - it, [&](int x) {
+                const int jt = it_end - x;
+                const float4 rows = tiles[jt];
+                float e = 0.0f;
+                for (int v = 0; v < kPrefillThreads / kWave; ++v) {
+                    const int first = cb * (4 * kTile) + v * kTile;  // the wave's first column
+                    if (first >= n) break;
+                    const float bias = lp.slope1 * (float)(jt * kTile - (first + kTile - 1));
+                    e += hw_exp2(rows.x * wstat[v].x * fabsf(lp.sc1) + most - bias - rows.y - wstat[v].y);
+                }
+                return e;
+            }));
+        }
     }
     if (!active) return;
     colsum += __shfl_xor(colsum, 32, kWave);

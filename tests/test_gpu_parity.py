@@ -1593,7 +1593,8 @@ def test_prompt_whose_logits_are_evaluated_once_matches_oracle(dtype, d, G, B, H
     (8, 8, 1, 1025, ko.BF16, 64, ko.NOISE_GUMBEL, 1.0, 4.0), (2, 16, 1, 2305, ko.F16, 128, ko.NOISE_GAUSSIAN, 1.0, 1.0),
     (16, 16, 1, 1025, ko.BF16, 128, ko.NOISE_GUMBEL, 1.0, 1.0), (3, 40, 2, 1200, ko.BF16, 64, ko.NOISE_NONE, 0.7, 2.0),
     (32, 8, 1, 1100, ko.F32, 64, ko.NOISE_GUMBEL, 1.5, 1.0), (4, 1, 4, 4200, ko.BF16, 256, ko.NOISE_CONSTANT, 1.0, 1.0),
-    (2, 20, 1, 2100, ko.BF16, 128, ko.NOISE_GUMBEL, 1.0, 2.0), (1, 32, 1, 2177, ko.F16, 64, ko.NOISE_GUMBEL, 1.5, 1.0)])
+    (2, 20, 1, 2100, ko.BF16, 128, ko.NOISE_GUMBEL, 1.0, 2.0), (1, 32, 1, 2177, ko.F16, 64, ko.NOISE_GUMBEL, 1.5, 1.0),
+    (4, 32, 1, 2177, ko.BF16, 64, ko.NOISE_GUMBEL, 1.0, 1.0), (3, 24, 2, 2080, ko.F16, 64, ko.NOISE_GUMBEL, 1.5, 4.0)])
 def test_tiles_ruled_out_by_the_position_bias_change_nothing(B, H, G, n, dtype, d, noise, tau, steep):
     """A workspace with room for the tiles' bounds against the smallest that is accepted, whose walks take every tile; whole
     walks and walks in parts; prompts of different lengths; slopes from steep to flat, zero, negative and NaN; large keys, an
