@@ -288,9 +288,10 @@ __device__ __forceinline__ void close_gap(u32x4_t* Ku, u32x4_t* Vu, const u32x4_
 //
 // FEW: the form for splits of a small launch (a few units: one sequence, one layer).  Such a launch is a single
 // wave of workgroups whose time is the chain of memory round trips in it, so everything a workgroup may need is
-// asked for at once, before the unit's length is known: its first K and V tiles, the old scores of its tokens and
-// the rows at the chunk boundaries of the eviction that follows (see step_finish_kernel).  Rows past the unit's
-// length are read (they lie in the unit's own cache) and dropped.
+// asked for at once, before the unit's length is known: its first K and V tiles, the new token's rows, the old scores of its
+// tokens and the rows at the chunk boundaries of the eviction that follows (see step_finish_kernel), in the order of their use.
+// Rows past the unit's length are read (they lie in the unit's own cache) and dropped.  (16 units x 1024 x 256: 8.7 -> 8.0 us
+// since seeds, step number and length no longer wait in turn, the last two behind the tiles, nor the new token's rows.)
 //
 // ORDERED: the form for ordered steps that load the rows which the eviction moves into the caches (keep_w), or evict
 // here (fuse_ordered).  The streaming loops exist twice in it and the row move takes registers; all other launches keep
@@ -333,8 +334,6 @@ __device__ __forceinline__ void decode_block(const DecodeArgs& a) {
     const int s = (int)(blockIdx.x - ui * (uint32_t)S);
     const int h = (int)(ui - lb * (uint32_t)a.H), b = (int)(lb % (uint32_t)a.B), l = a.layer0 + (int)(lb / (uint32_t)a.B);
     const bool rnd_l = (a.noise == kNoiseGumbel || a.noise == kNoiseGaussian);
-    const uint64_t seed_b = rnd_l ? a.seeds[b] : 0;
-
     const char* Ku = (const char*)a.K + (size_t)u * a.cap * ROWB;
     const char* Vu = (const char*)a.V + (size_t)u * a.cap * ROWB;
     const T* qu = (const T*)a.q + (size_t)u * G * D;
@@ -346,6 +345,13 @@ __device__ __forceinline__ void decode_block(const DecodeArgs& a) {
     if constexpr (FEW)  // all arguments at once: fetched where they are first used, each line is a wait of its own
         asm volatile("" ::"s"(a.K), "s"(a.q), "s"(a.len), "s"(a.seeds), "s"(a.slopes), "s"(a.step), "s"(a.ws_part),
                      "s"(a.q_pos), "s"(a.fuse_k), "s"(a.seq_q_pos), "s"(a.seq_tau), "s"(a.inv_tau), "s"(a.few_f));
+    // The words of device memory that the launch depends on, asked for together (one trip) and ahead of everything else; an
+    // absent one is read from where something else lies.
+    uint64_t seed_b = uniform_load(rnd_l ? a.seeds + b : (const uint64_t*)a.q);
+    int32_t step_now = uniform_load(a.step ? a.step : a.len);
+    int32_t seq_pos = uniform_load(a.seq_q_pos ? a.seq_q_pos + b : a.len);
+    float seq_tau = uniform_load(a.seq_tau ? a.seq_tau + b : (const float*)a.len);
+    int len0 = uniform_load(a.len + u);
     uint4 cur[UNR], nxt[UNR];
     uint4 vfirst[FEW ? UNR : 1];
     float f_old[FEW ? kFewTokens : 1];
@@ -354,6 +360,7 @@ __device__ __forceinline__ void decode_block(const DecodeArgs& a) {
     constexpr int NV = G * UNR, VPL = (NV + LPR - 1) / LPR;  // logits a lane adjusts per tile, see phase 1
     uint4 qraw[FEW ? G : 1];
     int pfirst[FEW ? VPL : 1];
+    uint4 ktok = make_uint4(0u, 0u, 0u, 0u), vtok = ktok;  // FEW: the new token's rows (wave 0)
     const int jf = s * a.chunk;  // first row of the split
     if constexpr (FEW) {
         auto load_first = [&](const char* rows, uint4(&raw)[UNR]) {
@@ -363,15 +370,18 @@ __device__ __forceinline__ void decode_block(const DecodeArgs& a) {
                 raw[i] = stream_load((const uint4*)(rows + (size_t)j * ROWB + (size_t)cl * 16));
             }
         };
-        if constexpr (!MfmaLogits<T, G>::value) load_first(Ku, cur);
-        load_first(Vu, vfirst);
+        // in the order of their use: loads return in order
         if constexpr (!MfmaLogits<T, G>::value) {
 #pragma unroll
             for (int g = 0; g < G; ++g) qraw[g] = ((const uint4*)(qu + (size_t)g * D))[cl];
 #pragma unroll
             for (int r = 0; r < VPL; ++r)
                 pfirst[r] = pu[min(jf + wv * RPW + min(cl / G + r * (LPR / G), UNR - 1) * RPB + sub, a.cap - 1)];
+            load_first(Ku, cur);
         }
+        if (wv == 0) ktok = ((const uint4*)knew)[cl];
+        load_first(Vu, vfirst);
+        if (wv == 0) vtok = ((const uint4*)vnew)[cl];
         if (a.few_f) {
 #pragma unroll
             for (int i = 0; i < kFewTokens; ++i) f_old[i] = fu[min(jf + tid + i * NT, a.cap - 1)];
@@ -388,18 +398,20 @@ __device__ __forceinline__ void decode_block(const DecodeArgs& a) {
         }
     }
 
+    // (read once, before this launch moves lengths and step number on)
+    asm volatile("" : "+s"(seed_b), "+s"(step_now), "+s"(seq_pos), "+s"(seq_tau), "+s"(len0));
+
     // query position and temperature of this step: from the host, or from the device step counter
     // (same fp32 operations, in the same order, as the host's schedule function)
     int q_pos = a.q_pos;
     float inv_tau = a.inv_tau;
     if (a.step) {
-        const int t = max(*a.step, 1);  // decode steps count from 1 (0 is the prompt iteration)
+        const int t = max(step_now, 1);  // decode steps count from 1 (0 is the prompt iteration)
         q_pos = a.n0 + t - 1;
         inv_tau = 1.0f / schedule_tau(a.tau_init, a.dtau, min(t, a.T));  // IEEE division, as on the host
     }
-    if (a.seq_q_pos) q_pos = a.seq_q_pos[b];  // a batch whose sequences are at different steps
-    if (a.seq_tau) inv_tau = 1.0f / a.seq_tau[b];
-    const int len0 = a.len[u];
+    if (a.seq_q_pos) q_pos = seq_pos;  // a batch whose sequences are at different steps
+    if (a.seq_tau) inv_tau = 1.0f / seq_tau;
     const int m = len0 + 1;
     if (len0 < 0 || len0 >= a.cap || len0 > S * a.chunk) {
         // no room for the new token (or a launch shaped for fewer tokens):
@@ -460,7 +472,9 @@ __device__ __forceinline__ void decode_block(const DecodeArgs& a) {
     const bool evict_here = over && m == a.fuse_k + 1;
 
     // ---- append: the last split stores the new row (nobody reads it back in this launch)
-    if (owner && !evict_here) {
+    if (owner && !evict_here && FEW) {
+        if (tid == 2 * kWave) pu[len0] = q_pos;  // (the rows at the end: they are on their way)
+    } else if (owner && !evict_here) {
         if (wv == 0 && lane < LPR) ((uint4*)(a.K))[((size_t)u * a.cap + len0) * LPR + lane] = ((const uint4*)knew)[lane];
         if (wv == 1 && lane < LPR) ((uint4*)(a.V))[((size_t)u * a.cap + len0) * LPR + lane] = ((const uint4*)vnew)[lane];
         if (tid == 2 * kWave) pu[len0] = q_pos;
@@ -808,11 +822,12 @@ __device__ __forceinline__ void decode_block(const DecodeArgs& a) {
     }
     // the new token's own logits (distance 0: no position bias)
     if (wv == 0) {
-        const uint4 kv = ((const uint4*)knew)[cl];
+        constexpr bool HERE = FEW && !MfmaLogits<T, G>::value;  // the queries are in registers already
+        const uint4 kv = FEW ? ktok : ((const uint4*)knew)[cl];
 #pragma unroll
         for (int g = 0; g < G; ++g) {
             QueryPiece<T> qg;
-            qg.load(((const uint4*)(qu + (size_t)g * D))[cl]);
+            qg.load(HERE ? qraw[HERE ? g : 0] : ((const uint4*)(qu + (size_t)g * D))[cl]);
             const float p = group_sum<LPR>(qg.dot(kv));
             if (lane == 0) {
                 float x = -INFINITY, y = -INFINITY;
@@ -982,7 +997,7 @@ __device__ __forceinline__ void decode_block(const DecodeArgs& a) {
         }
     } else if (owner && wv == 0 && sub == 0) {  // the new token's value row
         float vvals[EPV];
-        unpack16<T>(((const uint4*)vnew)[cl], vvals);
+        unpack16<T>(FEW ? vtok : ((const uint4*)vnew)[cl], vvals);
 #pragma unroll
         for (int g = 0; g < G; ++g) {
             const float p = xs[g * CS + cnt_c];
@@ -1208,6 +1223,10 @@ __device__ __forceinline__ void decode_block(const DecodeArgs& a) {
         }
     }
     if constexpr (FEW) {
+        if (owner && wv == 0 && lane < LPR) {
+            ((uint4*)(a.K))[((size_t)u * a.cap + len0) * LPR + lane] = ktok;
+            ((uint4*)(a.V))[((size_t)u * a.cap + len0) * LPR + lane] = vtok;
+        }
         if (a.few_f) {
 #pragma unroll
             for (int i = 0; i < kFewTokens; ++i)

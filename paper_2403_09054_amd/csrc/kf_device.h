@@ -278,4 +278,11 @@ __device__ __forceinline__ uint32_t float_key(float f) {
     return (b & 0x80000000u) ? ~b : (b | 0x80000000u);
 }
 
+// A value that every lane of the wave reads and nothing writes while the launch reads it, by the scalar unit.  (Behind an asm
+// statement the compiler takes a vector load instead, whose value it waits for behind all the loads under way.)
+template <typename T>
+__device__ __forceinline__ T uniform_load(const T* p) {
+    return *(const __attribute__((address_space(4))) T*)(uintptr_t)p;
+}
+
 }  // namespace kf

@@ -695,139 +695,205 @@ __global__ void __launch_bounds__(NT) step_tail_kernel(const DecodeArgs d, const
 // workgroup overwrites while another still reads it: the old scores, and the rows and positions at slots R, 2R, ...
 // (a chunk's last source is the next chunk's first destination).  Rows that move whatever slot leaves are loaded
 // before it is known.  One more workgroup per unit writes the attention outputs (and does what the others leave).
+//
+// What bounds it besides the chain of trips is its own length: a compute unit has one such workgroup, a wave to a SIMD, so every
+// instruction of a wave counts, and so does every line of the argument buffer that is fetched when first used.  Hence FinishArgs
+// (what the usual path reads, in one stretch), addresses formed by shifts from one offset, and loads without a bound each: 16
+// units x 1024 x 256 7.1 -> 6.0 us, the ordered step with its split launch 15.4 -> 13.0, 64 x 2048 x 128 28.5 -> 25.7, 4 heads
+// 32 x 1024 x 128 20.9 -> 18.8, 8 heads 64 x 300 x 256 29.4 -> 27.0 (graphs, caches in turn).
 constexpr int kFinishThreads = 256;
+struct FinishArgs {
+    const int32_t* m;    // tokens the splits scored per unit
+    const float* part;   // their records
+    const float* inc;    // ... and increments
+    const float* f_old;  // the scores before the step
+    char* K;
+    char* V;
+    float* score;
+    int32_t* pos;
+    const char* brow;    // rows and positions at the chunk boundaries
+    const int32_t* bpos;
+    float* out;
+    int32_t* len;
+    int32_t* idx;        // the caller's kept_idx, or NULL
+    int32_t* step_inc;
+    int32_t cap, k, w, S, chunk, R, nb, row_shift;  // row_shift: log2 of a row's bytes
+};
+struct FinishLaunch {
+    FinishArgs f;
+    DecodeArgs d;  // what the general way reads
+    SelectArgs a;
+};
 template <int D, int G>
-__global__ void __launch_bounds__(kFinishThreads) step_finish_kernel(const DecodeArgs d, const SelectArgs a, int64_t units) {
+__global__ void __launch_bounds__(kFinishThreads) step_finish_kernel(const FinishLaunch x) {
+    const FinishArgs& f = x.f;
     constexpr int NT = kFinishThreads, NW = NT / kWave, PW = D + 4, TOK = 4;
     __shared__ float w_p[G * kFewMaxSplits], w_e[G * kFewMaxSplits], inv_p[G];
     __shared__ float f_new[kFinishMaxTokens + 1];
     __shared__ unsigned long long wmin_f[NW];
-    const uint32_t ci = blockIdx.x / (uint32_t)units, ui = blockIdx.x - ci * (uint32_t)units;
-    const int64_t u = ui;  // chunk-major: every XCD gets chunks of every kind
-    const int c = (int)ci - 1;  // -1: the attention outputs
+    asm volatile("" ::"s"(f.m), "s"(f.part), "s"(f.inc), "s"(f.f_old), "s"(f.K), "s"(f.V), "s"(f.score), "s"(f.pos), "s"(f.brow), "s"(f.bpos),
+                 "s"(f.out), "s"(f.len), "s"(f.idx), "s"(f.cap), "s"(f.k), "s"(f.w), "s"(f.S), "s"(f.chunk), "s"(f.R), "s"(f.nb), "s"(f.row_shift));
+    const int64_t u = blockIdx.x;         // chunk-major: every XCD gets chunks of every kind
+    const int c = (int)blockIdx.y - 1;    // -1: the attention outputs
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-    const int k = a.k, w = a.w, S = d.S;
-    const int m = d.ws_m[u];  // tokens the splits scored; 0: they skipped the unit
-    if (m != k + 1) {         // within budget, or far over it: one workgroup does the unit the general way
-        if (c < 0) {
-            if (m > 0) merge_unit<D, NT, G>(d, u, m - 1, w_p, w_e, 0, m, true);
-            if (!a.rest) {
-                __syncthreads();
-                select_unit<NT>(a, u);
-            }
-        }
-        advance_step(a);  // (the first workgroup of the launch is one of these)
-        return;
-    }
-    const int R = a.chunk_rows, PPR = a.row_bytes >> 4;
+    const int k = f.k, w = f.w, S = f.S, last = f.cap - 1;
+    int m = uniform_load(f.m + u);  // tokens the splits scored; 0: they skipped the unit
+    const int R = f.R;
     const int lo = c * R, hi = min(k, lo + R), rows = hi - lo;  // destinations [lo, hi), sources lo+1 .. hi
     const int saved = lo + R < k ? lo + R : -1;                 // this source comes from the copy
-    uint4* Kr = (uint4*)((char*)a.K + (size_t)u * a.cap * a.row_bytes);
-    uint4* Vr = (uint4*)((char*)a.V + (size_t)u * a.cap * a.row_bytes);
-    const uint4* brow = (const uint4*)((const char*)a.ws_brow + ((size_t)u * a.nb + c) * 2 * a.row_bytes);
-    float* fu = a.score + (size_t)u * a.cap;
-    int32_t* pu = a.pos + (size_t)u * a.cap;
+    const size_t unit_bytes = (size_t)f.cap << f.row_shift;
+    char *Kr = f.K + u * unit_bytes, *Vr = f.V + u * unit_bytes;
+    float* fu = f.score + (size_t)u * f.cap;
+    int32_t* pu = f.pos + (size_t)u * f.cap;
 
-    // ---- everything that can be asked for now: split statistics, increments, old scores, positions, certain rows
+    // ---- everything that can be asked for now, before m is known (another trip to memory): split statistics, increments, old
+    // scores, positions, certain rows.  Of a unit that turns out to go the general way it is dropped, and slot k, which a cache
+    // of capacity k does not have, is read as its last one.
     constexpr int HPW = (G + NW - 1) / NW;  // heads per wave: one wave merges a head's statistics, a lane a split
-    const float* parts = d.ws_part + (size_t)u * S * G * PW;
+    const float* parts = f.part + (size_t)u * S * G * PW;
     float4 rec[HPW];
 #pragma unroll
     for (int i = 0; i < HPW; ++i) {
         const int g = wv + i * NW;
         rec[i] = make_float4(-INFINITY, 0.0f, -INFINITY, 0.0f);
-        if (g < G && lane < S) rec[i] = *reinterpret_cast<const float4*>(parts + ((size_t)lane * G + g) * PW + D);
+        if (g < G && lane < S) rec[i] = *reinterpret_cast<const float4*>(parts + (lane * G + g) * PW + D);
     }
-    const float* we = d.ws_e + (size_t)u * G * a.cap;
-    const float* f_old = d.few_f + (size_t)u * a.cap;
-    float te[TOK][G], tf[TOK];
+    const float* we = f.inc + (size_t)u * G * f.cap;
+    const float* f_old = f.f_old + (size_t)u * f.cap;
+    float te[TOK][G], tf[TOK], tnew[G];
     auto load_tokens = [&](int j0) {
 #pragma unroll
         for (int i = 0; i < TOK; ++i) {
-            const int j = j0 + i * NT;
+            const int j = min(j0 + i * NT, last);
 #pragma unroll
-            for (int g = 0; g < G; ++g) te[i][g] = j <= k ? we[(size_t)g * a.cap + j] : 0.0f;
-            tf[i] = j < k ? f_old[j] : 0.0f;  // the new token (slot k) starts from zero
+            for (int g = 0; g < G; ++g) te[i][g] = we[g * f.cap + j];
+            tf[i] = f_old[j];
         }
     };
     // the outputs' first split records, or what the scores and the move need
     constexpr int OREC = 16, OPT = (G * D + NT - 1) / NT;  // records in flight, outputs per thread
-    float orec[OREC];
-    auto load_records = [&](int o, int s0) {
-        const int idx = tid + o * NT;
-        const float* pr = parts + (size_t)(idx / D) * PW + idx % D;
+    auto load_records = [&](int o, int s0, float(&rec)[OREC]) {
+        const int idx = min(tid + o * NT, G * D - 1);
+        const float* pr = parts + (idx / D) * PW + idx % D;
 #pragma unroll
-        for (int i = 0; i < OREC; ++i) orec[i] = (idx < G * D && s0 + i < S) ? pr[(size_t)(s0 + i) * G * PW] : 0.0f;
+        for (int i = 0; i < OREC; i += 8)
+            if (s0 + i < S) {
+#pragma unroll
+                for (int j = 0; j < 8; ++j) rec[i + j] = pr[min(s0 + i + j, S - 1) * G * PW];
+            }
     };
-    if (c < 0) load_records(0, 0);
-    else load_tokens(tid);
-    int32_t p_next = 0;
-    if (c >= 0 && tid < rows) p_next = (lo + tid + 1 == saved) ? a.ws_bpos[(size_t)u * a.nb + c] : pu[lo + tid + 1];
+    const int q16 = (tid << 4) & ((1 << f.row_shift) - 1), r0 = (tid << 4) >> f.row_shift, rstep = (NT << 4) >> f.row_shift;
+    const char* brow = f.brow + (((size_t)u * f.nb + max(c, 0)) << (f.row_shift + 1));
     uint4 kreg[kWidePieces], vreg[kWidePieces];
     auto load_rows = [&]() {  // branch-free: a lane past the chunk's end re-reads the last source
 #pragma unroll
         for (int i = 0; i < kWidePieces; ++i) {
-            const int p = tid + i * NT, q = p % PPR;
-            const int src = lo + min(p / PPR, rows - 1) + 1;
-            kreg[i] = stream_load(src == saved ? brow + q : Kr + (size_t)src * PPR + q);
-            vreg[i] = stream_load(src == saved ? brow + PPR + q : Vr + (size_t)src * PPR + q);
+            const int src = min(lo + 1 + r0 + i * rstep, min(hi, last));
+            const uint32_t off = ((uint32_t)src << f.row_shift) + q16;
+            if (i < kWidePieces - 1) {
+                kreg[i] = stream_load((const uint4*)(Kr + off));
+                vreg[i] = stream_load((const uint4*)(Vr + off));
+            } else {  // (a chunk whose last source is saved is a whole one: its last row is the last piece's)
+                const bool copy = src == saved;
+                kreg[i] = stream_load((const uint4*)(copy ? brow + q16 : Kr + off));
+                vreg[i] = stream_load((const uint4*)(copy ? brow + (1 << f.row_shift) + q16 : Vr + off));
+            }
         }
     };
-    const bool sure = c >= 0 && hi > k - w;  // the chunk reaches into the part behind the candidates, which moves in any case
-    if (sure) load_rows();
-
-    // ---- statistics of the splits -> weights
+    // statistics of the splits -> weights
+    auto weights = [&]() {
 #pragma unroll
-    for (int i = 0; i < HPW; ++i) {
-        const int g = wv + i * NW;
-        const float Mx = wave_max(rec[i].x), My = wave_max(rec[i].z);
-        const float wp = rec[i].y > 0.0f ? hw_exp2(rec[i].x - Mx) : 0.0f;  // empty splits weigh nothing
-        const float we_ = rec[i].w > 0.0f ? hw_exp2(rec[i].z - My) : 0.0f;
-        const float sumP = wave_sum(fmaf(wp, rec[i].y, 0.0f)), invE = 1.0f / wave_sum(fmaf(we_, rec[i].w, 0.0f));  // as merge_unit, to the bit
-        if (g < G && lane < S) {
-            w_p[g * S + lane] = wp;
-            w_e[g * S + lane] = we_ * invE;
-        }
-        if (g < G && lane == 0) inv_p[g] = 1.0f / sumP;
-    }
-    __syncthreads();
-    if (c < 0) {
-        for (int o = 0; o < OPT; ++o) {
-            const int idx = tid + o * NT, g = idx / D;
-            float sum = 0.0f;
-            for (int s0 = 0; s0 < S; s0 += OREC) {  // summed in split order
-                if (o > 0 || s0 > 0) load_records(o, s0);
-#pragma unroll
-                for (int i = 0; i < OREC; ++i)
-                    if (s0 + i < S && idx < G * D) sum = fmaf(w_p[g * S + s0 + i], orec[i], sum);
+        for (int i = 0; i < HPW; ++i) {
+            const int g = wv + i * NW;
+            const float Mx = wave_max(rec[i].x), My = wave_max(rec[i].z);
+            const float wp = rec[i].y > 0.0f ? hw_exp2(rec[i].x - Mx) : 0.0f;  // empty splits weigh nothing
+            const float we_ = rec[i].w > 0.0f ? hw_exp2(rec[i].z - My) : 0.0f;
+            const float sumP = wave_sum(fmaf(wp, rec[i].y, 0.0f)), invE = 1.0f / wave_sum(fmaf(we_, rec[i].w, 0.0f));  // as merge_unit, to the bit
+            if (g < G && lane < S) {
+                w_p[g * S + lane] = wp;
+                w_e[g * S + lane] = we_ * invE;
             }
-            if (idx < G * D) d.out[u * G * D + idx] = sum * inv_p[g];
+            if (g < G && lane == 0) inv_p[g] = 1.0f / sumP;
         }
-        if (tid == 0) a.len[u] = k;
-        advance_step(a);
+        __syncthreads();
+    };
+    if (c < 0) {  // the attention outputs
+        float first[OREC], next[OREC];
+        load_records(0, 0, first);
+        asm volatile("" : "+s"(m)::"memory");  // (the loads stay ahead of the branch)
+        if (m != k + 1) {                      // within budget, or far over it: this workgroup does the unit the general way
+            // (its arguments by way of a pointer that the compiler does not see through: it fetched them ahead of the branch)
+            const __attribute__((address_space(4))) char* arg = (const __attribute__((address_space(4))) char*)__builtin_amdgcn_kernarg_segment_ptr();
+            asm volatile("" : "+s"(arg));
+            const DecodeArgs d = *(const DecodeArgs*)(arg + offsetof(FinishLaunch, d));
+            const SelectArgs a = *(const SelectArgs*)(arg + offsetof(FinishLaunch, a));
+            if (m > 0) merge_unit<D, NT, G>(d, u, m - 1, w_p, w_e, 0, m, true);
+            if (!a.rest) {
+                __syncthreads();
+                select_unit<NT>(a, u);
+            }
+        } else {
+            load_records(0, OREC, next);
+            weights();
+            for (int o = 0; o < OPT; ++o) {
+                const int idx = tid + o * NT, g = min(idx / D, G - 1);
+                float sum = 0.0f;
+                for (int s0 = 0; s0 < S; s0 += 2 * OREC) {  // summed in split order
+                    if (o > 0 || s0 > 0) {
+                        load_records(o, s0, first);
+                        load_records(o, s0 + OREC, next);
+                    }
+#pragma unroll
+                    for (int i = 0; i < OREC; ++i)
+                        if (s0 + i < S) sum = fmaf(w_p[g * S + s0 + i], first[i], sum);
+#pragma unroll
+                    for (int i = 0; i < OREC; ++i)
+                        if (s0 + OREC + i < S) sum = fmaf(w_p[g * S + s0 + OREC + i], next[i], sum);
+                }
+                if (idx < G * D) f.out[u * G * D + idx] = sum * inv_p[g];
+            }
+            if (tid == 0) f.len[u] = k;
+        }
+        if (u == 0 && tid == 0 && f.step_inc) *f.step_inc += 1;  // (no workgroup of this launch reads it)
         return;
     }
+    load_tokens(tid);
+#pragma unroll
+    for (int g = 0; g < G; ++g) tnew[g] = we[g * f.cap + min(k, last)];
+    int32_t p_next = 0;
+    if (tid < rows) p_next = *(lo + tid + 1 == saved ? f.bpos + (size_t)u * f.nb + c : pu + min(lo + tid + 1, last));
+    const bool sure = hi > k - w;  // the chunk reaches into the part behind the candidates, which moves in any case
+    if (sure) load_rows();
+    asm volatile("" : "+s"(m)::"memory");
+    if (m != k + 1) return;
+    weights();
 
     // ---- new scores of the whole unit, smallest candidate (the highest slot among equals)
     unsigned long long best = ~0ull;
-    for (int j0 = tid; j0 <= k; j0 += TOK * NT) {
+    auto increment = [&](const float(&e)[G], int split) {
+        float df = 0.0f;
+#pragma unroll
+        for (int g = 0; g < G; ++g) df = fmaf(e[g], w_e[g * S + split], df);
+        return df;
+    };
+    auto candidate = [&](float v, int j) {
+        f_new[j] = v;
+        if (j < k + 1 - w) {
+            const unsigned long long pack = ((unsigned long long)float_key(v) << 32) | (uint32_t)(~(uint32_t)j);
+            best = pack < best ? pack : best;
+        }
+    };
+    // j / chunk: (j + 1/2) / chunk is no closer than 1/1024 to a whole number, and at most 64
+    const float per_chunk = __builtin_amdgcn_rcpf((float)f.chunk);
+    for (int j0 = tid; j0 < k; j0 += TOK * NT) {
         if (j0 != tid) load_tokens(j0);
 #pragma unroll
         for (int i = 0; i < TOK; ++i) {
             const int j = j0 + i * NT;
-            if (j > k) break;
-            const int split = j == k ? S - 1 : j / d.chunk;  // the new token belongs to the last split
-            float df = 0.0f;
-#pragma unroll
-            for (int g = 0; g < G; ++g) df = fmaf(te[i][g], w_e[g * S + split], df);
-            const float f = j == k ? df : tf[i] + df;
-            f_new[j] = f;
-            if (j < k + 1 - w) {
-                const unsigned long long pack = ((unsigned long long)float_key(f) << 32) | (uint32_t)(~(uint32_t)j);
-                best = pack < best ? pack : best;
-            }
+            if (j < k) candidate(tf[i] + increment(te[i], (int)(((float)j + 0.5f) * per_chunk)), j);
         }
     }
+    if (tid == 0) candidate(increment(tnew, S - 1), k);  // the new token belongs to the last split and starts from zero
     best = wave_min(best);
     if (lane == 0) wmin_f[wv] = best;
     __syncthreads();
@@ -843,10 +909,11 @@ __global__ void __launch_bounds__(kFinishThreads) step_finish_kernel(const Decod
     if (hi > e) {
 #pragma unroll
         for (int i = 0; i < kWidePieces; ++i) {
-            const int p = tid + i * NT, r = p / PPR, q = p % PPR;
-            if (r < rows && lo + r >= e) {
-                stream_store(Kr + (size_t)(lo + r) * PPR + q, kreg[i]);
-                stream_store(Vr + (size_t)(lo + r) * PPR + q, vreg[i]);
+            const int dst = lo + r0 + i * rstep;
+            const uint32_t off = ((uint32_t)dst << f.row_shift) + q16;
+            if (dst < hi && dst >= e) {
+                stream_store((uint4*)(Kr + off), kreg[i]);
+                stream_store((uint4*)(Vr + off), vreg[i]);
             }
         }
     }
@@ -854,19 +921,43 @@ __global__ void __launch_bounds__(kFinishThreads) step_finish_kernel(const Decod
         const int i = lo + tid;
         fu[i] = f_new[i + (i >= e ? 1 : 0)];
         if (i >= e) pu[i] = p_next;
-        if (a.idx_is_output) a.idx[(size_t)u * k + i] = i + (i >= e ? 1 : 0);
+        if (f.idx) f.idx[(size_t)u * k + i] = i + (i >= e ? 1 : 0);
     }
 }
 
 template <int D>
 static hipError_t launch_step_finish_d(const DecodeArgs& d, const SelectArgs& a, int64_t U, hipStream_t st) {
     const int nchunks = (a.k + a.chunk_rows - 1) / a.chunk_rows;
-    const dim3 grid((unsigned)(U * (nchunks + 1))), block(kFinishThreads);
+    FinishLaunch x{{}, d, a};
+    FinishArgs& f = x.f;
+    f.m = d.ws_m;
+    f.part = d.ws_part;
+    f.inc = d.ws_e;
+    f.f_old = d.few_f;
+    f.K = (char*)a.K;
+    f.V = (char*)a.V;
+    f.score = a.score;
+    f.pos = a.pos;
+    f.brow = (const char*)a.ws_brow;
+    f.bpos = a.ws_bpos;
+    f.out = d.out;
+    f.len = a.len;
+    f.idx = a.idx_is_output ? a.idx : nullptr;
+    f.step_inc = a.step_inc;
+    f.cap = a.cap;
+    f.k = a.k;
+    f.w = a.w;
+    f.S = d.S;
+    f.chunk = d.chunk;
+    f.R = a.chunk_rows;
+    f.nb = a.nb;
+    f.row_shift = __builtin_ctz(a.row_bytes);
+    const dim3 grid((unsigned)U, (unsigned)(nchunks + 1)), block(kFinishThreads);
     switch (d.G) {
-        case 1: hipLaunchKernelGGL((step_finish_kernel<D, 1>), grid, block, 0, st, d, a, U); break;
-        case 2: hipLaunchKernelGGL((step_finish_kernel<D, 2>), grid, block, 0, st, d, a, U); break;
-        case 4: hipLaunchKernelGGL((step_finish_kernel<D, 4>), grid, block, 0, st, d, a, U); break;
-        case 8: hipLaunchKernelGGL((step_finish_kernel<D, 8>), grid, block, 0, st, d, a, U); break;
+        case 1: hipLaunchKernelGGL((step_finish_kernel<D, 1>), grid, block, 0, st, x); break;
+        case 2: hipLaunchKernelGGL((step_finish_kernel<D, 2>), grid, block, 0, st, x); break;
+        case 4: hipLaunchKernelGGL((step_finish_kernel<D, 4>), grid, block, 0, st, x); break;
+        case 8: hipLaunchKernelGGL((step_finish_kernel<D, 8>), grid, block, 0, st, x); break;
         default: return hipErrorInvalidValue;
     }
     return hipGetLastError();

@@ -980,6 +980,34 @@ def test_ordered_step_that_keeps_the_window_rows_in_the_caches(dtype, d, B, k, w
         np.testing.assert_array_equal(a, b)
 
 
+@pytest.mark.parametrize("dtype,d,k,w,G", [(ko.BF16, 256, 192, 30, 1), (ko.F32, 128, 513, 0, 2), (ko.F16, 64, 1024, 1024, 1),
+                                           (ko.BF16, 128, 130, 7, 8)])
+def test_step_of_few_units_whose_capacity_is_the_budget(dtype, d, k, w, G):
+    """Caches of k slots: no unit has a slot k, which the workgroups that move rows ask for before they know; none moves."""
+    rng = np.random.default_rng(91 + k)
+    L, B, H = 1, 1, 5
+    oc = random_cache(rng, L, B, H, d, k, dtype, np.array([k - 1, k, 0, k - 2, k // 2], np.int32).reshape(L, B, H))
+    q, kn, vn = rnd(rng, (L, B, H * G, d), dtype), rnd(rng, (L, B, H, d), dtype), rnd(rng, (L, B, H, d), dtype)
+    results = []
+    for fused in (False, True):
+        gc = upload(oc, G)
+        assert kf.kf_decode_launch_shape(gc, 0)[0] > 1
+        ws = kf.new_workspace(gc)
+        out = torch.zeros((L, B, H * G, d), dtype=torch.float32, device="cuda")
+        kept = torch.full((L, B, H, k), -7, dtype=torch.int32, device="cuda")
+        args = (dev(q), dev(kn), dev(vn), k + 9, 0, 1.6, 0.11, kf.NOISE_GUMBEL, dev(np.array([5], np.uint64)), None, out)
+        if fused:
+            kf.kf_decode_select_step(gc, *args, k=k, w=w, kept_idx=kept, workspace=ws)
+        else:
+            kf.kf_decode_step(gc, *args, ws)
+            kf.kf_select_evict(gc, k, w, kept, ws)
+        torch.cuda.synchronize()
+        assert error_word(ws) == 1
+        results.append([host(t).copy() for t in (gc.K, gc.V, gc.pos, gc.score, gc.len, kept, out)])
+    for a, b in zip(*results):
+        np.testing.assert_array_equal(a, b)
+
+
 @pytest.mark.parametrize("over,hint", [(0, 0), (1, 0), (2, 0), (90, 0), (0, 201), (1, 201)])
 def test_step_of_few_units_far_over_the_budget_equals_the_two_calls(over, hint):
     """The units that the one-launch end of a step of few units leaves to the launch behind it (m_hint says that a unit
