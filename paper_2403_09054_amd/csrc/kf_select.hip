@@ -419,6 +419,13 @@ __device__ __forceinline__ void evict_find(const SelectArgs& a, int64_t u, int n
 // the next chunk's first destination, comes from the copy the first launch saved.
 constexpr int kWideThreads = 256;
 constexpr int kWidePieces = 2048 / kWideThreads;  // 16-byte pieces per thread and tensor
+// LDS that a workgroup asks for and does not use: two of them on a compute unit (128 KB of rows in flight) instead of the five that
+// its registers allow.  A workgroup first only reads and then only writes; with fewer of them the memory changes direction less
+// often.  Ordered steps, caches in turn, at five / three / two / one on a compute unit: 32 x 9830 x 128 61.0 / 59.7 / 58.9 / 62.0 us,
+// 256 x 1501 x 128 with 4 query heads 63.5 / 61.4 / 61.1 / 63.3, 256 x 2048 x 128 73.0 / 71.8 / 72.4 / 75.6, 100 x 3000 x 128
+// 54.2 / 53.7 / 52.6 / 54.1, 32 x 32000 x 128 162 / 162 / 160 / 169.  (Eviction into another cache, whose workgroups read
+// and write a few rows at a time, loses by it: 399 us, 417 with six on a compute unit, 444 with five.)
+constexpr int kShiftLds = 60 * 1024;
 __global__ void __launch_bounds__(kWideThreads) shift_chunk_kernel(const SelectArgs a, int nchunks, int64_t units) {
     // chunk-major: the chunks that have work are the same few of every unit (those behind the evicted slot),
     // and consecutive workgroup ids go round-robin to the 8 XCDs -- unit-major ids would park all the work on
@@ -1252,7 +1259,7 @@ hipError_t launch_select(const SelectArgs& a, int64_t U, hipStream_t stream) {
 // Second launch of the two-launch eviction: every chunk of rows behind the evicted slot moves down by one.
 hipError_t launch_shift(const SelectArgs& a, int64_t U, hipStream_t stream) {
     const int nchunks = (a.k + a.chunk_rows - 1) / a.chunk_rows;
-    hipLaunchKernelGGL(shift_chunk_kernel, dim3((unsigned)(U * nchunks)), dim3(kWideThreads), 0, stream, a, nchunks, U);
+    hipLaunchKernelGGL(shift_chunk_kernel, dim3((unsigned)(U * nchunks)), dim3(kWideThreads), kShiftLds, stream, a, nchunks, U);
     return hipGetLastError();
 }
 
