@@ -2518,3 +2518,21 @@ def test_gptj_slice_free_running_reports_first_divergence():
             first_div = t
     print("gptj slice free-running: first divergence step:", first_div, "of", steps)
     assert first_div is None or first_div > 16
+
+
+def test_calls_without_a_stream_go_to_the_current_one():
+    """The handle a call takes when none is given: the calling thread's current stream, also inside a stream's context."""
+    import threading
+
+    from paper_2403_09054_amd import binding
+    side = torch.cuda.Stream()
+    torch.zeros(1, device="cuda")
+    seen = []
+    with torch.cuda.stream(side):
+        assert binding._stream(None) == side.cuda_stream
+        other = threading.Thread(target=lambda: seen.append((binding._stream(None), torch.cuda.current_stream().cuda_stream)))
+        other.start()
+        other.join()
+    assert seen[0][0] == seen[0][1] != side.cuda_stream
+    assert binding._stream(None) == torch.cuda.current_stream().cuda_stream
+    assert binding._stream(side) == side.cuda_stream
