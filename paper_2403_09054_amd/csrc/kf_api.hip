@@ -58,7 +58,7 @@ bool keep_pays(int64_t U, int32_t k, int32_t w, int32_t row_bytes) {
 }
 // A step of at most this many units is bound by the chain of memory round trips through its launches, not by bytes:
 // its splits are short, ask for everything at once, and (ordered layout) one launch merges, selects and moves the
-// rows instead of two.  28 layers of 16 heads, d = 256, k = 1024, a call each: 686 -> 469 us per token.  One ordered
+// rows instead of two.  28 layers of 16 heads, d = 256, k = 1024, a call each: 686 -> 469 us per token, 387 later.  One ordered
 // step against the launches for more units, caches in turn: 1.04 to 1.5 times as fast at 227 of 228 shapes (32 heads x
 // 1024 x 128 1.21, 128 x 700 x 128 1.31, 64 x 2048 x 128 1.16, 4 query heads 32 x 1024 x 128 1.11; 8 query heads
 // 64 x 300 x 256 0.98).  Longer splits (128 x 2048 x 128) are bound by their bytes: see plan_decode_few.
