@@ -357,9 +357,9 @@ __global__ void __launch_bounds__(kPrefillThreads, (kPrefillMinWaves<T, D>)) pre
         if (threadIdx.x < kTile) kfold[buf][threadIdx.x] = fold16((uint32_t)(jt * kTile + threadIdx.x) * kKposMul);
     };
 
-    // (A part behind the first starts from a finite reference below every logit: with -inf a tile of nothing but
-    // masked logits and NaN would not be told from an empty one.)
-    float M = !GUMBEL && part > 0 ? -0x1p127f : -INFINITY, Ssum = 0.0f;
+    // The plain form starts from the lowest finite reference: with -inf a tile whose unmasked logits are all NaN would not be
+    // told from one that has none.
+    float M = GUMBEL ? -INFINITY : -0x1.fffffep127f, Ssum = 0.0f;
     const bool skips = BIAS && a.ws_kn && lp.slope1 * (float)n > skip_reach(a.noise, a.inv_tau, n);  // of the unit
     float own = -INFINITY, qnorm = 0.0f;                     // the row's diagonal term, the norm of its query
     // how many of the walk's first `count` tiles do not matter to the block's rows (wstat is there)
@@ -483,13 +483,11 @@ __global__ void __launch_bounds__(kPrefillThreads, (kPrefillMinWaves<T, D>)) pre
 #pragma unroll
             for (int r = 1; r < 16; ++r) tmax = fmaxf(tmax, y2[r]);
             const float Mn = fmaxf(M, tmax);
-            if (Mn > -INFINITY) {
-                float ssum = 0.0f;
+            float ssum = 0.0f;
 #pragma unroll
-                for (int r = 0; r < 16; ++r) ssum += hw_exp2(y2[r] - Mn);
-                Ssum = Ssum * hw_exp2(M - Mn) + ssum;
-                M = Mn;
-            }
+            for (int r = 0; r < 16; ++r) ssum += hw_exp2(y2[r] - Mn);
+            Ssum = Ssum * hw_exp2(M - Mn) + ssum;
+            M = Mn;
             }
         }
         if (jt != jt_next) {

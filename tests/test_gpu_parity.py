@@ -1826,6 +1826,32 @@ def test_nan_in_the_last_key_reaches_every_column_in_parts_too(n, noise, tau):
     assert not nan[0, 0, [0, 2, 3]].any()
 
 
+@pytest.mark.parametrize("bias", [True, False])
+@pytest.mark.parametrize("noise,tau", [(ko.NOISE_NONE, 1.0), (ko.NOISE_GAUSSIAN, 0.7), (ko.NOISE_CONSTANT, 1.0), (ko.NOISE_GUMBEL, 1.0)])
+@pytest.mark.parametrize("B,H,n,first", [(1, 4, 1, 0), (1, 4, 5, 4), (1, 4, 33, 32), (1, 4, 37, 36), (1, 4, 90, 64), (2, 4, 385, 384), (2, 4, 389, 388),
+                                         (1, 4, 600, 544), (16, 8, 2049, 2048), (16, 8, 2053, 2052), (16, 8, 2170, 2144)])
+def test_nan_keys_up_to_the_last_reach_every_column(B, H, n, first, noise, tau, bias):
+    """Keys [first, n) of one head are NaN: rows whose unmasked logits of the tile that crosses the diagonal are all NaN, in one half of
+    the wave or both.  Whole walks (n < 129, and 128 units) and walks in parts (8 units x 385); flat and steep slopes."""
+    rng = np.random.default_rng(n)
+    d = 64
+    oc = random_cache(rng, 1, B, H, d, n, ko.BF16, 0)
+    oc.K[0, B - 1, 1, first:, 5] = 0x7FC0
+    Q = rnd(rng, (1, B, H, n, d), ko.BF16)
+    seeds = np.arange(5, 5 + B).astype(np.uint64)
+    slopes = np.linspace(0.001, 0.6, H).astype(np.float32) if bias else None
+    gc = upload(oc)
+    kf.kf_prefill_score(gc, dev(Q), n, tau, 0.125, noise, dev(seeds), dev(slopes) if bias else None, kf.new_workspace(gc, n))
+    got = host(gc.score)
+    nan = np.isnan(got)
+    assert nan[0, B - 1, 1].all()
+    nan[0, B - 1, 1] = False
+    assert not nan.any()
+    if B * H * n < 4000:
+        oc.prefill_score(Q, n, tau, 0.125, noise, seeds, slopes)
+        np.testing.assert_array_equal(np.isnan(got), np.isnan(oc.score))
+
+
 @pytest.mark.parametrize("cap,k,w", [(2047, 1000, 200), (2048, 2047, 2047), (2049, 1, 0), (8192, 3000, 0), (8193, 4000, 4000),
                                      (32768, 9830, 1966), (32769, 20000, 100), (64, 10, 9)])
 def test_survivor_lists_at_the_edges_of_their_register_forms(cap, k, w):
