@@ -1852,6 +1852,27 @@ def test_nan_keys_up_to_the_last_reach_every_column(B, H, n, first, noise, tau, 
         np.testing.assert_array_equal(np.isnan(got), np.isnan(oc.score))
 
 
+@pytest.mark.parametrize("n,noise,slope", [(20000, ko.NOISE_NONE, 1e-3), (20000, ko.NOISE_CONSTANT, 3e-3), (32768, ko.NOISE_NONE, 1e-3), (19001, ko.NOISE_NONE, 1e-5)])
+def test_long_prompts_with_position_bias_lose_nothing_of_their_far_tiles(n, noise, slope):
+    """Whole walks without a random adjustment against float64.  A row's far tiles, each less than half a unit of the sum's last place,
+    are hundreds: added one by one behind the near ones they would vanish, every score 3e-7 to 6e-7 high (4e-7 and 6.6e-7 in the norm).
+    Allowed: 1.2e-7 for the rounding of a normaliser (its exponent, at most 15 in base 2, in fp32 with half a unit of 4.8e-7 at the
+    logarithm, times ln 2, of either sign over the rows of a column: 3.3e-7 / sqrt(3) of one row), and as much for the terms."""
+    rng = torch.Generator(device="cuda").manual_seed(n)
+    d, scale = 64, 0.125
+    gc = kf.Cache.allocate(1, 1, 1, d, n, kf.BF16)
+    gc.K.copy_(torch.randn(gc.K.shape, device="cuda", generator=rng))
+    Q = torch.randn((1, 1, 1, n, d), device="cuda", generator=rng).to(torch.bfloat16)
+    slopes = torch.full((1,), slope, device="cuda")
+    kf.kf_prefill_score(gc, Q, n, 1.0, scale, noise, None, slopes, kf.new_workspace(gc, n))
+    K, j, want = gc.K[0, 0, 0].double().t().contiguous(), torch.arange(n, device="cuda")[None], torch.zeros(n, dtype=torch.float64, device="cuda")
+    for i0 in range(0, n, 2048):
+        i = torch.arange(i0, min(n, i0 + 2048), device="cuda")[:, None]
+        x = Q[0, 0, 0, i0:i0 + 2048].double() @ K * scale - slopes.double() * (i - j)
+        want += torch.softmax(x.masked_fill_(j > i, -float("inf")), 1).sum(0)
+    assert float((gc.score[0, 0, 0].double() - want).norm() / want.norm()) < 2.4e-7
+
+
 @pytest.mark.parametrize("cap,k,w", [(2047, 1000, 200), (2048, 2047, 2047), (2049, 1, 0), (8192, 3000, 0), (8193, 4000, 4000),
                                      (32768, 9830, 1966), (32769, 20000, 100), (64, 10, 9)])
 def test_survivor_lists_at_the_edges_of_their_register_forms(cap, k, w):
