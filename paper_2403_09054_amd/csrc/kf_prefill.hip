@@ -351,6 +351,8 @@ __global__ void __launch_bounds__(kPrefillThreads, (kPrefillMinWaves<T, D>)) pre
     lp.inv_tau = a.inv_tau;
     lp.gz = -kLog2Ln2 * a.inv_tau;
     lp.noise = a.noise;
+    lp.fixed = fixed_adjustment(a.noise) * a.inv_tau;
+    const bool fixed = a.noise == kNoiseNone || a.noise == kNoiseConstant;  // the same adjustment for every logit
     // a logit's hash input is rkey ^ (k_pos * kKposMul); both sides enter the loop folded (mix32's first step),
     // the keys' side as a table that travels with the tile
     const uint32_t rfold = fold16(rkey);
@@ -486,10 +488,15 @@ __global__ void __launch_bounds__(kPrefillThreads, (kPrefillMinWaves<T, D>)) pre
                 }
             } else {
             float y2[16];
+            if (fixed) {  // (asked once a tile, not for each logit)
 #pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const int ro = (r >> 2) * 8 + (r & 3);
-                y2[r] = logit2_other(lp, acc[r], dist0 - (float)ro, rkey, (uint32_t)(jl + ro));
+                for (int r = 0; r < 16; ++r) y2[r] = logit2_fixed(lp, acc[r], dist0 - (float)((r >> 2) * 8 + (r & 3)));
+            } else {
+#pragma unroll
+                for (int r = 0; r < 16; ++r) {
+                    const int ro = (r >> 2) * 8 + (r & 3);
+                    y2[r] = logit2_other(lp, acc[r], dist0 - (float)ro, rkey, (uint32_t)(jl + ro));
+                }
             }
             if (jb + kTile - 1 > i0) {  // the tile crosses the diagonal for some lane: causal mask
 #pragma unroll
@@ -553,7 +560,7 @@ __global__ void __launch_bounds__(kPrefillThreads, (kPrefillMinWaves<T, D>)) pre
 // Sum of this lane's 16 terms of a tile, a part of its key's column sum.  cs, rs: the tile's row statistics and row noise
 // keys (folded with the Gumbel adjustment); i_first: the lane's first query row.  MASK: the tile crosses the
 // diagonal or the end of the prompt.
-template <bool GUMBEL, bool BIAS, bool TAU1, bool MASK>
+template <bool GUMBEL, bool BIAS, bool TAU1, bool MASK, bool FIXED = false>
 __device__ __forceinline__ float column_sum(const LogitParams& lp, const f32x16& acc, const float* cs, const uint32_t* rs,
                                             int i_first, int half, int j, uint32_t kfold, int n) {
     float sum = 0.0f;  // of the tile: a long prompt's column takes n/2 terms, added one by one they would lose 1e-5
@@ -583,7 +590,8 @@ __device__ __forceinline__ float column_sum(const LogitParams& lp, const f32x16&
                 if (BIAS) t = fmaf(dist0 + (float)e, -lp.slope1, t);
                 z[e] = hw_exp2(fmaf(x, lp.sc1, t));
             } else {
-                z[e] = hw_exp2(logit2_other(lp, x, dist0 + (float)e, rv[e], (uint32_t)j) - cv[e]);
+                const float y2 = FIXED ? logit2_fixed(lp, x, dist0 + (float)e) : logit2_other(lp, x, dist0 + (float)e, rv[e], (uint32_t)j);
+                z[e] = hw_exp2(y2 - cv[e]);
             }
             const int i = i_first + q4 * 8 + e;
             if (MASK) z[e] = (i >= j && i < n) ? z[e] : 0.0f;
@@ -646,6 +654,8 @@ __global__ void __launch_bounds__(kPrefillThreads, (kPrefillMinWaves<T, D>)) pre
     lp.inv_tau = a.inv_tau;
     lp.gz = -kLog2Ln2 * a.inv_tau;
     lp.noise = a.noise;
+    lp.fixed = fixed_adjustment(a.noise) * a.inv_tau;
+    const bool fixed = a.noise == kNoiseNone || a.noise == kNoiseConstant;  // the same adjustment for every logit
     const uint32_t kfold = fold16((uint32_t)j * kKposMul);  // this lane's key in every hash (row keys come folded)
     const float* wc = a.ws_c + (size_t)u * a.n_pad;
     const uint32_t* wr = a.ws_r + (size_t)u * a.n_pad;
@@ -748,7 +758,10 @@ __global__ void __launch_bounds__(kPrefillThreads, (kPrefillMinWaves<T, D>)) pre
             if (edge) {
                 int first = ib + half * 4;  // (the empty asm keeps the masking compares inside this branch, as in pass 1)
                 asm volatile("" : "+v"(first));
-                add = column_sum<GUMBEL, BIAS, TAU1, true>(lp, acc, cs, rs, first, half, j, kfold, n);
+                if (!GUMBEL && fixed) add = column_sum<GUMBEL, BIAS, TAU1, true, true>(lp, acc, cs, rs, first, half, j, kfold, n);
+                else add = column_sum<GUMBEL, BIAS, TAU1, true>(lp, acc, cs, rs, first, half, j, kfold, n);
+            } else if (!GUMBEL && fixed) {
+                add = column_sum<GUMBEL, BIAS, TAU1, false, true>(lp, acc, cs, rs, ib + half * 4, half, j, kfold, n);
             } else {
                 add = column_sum<GUMBEL, BIAS, TAU1, false>(lp, acc, cs, rs, ib + half * 4, half, j, kfold, n);
             }
