@@ -425,7 +425,12 @@ constexpr int kWidePieces = 2048 / kWideThreads;  // 16-byte pieces per thread a
 // 256 x 1501 x 128 with 4 query heads 63.5 / 61.4 / 61.1 / 63.3, 256 x 2048 x 128 73.0 / 71.8 / 72.4 / 75.6, 100 x 3000 x 128
 // 54.2 / 53.7 / 52.6 / 54.1, 32 x 32000 x 128 162 / 162 / 160 / 169.  (Eviction into another cache, whose workgroups read
 // and write a few rows at a time, loses by it: 399 us, 417 with six on a compute unit, 444 with five.)
+// Launches of many units and chunks lose by it too (ordered steps, two / five on a compute unit, a window of half / nine tenths of the
+// budget): 128 x 16000 x 128 497 / 493 and 578 / 568 us, 128 x 32000 999 / 978 and 1169 / 1134, 256 x 16000 1011 / 986 and 1182 /
+// 1146.  The same or a gain: 256 x 8192 479 / 482 and 559 / 558, 64 x 16000 225 / 230 and 293 / 294, 32 x 60000 462 / 465 and 530 / 532.
 constexpr int kShiftLds = 60 * 1024;
+constexpr int64_t kShiftLdsMaxWorkgroups = 12288;  // above, only launches of up to this many units ask for it:
+constexpr int64_t kShiftLdsMaxUnits = 32;
 __global__ void __launch_bounds__(kWideThreads) shift_chunk_kernel(const SelectArgs a, int nchunks, int64_t units) {
     // chunk-major: the chunks that have work are the same few of every unit (those behind the evicted slot),
     // and consecutive workgroup ids go round-robin to the 8 XCDs -- unit-major ids would park all the work on
@@ -1259,7 +1264,8 @@ hipError_t launch_select(const SelectArgs& a, int64_t U, hipStream_t stream) {
 // Second launch of the two-launch eviction: every chunk of rows behind the evicted slot moves down by one.
 hipError_t launch_shift(const SelectArgs& a, int64_t U, hipStream_t stream) {
     const int nchunks = (a.k + a.chunk_rows - 1) / a.chunk_rows;
-    hipLaunchKernelGGL(shift_chunk_kernel, dim3((unsigned)(U * nchunks)), dim3(kWideThreads), kShiftLds, stream, a, nchunks, U);
+    const int lds = U * nchunks <= kShiftLdsMaxWorkgroups || U <= kShiftLdsMaxUnits ? kShiftLds : 0;
+    hipLaunchKernelGGL(shift_chunk_kernel, dim3((unsigned)(U * nchunks)), dim3(kWideThreads), lds, stream, a, nchunks, U);
     return hipGetLastError();
 }
 

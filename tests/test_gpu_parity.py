@@ -219,6 +219,34 @@ def test_select_adversarial_eviction_slots():
     assert [sorted(set(range(n)) - set(kept_ref[0, 0, h].tolist()))[0] for h in range(4)] == [0, n - w - 1, 100, 150]
 
 
+@pytest.mark.parametrize("H,k", [(33, 256 * 373 - 1), (128, 256 * 96 + 5), (32, 256 * 385)])
+def test_eviction_whose_row_move_is_a_launch_of_many_workgroups(H, k):
+    """More than 12288 chunks of 256 rows (one workgroup each): the move of up to 32 units and of more, against a gather."""
+    d, w, cap = 64, k // 3, k + 1
+    gc = kf.Cache.allocate(1, 1, H, d, cap, kf.BF16)
+    assert H * ((k + 255) // 256) > 12288
+    gen = torch.Generator(device="cuda").manual_seed(k)
+    gc.K.view(torch.int16).copy_(torch.randint(-30000, 30000, gc.K.shape, device="cuda", generator=gen, dtype=torch.int16))
+    gc.V.view(torch.int16).copy_(gc.K.view(torch.int16) ^ 0x55)
+    gc.score.copy_(torch.rand(gc.score.shape, device="cuda", generator=gen))
+    evicted = torch.randint(0, cap - w, (H,), device="cuda", generator=gen)
+    evicted[:4] = torch.tensor([0, cap - w - 1, 255, 256])
+    gc.score[0, 0, torch.arange(H), evicted] = -1.0
+    gc.pos.copy_(torch.arange(cap, device="cuda", dtype=torch.int32).expand_as(gc.pos))
+    gc.len.fill_(cap)
+    j = torch.arange(k, device="cuda")[None]
+    kept = j + (j >= evicted[:, None])
+    score = torch.gather(gc.score[0, 0], 1, kept)
+    K0, V0 = gc.K.view(torch.int16).clone(), gc.V.view(torch.int16).clone()
+    kf.kf_select_evict(gc, k, w, None, kf.new_workspace(gc))
+    torch.cuda.synchronize()
+    assert (gc.len == k).all()
+    assert torch.equal(gc.pos[0, 0, :, :k], kept.int()) and torch.equal(gc.score[0, 0, :, :k], score)
+    for h in range(H):
+        assert torch.equal(gc.K.view(torch.int16)[0, 0, h, :k], K0[0, 0, h, kept[h]])
+        assert torch.equal(gc.V.view(torch.int16)[0, 0, h, :k], V0[0, 0, h, kept[h]])
+
+
 @pytest.mark.parametrize("d,dtype,k,w", [(128, ko.BF16, 256, 0), (128, ko.BF16, 300, 40), (128, ko.BF16, 100, 10),
                                         (256, ko.BF16, 128, 0), (64, ko.F32, 257, 1), (64, ko.BF16, 512, 100)])
 def test_select_two_launch_eviction_at_chunk_boundaries(d, dtype, k, w):
