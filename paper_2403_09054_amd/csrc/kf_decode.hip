@@ -473,7 +473,7 @@ __device__ __forceinline__ void decode_block(const DecodeArgs& a) {
 
     // ---- append: the last split stores the new row (nobody reads it back in this launch)
     if (owner && !evict_here && FEW) {
-        if (tid == 2 * kWave) pu[len0] = q_pos;  // (the rows at the end: they are on their way)
+        if (tid == 2 * kWave) pu[len0] = q_pos;  // (the rows at the end, behind the records of a launch of splits: they are on their way)
     } else if (owner && !evict_here) {
         if (wv == 0 && lane < LPR) ((uint4*)(a.K))[((size_t)u * a.cap + len0) * LPR + lane] = ((const uint4*)knew)[lane];
         if (wv == 1 && lane < LPR) ((uint4*)(a.V))[((size_t)u * a.cap + len0) * LPR + lane] = ((const uint4*)vnew)[lane];
@@ -1555,6 +1555,7 @@ static hipError_t launch_decode_t(const DecodeArgs& a, int64_t U, size_t lds, hi
 static hipError_t launch_decode_any(const DecodeArgs& a, int64_t U, int32_t d, int32_t dtype, size_t lds_bytes,
                                     hipStream_t stream, bool merge) {
     if (a.S > kDecodeMaxSplits) return hipErrorInvalidValue;
+    if (a.few && a.S < 2) return hipErrorInvalidValue;  // that form stores the new token's rows with the records of its splits
     if (dtype == KF_BF16) {
         if (d == 64) return launch_decode_t<bf16_t, 64>(a, U, lds_bytes, stream, merge);
         if (d == 128) return launch_decode_t<bf16_t, 128>(a, U, lds_bytes, stream, merge);

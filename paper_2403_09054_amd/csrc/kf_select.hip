@@ -23,6 +23,8 @@
 //            destinations are written.  Every source lies at or after its
 //            destination, so a tile never overwrites a row a later tile still
 //            has to read.  Rows that stay where they are are not touched.
+#include <type_traits>
+
 #include "kf_device.h"
 #include "kf_internal.h"
 #include "kf_merge.h"
@@ -936,6 +938,10 @@ __global__ void __launch_bounds__(kFinishThreads) step_finish_kernel(const Finis
         if (f.idx) f.idx[(size_t)u * k + i] = i + (i >= e ? 1 : 0);
     }
 }
+
+// The kernel reads parts of its argument by way of the argument buffer: it is the only one, so it lies at the buffer's begin.
+static_assert(std::is_same<decltype(&step_finish_kernel<64, 1>), void (*)(FinishLaunch)>::value, "one argument");
+static_assert(std::is_standard_layout<FinishLaunch>::value && std::is_trivially_copyable<FinishLaunch>::value, "read as bytes");
 
 template <int D>
 static hipError_t launch_step_finish_d(const DecodeArgs& d, const SelectArgs& a, int64_t U, hipStream_t st) {
