@@ -199,7 +199,10 @@ def _stream(stream):
     if stream is None:
         import torch
         if torch.cuda.is_initialized():
-            return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+            try:
+                return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+            except AttributeError:  # a torch without these two: by way of its stream object
+                pass
         return torch.cuda.current_stream().cuda_stream if torch.cuda.is_available() else None
     if isinstance(stream, int):
         return stream

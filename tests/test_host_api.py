@@ -300,3 +300,19 @@ def test_built_in_scratch_rejects_shapes_it_cannot_hold():
                                          0x4000, k=2048, w=410)
     assert e.value.status == binding.KF_EWORKSPACE and "built-in" in str(e.value)
     assert kf.kf_workspace_bytes(fake_cache()) <= kf.NOALLOC_SCRATCH_BYTES
+
+
+def test_current_stream_on_a_torch_without_the_raw_getters(monkeypatch):
+    """A call without a stream takes the current one, also where torch lacks the two functions that read its handle."""
+    import types
+
+    import torch
+    monkeypatch.setattr(torch.cuda, "is_initialized", lambda: True)
+    monkeypatch.setattr(torch.cuda, "is_available", lambda: True)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda: types.SimpleNamespace(cuda_stream=0x77))
+    for name in ("_cuda_getCurrentRawStream", "_cuda_getDevice"):
+        with monkeypatch.context() as m:
+            m.delattr(torch._C, name, raising=False)
+            m.setattr(torch._C, {"_cuda_getDevice": "_cuda_getCurrentRawStream", "_cuda_getCurrentRawStream": "_cuda_getDevice"}[name],
+                      lambda *a: 0, raising=False)
+            assert binding._stream(None) == 0x77
