@@ -180,7 +180,8 @@ struct TileStage {
 // against the diagonal term alone, which is 2^15 smaller in the rows that decide; and the terms' bounds added up tile by
 // tile, the far ones being smaller by the bias, instead of n times the largest: 22 of 95 bits that the bias has to outweigh.
 // One layer of 8 x 32 heads x 4096 rows with slopes 2^(-h/4), h = 1..32, 2676 us with all tiles: 1678 against the diagonal terms;
-// 1556 so, later, and 1470 against the sums on the same box, the error against float64 unchanged.)
+// 1556 so, later, and 1470 against the sums on the same box.  Sums that begin with their largest tiles are added up with a carry,
+// `lost` below and carry_sum, so that the error against float64 is none the larger.)
 // A part of a walk does not have the others' sums: pass 1 takes the diagonal term instead, and so does pass 2, there with n
 // times the largest term for the sum over the tiles, whose normalisers it has not.
 // The bounds are taken from the data (norms, sums and normalisers per tile); a NaN or an infinity in any of them makes every
@@ -200,7 +201,6 @@ __device__ __forceinline__ float skip_reach(int noise, float inv_tau, int n) {
     return largest_adjustment(noise) * inv_tau + kSkipBits + hw_log2((float)n);
 }
 constexpr int kSkipAhead = 2;
-constexpr int kCarryTiles = 4;
 constexpr float kSkipTileBits = kSkipBits + 5.0f;  // a tile's terms of a row (or column): 32 of the bound each
 __device__ __forceinline__ float not_above(float x) { return x > -INFINITY ? x : -INFINITY; }  // lower bound: NaN is none
 __device__ __forceinline__ float wave_min(float v) { return -wave_max(-v); }
@@ -222,6 +222,20 @@ __device__ __forceinline__ int tiles_ruled_out(int count, F term) {
         before += __shfl(e, kWave - 1, kWave);
     }
     return count;
+}
+// The plain form's walk from the diagonal: what has been summed since the last call joins the walk's sum `all`, against the
+// reference M from now on (Mall: the one before), with a carry.  (A function: written as a lambda in the kernel, it changes where
+// the compiler puts the blocks of the forms that have none of it.)
+constexpr int kCarryTiles = 4;
+__device__ __forceinline__ void carry_sum(float M, float& Ssum, float& all, float& Mall, float& lost) {
+    const float down = hw_exp2(Mall - M);
+    all *= down;
+    lost *= down;
+    Mall = M;
+    const float add = Ssum - lost, sum = all + add;
+    lost = (sum - all) - add;
+    all = sum;
+    Ssum = 0.0f;
 }
 // Norm from its square: never too small (256 squares that underflowed are 3e-36 together), infinite where the square is no
 // number (every maximum that follows would pass a NaN over).
@@ -351,8 +365,8 @@ __global__ void __launch_bounds__(kPrefillThreads, (kPrefillMinWaves<T, D>)) pre
     lp.inv_tau = a.inv_tau;
     lp.gz = -kLog2Ln2 * a.inv_tau;
     lp.noise = a.noise;
-    lp.fixed = fixed_adjustment(a.noise) * a.inv_tau;
-    const bool fixed = a.noise == kNoiseNone || a.noise == kNoiseConstant;  // the same adjustment for every logit
+    if constexpr (!GUMBEL) lp.fixed = fixed_adjustment(a.noise) * a.inv_tau;
+    const bool fixed = !GUMBEL && (a.noise == kNoiseNone || a.noise == kNoiseConstant);  // the same adjustment for every logit
     // a logit's hash input is rkey ^ (k_pos * kKposMul); both sides enter the loop folded (mix32's first step),
     // the keys' side as a table that travels with the tile
     const uint32_t rfold = fold16(rkey);
@@ -416,21 +430,6 @@ __global__ void __launch_bounds__(kPrefillThreads, (kPrefillMinWaves<T, D>)) pre
     // The plain form takes a sum of kCarryTiles tiles at a time and adds that to the walk's (`all`, against reference Mall).
     // Scores without adjustment against float64, slope 1e-3: 20000 rows 4.0e-7 -> 0.4e-7, 32768 rows 6.6e-7 -> 0.4e-7 (upwards, without: 0.8e-7).
     float all = 0.0f, Mall = M;
-    auto carry = [&]() {
-        const float down = hw_exp2(Mall - M);
-        all *= down;
-        lost *= down;
-        Mall = M;
-        const float add = Ssum - lost, sum = all + add;
-        lost = (sum - all) - add;
-        all = sum;
-        Ssum = 0.0f;
-    };
-    auto sum_so_far = [&]() {  // against M
-        if (!BIAS || GUMBEL) return Ssum;
-        carry();
-        return all;
-    };
     // the walk: upwards, or with a position bias from the diagonal down
     const int jt_begin = BIAS ? max(jt_last, jt_first) : min(jt_first, jt_last), looks_at = skips && a.parts == 1 ? rb * 4 - kSkipAhead : -1;
     typename Stage::Regs stage = Stage::fetch(Ku, min(jt_begin, jt_last) * kTile, n);
@@ -517,7 +516,9 @@ __global__ void __launch_bounds__(kPrefillThreads, (kPrefillMinWaves<T, D>)) pre
             for (int r = 0; r < 16; ++r) ssum += hw_exp2(y2[r] - Mn);
             Ssum = Ssum * hw_exp2(M - Mn) + ssum;
             M = Mn;
-            if (BIAS && jt % kCarryTiles == 0) carry();
+            if constexpr (BIAS) {
+                if (jt % kCarryTiles == 0) carry_sum(M, Ssum, all, Mall, lost);
+            }
             }
         }
         if (jt != jt_next) {
@@ -526,7 +527,11 @@ __global__ void __launch_bounds__(kPrefillThreads, (kPrefillMinWaves<T, D>)) pre
         }
         const bool looks = BIAS && jt == looks_at;  // workgroup-uniform
         if (looks) {
-            const float S = sum_so_far();
+            float S = Ssum;
+            if constexpr (BIAS && !GUMBEL) {
+                carry_sum(M, Ssum, all, Mall, lost);
+                S = all;
+            }
             const float M2 = __shfl_xor(M, 32, kWave), S2 = __shfl_xor(S, 32, kWave), Mt = fmaxf(M, M2);
             const float c = log2_of_sum(Mt, (M > -INFINITY ? S * hw_exp2(M - Mt) : 0.0f) + (M2 > -INFINITY ? S2 * hw_exp2(M2 - Mt) : 0.0f));
             const float least = wave_min(i < n ? not_above(c) : INFINITY);
@@ -537,7 +542,11 @@ __global__ void __launch_bounds__(kPrefillThreads, (kPrefillMinWaves<T, D>)) pre
     }
     if (!active) return;
     // the two halves of the wave hold disjoint key subsets of the same query
-    const float S = sum_so_far();
+    float S = Ssum;
+    if constexpr (BIAS && !GUMBEL) {
+        carry_sum(M, Ssum, all, Mall, lost);
+        S = all;
+    }
     const float M2 = __shfl_xor(M, 32, kWave), S2 = __shfl_xor(S, 32, kWave);
     const float Mt = fmaxf(M, M2);
     const float St = (M > -INFINITY ? S * hw_exp2(M - Mt) : 0.0f) + (M2 > -INFINITY ? S2 * hw_exp2(M2 - Mt) : 0.0f);
@@ -657,8 +666,8 @@ __global__ void __launch_bounds__(kPrefillThreads, (kPrefillMinWaves<T, D>)) pre
     lp.inv_tau = a.inv_tau;
     lp.gz = -kLog2Ln2 * a.inv_tau;
     lp.noise = a.noise;
-    lp.fixed = fixed_adjustment(a.noise) * a.inv_tau;
-    const bool fixed = a.noise == kNoiseNone || a.noise == kNoiseConstant;  // the same adjustment for every logit
+    if constexpr (!GUMBEL) lp.fixed = fixed_adjustment(a.noise) * a.inv_tau;
+    const bool fixed = !GUMBEL && (a.noise == kNoiseNone || a.noise == kNoiseConstant);  // the same adjustment for every logit
     const uint32_t kfold = fold16((uint32_t)j * kKposMul);  // this lane's key in every hash (row keys come folded)
     const float* wc = a.ws_c + (size_t)u * a.n_pad;
     const uint32_t* wr = a.ws_r + (size_t)u * a.n_pad;
@@ -761,9 +770,9 @@ __global__ void __launch_bounds__(kPrefillThreads, (kPrefillMinWaves<T, D>)) pre
             if (edge) {
                 int first = ib + half * 4;  // (the empty asm keeps the masking compares inside this branch, as in pass 1)
                 asm volatile("" : "+v"(first));
-                if (!GUMBEL && fixed) add = column_sum<GUMBEL, BIAS, TAU1, true, true>(lp, acc, cs, rs, first, half, j, kfold, n);
+                if (fixed) add = column_sum<GUMBEL, BIAS, TAU1, true, true>(lp, acc, cs, rs, first, half, j, kfold, n);
                 else add = column_sum<GUMBEL, BIAS, TAU1, true>(lp, acc, cs, rs, first, half, j, kfold, n);
-            } else if (!GUMBEL && fixed) {
+            } else if (fixed) {
                 add = column_sum<GUMBEL, BIAS, TAU1, false, true>(lp, acc, cs, rs, ib + half * 4, half, j, kfold, n);
             } else {
                 add = column_sum<GUMBEL, BIAS, TAU1, false>(lp, acc, cs, rs, ib + half * 4, half, j, kfold, n);
