@@ -8,8 +8,8 @@
 //   * all exponentials, row sums over lanes and waves, one barrier.  The exponentials are taken as they are: a softmax
 //     needs a row's maximum only where a term leaves the range of fp32 or all of them vanish, and then the strip is
 //     evaluated again and every row taken against its maximum, and so are the next ones, at once, while their maxima ask
-//     for it (all logits beyond the range: 256 x 2048 x 128 740 us, 1024 x 512 x 128 273, 300 x 100 x 64 22; every strip twice
-//     1183, 392, 29; two passes 795, 334, 24);
+//     for it (all logits beyond the range: 256 x 2048 x 128 686 us, 1024 x 512 x 128 269, 300 x 100 x 64 22; two passes 683, 261,
+//     16; every strip twice 1183, 392, 29 where two passes took 795, 334, 24);
 //   * each term times its row's 1/sum goes into the lane's column sums, which stay in registers over all strips that
 //     the workgroup walks, and are written once.
 // Two waves per SIMD at 256 registers a lane: 8 waves (2048 keys), or two workgroups of 4 waves (1024 keys) on a CU.
@@ -28,12 +28,17 @@
 // 530, 68.4, 48.5 and, 64 x 1024 x 256, 52 -> 56; noise keys asked for a batch ahead: the same, 5 to 13 registers spilled.  With
 // 512-byte rows the keys alone, 16 KB a tile, take 33 of 105 thousand cycles of a CU's way from its L2 at 64 bytes each.
 //
-// What bounds it: the vector pipe, 22 instructions a logit in all where the two passes take 32 (8 x 32 heads x 2048 x 128, pipe
-// busy 58 % of the time; 16 x 2048 x 256 24 where they take 38, 41 %, before the order above); the rest is the strips' ends, where
-// a workgroup's waves wait for each other.  8 x 32 heads x 2048 x 128 take 569 us, the two passes 731 on the same box.  On the way, on a box where the
-// last of these took 552: 672 us with the key rows read from memory as operands, 664 by way of LDS (512-byte rows 1.3 times as
-// fast), 595 with products ahead, 552 without row references formed ahead of a strip and with row sums folded inside the lanes'
-// rows.  Against float64 0.7e-7 to 1.1e-7 relative (the passes 1.1e-7 to 2.5e-7): numerator and sum hold the same rounded term.
+// (Also left: with 512-byte rows and 4 waves the two settle at a few shapes 2 to 3 % behind the order before, 160 heads x 478 x 256
+// 52.0 -> 53.5 us, where most gain as much, 160 x 900 125.2 -> 121.4; without the raised priority the first take 52.2, the second
+// 122.1, with the noise keys behind the operands 54.0 and 129.9.)
+//
+// What bounds it: the vector pipe, 21 instructions a logit in all where the two passes take 32 (8 x 32 heads x 2048 x 128, pipe
+// busy 64 % of the time; 16 x 2048 x 256 24 where they take 38, 40 %); the rest is the strips' ends, where a workgroup's waves wait
+// for each other, and with 512-byte rows the LDS (a wave waits for it an eighth of its time, with 256-byte rows a sixteenth).  8 x
+// 32 heads x 2048 x 128 take 506 us, the two passes 690 on the same box.  On the way, when this took 552: 672 us with the key rows
+// read from memory as operands, 664 by way of LDS (512-byte rows 1.3 times as fast), 595 with products ahead, 552 without row
+// references formed ahead of a strip and with row sums folded inside the lanes' rows.  Against float64 0.7e-7 to 1.1e-7 relative
+// (the passes 1.1e-7 to 2.5e-7): numerator and sum hold the same rounded term.
 #include "kf_prefill.h"
 
 namespace kf {
@@ -448,14 +453,16 @@ __global__ void __launch_bounds__(256) strips_sum_kernel(const PrefillArgs a, in
     a.score[(size_t)u * a.cap + j] = s;
 }
 
-// Which prompts are scored this way.  Against the two passes (whole calls, 1.0 = the same time; d = 64 to 256, 2 to 2048
-// units): few units 1.2 to 2.5 from 128 rows on (16 heads x 2048 x 256 95 -> 52 us, 32 x 2048 x 128 121 -> 73, 32 x 1024
-// 53 -> 25), the same below; 256 units 1.1 to 1.9 (x 2048 x 128 731 -> 569 us; fp32, whose products take the time, 1.9).  With
-// more units the passes fill the chip by themselves, and a short strip's sums and barrier weigh more than its logits:
-// 512 units 0.91 to 1.2 below 200 rows, 1.2 to 1.6 at 256; 1024 units 0.86 to 1.03 below 200 rows, 0.97 to 1.4 at 256; 2048 units
-// 0.89 to 1.3 at 256, 0.98 to 1.7 at 400, 1.16 to 2 at 512.  Just above 1024 rows, where every strip goes to 8 waves, 16-bit
-// rows 1.03 to 1.08 with 160 units, 0.92 to 1.07 with 256, 0.87 with 512; from 1280 rows on 1.0 to 1.3.  With a position bias
-// the passes leave out tiles from 1025 rows on: 1024 units 0.95, up to 256 1.1 to 1.8.
+// Which prompts are scored this way.  Against the two passes (whole calls, 1.0 = the same time; d = 64 to 256; "units" are heads
+// times sequences times layers).  Up to 256 units 1.03 to 2.2 everywhere (16 heads x 2048 x 256 96 -> 49 us, 32 x 2048 x 128
+// 115 -> 66, 32 x 1024 52 -> 24, 256 x 2048 x 128 690 -> 506; fp32, whose products take the time, 256 x 1024 x 128 1016 -> 453).
+// With more units the passes fill the chip by themselves, and a short strip's sums and barrier weigh more than its logits.  Below
+// 256 rows 320 units 0.95 to 1.8, 512 0.9 to 2.3, 1024 0.8 to 1.2; 256 to 399 rows 512 units 1.27 to 1.6, 1024 0.9 to 1.2;
+// from 400 rows on (512-byte rows: 512) 1.02 to 1.8 up to 2048 units.  From 1025 rows on, where every strip goes to 8 waves, 160
+// units 1.13 to 1.35, 256 1.07 to 1.28, 512 0.94 to 1.12, and from 1280 rows on 1.03 to 1.34 up to 1024 units.  With a position
+// bias the passes leave out tiles from 1025 rows on: up to 256 units 1.03 to 2.1, 384 0.98 to 1.12, 512 0.93 to 1.05, 1024 0.86 to
+// 1.03 with slopes 2^(-8h/H); with slopes that rule nothing out 1.16 to 1.5, fp32 1.3 to 1.6.  (The limits were drawn when strips
+// cost an eighth more: those at 256 and 1280 rows, and that of fp32 with a bias, now leave out shapes that would gain.)
 static int64_t most_strip_units(int32_t n, int32_t dtype, int32_t row_bytes, bool bias) {
     const bool narrow = dtype != KF_F32;
     int64_t most = n < 256 ? 320 : n < (narrow && row_bytes > 256 ? 512 : 400) ? 512 : INT64_MAX;
